@@ -26,8 +26,7 @@ def calibration_copy(dst, src):
     dst = dq8._dev(dst, torch.float32, "dst")
     if dst.numel() < src.numel():
         raise ValueError("dst too small")
-    with dq8._on(src.device):
-        dq8._check(_lib().dq8_internal_copy(dst.data_ptr(), src.data_ptr(), src.numel(), dq8._stream()), "dq8_internal_copy")
+    dq8._enqueue(_lib().dq8_internal_copy, src.get_device(), dst.data_ptr(), src.data_ptr(), src.numel())
     return dst
 
 

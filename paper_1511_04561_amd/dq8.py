@@ -81,26 +81,21 @@ def _dev(t, dtype, what):
     return t
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _enqueue(fn, index, *args):
+    """Calls the library function `fn` with `args` and torch's current stream on device `index`, which is made current for the
+    call if it is not.
 
-
-class _NoSwitch:
-    def __enter__(self):
-        return None
-
-    def __exit__(self, *exc):
-        return False
-
-
-_NO_SWITCH = _NoSwitch()
-
-
-def _on(device):
-    """Makes `device` current for the call; nothing to do (and nothing spent) when it already is."""
-    if device.index is None or device.index == torch.cuda.current_device():
-        return _NO_SWITCH
-    return torch.cuda.device(device)
+    The stream is asked for as the raw handle: torch.cuda.current_stream() builds a Stream object first, which took 2.9 us
+    of the 8.0 us that a call on 4096 elements took (the handle: 0.07 us; such a call now: 5.4 us, 3.5 of
+    them in the library, most of that one kernel launch)."""
+    c = torch._C
+    if index == c._cuda_getDevice():
+        rc = fn(*args, c._cuda_getCurrentRawStream(index))
+    else:
+        with torch.cuda.device(index):
+            rc = fn(*args, c._cuda_getCurrentRawStream(index))
+    if rc != 0:
+        _check(rc, fn.__name__)
 
 
 def codebook(kind):
@@ -122,8 +117,7 @@ def absmax(x, block=0, scales=None):
     _dev(scales, torch.float32, "scales")
     if scales.numel() < n_blocks(n, block):
         raise ValueError("scales too small")
-    with _on(x.device):
-        _check(lib().dq8_absmax(x.data_ptr(), n, int(block), scales.data_ptr(), _stream()), "dq8_absmax")
+    _enqueue(lib().dq8_absmax, x.get_device(), x.data_ptr(), n, int(block), scales.data_ptr())
     return scales
 
 
@@ -141,9 +135,8 @@ def encode(kind, x, block=0, scales=None, codes=None, scales_given=False):
     _dev(codes, torch.uint8, "codes")
     if scales.numel() < n_blocks(n, block) or codes.numel() < n:
         raise ValueError("output buffers too small")
-    with _on(x.device):
-        _check(lib().dq8_encode(int(kind), x.data_ptr(), n, int(block), scales.data_ptr(), codes.data_ptr(),
-                                SCALES_GIVEN if scales_given else 0, _stream()), "dq8_encode")
+    _enqueue(lib().dq8_encode, x.get_device(), int(kind), x.data_ptr(), n, int(block), scales.data_ptr(), codes.data_ptr(),
+             SCALES_GIVEN if scales_given else 0)
     return codes, scales
 
 
@@ -158,9 +151,7 @@ def decode(kind, codes, scales, block=0, out=None):
     _dev(out, torch.float32, "out")
     if out.numel() < n:
         raise ValueError("out too small")
-    with _on(codes.device):
-        _check(lib().dq8_decode(int(kind), codes.data_ptr(), scales.data_ptr(), n, int(block), out.data_ptr(),
-                                _stream()), "dq8_decode")
+    _enqueue(lib().dq8_decode, codes.get_device(), int(kind), codes.data_ptr(), scales.data_ptr(), n, int(block), out.data_ptr())
     return out
 
 
@@ -183,9 +174,7 @@ def absmax_segments(x, bounds, scales=None):
     _dev(scales, torch.float32, "scales")
     if scales.numel() < n_seg:
         raise ValueError("scales too small")
-    with _on(x.device):
-        _check(lib().dq8_absmax_segments(x.data_ptr(), x.numel(), b.data_ptr(), n_seg, scales.data_ptr(), _stream()),
-               "dq8_absmax_segments")
+    _enqueue(lib().dq8_absmax_segments, x.get_device(), x.data_ptr(), x.numel(), b.data_ptr(), n_seg, scales.data_ptr())
     return scales
 
 
@@ -204,9 +193,8 @@ def encode_segments(kind, x, bounds, scales=None, codes=None, scales_given=False
     _dev(codes, torch.uint8, "codes")
     if scales.numel() < n_seg or codes.numel() < n:
         raise ValueError("output buffers too small")
-    with _on(x.device):
-        _check(lib().dq8_encode_segments(int(kind), x.data_ptr(), n, b.data_ptr(), n_seg, scales.data_ptr(), codes.data_ptr(),
-                                         SCALES_GIVEN if scales_given else 0, _stream()), "dq8_encode_segments")
+    _enqueue(lib().dq8_encode_segments, x.get_device(), int(kind), x.data_ptr(), n, b.data_ptr(), n_seg, scales.data_ptr(),
+             codes.data_ptr(), SCALES_GIVEN if scales_given else 0)
     return codes, scales
 
 
@@ -222,9 +210,8 @@ def decode_segments(kind, codes, scales, bounds, out=None):
     _dev(out, torch.float32, "out")
     if out.numel() < n:
         raise ValueError("out too small")
-    with _on(codes.device):
-        _check(lib().dq8_decode_segments(int(kind), codes.data_ptr(), scales.data_ptr(), n, b.data_ptr(), n_seg, out.data_ptr(),
-                                         _stream()), "dq8_decode_segments")
+    _enqueue(lib().dq8_decode_segments, codes.get_device(), int(kind), codes.data_ptr(), scales.data_ptr(), n, b.data_ptr(),
+             n_seg, out.data_ptr())
     return out
 
 
@@ -257,13 +244,11 @@ def decode_accumulate_avg(kind, codes_list, scales_list, block=0, out=None, loca
     _dev(out, torch.float32, "out")
     if out.numel() < n:
         raise ValueError("out too small")
-    with _on(out.device):
-        if local is None:
-            _check(lib().dq8_decode_accumulate_avg(int(kind), cp, sp, K, n, int(block), out.data_ptr(), _stream()),
-                   "dq8_decode_accumulate_avg")
-        else:
-            _check(lib().dq8_decode_accumulate_avg_local(int(kind), cp, sp, K, local.data_ptr(), n, int(block),
-                                                         out.data_ptr(), _stream()), "dq8_decode_accumulate_avg_local")
+    if local is None:
+        _enqueue(lib().dq8_decode_accumulate_avg, out.get_device(), int(kind), cp, sp, K, n, int(block), out.data_ptr())
+    else:
+        _enqueue(lib().dq8_decode_accumulate_avg_local, out.get_device(), int(kind), cp, sp, K, local.data_ptr(), n, int(block),
+                 out.data_ptr())
     return out
 
 
@@ -288,10 +273,8 @@ def decode_accumulate_avg_segments(kind, codes_list, scales_list, bounds, out=No
     _dev(out, torch.float32, "out")
     if out.numel() < n:
         raise ValueError("out too small")
-    with _on(out.device):
-        _check(lib().dq8_decode_accumulate_avg_segments(int(kind), cp, sp, K, None if local is None else local.data_ptr(), n,
-                                                        b.data_ptr(), n_seg, out.data_ptr(), _stream()),
-               "dq8_decode_accumulate_avg_segments")
+    _enqueue(lib().dq8_decode_accumulate_avg_segments, out.get_device(), int(kind), cp, sp, K,
+             None if local is None else local.data_ptr(), n, b.data_ptr(), n_seg, out.data_ptr())
     return out
 
 
@@ -309,10 +292,8 @@ def decode_avg_encode(kind, codes_list, scales_list, block=0, local=None, scales
     _dev(codes, torch.uint8, "codes")
     if scales.numel() < n_blocks(n, block) or codes.numel() < n:
         raise ValueError("output buffers too small")
-    with _on(codes.device):
-        _check(lib().dq8_decode_avg_encode(int(kind), cp, sp, K, None if local is None else local.data_ptr(), n,
-                                           int(block), scales.data_ptr(), codes.data_ptr(), _stream()),
-               "dq8_decode_avg_encode")
+    _enqueue(lib().dq8_decode_avg_encode, codes.get_device(), int(kind), cp, sp, K, None if local is None else local.data_ptr(),
+             n, int(block), scales.data_ptr(), codes.data_ptr())
     return codes, scales
 
 
@@ -338,10 +319,8 @@ def error_stats(kind, x, block=0, scales=None, scales_given=False, stats=None, m
     _dev(means, torch.float64, "means")
     if scales.numel() < nb or stats.numel() < 4 * nb or means.numel() < 2:
         raise ValueError("output buffers too small")
-    with _on(x.device):
-        _check(lib().dq8_error_stats(int(kind), x.data_ptr(), n, int(block), scales.data_ptr(),
-                                     SCALES_GIVEN if scales_given else 0, stats.data_ptr(), means.data_ptr(), _stream()),
-               "dq8_error_stats")
+    _enqueue(lib().dq8_error_stats, x.get_device(), int(kind), x.data_ptr(), n, int(block), scales.data_ptr(),
+             SCALES_GIVEN if scales_given else 0, stats.data_ptr(), means.data_ptr())
     return stats, means
 
 
