@@ -340,7 +340,9 @@ WorkerPtrs advance_workers(const WorkerPtrs &wp, int K, size_t done, size_t bloc
     return r;
 }
 
-int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream)
+// `zeroed`: the caller has set the scales to +0 already.
+int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream,
+                  bool zeroed = false)
 {
     const size_t Bq = block_length(n, block);
     size_t done = 0;
@@ -376,10 +378,12 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
     Plan p = make_plan(n, block, st.cus, wpc, 1, kWavesPerWg, (size_t)q * 4 * kWave);
     size_t per_wave = 0;
     if (p.upb > 1) {
-        unsigned g = (unsigned)((p.nb + 255) / 256);
-        hipLaunchKernelGGL(k_fill_zero, dim3(g), dim3(256), 0, stream, scales, p.nb);
-        int rc = after_launch("k_fill_zero", stream);
-        if (rc) return rc;
+        if (!zeroed) {
+            unsigned g = (unsigned)((p.nb + 255) / 256);
+            hipLaunchKernelGGL(k_fill_zero, dim3(g), dim3(256), 0, stream, scales, p.nb);
+            int rc = after_launch("k_fill_zero", stream);
+            if (rc) return rc;
+        }
         per_wave = (p.n_units + p.n_teams - 1) / p.n_teams;
     }
 #define DQ8_AMAX(Q, NT)                                                                                          \
@@ -549,8 +553,9 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
     return after_launch("k_encode", stream);
 }
 
-// Error statistics of compress-then-decompress into stats[4 nb] (and means[2] when not NULL).
-int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n, size_t block, const float *scales,
+// Error statistics of compress-then-decompress into stats[4 nb] (and means[2] when not NULL); given: the scales are
+// an input, otherwise they are the block maxima and written first.
+int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n, size_t block, float *scales, bool given,
                        double *stats, double *means, hipStream_t stream)
 {
     constexpr int Q = 4;
@@ -565,25 +570,33 @@ int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n
     const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
     const size_t lds = (size_t)st.search_words[kind] * sizeof(uint32_t);
     int rc;
+    bool zeroed = false;
+    if (!own) {  // one kernel clears the rows, the count of workgroups in means[0] and, for blocks of several units, the scales
+        const size_t zero_words = 8 * p.nb, zero_scales = given ? 0 : p.nb, zero_means = means ? 4 : 0;
+        const size_t most = zero_words > zero_means ? zero_words : zero_means;
+        hipLaunchKernelGGL(k_fill_zero_three, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, stream,
+                           reinterpret_cast<float *>(stats), zero_words, scales, zero_scales, reinterpret_cast<float *>(means), zero_means);
+        rc = after_launch("k_fill_zero_three", stream);
+        if (rc) return rc;
+        zeroed = true;
+    }
+    if (!given) {
+        rc = launch_absmax(st, x, n, block, scales, stream, zeroed);
+        if (rc) return rc;
+    }
     if (own) {
         const unsigned grid = (unsigned)(all_waves / kStatsWaves);
         hipLaunchKernelGGL((k_error_stats<Q, true>), dim3(grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
-                           p.n_units, (size_t)0, all_waves, scales, stats);
+                           p.n_units, (size_t)0, all_waves, scales, stats, (double *)nullptr);
         rc = after_launch("k_error_stats", stream);
-    } else {
-        const size_t zero_words = 8 * p.nb;  // 4 binary64 zeros per block
-        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((zero_words + 255) / 256)), dim3(256), 0, stream,
-                           reinterpret_cast<float *>(stats), zero_words);
-        rc = after_launch("k_fill_zero", stream);
-        if (rc) return rc;
-        const size_t per_wave = (p.n_units + n_waves - 1) / n_waves;
-        hipLaunchKernelGGL((k_error_stats<Q, false>), dim3(p.grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
-                           p.n_units, per_wave, n_waves, scales, stats);
-        rc = after_launch("k_error_stats", stream);
+        if (rc || !means) return rc;
+        hipLaunchKernelGGL(k_error_means, dim3(1), dim3(kMeansThreads), 0, stream, stats, p.nb, n, means);
+        return after_launch("k_error_means", stream);
     }
-    if (rc || !means) return rc;
-    hipLaunchKernelGGL(k_error_means, dim3(1), dim3(kMeansThreads), 0, stream, stats, p.nb, n, means);
-    return after_launch("k_error_means", stream);
+    const size_t per_wave = (p.n_units + n_waves - 1) / n_waves;
+    hipLaunchKernelGGL((k_error_stats<Q, false>), dim3(p.grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
+                       p.n_units, per_wave, n_waves, scales, stats, means);
+    return after_launch("k_error_stats", stream);
 }
 
 int launch_decode(const DeviceState &st, int kind, const uint8_t *codes, const float *scales, size_t n, size_t block,
@@ -1478,11 +1491,7 @@ int dq8_error_stats(int kind, const float *x, size_t n, size_t block, float *sca
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!(flags & DQ8_SCALES_GIVEN)) {
-        rc = launch_absmax(*st, x, n, block, scales, stream);
-        if (rc) return rc;
-    }
-    return launch_error_stats(*st, kind, x, n, block, scales, stats, means, stream);
+    return launch_error_stats(*st, kind, x, n, block, scales, (flags & DQ8_SCALES_GIVEN) != 0, stats, means, stream);
 }
 
 int dq8_model_penalty(const double *transfer_ms, const double *compute_ms, size_t count, double *penalty_ms)

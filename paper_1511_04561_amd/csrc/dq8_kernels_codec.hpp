@@ -10,6 +10,15 @@ __global__ void k_fill_zero(float *p, size_t n)
     if (i < n) p[i] = 0.0f;
 }
 
+// Three arrays at once (the second and third no longer than the grid): one launch instead of three.
+__global__ void k_fill_zero_three(float *a, size_t na, float *b, size_t nb, float *c, size_t nc)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < na) a[i] = 0.0f;
+    if (i < nb) b[i] = 0.0f;
+    if (i < nc) c[i] = 0.0f;
+}
+
 // Plain fp32 copy with the access pattern of the codec kernels (units of Q * 256 elements,
 // 128-bit accesses).  Exists to calibrate bandwidth and hardware-counter readings against a
 // kernel whose traffic is known exactly: 4 bytes read and 4 bytes written per element.

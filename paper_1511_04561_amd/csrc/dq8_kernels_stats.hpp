@@ -61,15 +61,25 @@ struct ErrorSums {
 // last, partial round are spread evenly over the wavefronts), adds a block's terms in a fixed order and stores the
 // four numbers: no atomics, stats[] need not be zeroed, and the sums are the same in every launch.
 // OWN = false (blocks too long or too few for that): a wavefront walks a contiguous run of `per_wave` units and
-// merges its sums into stats[], which the host has zeroed, with atomics when the block changes and at the end:
-// the count and the maximum are exact in any order (integers below 2^53, and non-negative binary64 numbers order
-// like their bit patterns); the two sums depend on the order only in their last bits.
+// merges its sums into stats[], which a kernel before this one has zeroed, with atomics when the block changes and at
+// the end: the count and the maximum are exact in any order (integers below 2^53, and non-negative binary64 numbers
+// order like their bit patterns); the two sums depend on the order only in their last bits.  Atomics on one address
+// are served one after the other, about 10 ns each whoever sends them, so what the wavefronts of a workgroup still hold
+// at the end is combined in LDS first and lanes 0 .. 3 of a group of four send the four numbers in one instruction.
+// (25 million elements as one block: four atomics from each of 6104 wavefronts took 304 us, ten times the arithmetic;
+// with 512 workgroups that combine first 43 us.)
+// means (may be NULL): the workgroup that finishes last forms them from stats[], which saves the launch of
+// k_error_means.  means[0], zeroed like stats[], counts the workgroups until then; every workgroup counts itself after
+// its atomics have been performed, so the one that counts last sees them all (it reads with atomic loads: plain ones
+// could come from its own compute unit's cache).  Nothing but atomics has to be seen, so waiting for them is enough: a
+// release fence would also write the XCD's L2 back, for every wavefront (120 us in all).
 // Units are Q * 256 elements; the loads of a wavefront's next unit are issued before the current one is worked on.
 template <int Q, bool OWN>
 __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const uint32_t *__restrict__ tab, const float *__restrict__ x,
                                                          size_t n, size_t B, size_t nb, size_t upb, size_t n_units,
                                                          size_t per_wave, size_t n_waves,
-                                                         const float *__restrict__ scales, double *__restrict__ stats)
+                                                         const float *__restrict__ scales, double *__restrict__ stats,
+                                                         double *__restrict__ means)
 {
     constexpr int U = Q * 4 * kWave;
     __shared__ __align__(256) float lut[256 * kLutCopies];
@@ -93,27 +103,37 @@ __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const
         const double rel = quotient_of_magnitudes(e, ax);
         acc.sum_rel += nz ? rel : 0.0;
     };
-    // The wave's sums for block blk: a fixed tree over the lanes, then lane 0 stores or merges them.
-    auto flush = [&](size_t blk) {
+    // The wave's sums to every lane: a fixed tree over the lanes.
+    auto combine_lanes = [&] {
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) {
             acc.sum_abs += __shfl_xor(acc.sum_abs, m);
             acc.sum_rel += __shfl_xor(acc.sum_rel, m);
             acc.worst = __builtin_fmax(acc.worst, __shfl_xor(acc.worst, m));
         }
-        if (lane == 0) {
-            double *p = stats + 4 * blk;
-            if (OWN) {
+    };
+    // Adds number c (0 .. 3) of a block's four to stats[].
+    auto merge = [&](size_t blk, uint32_t c, double v) {
+        double *p = stats + 4 * blk + c;
+        if (c == 3)
+            atomicMax(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v));
+        else
+            atomicAdd(p, v);
+    };
+    // The wave's sums for block blk are complete: stored, or merged by four lanes.
+    auto flush = [&](size_t blk) {
+        combine_lanes();
+        const double cnt = (double)acc.count;
+        if (OWN) {
+            if (lane == 0) {
+                double *p = stats + 4 * blk;
                 p[0] = acc.sum_abs;
                 p[1] = acc.sum_rel;
-                p[2] = (double)acc.count;
+                p[2] = cnt;
                 p[3] = acc.worst;
-            } else {
-                atomicAdd(p, acc.sum_abs);
-                atomicAdd(p + 1, acc.sum_rel);
-                atomicAdd(p + 2, (double)acc.count);
-                atomicMax(reinterpret_cast<unsigned long long *>(p + 3), (unsigned long long)__double_as_longlong(acc.worst));
             }
+        } else if (lane < 4) {
+            merge(blk, lane, lane == 0 ? acc.sum_abs : (lane == 1 ? acc.sum_rel : (lane == 2 ? cnt : acc.worst)));
         }
         acc = ErrorSums();
     };
@@ -237,35 +257,102 @@ __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const
     } else {
         const size_t u0 = wave * per_wave;
         const size_t u1 = u0 + per_wave < n_units ? u0 + per_wave : n_units;
-        if (u0 >= u1) return;
-        v4f va[Q], vb[Q];
-        Unit cur = unit_of<U>(u0, n, B, nb, upb);
-        bool cur_fast = is_fast(cur);
-        if (cur_fast) load(cur, va);
-        for (size_t u = u0; u < u1; ++u) {
-            const bool more = u + 1 < u1;
-            Unit nxt = cur;
-            bool nxt_fast = false;
-            if (more) {
-                nxt = unit_of<U>(u + 1, n, B, nb, upb);
-                nxt_fast = is_fast(nxt);
-                if (nxt_fast) load(nxt, vb);
+        constexpr size_t kNoBlock = ~(size_t)0;
+        size_t held = kNoBlock;  // the block that acc belongs to after the walk
+        if (u0 < u1) {
+            v4f va[Q], vb[Q];
+            Unit cur = unit_of<U>(u0, n, B, nb, upb);
+            bool cur_fast = is_fast(cur);
+            if (cur_fast) load(cur, va);
+            for (size_t u = u0; u < u1; ++u) {
+                const bool more = u + 1 < u1;
+                Unit nxt = cur;
+                bool nxt_fast = false;
+                if (more) {
+                    nxt = unit_of<U>(u + 1, n, B, nb, upb);
+                    nxt_fast = is_fast(nxt);
+                    if (nxt_fast) load(nxt, vb);
+                }
+                work(cur, cur_fast, va);
+                if (more && nxt.block != cur.block) flush(cur.block);
+                for (int j = 0; j < Q; ++j) va[j] = vb[j];
+                if (!more) held = cur.block;
+                cur = nxt;
+                cur_fast = nxt_fast;
             }
-            work(cur, cur_fast, va);
-            if (!more || nxt.block != cur.block) flush(cur.block);
-            for (int j = 0; j < Q; ++j) va[j] = vb[j];
-            cur = nxt;
-            cur_fast = nxt_fast;
+            combine_lanes();
+        }
+        // The workgroup's wavefronts post what they hold (the value table is not needed any more) and four threads per
+        // wavefront speak for all that hold the same block, if theirs is the first of them.
+        __syncthreads();
+        double *post = reinterpret_cast<double *>(lut);                                // 4 numbers per wavefront
+        uint64_t *post_block = reinterpret_cast<uint64_t *>(post + 4 * kStatsWaves);  // and their block
+        uint32_t *last_flag = reinterpret_cast<uint32_t *>(post_block + kStatsWaves);
+        const uint32_t wv = wave_in_wg();
+        if (lane == 0) {
+            post[4 * wv + 0] = acc.sum_abs;
+            post[4 * wv + 1] = acc.sum_rel;
+            post[4 * wv + 2] = (double)acc.count;
+            post[4 * wv + 3] = acc.worst;
+            post_block[wv] = held;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4 * kStatsWaves) {
+            const uint32_t w = threadIdx.x >> 2, c = threadIdx.x & 3;
+            const uint64_t b = post_block[w];
+            if (b != kNoBlock && (w == 0 || post_block[w - 1] != b)) {  // runs are in ascending order: equal blocks are neighbours
+                double v = post[4 * w + c];
+                for (uint32_t i = w + 1; i < (uint32_t)kStatsWaves && post_block[i] == b; ++i) {
+                    const double o = post[4 * i + c];
+                    v = c == 3 ? __builtin_fmax(v, o) : v + o;
+                }
+                merge(b, c, v);
+            }
+        }
+        if (means == nullptr) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's atomics, the ones on the way included, are performed
+        __syncthreads();
+        if (threadIdx.x == 0)
+            *last_flag = __hip_atomic_fetch_add(reinterpret_cast<unsigned int *>(means), 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        __syncthreads();
+        if (*last_flag == 0) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        double a = 0.0, r = 0.0, c = 0.0;
+        for (size_t b = threadIdx.x; b < nb; b += kStatsWg) {
+            a += __hip_atomic_load(stats + 4 * b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            r += __hip_atomic_load(stats + 4 * b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            c += __hip_atomic_load(stats + 4 * b + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            a += __shfl_xor(a, m);
+            r += __shfl_xor(r, m);
+            c += __shfl_xor(c, m);
+        }
+        if (lane == 0) {
+            post[3 * wv + 0] = a;
+            post[3 * wv + 1] = r;
+            post[3 * wv + 2] = c;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (uint32_t i = 1; i < (uint32_t)kStatsWaves; ++i) {
+                a += post[3 * i + 0];
+                r += post[3 * i + 1];
+                c += post[3 * i + 2];
+            }
+            means[0] = a / (double)n;
+            means[1] = c > 0.0 ? r / c : 0.0;
         }
     }
 }
 
 // Means over all blocks from the per-block statistics: means[0] = (sum of absolute errors) / n,
 // means[1] = (sum of relative errors) / (number of non-zero inputs), 0 when there is none.
-// One workgroup of 1024 threads; thread t adds blocks t, t + 1024, ... in that order and the threads'
-// sums are combined by a fixed tree, so the result is the same in every launch.  (A separate launch because a
-// fold into the statistics kernel would need a grid-wide counter, and the library keeps no device memory of
-// its own that concurrent calls could share.)
+// For the statistics kernel in which wavefronts own whole blocks.  One workgroup of 1024 threads; thread t adds blocks
+// t, t + 1024, ... in that order and the threads' sums are combined by a fixed tree, so the result is the same in every
+// launch.  (A separate launch: that kernel needs no zeroed memory, and a count of its workgroups would.)
 constexpr uint32_t kMeansThreads = 1024;
 __global__ __launch_bounds__(kMeansThreads) void k_error_means(const double *__restrict__ stats, size_t nb, size_t n,
                                                               double *__restrict__ means)
