@@ -447,28 +447,28 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
 #undef DQ8_ENC_FULL
         return after_launch("k_encode_full", stream);
     }
-    // Blocks of 4097 .. 16384 elements in whole quads, aligned buffers: the team holds a block in 8, 12 or 16
-    // quads per lane.
     const size_t tail = n % p.B;
-    // Blocks of up to 1024 elements in whole quads, aligned buffers: one wavefront per block with its loads
-    // always a block ahead (blocks of 4 .. 128 elements that are powers of two went to the small kernels before).
-    if (fused && g_tune.enc_wave && p.B >= (size_t)g_tune.enc_wave_min && p.B <= (size_t)g_tune.enc_wave && (p.B & 3) == 0 && (tail & 3) == 0 &&
-        p.nb > 1 && p.nb < 0xFFFFFFFFull && ((uintptr_t)x & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
-        const uint32_t bq = (uint32_t)(p.B / 4), tail_q = (uint32_t)(tail / 4);
+    // blocks of the two kernels below that are units of theirs; a last block of fewer than four elements is not
+    const size_t blocks = tail != 0 && tail < 4 ? p.nb - 1 : p.nb;
+    // Blocks of up to 1024 elements, of any length and at any alignment of an element: one wavefront per block with its
+    // loads always a block ahead (blocks of 4 .. 128 elements that are powers of two went to the small kernels before).
+    if (fused && g_tune.enc_wave && p.B >= (size_t)g_tune.enc_wave_min && p.B <= (size_t)g_tune.enc_wave &&
+        p.nb > 1 && p.nb < 0xFFFFFFFFull && ((uintptr_t)x & 3) == 0) {
+        const uint32_t bq = (uint32_t)((p.B + 3) / 4);
         const int wq = bq <= 64 ? 1 : (bq <= 128 ? 2 : (bq <= 256 ? 4 : 8));  // quads per lane
         const int ww = 16;                                                     // wavefronts per workgroup
         size_t waves = (size_t)st.cus * (size_t)(wq == 8 ? g_tune.enc_wave_wpc8 : g_tune.enc_wave_wpc);
-        if (waves > p.nb) waves = p.nb;
+        if (waves > blocks) waves = blocks;
         const unsigned grid = (unsigned)((waves + ww - 1) / ww);
         const uint32_t n_waves = grid * (uint32_t)ww;
         const size_t wlds = (size_t)st.search_words[kind] * sizeof(uint32_t);
 #define DQ8_ENC_WAVE(QL)                                                                                              \
     if (st.has_remap[kind]) {                                                                                         \
         hipLaunchKernelGGL((k_encode_wave<QL, 1, 16, true>), dim3(grid), dim3(kWave * 16), wlds, stream, tab, x,      \
-                           (uint32_t)p.nb, n_waves, bq, tail_q, scales, codes);                                       \
+                           (uint32_t)blocks, n_waves, (uint32_t)p.B, (uint32_t)tail, scales, codes);                                       \
     } else {                                                                                                          \
         hipLaunchKernelGGL((k_encode_wave<QL, 1, 16, false>), dim3(grid), dim3(kWave * 16), wlds, stream, tab, x,     \
-                           (uint32_t)p.nb, n_waves, bq, tail_q, scales, codes);                                       \
+                           (uint32_t)blocks, n_waves, (uint32_t)p.B, (uint32_t)tail, scales, codes);                                       \
     }
         switch (wq) {
         case 1: DQ8_ENC_WAVE(1) break;
@@ -482,20 +482,19 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
     const bool long_block = unit > (size_t)kUnit;
     // blocks of 1537 .. 3072 elements too: 2 or 3 quads per lane (2 to 7 % faster than a wavefront per block there)
     const bool mid_block = g_tune.enc_mid && p.B > (size_t)g_tune.enc_mid && p.B <= 3072;
-    if (fused && g_tune.enc_long == 1 && (long_block || mid_block) && (p.B & 3) == 0 &&
-        (tail & 3) == 0 && p.nb < 0xFFFFFFFFull && ((uintptr_t)x & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
-        const uint32_t bq = (uint32_t)(p.B / 4), tail_q = (uint32_t)(tail / 4);
+    if (fused && g_tune.enc_long == 1 && (long_block || mid_block) && p.nb < 0xFFFFFFFFull && ((uintptr_t)x & 3) == 0) {
+        const uint32_t bq = (uint32_t)((p.B + 3) / 4);
         const int qpl = bq <= 512 ? 2 : (bq <= 768 ? 3 : (bq <= 1536 ? 6 : (bq <= 2048 ? 8 : (bq <= 3072 ? 12 : 16))));  // quads per lane
         const int lwpc = qpl <= 3 ? g_tune.enc_wpc4 : (qpl == 6 ? g_tune.enc_wpc6 : (qpl == 8 ? g_tune.enc_wpc8 : (qpl == 12 ? g_tune.enc_wpc12 : g_tune.enc_wpc16)));
         size_t teams = (size_t)st.cus * (size_t)lwpc / 4;
-        if (teams > p.nb) teams = p.nb;
+        if (teams > blocks) teams = blocks;
 #define DQ8_ENC_LONG(QPL)                                                                                             \
     if (st.has_remap[kind]) {                                                                                         \
         hipLaunchKernelGGL((k_encode_long<QPL, 1, true>), dim3((unsigned)teams), dim3(kWg), lds, stream, tab, x,      \
-                           (uint32_t)p.nb, (uint32_t)teams, bq, tail_q, scales, codes);                               \
+                           (uint32_t)blocks, (uint32_t)teams, (uint32_t)p.B, (uint32_t)tail, scales, codes);                               \
     } else {                                                                                                          \
         hipLaunchKernelGGL((k_encode_long<QPL, 1, false>), dim3((unsigned)teams), dim3(kWg), lds, stream, tab, x,     \
-                           (uint32_t)p.nb, (uint32_t)teams, bq, tail_q, scales, codes);                               \
+                           (uint32_t)blocks, (uint32_t)teams, (uint32_t)p.B, (uint32_t)tail, scales, codes);                               \
     }
         if (qpl == 2) {
             DQ8_ENC_LONG(2)
@@ -613,11 +612,11 @@ int launch_decode(const DeviceState &st, int kind, const uint8_t *codes, const f
     const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
     const bool ragged = p.nb > 1 && p.B % ((size_t)q * 4 * kWave) != 0;  // blocks end inside units
     // Blocks that do not consist of whole units (or, dec_flat == 2, any): units by position, not by block, with up
-    // to eight blocks' scales per unit.  Needs blocks of whole quads and aligned buffers.
+    // to eight blocks' scales per unit.  Needs blocks of whole quads.
     const size_t bq = p.B / 4;
     // (also blocks of 2048 elements: 54 against 57 us with units of that length)
     if (g_tune.dec_flat && (ragged || g_tune.dec_flat == 2 || p.B == 2048) && p.nb > 1 && (p.B & 3) == 0 && bq >= 10 && bq < (1u << 28) &&
-        ((uintptr_t)out & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
+        ((uintptr_t)out & 3) == 0) {
         int fq = 16, fwpc = g_tune.dec_wpc;
         while ((size_t)fq * kWave > 7 * bq) {  // at most eight blocks per unit
             fq >>= 1;

@@ -424,30 +424,75 @@ __device__ __forceinline__ void stg_at(T *uniform_base, uint32_t idx, T v)
         g[idx] = v;
 }
 
+// Quads at addresses that are aligned for an element only: a row of 1001 values starts at every alignment.  The memory
+// unit takes 128-bit accesses at any multiple of 4 bytes and 32-bit accesses at any byte, so these are the same single
+// instructions as the aligned accesses; a wave instruction then touches one more cache line than its bytes fill.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+// Four floats from element i on, four code bytes from element i on (uniform base pointer, see ldg_at).
+template <int NT>
+__device__ __forceinline__ v4f ldg_floats(const float *uniform_base, uint32_t i)
+{
+    const DQ8_GLOBAL v4f_any *g = (const DQ8_GLOBAL v4f_any *)(uniform_global(uniform_base) + i);
+    if constexpr (NT != 0)
+        return __builtin_nontemporal_load(g);
+    else
+        return *g;
+}
+
+template <int NT>
+__device__ __forceinline__ uint32_t ldg_codes(const uint8_t *uniform_base, uint32_t i)
+{
+    const DQ8_GLOBAL u32_any *g = (const DQ8_GLOBAL u32_any *)(uniform_global(uniform_base) + i);
+    if constexpr (NT != 0)
+        return __builtin_nontemporal_load(g);
+    else
+        return *g;
+}
+
+template <int NT>
+__device__ __forceinline__ void stg_codes(uint8_t *uniform_base, uint32_t i, uint32_t v)
+{
+    DQ8_GLOBAL u32_any *g = (DQ8_GLOBAL u32_any *)(uniform_global(uniform_base) + i);
+    if constexpr (NT != 0)
+        __builtin_nontemporal_store(v, g);
+    else
+        *g = v;
+}
+
+// (stg's 128-bit stores take any multiple of 4 bytes in the form of policy 2; the others need the type that says so.)
+template <int NT>
+__device__ __forceinline__ void stg_floats(float *p, v4f v)
+{
+    if constexpr (NT == 2)
+        stg<2>(reinterpret_cast<v4f *>(p), v);
+    else if constexpr (NT == 1)
+        __builtin_nontemporal_store(v, reinterpret_cast<v4f_any *>(p));
+    else
+        *reinterpret_cast<v4f_any *>(p) = v;
+}
+
+// Where quad q of a run of len >= 4 elements starts: at 4 q, or, for the last quad of a run that is no whole number of
+// quads and for every quad past it, four elements before the end.  The overlap is read twice (a maximum does not
+// change) and written twice with the same bytes; quads with 4 q >= len are loaded (valid memory, no branch) and not stored.
+__device__ __forceinline__ uint32_t quad_start(uint32_t q, uint32_t len)
+{
+    return q * 4 < len - 4 ? q * 4 : len - 4;
+}
+
 __device__ __forceinline__ uint32_t wave_in_wg() { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // Index of this wavefront in the grid = the first unit it owns; held in scalar registers.
 __device__ __forceinline__ size_t first_unit(int waves_per_wg = kWavesPerWg) { return (size_t)blockIdx.x * waves_per_wg + wave_in_wg(); }
 
-// Maximum of |x[0..len)| over the elements this lane takes, for a unit that is short or not
-// 16-byte aligned: whole quads with 128-bit loads when the start is aligned (the STRIDE lanes that
-// share the unit take quads lane, lane + STRIDE, ...; a tail of fewer than four elements goes one by
-// one), else element by element.
-template <int NT, uint32_t STRIDE = kWave>
+// Maximum of |x[0..len)| over the elements this lane takes, one by one: units of fewer than four elements, and floats
+// whose address is no multiple of 4.
+template <uint32_t STRIDE = kWave>
 __device__ __forceinline__ uint32_t slow_absmax(const float *px, uint32_t len, uint32_t lane)
 {
     uint32_t m = 0;
-    uint32_t done = 0;
-    if (((uintptr_t)px & 15) == 0) {
-        const v4f *p4 = reinterpret_cast<const v4f *>(px);
-        const uint32_t nq = len >> 2;
-        float fm = 0.0f;
-#pragma unroll 4
-        for (uint32_t q = lane; q < nq; q += STRIDE) fm = max4_abs(ldg<NT>(p4 + q), fm);
-        m = f2u(fm);
-        done = nq << 2;
-    }
-    for (uint32_t i = done + lane; i < len; i += STRIDE) {
+    for (uint32_t i = lane; i < len; i += STRIDE) {
         const uint32_t a = abs_bits(px[i]);
         m = m > a ? m : a;
     }

@@ -68,11 +68,14 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
     v4f v[Q];
     auto open_unit = [&](size_t uu, Unit &q, bool &f) {
         q = unit_of<U>(uu, n, B, nb, upb);
-        f = q.len == U && ((uintptr_t)(x + q.start) & 15) == 0;
-        if (f) {
-            const v4f *p4 = reinterpret_cast<const v4f *>(x + q.start);
+        f = q.len >= 4 && ((uintptr_t)x & 3) == 0;
+        const float *px = x + q.start;
+        if (f && q.len == U) {
 #pragma unroll
-            for (int j = 0; j < Q; ++j) v[j] = ldg<NT>(p4 + j * kWave + lane);
+            for (int j = 0; j < Q; ++j) v[j] = ldg_floats<NT>(px, 4 * (j * kWave + lane));
+        } else if (f) {
+#pragma unroll
+            for (int j = 0; j < Q; ++j) v[j] = ldg_floats<NT>(px, quad_start(j * kWave + lane, q.len));
         }
     };
     if (u < end) open_unit(u, un, fast);
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
             for (int j = 0; j < Q; ++j) fm = max4_abs(v[j], fm);
             m = f2u(fm);
         } else {
-            m = slow_absmax<NT>(x + un.start, un.len, lane);
+            m = slow_absmax(x + un.start, un.len, lane);
         }
         const size_t blk = un.block;
         u += stride;
@@ -114,9 +117,8 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
 // The loop is software-pipelined: the loads of a team's next unit are issued before the
 // current unit is reduced and quantised, so each wavefront always has loads in flight.
 // A unit shorter than that (a block that is not a power of two, the end of a block or of the
-// array) takes the same path when it consists of whole aligned quads: a lane whose quad lies
-// past the end loads the unit's last quad instead (an unconditional load of valid memory: the
-// maximum does not change and the lane stores nothing).
+// array) takes the same path (see quad_start); only units of fewer than four elements, and floats at addresses that
+// are not a multiple of 4, go element by element.
 template <int WPB, int QL, int NT, bool FUSED, bool FASTDIV>
 struct Encoder {
     static constexpr int Q = QL;
@@ -144,19 +146,15 @@ struct Encoder {
     {
         sl.un = unit_of<U>(u, n, B, nb, upb);
         const float *px = x + sl.un.start;
-        sl.fast = sl.un.len >= 4 && (sl.un.len & 3) == 0 && ((uintptr_t)px & 15) == 0 &&
-                  ((uintptr_t)(codes + sl.un.start) & 3) == 0;
+        sl.fast = sl.un.len >= 4 && ((uintptr_t)x & 3) == 0;
         if (sl.fast) {
-            const v4f *p4 = reinterpret_cast<const v4f *>(px);
-            const uint32_t last = (sl.un.len >> 2) - 1;
 #pragma unroll
             for (int it = 0; it < Q; ++it) {
-                const uint32_t q = it * TEAM + tl;
-                if (kSkipRows && it * TEAM > last) {  // the same for the whole team: a row past the end of the unit
+                if (kSkipRows && it * TEAM * 4 >= sl.un.len) {  // the same for the whole team: a row past the end of the unit
                     sl.v[it] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
                     continue;
                 }
-                sl.v[it] = ldg<NT>(p4 + (q < last ? q : last));
+                sl.v[it] = ldg_floats<NT>(px, quad_start(it * TEAM + tl, sl.un.len));
             }
         }
     }
@@ -175,7 +173,7 @@ struct Encoder {
                 for (int it = 0; it < Q; ++it) fm = max4_abs(sl.v[it], fm);
                 m = f2u(fm);
             } else {
-                m = slow_absmax<NT, TEAM>(px, un.len, tl);
+                m = slow_absmax<TEAM>(px, un.len, tl);
             }
             m = wave_max_u32(m);
             if (WPB > 1) {
@@ -195,35 +193,25 @@ struct Encoder {
         const float r = 1.0f / d;
         const bool recip = reciprocal_ok(d);
         if (sl.fast) {
-            uint32_t *c4 = reinterpret_cast<uint32_t *>(pc);
-            const uint32_t nq = un.len >> 2;
             // quads whose table lookups are issued together; the team variant runs six teams per compute unit
             // and has no registers to spare for that
             constexpr int G = WPB > 1 ? 1 : (Q < 4 ? Q : 4);
 #pragma unroll
             for (int g = 0; g < Q; g += G) {
-                if (kSkipRows && g * TEAM >= nq) continue;
+                if (kSkipRows && g * TEAM * 4 >= un.len) continue;
                 v4f vv[G];
                 uint32_t cw[G];
 #pragma unroll
                 for (int it = 0; it < G; ++it) vv[it] = sl.v[g + it];
                 encode_quads<FASTDIV, G>(sr, vv, d, r, recip, cw);
 #pragma unroll
-                for (int it = 0; it < G; ++it)
-                    if ((g + it) * TEAM + tl < nq) stg<NT>(c4 + (g + it) * TEAM + tl, cw[it]);
+                for (int it = 0; it < G; ++it) {
+                    const uint32_t q = (g + it) * TEAM + tl;
+                    if (q * 4 < un.len) stg_codes<NT>(pc, quad_start(q, un.len), cw[it]);
+                }
             }
         } else {
-            // a misaligned unit or one that does not consist of whole quads: whole quads where the addresses allow (the lanes of the team take quads
-            // tl, tl + TEAM, ...), the rest element by element
-            uint32_t done = 0;
-            if ((((uintptr_t)px & 15) | ((uintptr_t)pc & 3)) == 0) {
-                const v4f *p4 = reinterpret_cast<const v4f *>(px);
-                uint32_t *c4 = reinterpret_cast<uint32_t *>(pc);
-                const uint32_t nq = un.len >> 2;
-                for (uint32_t q = tl; q < nq; q += TEAM) stg<NT>(c4 + q, encode_quad<FASTDIV>(sr, ldg<NT>(p4 + q), d, r, recip));
-                done = nq << 2;
-            }
-            for (uint32_t i = done + tl; i < un.len; i += TEAM) pc[i] = (uint8_t)encode_one<FASTDIV>(sr, px[i], d, r, recip);
+            for (uint32_t i = tl; i < un.len; i += TEAM) pc[i] = (uint8_t)encode_one<FASTDIV>(sr, px[i], d, r, recip);
         }
     }
 };
@@ -349,28 +337,52 @@ __global__ __launch_bounds__(kWg) void k_encode_full(const uint32_t *__restrict_
     if (tail_len != 0 && blockIdx.x == gridDim.x - 1) {
         const float *px = x + (size_t)n_full * kUnit;
         uint8_t *pc = codes + (size_t)n_full * kUnit;
-        uint32_t m = 0;
-        for (uint32_t i = tl; i < tail_len; i += kWg) {
-            const uint32_t v = abs_bits(px[i]);
-            m = m > v ? m : v;
+        const bool quads = tail_len >= 4;  // see quad_start
+        float fm = 0.0f;
+        if (quads) {
+#pragma unroll
+            for (int it = 0; it < Q; ++it) a[it] = ldg_floats<NT>(px, quad_start(it * kWg + tl, tail_len));
+#pragma unroll
+            for (int it = 0; it < Q; ++it) fm = max4_abs(a[it], fm);
+        } else if (tl < tail_len) {
+            fm = __builtin_fabsf(px[tl]);
         }
-        const float s = u2f(team_max(wave_max_u32(m)));
+        const float s = u2f(team_max(wave_max_u32(f2u(fm))));
         if (tl == 0) scales[n_full] = s;
         const float d = s == 0.0f ? 1.0f : s;
         const float r = 1.0f / d;
         const bool recip = reciprocal_ok(d);
-        for (uint32_t i = tl; i < tail_len; i += kWg) pc[i] = (uint8_t)encode_one<FASTDIV>(sr, px[i], d, r, recip);
+        if (quads) {
+#pragma unroll
+            for (int it = 0; it < Q; ++it) {
+                const uint32_t q = it * kWg + tl;
+                const uint32_t cw = encode_quad<FASTDIV>(sr, a[it], d, r, recip);
+                if (q * 4 < tail_len) stg_codes<NT>(pc, quad_start(q, tail_len), cw);
+            }
+        } else if (tl < tail_len) {
+            pc[tl] = (uint8_t)encode_one<FASTDIV>(sr, px[tl], d, r, recip);
+        }
     }
 }
 
+// One wavefront compresses a last block of fewer than four elements (pointers to its elements, code bytes and scale).
+__device__ __forceinline__ void encode_under_a_quad(const Search &sr, const float *px, uint32_t len, float *scale, uint8_t *pc, uint32_t lane)
+{
+    const float v = lane < len ? px[lane] : 0.0f;
+    const float s = u2f(wave_max_u32(abs_bits(v)));
+    const float d = s == 0.0f ? 1.0f : s;
+    if (lane == 0) *scale = s;
+    if (lane < len) pc[lane] = (uint8_t)code_exact(sr, v, d);
+}
+
 // Compression of blocks of up to QL * 256 elements, one wavefront per block: k_encode_long without the exchange
-// between wavefronts.  Blocks are whole quads (bq of them), x is 16-byte and codes 4-byte aligned; a lane whose
-// quad lies past the end of the block loads the block's last quad instead and stores nothing; the last block
-// may be shorter (tail_q quads, 0: none).  Wavefront w of the grid takes blocks w, w + n_waves, ...
+// between wavefronts.  Blocks have B >= 4 elements and start at every alignment of an element (see quad_start); the last
+// block may be shorter (tail elements, 0: none; one of fewer than four elements is no unit and done after the loop).
+// Wavefront w of the grid takes blocks w, w + n_waves, ...
+// Rows of 1001 elements (2048 of them) took 14.0 us while such rows went element by element.
 template <int QL, int NT, int WPW, bool REMAP>
 __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__restrict__ tab, const float *__restrict__ x,
-                                                            uint32_t n_units, uint32_t n_waves, uint32_t bq,
-                                                            uint32_t tail_q, float *__restrict__ scales,
+                                                            uint32_t n_units, uint32_t n_waves, uint32_t B, uint32_t tail, float *__restrict__ scales,
                                                             uint8_t *__restrict__ codes)
 {
     constexpr int Q = QL;
@@ -379,15 +391,12 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
     extern __shared__ uint32_t lds[];  // the bucket table
     const uint32_t lane = threadIdx.x & 63;
     Search sr;
-    auto quads_of = [&](uint32_t u) { return (tail_q != 0 && u == n_units - 1) ? tail_q : bq; };
+    auto length_of = [&](uint32_t u) { return (tail >= 4 && u == n_units - 1) ? tail : B; };
     auto fetch = [&](uint32_t u, v4f(&v)[Q]) {
-        const v4f *p4 = reinterpret_cast<const v4f *>(x) + (size_t)u * bq;
-        const uint32_t last = quads_of(u) - 1;
+        const float *px = x + (size_t)u * B;
+        const uint32_t len = length_of(u);
 #pragma unroll
-        for (int it = 0; it < Q; ++it) {
-            const uint32_t q = it * kWave + lane;
-            v[it] = ldg_at<NT>(p4, q < last ? q : last);
-        }
+        for (int it = 0; it < Q; ++it) v[it] = ldg_floats<NT>(px, quad_start(it * kWave + lane, len));
     };
     auto process = [&](uint32_t u, v4f(&v)[Q]) {
         float fm = 0.0f;
@@ -398,8 +407,8 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
         const float d = s == 0.0f ? 1.0f : s;
         const float r = 1.0f / d;
         const bool recip = reciprocal_ok(d);
-        uint32_t *c4 = reinterpret_cast<uint32_t *>(codes) + (size_t)u * bq;
-        const uint32_t nq = quads_of(u);
+        uint8_t *pc = codes + (size_t)u * B;
+        const uint32_t len = length_of(u);
 #pragma unroll
         for (int g = 0; g < Q; g += G) {
             v4f vv[G];
@@ -410,7 +419,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
 #pragma unroll
             for (int it = 0; it < G; ++it) {
                 const uint32_t q = (g + it) * kWave + lane;
-                if (q < nq) stg_at<NT>(c4, q, cw[it]);
+                if (q * 4 < len) stg_codes<NT>(pc, quad_start(q, len), cw[it]);
             }
         }
     };
@@ -442,6 +451,8 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
             u = nx;
         }
     }
+    if (tail != 0 && tail < 4 && blockIdx.x == gridDim.x - 1 && wave_in_wg() == 0)
+        encode_under_a_quad(sr, x + (size_t)n_units * B, tail, scales + n_units, codes + (size_t)n_units * B, lane);
 }
 
 // Decompression with units that do not follow the blocks: unit u is quads [u Q 64, (u + 1) Q 64) of the array
@@ -450,7 +461,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
 // blocks, whose scales are NS scalar loads (indices clamped to the last block), and every quad selects its own
 // by comparing its offset from the start of the unit's first block with bq, 2 bq, ...  The block index and
 // offset of a wavefront's unit advance by the same step every iteration (step_b blocks and step_r < bq
-// quads), so there is one division per wavefront.  out is 16-byte, codes 4-byte aligned; the last unit may be
+// quads), so there is one division per wavefront.  Buffers may start at any element; the last unit may be
 // short (a lane past the end repeats the last code word's load and stores nothing); `left` elements after the
 // last whole quad (they belong to the last block) are done one by one by the wavefront that has the last unit.
 template <int Q, int NS, int NT, int WPW>
@@ -469,14 +480,14 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_flat(const uint32_t *__r
     uint32_t w[Q], len = 0;
     float sc[NS];
     auto open_unit = [&](uint64_t uu, uint64_t bb) {
-        const uint32_t *c4 = reinterpret_cast<const uint32_t *>(codes) + uu * UQ;
+        const uint8_t *pc = codes + uu * UQ * 4;
         const uint64_t rest = nq - uu * UQ;
         len = rest < UQ ? (uint32_t)rest : UQ;
         const uint32_t last = len - 1;
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
             const uint32_t i = j * kWave + lane;
-            w[j] = ldg_at<NT>(c4, i < last ? i : last);
+            w[j] = ldg_codes<NT>(pc, 4 * (i < last ? i : last));
         }
 #pragma unroll
         for (int t = 0; t < NS; ++t) sc[t] = scales[bb + t < nb ? bb + t : nb - 1];
@@ -492,7 +503,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_flat(const uint32_t *__r
 #pragma unroll
         for (int t = 0; t < NS; ++t) cs[t] = sc[t];
         const uint32_t nqu = len, base = r0 + lane;
-        v4f *o4 = reinterpret_cast<v4f *>(out) + u * UQ;
+        float *po = out + u * UQ * 4;
         const bool last_unit = u == n_units - 1;
         const uint64_t last_block = nb - 1;
         u += n_waves;
@@ -514,7 +525,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_flat(const uint32_t *__r
             r.y = lut_at<1>(lut, cur[j], lane4) * s;
             r.z = lut_at<2>(lut, cur[j], lane4) * s;
             r.w = lut_at<3>(lut, cur[j], lane4) * s;
-            if (j * kWave + lane < nqu) stg<NT>(o4 + j * kWave + lane, r);
+            if (j * kWave + lane < nqu) stg_floats<NT>(po + 4 * (j * kWave + lane), r);
         }
         if (last_unit && lane < left) {
             const uint64_t e = nq * 4 + lane;
@@ -527,13 +538,12 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_flat(const uint32_t *__r
 
 // Compression of blocks of up to 16384 elements from one read of x: the scheme of k_encode_full with QPL
 // quads per lane (a team of four wavefronts holds up to QPL * 1024 elements) and a block length given
-// at run time.  Blocks are whole quads (bq of them) and x is 16-byte, codes 4-byte aligned, so every block
-// starts on aligned addresses.  A lane whose quad lies past the end of the block loads the block's last quad
-// instead (an unconditional load of valid memory: the maximum does not change and the lane stores nothing).
-// The last block may be shorter (tail_q quads, 0: none): it is one more unit, with its own length.
+// at run time.  Blocks have B >= 4 elements and start at every alignment of an element (see quad_start).  The last block
+// may be shorter (tail elements, 0: none): it is one more unit, with its own length; one of fewer than four elements is
+// no unit and done after the loop.
 template <int QPL, int NT, bool REMAP>
 __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict__ tab, const float *__restrict__ x,
-                                                    uint32_t n_units, uint32_t n_teams, uint32_t bq, uint32_t tail_q,
+                                                    uint32_t n_units, uint32_t n_teams, uint32_t B, uint32_t tail,
                                                     float *__restrict__ scales, uint8_t *__restrict__ codes)
 {
     constexpr int Q = QPL;
@@ -544,15 +554,12 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
     const uint32_t lane = threadIdx.x & 63, wave = wave_in_wg(), tl = threadIdx.x;
     uint32_t phase = 0;
     Search sr;
-    auto quads_of = [&](uint32_t u) { return (tail_q != 0 && u == n_units - 1) ? tail_q : bq; };
+    auto length_of = [&](uint32_t u) { return (tail >= 4 && u == n_units - 1) ? tail : B; };
     auto fetch = [&](uint32_t u, v4f(&v)[Q]) {
-        const v4f *p4 = reinterpret_cast<const v4f *>(x) + (size_t)u * bq;
-        const uint32_t last = quads_of(u) - 1;
+        const float *px = x + (size_t)u * B;
+        const uint32_t len = length_of(u);
 #pragma unroll
-        for (int it = 0; it < Q; ++it) {
-            const uint32_t q = it * kWg + tl;
-            v[it] = ldg_at<NT>(p4, q < last ? q : last);
-        }
+        for (int it = 0; it < Q; ++it) v[it] = ldg_floats<NT>(px, quad_start(it * kWg + tl, len));
     };
     auto team_max = [&](uint32_t m) {
         if (lane == 0) slots[phase * kWavesPerWg + wave] = m;
@@ -571,8 +578,8 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
         const float d = s == 0.0f ? 1.0f : s;
         const float r = 1.0f / d;
         const bool recip = reciprocal_ok(d);
-        uint32_t *c4 = reinterpret_cast<uint32_t *>(codes) + (size_t)u * bq;
-        const uint32_t nq = quads_of(u);
+        uint8_t *pc = codes + (size_t)u * B;
+        const uint32_t len = length_of(u);
 #pragma unroll
         for (int g = 0; g < Q; g += G) {
             v4f vv[G];
@@ -583,7 +590,7 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
 #pragma unroll
             for (int it = 0; it < G; ++it) {
                 const uint32_t q = (g + it) * kWg + tl;
-                if (q < nq) stg_at<NT>(c4, q, cw[it]);
+                if (q * 4 < len) stg_codes<NT>(pc, quad_start(q, len), cw[it]);
             }
         }
     };
@@ -615,14 +622,16 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
             u = nx;
         }
     }
+    if (tail != 0 && tail < 4 && blockIdx.x == gridDim.x - 1 && wave_in_wg() == 0)
+        encode_under_a_quad(sr, x + (size_t)n_units * B, tail, scales + n_units, codes + (size_t)n_units * B, lane);
 }
 
 // Decompression of one buffer: out = table[code] * scale.  One wavefront per unit of Q * 256
 // elements: Q code words (4 codes each) per lane; the next unit's words are loaded before the
 // current ones are expanded.
-// RAGGED = true (chosen by the host when blocks are not whole units): a unit of fewer whole aligned
-// quads stays on this path; a lane whose quad lies past the end loads the unit's last code word
-// instead (unconditional, valid memory) and stores nothing.
+// RAGGED = true (chosen by the host when blocks are not whole units): a short unit of four elements or more stays on
+// the pipelined path (see quad_start).  Otherwise a short unit is the last of the array: its loads are not ahead, but
+// in flight together.
 template <int Q, int NT, int WPW, bool RAGGED>
 __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
                                                        const float *__restrict__ scales, size_t n, size_t B, size_t nb,
@@ -636,17 +645,23 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restri
     Unit un;
     bool fast = false;
     uint32_t w[Q];
+    auto expand = [&](uint32_t cw, float s) {
+        v4f r;
+        r.x = lut_at<0>(lut, cw, lane4) * s;
+        r.y = lut_at<1>(lut, cw, lane4) * s;
+        r.z = lut_at<2>(lut, cw, lane4) * s;
+        r.w = lut_at<3>(lut, cw, lane4) * s;
+        return r;
+    };
     auto open_unit = [&](size_t uu, Unit &q, bool &f) {
         q = unit_of<U>(uu, n, B, nb, upb);
-        f = ((uintptr_t)(out + q.start) & 15) == 0 && ((uintptr_t)(codes + q.start) & 3) == 0;
-        f = f && (RAGGED ? (q.len >= 4 && (q.len & 3) == 0) : q.len == U);
+        f = ((uintptr_t)out & 3) == 0 && (RAGGED ? q.len >= 4 : q.len == U);
         if (f) {
-            const uint32_t *c4 = reinterpret_cast<const uint32_t *>(codes + q.start);
-            const uint32_t last = (q.len >> 2) - 1;
+            const uint8_t *pc = codes + q.start;
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
                 const uint32_t i = j * kWave + lane;
-                w[j] = ldg<NT>(c4 + (RAGGED ? (i < last ? i : last) : i));
+                w[j] = ldg_codes<NT>(pc, RAGGED ? quad_start(i, q.len) : 4 * i);
             }
         }
     };
@@ -660,40 +675,32 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restri
             uint32_t cur[Q];
 #pragma unroll
             for (int j = 0; j < Q; ++j) cur[j] = w[j];
-            const uint32_t nq = un.len >> 2;
+            const uint32_t len = un.len;
             u += n_waves;
             if (u < n_units) open_unit(u, un, fast);
-            v4f *o4 = reinterpret_cast<v4f *>(po);
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-                v4f r;
-                r.x = lut_at<0>(lut, cur[j], lane4) * s;
-                r.y = lut_at<1>(lut, cur[j], lane4) * s;
-                r.z = lut_at<2>(lut, cur[j], lane4) * s;
-                r.w = lut_at<3>(lut, cur[j], lane4) * s;
-                if (!RAGGED || j * kWave + lane < nq) stg<NT>(o4 + j * kWave + lane, r);
+                const uint32_t q = j * kWave + lane;
+                const v4f r = expand(cur[j], s);
+                if (!RAGGED)
+                    stg_floats<NT>(po + 4 * q, r);
+                else if (q * 4 < len)
+                    stg_floats<NT>(po + quad_start(q, len), r);
             }
         } else {
-            // a short or misaligned unit: whole quads with 128-bit stores where the addresses allow, the rest
-            // element by element
             const uint8_t *pc = codes + un.start;
-            uint32_t done = 0;
-            if ((((uintptr_t)po & 15) | ((uintptr_t)pc & 3)) == 0) {
-                const uint32_t *c4 = reinterpret_cast<const uint32_t *>(pc);
-                v4f *o4 = reinterpret_cast<v4f *>(po);
-                const uint32_t nq = un.len >> 2;
-                for (uint32_t q = lane; q < nq; q += kWave) {
-                    const uint32_t cw = ldg<NT>(c4 + q);
-                    v4f r;
-                    r.x = lut_at<0>(lut, cw, lane4) * s;
-                    r.y = lut_at<1>(lut, cw, lane4) * s;
-                    r.z = lut_at<2>(lut, cw, lane4) * s;
-                    r.w = lut_at<3>(lut, cw, lane4) * s;
-                    stg<NT>(o4 + q, r);
+            if (!RAGGED && un.len >= 4 && ((uintptr_t)out & 3) == 0) {  // the short last unit of the array
+                uint32_t cur[Q];
+#pragma unroll
+                for (int j = 0; j < Q; ++j) cur[j] = ldg_codes<NT>(pc, quad_start(j * kWave + lane, un.len));
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const uint32_t q = j * kWave + lane;
+                    if (q * 4 < un.len) stg_floats<NT>(po + quad_start(q, un.len), expand(cur[j], s));
                 }
-                done = nq << 2;
+            } else {
+                for (uint32_t i = lane; i < un.len; i += kWave) po[i] = lut_code(lut, pc[i], lane4) * s;
             }
-            for (uint32_t i = done + lane; i < un.len; i += kWave) po[i] = lut_code(lut, pc[i], lane4) * s;
             u += n_waves;
             if (u < n_units) open_unit(u, un, fast);
         }

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_1511_04561_amd import workloads
-from tests.test_gpu_parity import Guarded, check_error_stats, dev, same_bits  # noqa: F401
+from tests.test_gpu_parity import Guarded, check_encode_decode, check_error_stats, dev, same_bits  # noqa: F401
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -37,3 +37,17 @@ def test_error_stats_shared_blocks(dq8, n, block):
     check_error_stats(dq8, 0, x, block, tag="shared")
     nb = oracle.dq8_oracle.n_blocks(n, block)
     check_error_stats(dq8, 3, x, block, given=np.full(nb, 4.0, np.float32), tag="shared, given")
+
+
+@pytest.mark.parametrize("n,block", [
+    (2048 * 3 + 1001, 1001), (1001 * 40, 1001), (9 * 700 + 3, 9), (257 * 300 + 1, 257), (1023 * 33 + 2, 1023),  # a wavefront per block; last block of 1, 2, 3
+    (1500 * 9 + 1, 1500), (2047 * 20 + 5, 2047), (3071 * 13 + 3, 3071), (1300 * 30 + 7, 1300), (3500 * 9 + 2, 3500),  # teams, and the general kernel
+    (4096 * 7 + 1, 4096), (4096 * 7 + 4095, 4096), (4097 * 11, 4097), (6143 * 5 + 3, 6143), (12289 * 3 + 1, 12289), (16383 * 3 + 2, 16383),
+    (4096 * 9 + 3, 0), (16385, 0), (100003, 0), (70000 * 3 + 1, 70000), (5, 0), (3, 0), (1003 * 4 + 3, 20000)])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_blocks_that_start_at_any_element(dq8, n, block, offset):
+    """Blocks, last blocks and arrays that are no whole number of quads or start at an address that is aligned for an element only."""
+    rng = np.random.Generator(np.random.PCG64(7300 + n % 89))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    check_encode_decode(dq8, (n + offset) % 4, x, block, x_off=offset, c_off=offset, tag="offset %d" % offset)
+    check_encode_decode(dq8, (n + offset + 1) % 4, x, block, x_off=offset, c_off=(offset + 1) % 4, tag="offsets %d" % offset)
