@@ -340,11 +340,46 @@ WorkerPtrs advance_workers(const WorkerPtrs &wp, int K, size_t done, size_t bloc
     return r;
 }
 
-// `zeroed`: the caller has set the scales to +0 already.
+// Units of `unit` elements: a last one of fewer than four elements is none, and there are none at all when floats lie at
+// addresses that are no multiple of 4.
+size_t whole_units(size_t n, size_t unit, bool aligned) { return aligned ? n / unit + (n % unit >= 4) : 0; }
+
+// Grid of the kernels for an array that is one block: workgroups of kOneWaves wavefronts, up to per_cu on a compute unit.
+unsigned one_block_grid(const DeviceState &st, size_t n, size_t unit, int per_cu)
+{
+    const size_t all = (n + unit * kOneWaves - 1) / (unit * kOneWaves), most = (size_t)st.cus * (size_t)per_cu;
+    return (unsigned)(all < most ? all : most);
+}
+
+// `zeroed`: the caller has set the scales to +0 already.  `again`: a kernel that reads x follows.
 int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream,
-                  bool zeroed = false)
+                  bool zeroed = false, bool again = false)
 {
     const size_t Bq = block_length(n, block);
+    if (Bq == n && n > (size_t)kUnit) {  // one block of several units
+        if (!zeroed) {
+            hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(256), 0, stream, scales, (size_t)1);
+            const int rc = after_launch("k_fill_zero", stream);
+            if (rc) return rc;
+        }
+        // 16 quads per lane when every wavefront of a workgroup per compute unit still gets two such units, else 4: there
+        // the number of wavefronts counts
+        const bool wide = n >= (size_t)st.cus * kOneWaves * 2 * 4096, aligned = ((uintptr_t)x & 3) == 0;
+        const size_t unit = wide ? 4096 : 1024, units = whole_units(n, unit, aligned);
+        const unsigned grid = one_block_grid(st, n, unit, 1);
+        const size_t waves = (size_t)grid * kOneWaves;
+#define DQ8_AMAX_ONE(Q, NT) hipLaunchKernelGGL((k_absmax_one<Q, NT>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, scales)
+        if (wide && again)
+            DQ8_AMAX_ONE(16, 0);
+        else if (wide)
+            DQ8_AMAX_ONE(16, 1);
+        else if (again)
+            DQ8_AMAX_ONE(4, 0);
+        else
+            DQ8_AMAX_ONE(4, 1);
+#undef DQ8_AMAX_ONE
+        return after_launch("k_absmax_one", stream);
+    }
     size_t done = 0;
     int rc0 = small_absmax(st, x, n, Bq, scales, stream, &done);
     if (rc0 || done == n) return rc0;
@@ -424,6 +459,16 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
     Plan p = make_plan(n, block, st.cus, wpc, wpb, kWavesPerWg, unit);
     const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
     const size_t lds = ((size_t)st.search_words[kind] + kTeamSlots) * sizeof(uint32_t);
+    if (!fused && p.nb == 1) {  // one scale, in memory
+        const size_t units = whole_units(n, 1024, ((uintptr_t)x & 3) == 0);
+        const unsigned grid = one_block_grid(st, n, 1024, 2);
+        const size_t waves = (size_t)grid * kOneWaves, olds = (size_t)st.search_words[kind] * sizeof(uint32_t);
+        if (st.has_remap[kind])
+            hipLaunchKernelGGL((k_encode_one<true>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, codes);
+        else
+            hipLaunchKernelGGL((k_encode_one<false>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, codes);
+        return after_launch("k_encode_one", stream);
+    }
     // Whole aligned blocks of exactly one unit: the kernel without slow paths in its loop.
     if (fused && g_tune.enc_lean && p.B == (size_t)kUnit && n / kUnit >= 1 && n / kUnit < 0xFFFFFFFFull &&
         ((uintptr_t)x & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
@@ -580,7 +625,7 @@ int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n
         zeroed = true;
     }
     if (!given) {
-        rc = launch_absmax(st, x, n, block, scales, stream, zeroed);
+        rc = launch_absmax(st, x, n, block, scales, stream, zeroed, true);
         if (rc) return rc;
     }
     if (own) {
@@ -1183,10 +1228,15 @@ static int launch_segment_absmax(const DeviceState &st, const float *x, size_t n
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, stream, scales, n_seg);
     int rc = after_launch("k_fill_zero", stream);
     if (rc) return rc;
-    const SegPlan p = make_segment_plan(st.cus, n, n_seg, 32, true);
-    const uint32_t aligned = ((uintptr_t)x & 15) == 0;
-    hipLaunchKernelGGL(k_seg_absmax, dim3(p.grid), dim3(kWave * kSegWaves), p.lds, stream, x, n, bounds, (uint32_t)n_seg,
-                       p.n_units, p.n_items, p.n_waves, p.group, aligned, scales);
+    const SegPlan p = make_segment_plan(st.cus, n, n_seg, kSegWaves, true);
+    const size_t units = whole_units(n, (size_t)p.group * kSegUnit, ((uintptr_t)x & 3) == 0);
+    const size_t lds = p.lds + n_seg * sizeof(uint32_t);
+    if (p.group == 4)
+        hipLaunchKernelGGL((k_seg_absmax<4 * kSegQ>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units,
+                           p.n_waves, scales);
+    else
+        hipLaunchKernelGGL((k_seg_absmax<kSegQ>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units,
+                           p.n_waves, scales);
     return after_launch("k_seg_absmax", stream);
 }
 
@@ -1231,7 +1281,7 @@ int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, 
     // the block fits one unit: absmax and encode in one kernel
     const bool fused = !given && Bq <= (g_tune.enc_long ? kLongestHeldBlock : (size_t)kUnit);
     if (!given && !fused) {
-        rc = launch_absmax(*st, x, n, block, scales, stream);
+        rc = launch_absmax(*st, x, n, block, scales, stream, false, true);
         if (rc) return rc;
     }
     return launch_encode(*st, kind, x, n, block, scales, codes, fused, stream);
@@ -1402,16 +1452,16 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
         rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream);
         if (rc) return rc;
     }
-    SegPlan p = make_segment_plan(st->cus, n, n_seg, 32);
+    SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves);
     p.lds += (size_t)st->search_words[kind] * sizeof(uint32_t);
-    const uint32_t aligned = (((uintptr_t)x & 15) | ((uintptr_t)codes & 3)) == 0;
+    const size_t units = whole_units(n, kSegUnit, ((uintptr_t)x & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
     if (st->has_remap[kind])
-        hipLaunchKernelGGL((k_seg_encode<true>), dim3(p.grid), dim3(kWave * kSegWaves), p.lds, stream, tab, x, n, bounds,
-                           (uint32_t)n_seg, p.n_units, p.n_waves, aligned, scales, codes);
+        hipLaunchKernelGGL((k_seg_encode<true>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, units,
+                           p.n_waves, scales, codes);
     else
-        hipLaunchKernelGGL((k_seg_encode<false>), dim3(p.grid), dim3(kWave * kSegWaves), p.lds, stream, tab, x, n, bounds,
-                           (uint32_t)n_seg, p.n_units, p.n_waves, aligned, scales, codes);
+        hipLaunchKernelGGL((k_seg_encode<false>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, units,
+                           p.n_waves, scales, codes);
     return after_launch("k_seg_encode", stream);
 }
 
@@ -1431,11 +1481,11 @@ int dq8_decode_segments(int kind, const uint8_t *codes, const float *scales, siz
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 16);
-    const uint32_t aligned = (((uintptr_t)out & 15) | ((uintptr_t)codes & 3)) == 0;
+    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves);
+    const size_t units = whole_units(n, kSegUnit, ((uintptr_t)out & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    hipLaunchKernelGGL(k_seg_decode, dim3(p.grid), dim3(kWave * kSegWaves), p.lds, stream, tab, codes, scales, n, bounds,
-                       (uint32_t)n_seg, p.n_units, p.n_waves, aligned, out);
+    hipLaunchKernelGGL(k_seg_decode, dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, codes, scales, n, bounds, (uint32_t)n_seg, units,
+                       p.n_waves, out);
     return after_launch("k_seg_decode", stream);
 }
 
@@ -1462,11 +1512,14 @@ int dq8_decode_accumulate_avg_segments(int kind, const uint8_t *const *codes, co
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const SegPlan p = make_segment_plan(st->cus, n, n_seg, 16);
-    bool aligned = ((uintptr_t)out & 15) == 0 && ((uintptr_t)local & 15) == 0;
-    for (int k = 0; k < K; ++k) aligned = aligned && ((uintptr_t)wp.codes[k] & 3) == 0;
+    const size_t units = whole_units(n, kSegUnit, (((uintptr_t)out | (uintptr_t)local) & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    hipLaunchKernelGGL(k_seg_avg, dim3(p.grid), dim3(kWave * kSegWaves), p.lds, stream, tab, wp, K, local, n, bounds,
-                       (uint32_t)n_seg, p.n_units, p.n_waves, (uint32_t)aligned, out);
+    if (K <= 4)  // all workers' codes in flight at once
+        hipLaunchKernelGGL((k_seg_avg<4>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds, (uint32_t)n_seg,
+                           units, p.n_waves, out);
+    else
+        hipLaunchKernelGGL((k_seg_avg<8>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds, (uint32_t)n_seg,
+                           units, p.n_waves, out);
     return after_launch("k_seg_avg", stream);
 }
 

@@ -499,4 +499,30 @@ __device__ __forceinline__ uint32_t slow_absmax(const float *px, uint32_t len, u
     return m;
 }
 
+// The steady state of kernels that walk units u, u + n_waves, ...: the loads of a wavefront's next unit are issued without a condition before the work
+// on the current one (see k_encode_full).  fetch(u, slot) loads, process(u, slot) works; a, b: two slots of registers.
+template <typename Slot, typename Fetch, typename Process>
+__device__ __forceinline__ void walk_units(size_t u, size_t n_units, size_t n_waves, Slot &a, Slot &b, Fetch fetch, Process process)
+{
+    if (u >= n_units) return;
+    for (;;) {
+        size_t nx = u + n_waves;
+        if (!(nx < n_units)) {
+            process(u, a);
+            break;
+        }
+        fetch(nx, b);
+        process(u, a);
+        u = nx;
+        nx = u + n_waves;
+        if (!(nx < n_units)) {
+            process(u, b);
+            break;
+        }
+        fetch(nx, a);
+        process(u, b);
+        u = nx;
+    }
+}
+
 }  // namespace

@@ -108,6 +108,98 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
     }
 }
 
+// Maximum of an array that is one block, into a zeroed scale.  Units of Q * 256 elements, strided over the grid: at any
+// moment the chip reads one narrow window of the array (37.7 M elements: 29.7 us while every wavefront had a stretch of
+// its own, 27.0 us now).  A workgroup sends one atomic: atomics on one address are served one after the other, about 10 ns
+// each.  NT = 0, plain loads, when the array is read again after this: then it stays in the memory-side cache (256 MB),
+// which takes the second pass over 37.7 M elements from 33.4 to 26.8 us and costs this one a microsecond.
+// n_units: whole units and a last one of at least four elements (see quad_start); the elements past them (at most three;
+// all of them when x is no multiple of 4) go one by one.
+constexpr int kOneWaves = 8;
+constexpr int kOneWg = kWave * kOneWaves;
+
+template <int Q, int NT>
+__global__ __launch_bounds__(kOneWg) void k_absmax_one(const float *__restrict__ x, size_t n, size_t n_units, size_t n_waves,
+                                                       float *__restrict__ scale)
+{
+    constexpr int U = Q * 4 * kWave;
+    __shared__ uint32_t part[kOneWaves];
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t m = 0;
+    v4f v[Q];
+    auto fetch = [&](size_t u) {
+        const float *px = x + u * (size_t)U;
+        const uint32_t len = cap_to_unit<U>(n - u * (size_t)U);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) v[j] = ldg_floats<NT>(px, quad_start(j * kWave + lane, len));
+    };
+    size_t u = first_unit(kOneWaves);
+    if (u < n_units) fetch(u);
+    while (u < n_units) {
+        float fm = 0.0f;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) fm = max4_abs(v[j], fm);
+        u += n_waves;
+        if (u < n_units) fetch(u);
+        m = m > f2u(fm) ? m : f2u(fm);
+    }
+    for (size_t i = n_units * (size_t)U + (size_t)blockIdx.x * kOneWg + threadIdx.x; i < n; i += n_waves * kWave) {
+        const uint32_t a = abs_bits(x[i]);
+        m = m > a ? m : a;
+    }
+    m = wave_max_u32(m);
+    if (lane == 0) part[wave_in_wg()] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < kOneWaves; ++w) m = m > part[w] ? m : part[w];
+        if (m != 0) atomicMax(reinterpret_cast<unsigned int *>(scale), m);
+    }
+}
+
+// Compression of an array that is one block with its scale in memory: units of 1024 elements, the next unit's loads always
+// ahead (37.7 M elements right after k_absmax_one: 30.3 us; 36.6 us in k_encode, which has conditions in its loop).
+// n_units as in k_absmax_one.
+template <bool REMAP>
+__global__ __launch_bounds__(kOneWg) void k_encode_one(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                       size_t n_units, size_t n_waves, const float *__restrict__ scale,
+                                                       uint8_t *__restrict__ codes)
+{
+    constexpr int Q = 4, U = Q * 4 * kWave;
+    extern __shared__ uint32_t lds[];  // the bucket table
+    const uint32_t lane = threadIdx.x & 63;
+    struct Slot {
+        v4f v[Q];
+    } a, b;
+    auto fetch = [&](size_t u, Slot &sl) {
+        const uint32_t len = cap_to_unit<U>(n - u * (size_t)U);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) sl.v[j] = ldg_floats<1>(x + u * (size_t)U, quad_start(j * kWave + lane, len));
+    };
+    const size_t u0 = first_unit(kOneWaves);
+    if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the table is copied
+    const float s = *scale;
+    const float d = s == 0.0f ? 1.0f : s;
+    const float r = 1.0f / d;
+    const bool recip = reciprocal_ok(d);
+    Search sr = load_bucket_table(tab, lds, kOneWg);
+    sr.marks = REMAP;
+    __syncthreads();
+    walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
+        const uint32_t len = cap_to_unit<U>(n - u * (size_t)U);
+        uint8_t *pc = codes + u * (size_t)U;
+        uint32_t cw[Q];
+        encode_quads<true, Q>(sr, sl.v, d, r, recip, cw);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const uint32_t q = j * kWave + lane;
+            if (q * 4 < len) stg_codes<1>(pc, quad_start(q, len), cw[j]);
+        }
+    });
+    for (size_t i = n_units * (size_t)U + (size_t)blockIdx.x * kOneWg + threadIdx.x; i < n; i += n_waves * kWave)
+        codes[i] = (uint8_t)encode_one<true>(sr, x[i], d, r, recip);
+}
+
 // Compression.  A team of WPB wavefronts owns a unit of WPB * QL * 256 elements, QL quads per lane:
 // WPB == 1, each wavefront of the workgroup walks its own units; WPB == 4, the workgroup's four
 // wavefronts share a unit and combine their maxima through LDS.

@@ -7,19 +7,24 @@
 // outside [0, n): the kernels walk the array in units of 1024 elements by position, and the segment of an
 // element is looked up, never the elements of a segment.  Entries that do not ascend give meaningless
 // results inside the arrays.
-// A wavefront takes a unit at a time.  The segment of the unit's first element comes from two votes over
-// the bounds (64 evenly spaced ones, then the 64 of the stretch the first vote names).  A unit that lies inside
-// one segment and is a whole aligned unit takes the register path of the other kernels with that segment's
-// scale; any other unit (a segment ends inside it, the end of the array, misaligned arrays) gives every lane
-// sixteen consecutive elements: one binary search for the first, then a step to the next segment whenever an
-// element reaches the next bound.
+// A wavefront takes a unit at a time, its loads (which do not depend on the segments) issued a unit ahead and without a
+// condition, as in k_encode_full.  The segment of the unit's first element comes from two votes over the bounds (64
+// evenly spaced ones, then the 64 of the stretch the first vote names).  A unit inside one segment goes on with that
+// segment's scale; in any other unit every lane looks the segments of its elements up between the unit's first and last
+// segment and the same registers go on with scales per quad (per element in the rows of quads in which a segment ends).
+// What bounds the kernels: HBM on long arrays, latency on short ones.  Mixed units used to walk sixteen consecutive
+// elements per lane one after the other: the convnet's ten tensors (1.76 M elements), seven workers and the own
+// gradients averaged: 30.7 us, 11.8 us now (8.3 us when no segment ends inside a unit); that set compressed 16.0 -> 10.4 us; the
+// AlexNet-shaped bucket's sixteen matrices (61 M elements), maxima 53.8 -> 42.5 and compression 59.4 -> 49.0 us.
+// Elements that are in no unit (fewer than four at the end of the array; all of them when floats lie at addresses that
+// are no multiple of 4) go one by one.
 #pragma once
 #include "dq8_device.hpp"
 
 namespace {
 
-constexpr int kSegMax = DQ8_MAX_SEGMENTS;           // segments per call: the bounds fit 32 KiB of LDS
-constexpr int kSegRun = kSegUnit / kWave;           // 16 consecutive elements per lane on the slow path
+constexpr int kSegMax = DQ8_MAX_SEGMENTS;  // segments per call: the bounds fit 32 KiB of LDS
+constexpr int kSegWg = kWave * kSegWaves;
 
 // Copies bounds[0 .. n_seg] to LDS, clamped to n.  The caller synchronises the workgroup.
 __device__ __forceinline__ void load_bounds(const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n, uint64_t *lds)
@@ -61,259 +66,305 @@ __device__ __forceinline__ uint32_t segment_of_lane(const uint64_t *lds, uint32_
     return lo;
 }
 
-// Geometry of unit u and what it needs: its first element, its length, the segment of its first element and
-// whether that segment holds the whole unit.
-struct SegUnit {
+// The elements [start, start + len) of a unit or of a stretch of one, and the segments of its first and last element.
+// first == last: the stretch lies inside that segment (the last segment takes whatever lies beyond its end).
+struct SegSpan {
     size_t start;
-    uint32_t len, seg;
-    bool single;
+    uint32_t len, first, last;
 };
 
-__device__ __forceinline__ SegUnit open_segment_unit(const uint64_t *lds, uint32_t n_seg, size_t n, size_t u, uint32_t lane)
+__device__ __forceinline__ SegSpan open_span(const uint64_t *lds, uint32_t n_seg, size_t start, uint32_t len, uint32_t lane)
 {
-    SegUnit q;
-    q.start = u * (size_t)kSegUnit;
-    q.len = cap_to_unit<kSegUnit>(n - q.start);
-    q.seg = segment_of_uniform(lds, n_seg, q.start, lane);
-    // (the last segment takes whatever lies beyond its end: bounds[n_seg] is n for well-formed bounds)
-    q.single = q.seg == n_seg - 1 || lds[q.seg + 1] >= q.start + q.len;
+    SegSpan q;
+    q.start = start;
+    q.len = len;
+    q.first = segment_of_uniform(lds, n_seg, start, lane);
+    q.last = q.first;
+    if (q.first != n_seg - 1 && lds[q.first + 1] < start + len) {
+        const uint32_t s = segment_of_uniform(lds, n_seg, start + len - 1, lane);
+        q.last = s > q.first ? s : q.first;
+    }
     return q;
 }
 
-// Slow path: calls f(element index, segment) for the lane's run of up to sixteen consecutive elements of the unit.
-template <typename F>
-__device__ __forceinline__ void for_each_in_run(const uint64_t *lds, uint32_t n_seg, const SegUnit &q, uint32_t lane, F f)
+// Elements at .. of a unit with several segments, up to 1024 of them and at least four: where fewer are left, the unit's
+// last four (some of them once more).  Units of more than 1024 elements are read again for this: their registers would
+// have to be indexed at run time, and few units hold several segments.
+__device__ __forceinline__ SegSpan open_part(const uint64_t *lds, uint32_t n_seg, const SegSpan &unit, uint32_t at, uint32_t lane)
 {
-    const uint32_t first = lane * kSegRun;
-    if (first >= q.len) return;
-    const uint32_t count = q.len - first < (uint32_t)kSegRun ? q.len - first : (uint32_t)kSegRun;
-    const size_t i0 = q.start + first;
-    uint32_t seg = q.single ? q.seg : segment_of_lane(lds, n_seg, i0);
-    uint64_t next = seg + 1 < n_seg ? lds[seg + 1] : ~(uint64_t)0;  // the last segment has no end
-    for (uint32_t i = 0; i < count; ++i) {
-        const size_t idx = i0 + i;
-        while (idx >= next) {  // empty segments are stepped over
-            ++seg;
-            next = seg + 1 < n_seg ? lds[seg + 1] : ~(uint64_t)0;
-        }
-        f(idx, seg);
-    }
+    const uint32_t left = unit.len - at;
+    if (left >= 4) return open_span(lds, n_seg, unit.start + at, left < (uint32_t)kSegUnit ? left : (uint32_t)kSegUnit, lane);
+    return open_span(lds, n_seg, unit.start + unit.len - 4, 4, lane);
 }
 
-// An item of work is `group` consecutive units, 1 or 4 (the host takes 4 when that still leaves every wavefront of
-// the chip several items).  Four units that lie inside one segment and are whole and aligned are taken at once,
-// sixteen quads per lane with all their loads in flight together; otherwise each unit of the item by itself.
-struct SegItem {
-    size_t first_unit;   // of the item
-    uint32_t units;      // that exist
-    bool whole;          // the four-unit register path applies
-    uint32_t seg;        // then: the segment
+// Segments of the elements that a lane holds of a stretch of 1024: quads quad_start(j * 64 + lane, len), j = 0 .. 3.
+// split[j] (the same in all lanes): a segment ends inside a quad of row j, seg[j][1 .. 3] may differ from seg[j][0].
+struct SegQuads {
+    uint32_t seg[kSegQ][4];
+    bool split[kSegQ];
 };
 
-__device__ __forceinline__ SegItem open_segment_item(const uint64_t *lds, uint32_t n_seg, size_t n, size_t n_units, size_t item,
-                                                     uint32_t group, uint32_t aligned, uint32_t lane)
+__device__ __forceinline__ SegQuads segments_of_quads(const uint64_t *lds, const SegSpan &q, uint32_t lane)
 {
-    SegItem it;
-    it.first_unit = item * group;
-    const size_t left = n_units - it.first_unit;
-    it.units = left < group ? (uint32_t)left : group;
-    it.whole = false;
-    it.seg = 0;
-    if (group == 4 && aligned) {
-        const size_t start = it.first_unit * (size_t)kSegUnit;
-        if (n - start >= (size_t)(4 * kSegUnit)) {
-            it.seg = segment_of_uniform(lds, n_seg, start, lane);
-            it.whole = it.seg == n_seg - 1 || lds[it.seg + 1] >= start + 4 * kSegUnit;
+    SegQuads r;
+    // Whether segment i has begun at offset off of the stretch, for i in (first, last]: those begin inside the stretch,
+    // so the difference fits 32 bits.
+    auto begun = [&](uint32_t i, uint32_t off) { return (uint32_t)lds[i] - (uint32_t)q.start <= off; };
+    const uint32_t span = q.last - q.first;
+    const uint32_t top = span ? 1u << (31 - __builtin_clz(span)) : 0;
+#pragma unroll
+    for (int j = 0; j < kSegQ; ++j) r.seg[j][0] = q.first;
+    for (uint32_t step = top; step != 0; step >>= 1) {
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) {
+            const uint32_t mid = r.seg[j][0] + step, in = mid < q.last ? mid : q.last;
+            if (begun(in, quad_start(j * kWave + lane, q.len)) && mid <= q.last) r.seg[j][0] = mid;
         }
     }
-    return it;
+#pragma unroll
+    for (int j = 0; j < kSegQ; ++j) {
+        const uint32_t off = quad_start(j * kWave + lane, q.len);
+        uint32_t s = r.seg[j][0];
+        const bool ends = s < q.last && begun(s + 1, off + 3);
+        r.split[j] = __builtin_amdgcn_ballot_w64(ends) != 0;
+#pragma unroll
+        for (uint32_t c = 1; c < 4; ++c) {
+            if (ends)
+                while (s < q.last && begun(s + 1, off + c)) ++s;  // empty segments are stepped over
+            r.seg[j][c] = s;
+        }
+    }
+    return r;
 }
 
-// Maxima of the segments into zeroed scales (non-negative binary32 numbers order like their bit patterns, so
-// the pieces of a segment merge with an integer atomic max).  The sixteen wavefronts of a workgroup take sixteen
-// consecutive items at a time and merge what they found through LDS first, so that a long segment costs one
-// atomic per sixteen items: thousands of atomics on one address take longer than reading the array.
-__global__ __launch_bounds__(kWave * kSegWaves) void k_seg_absmax(const float *__restrict__ x, size_t n,
-                                                                  const uint64_t *__restrict__ bounds, uint32_t n_seg,
-                                                                  size_t n_units, size_t n_items, size_t n_waves, uint32_t group,
-                                                                  uint32_t aligned, float *__restrict__ scales)
+// Scales of the four elements of row j.
+__device__ __forceinline__ v4f scales_of_quad(const float *scales, const SegQuads &sq, int j)
 {
-    extern __shared__ uint64_t seg_lds[];
-    __shared__ uint32_t post_seg[kSegWaves], post_max[kSegWaves];
-    const uint32_t lane = threadIdx.x & 63, wave = wave_in_wg();
+    const float s = scales[sq.seg[j][0]];
+    v4f r = {s, s, s, s};
+    if (sq.split[j]) {
+        r.y = scales[sq.seg[j][1]];
+        r.z = scales[sq.seg[j][2]];
+        r.w = scales[sq.seg[j][3]];
+    }
+    return r;
+}
+
+// Elements of unit u (units of U elements; the last one may be shorter, at least four).
+template <int U>
+__device__ __forceinline__ uint32_t seg_unit_len(size_t u, size_t n)
+{
+    return cap_to_unit<U>(n - u * (size_t)U);
+}
+
+// Calls f(element, segment) for the elements from `from` on, one per lane of the grid at a time.
+template <typename F>
+__device__ __forceinline__ void for_each_element(const uint64_t *lds, uint32_t n_seg, size_t from, size_t n, size_t n_waves, F f)
+{
+    for (size_t i = from + (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += n_waves * kWave)
+        f(i, segment_of_lane(lds, n_seg, i));
+}
+
+// Maxima of the segments into zeroed scales (non-negative binary32 numbers order like their bit patterns, so the pieces
+// of a segment merge with an integer atomic max).  A workgroup keeps the maxima of all segments in LDS and sends those
+// that are not zero at its end, sixty-four of them in an instruction: atomics on one address are served one after the
+// other, about 10 ns each, and the walk by position brings every workgroup to every long segment.
+// Units of Q * 256 elements: 16 quads per lane on long arrays, 4 where that leaves wavefronts without work (the plan's
+// items of four units and of one).
+// Plain loads: the array stays in the memory-side cache (256 MB), from which k_seg_encode reads it again; with
+// non-temporal loads here that second pass takes 33.4 instead of 26.8 us at 37.7 M elements and 53 instead of 43 us at
+// 61 M, this one 1 to 2 us less.
+template <int Q>
+__global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__ x, size_t n, const uint64_t *__restrict__ bounds,
+                                                       uint32_t n_seg, size_t n_units, size_t n_waves, float *__restrict__ scales)
+{
+    constexpr int U = Q * 4 * kWave;
+    extern __shared__ uint64_t seg_lds[];  // the bounds, then the maxima
+    uint32_t *best = reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1);
+    const uint32_t lane = threadIdx.x & 63;
+    v4f v[Q];
+    auto fetch = [&](size_t u) {
+        const uint32_t len = seg_unit_len<U>(u, n);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) v[j] = ldg_floats<0>(x + u * (size_t)U, quad_start(j * kWave + lane, len));
+    };
+    size_t u = first_unit(kSegWaves);
+    if (u < n_units) fetch(u);
     load_bounds(bounds, n_seg, n, seg_lds);
+    for (uint32_t i = threadIdx.x; i < n_seg; i += kSegWg) best[i] = 0;
     __syncthreads();
-    unsigned int *sc = reinterpret_cast<unsigned int *>(scales);
-    // every wavefront of the workgroup makes the same number of rounds (the barriers below)
-    for (size_t base = (size_t)blockIdx.x * kSegWaves; base < n_items; base += n_waves) {
-        const size_t item = base + wave;
-        uint32_t my_seg = ~0u, my_max = 0;  // what this wavefront's item adds to one segment, if it is that simple
-        if (item < n_items) {
-            const SegItem it = open_segment_item(seg_lds, n_seg, n, n_units, item, group, aligned, lane);
-            if (it.whole) {
-                const v4f *p4 = reinterpret_cast<const v4f *>(x + it.first_unit * (size_t)kSegUnit);
-                v4f v[4 * kSegQ];
+    uint32_t run = 0, run_seg = 0;  // of the whole units of one segment so far
+    auto post = [&] {
+        const uint32_t m = wave_max_u32(run);
+        if (lane == 0 && m != 0) atomicMax(best + run_seg, m);
+        run = 0;
+    };
+    for (; u < n_units; u += n_waves) {
+        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)U, seg_unit_len<U>(u, n), lane);
+        if (q.first == q.last) {
+            float fm = 0.0f;
 #pragma unroll
-                for (int j = 0; j < 4 * kSegQ; ++j) v[j] = ldg<1>(p4 + j * kWave + lane);
-                float fm = 0.0f;
+            for (int j = 0; j < Q; ++j) fm = max4_abs(v[j], fm);
+            if (u + n_waves < n_units) fetch(u + n_waves);
+            if (q.first != run_seg) {
+                post();
+                run_seg = q.first;
+            }
+            run = run > f2u(fm) ? run : f2u(fm);
+        } else {
+            for (uint32_t at = 0; at < q.len; at += kSegUnit) {
+                const SegSpan part = open_part(seg_lds, n_seg, q, at, lane);
+                v4f w[kSegQ];
 #pragma unroll
-                for (int j = 0; j < 4 * kSegQ; ++j) fm = max4_abs(v[j], fm);
-                my_seg = it.seg;
-                my_max = wave_max_u32(f2u(fm));
-            } else {
-                for (uint32_t r = 0; r < it.units; ++r) {
-                    const SegUnit q = open_segment_unit(seg_lds, n_seg, n, it.first_unit + r, lane);
-                    if (q.single && q.len == (uint32_t)kSegUnit && aligned) {
-                        const v4f *p4 = reinterpret_cast<const v4f *>(x + q.start);
-                        float fm = 0.0f;
+                for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<0>(x + part.start, quad_start(j * kWave + lane, part.len));
+                const SegQuads sq = segments_of_quads(seg_lds, part, lane);
 #pragma unroll
-                        for (int j = 0; j < kSegQ; ++j) fm = max4_abs(ldg<1>(p4 + j * kWave + lane), fm);
-                        const uint32_t m = wave_max_u32(f2u(fm));
-                        if (group == 1) {  // the item is this unit: merged with the workgroup's other items below
-                            my_seg = q.seg;
-                            my_max = m;
-                        } else if (lane == 0 && m != 0) {
-                            atomicMax(sc + q.seg, m);
-                        }
+                for (int j = 0; j < kSegQ; ++j) {
+                    const uint32_t a[4] = {abs_bits(w[j].x), abs_bits(w[j].y), abs_bits(w[j].z), abs_bits(w[j].w)};
+                    if (sq.split[j]) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (a[c] != 0) atomicMax(best + sq.seg[j][c], a[c]);
                     } else {
-                        uint32_t run = 0, run_seg = 0;
-                        for_each_in_run(seg_lds, n_seg, q, lane, [&](size_t idx, uint32_t seg) {
-                            if (seg != run_seg) {
-                                if (run != 0) atomicMax(sc + run_seg, run);
-                                run = 0;
-                                run_seg = seg;
-                            }
-                            const uint32_t a = abs_bits(x[idx]);
-                            run = run > a ? run : a;
-                        });
-                        if (run != 0) atomicMax(sc + run_seg, run);
+                        const uint32_t m01 = a[0] > a[1] ? a[0] : a[1], m23 = a[2] > a[3] ? a[2] : a[3];
+                        const uint32_t m = m01 > m23 ? m01 : m23;
+                        if (m != 0) atomicMax(best + sq.seg[j][0], m);
                     }
                 }
             }
+            if (u + n_waves < n_units) fetch(u + n_waves);
         }
-        if (lane == 0) {
-            post_seg[wave] = my_seg;
-            post_max[wave] = my_max;
-        }
-        __syncthreads();
-        if (wave == 0 && lane < (uint32_t)kSegWaves) {
-            // lane l speaks for the wavefronts that posted the same segment as wavefront l, if it is the first of them
-            const uint32_t s = post_seg[lane];
-            uint32_t m = 0;
-            bool first = true;
-            for (uint32_t j = 0; j < (uint32_t)kSegWaves; ++j) {
-                if (post_seg[j] == s) {
-                    if (j < lane) first = false;
-                    m = m > post_max[j] ? m : post_max[j];
-                }
-            }
-            if (first && s != ~0u && m != 0) atomicMax(sc + s, m);
-        }
-        __syncthreads();  // the posts are rewritten in the next round
     }
+    post();
+    for_each_element(seg_lds, n_seg, n_units * (size_t)U, n, n_waves, [&](size_t i, uint32_t seg) {
+        const uint32_t a = abs_bits(x[i]);
+        if (a != 0) atomicMax(best + seg, a);
+    });
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n_seg; i += kSegWg)
+        if (best[i] != 0) atomicMax(reinterpret_cast<unsigned int *>(scales) + i, best[i]);
 }
 
-// Compression with the segments' scales (computed by k_seg_absmax or handed in).
+// Compression with the segments' scales (computed by k_seg_absmax or handed in).  (61 M elements right after their
+// maxima: 49 us with 8, 16, 24 or 32 wavefronts per compute unit.)
 template <bool REMAP>
-__global__ __launch_bounds__(kWave * kSegWaves) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x,
-                                                                  size_t n, const uint64_t *__restrict__ bounds, uint32_t n_seg,
-                                                                  size_t n_units, size_t n_waves, uint32_t aligned,
-                                                                  const float *__restrict__ scales, uint8_t *__restrict__ codes)
+__global__ __launch_bounds__(kSegWg) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                       const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                       size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
 {
-    extern __shared__ uint64_t seg_lds[];  // the bounds (n_seg + 1 entries, rounded up to an even count of words), then the search table
+    extern __shared__ uint64_t seg_lds[];  // the bounds (n_seg + 1 entries), then the search table
     const uint32_t lane = threadIdx.x & 63;
+    struct Slot {
+        v4f v[kSegQ];
+    } a, b;
+    auto fetch = [&](size_t u, Slot &sl) {
+        const uint32_t len = seg_unit_len<kSegUnit>(u, n);
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) sl.v[j] = ldg_floats<1>(x + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
+    };
+    const size_t u0 = first_unit(kSegWaves);
+    if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are copied
     load_bounds(bounds, n_seg, n, seg_lds);
-    Search sr = load_bucket_table(tab, reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1), kWave * kSegWaves);
+    Search sr = load_bucket_table(tab, reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1), kSegWg);
     sr.marks = REMAP;
     __syncthreads();
-    for (size_t u = first_unit(kSegWaves); u < n_units; u += n_waves) {
-        const SegUnit q = open_segment_unit(seg_lds, n_seg, n, u, lane);
-        if (q.single && q.len == (uint32_t)kSegUnit && aligned) {
-            const v4f *p4 = reinterpret_cast<const v4f *>(x + q.start);
-            v4f v[kSegQ];
-#pragma unroll
-            for (int j = 0; j < kSegQ; ++j) v[j] = ldg<1>(p4 + j * kWave + lane);
-            const float s = scales[q.seg];
+    walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
+        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        uint32_t cw[kSegQ];
+        if (q.first == q.last) {
+            const float s = scales[q.first];
             const float d = s == 0.0f ? 1.0f : s;
-            const float r = 1.0f / d;
-            const bool recip = reciprocal_ok(d);
-            uint32_t cw[kSegQ];
-            encode_quads<true, kSegQ>(sr, v, d, r, recip, cw);
-            uint32_t *c4 = reinterpret_cast<uint32_t *>(codes + q.start);
-#pragma unroll
-            for (int j = 0; j < kSegQ; ++j) stg<1>(c4 + j * kWave + lane, cw[j]);
+            encode_quads<true, kSegQ>(sr, sl.v, d, 1.0f / d, reciprocal_ok(d), cw);
         } else {
-            uint32_t cur = ~0u;
-            float d = 1.0f, r = 1.0f;
-            bool recip = true;
-            for_each_in_run(seg_lds, n_seg, q, lane, [&](size_t idx, uint32_t seg) {
-                if (seg != cur) {
-                    cur = seg;
-                    const float s = scales[seg];
-                    d = s == 0.0f ? 1.0f : s;
-                    r = 1.0f / d;
-                    recip = reciprocal_ok(d);
-                }
-                codes[idx] = (uint8_t)encode_one<false>(sr, x[idx], d, r, recip);
-            });
+            const SegQuads sq = segments_of_quads(seg_lds, q, lane);
+            v4f d[kSegQ];
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) d[j] = scales_of_quad(scales, sq, j);
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) {
+                const v4f v = sl.v[j];
+                const uint32_t s0 = search_sum_exact(sr, v.x / (d[j].x == 0.0f ? 1.0f : d[j].x));
+                const uint32_t s1 = search_sum_exact(sr, v.y / (d[j].y == 0.0f ? 1.0f : d[j].y));
+                const uint32_t s2 = search_sum_exact(sr, v.z / (d[j].z == 0.0f ? 1.0f : d[j].z));
+                const uint32_t s3 = search_sum_exact(sr, v.w / (d[j].w == 0.0f ? 1.0f : d[j].w));
+                cw[j] = pack_codes(sr, s0, s1, s2, s3, v);
+            }
         }
-    }
+        uint8_t *pc = codes + q.start;
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) {
+            const uint32_t k = j * kWave + lane;
+            if (k * 4 < q.len) stg_codes<1>(pc, quad_start(k, q.len), cw[j]);
+        }
+    });
+    for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves, [&](size_t i, uint32_t seg) {
+        const float s = scales[seg];
+        codes[i] = (uint8_t)code_exact(sr, x[i], s == 0.0f ? 1.0f : s);
+    });
 }
 
-// Decompression with the segments' scales.
-__global__ __launch_bounds__(kWave * kSegWaves) void k_seg_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
-                                                                  const float *__restrict__ scales, size_t n,
-                                                                  const uint64_t *__restrict__ bounds, uint32_t n_seg,
-                                                                  size_t n_units, size_t n_waves, uint32_t aligned,
-                                                                  float *__restrict__ out)
+// Decompression with the segments' scales.  (61 M elements: 64.8 us with conditions around the loads, 56.6 us so, with two
+// workgroups per compute unit; 61.5 us with one, 61 to 66 us with 8 or 16 code words per lane.  Plain stores: 50.8 us,
+// but the kernel that follows waits for the caches to be written back: compression and expansion together 180 instead
+// of 150 us.)
+__global__ __launch_bounds__(kSegWg) void k_seg_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
+                                                       const float *__restrict__ scales, size_t n,
+                                                       const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                       size_t n_waves, float *__restrict__ out)
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     extern __shared__ uint64_t seg_lds[];
     const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
+    struct Slot {
+        uint32_t w[kSegQ];
+    } a, b;
+    auto fetch = [&](size_t u, Slot &sl) {
+        const uint32_t len = seg_unit_len<kSegUnit>(u, n);
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) sl.w[j] = ldg_codes<1>(codes + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
+    };
+    const size_t u0 = first_unit(kSegWaves);
+    if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are built
     load_bounds(bounds, n_seg, n, seg_lds);
     load_lut(tab, lut);
     __syncthreads();
-    for (size_t u = first_unit(kSegWaves); u < n_units; u += n_waves) {
-        const SegUnit q = open_segment_unit(seg_lds, n_seg, n, u, lane);
-        if (q.single && q.len == (uint32_t)kSegUnit && aligned) {
-            const uint32_t *c4 = reinterpret_cast<const uint32_t *>(codes + q.start);
-            uint32_t w[kSegQ];
+    walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
+        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        float *po = out + q.start;
+        auto expand = [&](int j, v4f s) {
+            const uint32_t k = j * kWave + lane;
+            v4f r;
+            r.x = lut_at<0>(lut, sl.w[j], lane4) * s.x;
+            r.y = lut_at<1>(lut, sl.w[j], lane4) * s.y;
+            r.z = lut_at<2>(lut, sl.w[j], lane4) * s.z;
+            r.w = lut_at<3>(lut, sl.w[j], lane4) * s.w;
+            if (k * 4 < q.len) stg_floats<2>(po + quad_start(k, q.len), r);
+        };
+        if (q.first == q.last) {
+            const float s = scales[q.first];
 #pragma unroll
-            for (int j = 0; j < kSegQ; ++j) w[j] = ldg<1>(c4 + j * kWave + lane);
-            const float s = scales[q.seg];
-            v4f *o4 = reinterpret_cast<v4f *>(out + q.start);
-#pragma unroll
-            for (int j = 0; j < kSegQ; ++j) {
-                v4f r;
-                r.x = lut_at<0>(lut, w[j], lane4) * s;
-                r.y = lut_at<1>(lut, w[j], lane4) * s;
-                r.z = lut_at<2>(lut, w[j], lane4) * s;
-                r.w = lut_at<3>(lut, w[j], lane4) * s;
-                stg<2>(o4 + j * kWave + lane, r);
-            }
+            for (int j = 0; j < kSegQ; ++j) expand(j, v4f{s, s, s, s});
         } else {
-            uint32_t cur = ~0u;
-            float s = 0.0f;
-            for_each_in_run(seg_lds, n_seg, q, lane, [&](size_t idx, uint32_t seg) {
-                if (seg != cur) {
-                    cur = seg;
-                    s = scales[seg];
-                }
-                out[idx] = lut_code(lut, codes[idx], lane4) * s;
-            });
+            const SegQuads sq = segments_of_quads(seg_lds, q, lane);
+            v4f s[kSegQ];
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) s[j] = scales_of_quad(scales, sq, j);
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) expand(j, s[j]);
         }
-    }
+    });
+    for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves,
+                     [&](size_t i, uint32_t seg) { out[i] = lut_code(lut, codes[i], lane4) * scales[seg]; });
 }
 
 // Decompression of K workers' buffers and their average (optionally with a local fp32 array as the first term)
 // with the segments' scales: the ordered sum of the other averaging kernels (product and sum rounded separately,
-// workers in index order, then the division by the number of terms), any number of workers, four at a time in
-// flight on the register path.
-__global__ __launch_bounds__(kWave * kSegWaves) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
-                                                               const float *__restrict__ local, size_t n,
-                                                               const uint64_t *__restrict__ bounds, uint32_t n_seg,
-                                                               size_t n_units, size_t n_waves, uint32_t aligned,
-                                                               float *__restrict__ out)
+// workers in index order, then the division by the number of terms), any number of workers, AHEAD at a time in flight.
+template <int AHEAD>
+__global__ __launch_bounds__(kSegWg) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
+                                                    const float *__restrict__ local, size_t n,
+                                                    const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                    size_t n_waves, float *__restrict__ out)
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     extern __shared__ uint64_t seg_lds[];
@@ -323,62 +374,102 @@ __global__ __launch_bounds__(kWave * kSegWaves) void k_seg_avg(const uint32_t *_
     const bool pow2 = (terms & (terms - 1)) == 0;  // then acc * (1 / terms) equals acc / terms exactly
     const float rk = 1.0f / fk;
     auto mean_of = [&](float acc) { return pow2 ? acc * rk : acc / fk; };
+    uint32_t w[AHEAD][kSegQ];
+    v4f acc[kSegQ];
+    // The local term's quads of unit u and the first AHEAD workers' codes.
+    auto fetch_workers = [&](size_t start, uint32_t len, int k0) {
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) {
+            const uint8_t *pc = p.codes[k0 + c < K ? k0 + c : K - 1] + start;  // a place past the last worker repeats it and is not added
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) w[c][j] = ldg_codes<1>(pc, quad_start(j * kWave + lane, len));
+        }
+    };
+    auto fetch = [&](size_t u) {
+        const size_t start = u * (size_t)kSegUnit;
+        const uint32_t len = seg_unit_len<kSegUnit>(u, n);
+        if (local) {
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) acc[j] = ldg_floats<1>(local + start, quad_start(j * kWave + lane, len));
+        } else {
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) acc[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        if (K > 0) fetch_workers(start, len, 0);
+    };
+    size_t u = first_unit(kSegWaves);
+    if (u < n_units) fetch(u);  // the first loads are in flight while the tables are built
     load_bounds(bounds, n_seg, n, seg_lds);
     load_lut(tab, lut);
     __syncthreads();
-    constexpr int kAhead = 4;  // workers whose code words are requested together
-    for (size_t u = first_unit(kSegWaves); u < n_units; u += n_waves) {
-        const SegUnit q = open_segment_unit(seg_lds, n_seg, n, u, lane);
-        if (q.single && q.len == (uint32_t)kSegUnit && aligned) {
-            v4f acc[kSegQ];
-            if (local) {  // the sum starts at +0: a local -0 becomes +0
-                const v4f *l4 = reinterpret_cast<const v4f *>(local + q.start);
+    for (; u < n_units; u += n_waves) {
+        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
 #pragma unroll
-                for (int j = 0; j < kSegQ; ++j) {
-                    const v4f l = ldg<1>(l4 + j * kWave + lane);
-                    acc[j] = v4f{0.0f + l.x, 0.0f + l.y, 0.0f + l.z, 0.0f + l.w};
-                }
-            } else {
+        for (int j = 0; j < kSegQ; ++j)  // the sum starts at +0: a local -0 becomes +0
+            acc[j] = v4f{0.0f + acc[j].x, 0.0f + acc[j].y, 0.0f + acc[j].z, 0.0f + acc[j].w};
+        auto add = [&](int c, int j, v4f s) {
+            acc[j].x = acc[j].x + lut_at<0>(lut, w[c][j], lane4) * s.x;
+            acc[j].y = acc[j].y + lut_at<1>(lut, w[c][j], lane4) * s.y;
+            acc[j].z = acc[j].z + lut_at<2>(lut, w[c][j], lane4) * s.z;
+            acc[j].w = acc[j].w + lut_at<3>(lut, w[c][j], lane4) * s.w;
+        };
+        if (q.first == q.last) {
+            for (int k0 = 0; k0 < K; k0 += AHEAD) {
+                if (k0 != 0) fetch_workers(q.start, q.len, k0);
+                float s[AHEAD];
 #pragma unroll
-                for (int j = 0; j < kSegQ; ++j) acc[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-            }
-            for (int k0 = 0; k0 < K; k0 += kAhead) {
-                uint32_t w[kAhead][kSegQ];
-                float sc[kAhead];
+                for (int c = 0; c < AHEAD; ++c) s[c] = p.scales[k0 + c < K ? k0 + c : K - 1][q.first];
 #pragma unroll
-                for (int c = 0; c < kAhead; ++c) {
-                    const int k = k0 + c < K ? k0 + c : K - 1;  // a place past the last worker repeats it and is not added
-                    const uint32_t *c4 = reinterpret_cast<const uint32_t *>(p.codes[k] + q.start);
-                    sc[c] = p.scales[k][q.seg];
-#pragma unroll
-                    for (int j = 0; j < kSegQ; ++j) w[c][j] = ldg<1>(c4 + j * kWave + lane);
-                }
-#pragma unroll
-                for (int c = 0; c < kAhead; ++c) {
+                for (int c = 0; c < AHEAD; ++c) {
                     if (k0 + c < K) {
 #pragma unroll
-                        for (int j = 0; j < kSegQ; ++j) {
-                            acc[j].x = acc[j].x + lut_at<0>(lut, w[c][j], lane4) * sc[c];
-                            acc[j].y = acc[j].y + lut_at<1>(lut, w[c][j], lane4) * sc[c];
-                            acc[j].z = acc[j].z + lut_at<2>(lut, w[c][j], lane4) * sc[c];
-                            acc[j].w = acc[j].w + lut_at<3>(lut, w[c][j], lane4) * sc[c];
-                        }
+                        for (int j = 0; j < kSegQ; ++j) add(c, j, v4f{s[c], s[c], s[c], s[c]});
                     }
                 }
             }
-            v4f *o4 = reinterpret_cast<v4f *>(out + q.start);
-#pragma unroll
-            for (int j = 0; j < kSegQ; ++j)
-                stg<2>(o4 + j * kWave + lane, v4f{mean_of(acc[j].x), mean_of(acc[j].y), mean_of(acc[j].z), mean_of(acc[j].w)});
         } else {
-            for_each_in_run(seg_lds, n_seg, q, lane, [&](size_t idx, uint32_t seg) {
-                float a = 0.0f;
-                if (local) a = a + local[idx];
-                for (int k = 0; k < K; ++k) a = a + lut_code(lut, p.codes[k][idx], lane4) * p.scales[k][seg];
-                out[idx] = mean_of(a);
-            });
+            const SegQuads sq = segments_of_quads(seg_lds, q, lane);
+            for (int k0 = 0; k0 < K; k0 += AHEAD) {
+                if (k0 != 0) fetch_workers(q.start, q.len, k0);
+                float s[AHEAD][kSegQ];
+#pragma unroll
+                for (int c = 0; c < AHEAD; ++c)
+#pragma unroll
+                    for (int j = 0; j < kSegQ; ++j) s[c][j] = p.scales[k0 + c < K ? k0 + c : K - 1][sq.seg[j][0]];
+#pragma unroll
+                for (int j = 0; j < kSegQ; ++j) {
+                    if (!sq.split[j]) {
+#pragma unroll
+                        for (int c = 0; c < AHEAD; ++c)
+                            if (k0 + c < K) add(c, j, v4f{s[c][j], s[c][j], s[c][j], s[c][j]});
+                    } else {
+                        v4f t[AHEAD];
+#pragma unroll
+                        for (int c = 0; c < AHEAD; ++c) t[c] = scales_of_quad(p.scales[k0 + c < K ? k0 + c : K - 1], sq, j);
+#pragma unroll
+                        for (int c = 0; c < AHEAD; ++c)
+                            if (k0 + c < K) add(c, j, t[c]);
+                    }
+                }
+            }
+        }
+        v4f r[kSegQ];
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) r[j] = v4f{mean_of(acc[j].x), mean_of(acc[j].y), mean_of(acc[j].z), mean_of(acc[j].w)};
+        if (u + n_waves < n_units) fetch(u + n_waves);
+        float *po = out + q.start;
+#pragma unroll
+        for (int j = 0; j < kSegQ; ++j) {
+            const uint32_t k = j * kWave + lane;
+            if (k * 4 < q.len) stg_floats<2>(po + quad_start(k, q.len), r[j]);
         }
     }
+    for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves, [&](size_t i, uint32_t seg) {
+        float a = 0.0f;
+        if (local) a = a + local[i];
+        for (int k = 0; k < K; ++k) a = a + lut_code(lut, p.codes[k][i], lane4) * p.scales[k][seg];
+        out[i] = mean_of(a);
+    });
 }
 
 }  // namespace

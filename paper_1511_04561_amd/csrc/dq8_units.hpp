@@ -22,7 +22,7 @@ constexpr int kUnitQuads = kUnit / (4 * kWave);  // 16 quads per lane when one w
 // The kernels for tensors back to back with one scale each (segments) walk the array in units of their own.
 constexpr int kSegQ = 4;                     // quads per lane
 constexpr int kSegUnit = kSegQ * 4 * kWave;  // 1024 elements per unit
-constexpr int kSegWaves = 16;                // wavefronts per workgroup
+constexpr int kSegWaves = 8;                 // wavefronts per workgroup
 
 // Geometry of unit u.  All values are wave-uniform.
 struct Unit {

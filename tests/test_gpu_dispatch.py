@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_1511_04561_amd import workloads
-from tests.test_gpu_parity import Guarded, check_encode_decode, check_error_stats, dev, same_bits  # noqa: F401
+from tests.test_gpu_parity import Guarded, bounds_dev, check_encode_decode, check_error_stats, check_segments, dev, same_bits  # noqa: F401
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -51,3 +51,28 @@ def test_blocks_that_start_at_any_element(dq8, n, block, offset):
     x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
     check_encode_decode(dq8, (n + offset) % 4, x, block, x_off=offset, c_off=offset, tag="offset %d" % offset)
     check_encode_decode(dq8, (n + offset + 1) % 4, x, block, x_off=offset, c_off=(offset + 1) % 4, tag="offsets %d" % offset)
+
+
+# units of 1024 and 4096 elements and a last one of four or more; 1 to 3 elements that are in none; a wavefront, a workgroup, more
+# than the grid; the array from which maxima take 16 quads per lane (16 Mi elements), and a little less
+@pytest.mark.parametrize("n", [3, 4, 5, 1027, 1028, 8 * 1024 + 1, 4096 * 1024 + 2, (1 << 24) - 1, (1 << 24) + 4099])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_segments_and_whole_arrays_at_any_element(dq8, n, offset):
+    """Tensors back to back, and arrays with one scale, whose ends and starts are aligned for an element only."""
+    rng = np.random.Generator(np.random.PCG64(8200 + n % 83 + offset))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    kind = (n + offset) % 4
+    if n > 4096:
+        check_encode_decode(dq8, kind, x, 0, x_off=offset, c_off=offset, tag="one block, offset %d" % offset)
+    inner = np.concatenate([rng.integers(0, n + 1, 5), n - np.minimum(n, [1, 2, 5, 7]), np.minimum(n, [1, 2, 6])])
+    bounds = np.concatenate([[0], np.sort(inner), [n]])
+    check_segments(dq8, kind, x, bounds, x_off=offset, c_off=(offset + n) % 4, tag="any element")
+    K, n_seg = (9 if n % 2 else 3), len(bounds) - 1
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
+    want = oracle.decode_accumulate_avg_segments(kind, cl, sl, bounds, local=x)
+    go = Guarded(n, np.float32, offset)
+    dq8.decode_accumulate_avg_segments(kind, [dev(c, (offset + k) % 4) for k, c in enumerate(cl)], [dev(s) for s in sl], bounds_dev(bounds),
+                                       out=go.t, local=dev(x, offset))
+    same_bits(go.t, want, "segment average")
+    go.check("segment average")
