@@ -19,13 +19,15 @@ namespace {
 // them): 0 <= e < 2^129, 2^-149 <= |x| < 2^128.  The quotient and every intermediate of the division are
 // therefore normal binary64 numbers far from overflow and underflow, which is the one case in which the
 // division's range reduction, its rescaling and its special-case selection do nothing.  What is left is the
-// reciprocal estimate, two Newton steps on it, the quotient estimate and its correction with the exactly
-// computed remainder, which yields the correctly rounded quotient (same operations, same order as the general
-// division).
+// reciprocal estimate (v_rcp_f64, 2^29 units in the last place: a relative error of 2^-23), Newton steps on it, the
+// quotient estimate and its correction with the remainder.  One Newton step is enough because |x| has 24 bits: it leaves
+// a relative error of 2^-46, so e * r is off by as much, the remainder e - |x| q has at most 31 significant bits and is
+// exact, and what is rounded in the last operation is off by 2^-92 of the quotient.  The quotient of a 53-bit and a 24-bit
+// number that is not halfway between two binary64 numbers is at least 2^-78 of itself away from there, and it cannot be
+// halfway (e would need 54 bits): the result is the correctly rounded quotient.
 __device__ __forceinline__ double quotient_of_magnitudes(double e, double ax)
 {
     double r = __builtin_amdgcn_rcp(ax);
-    r = __builtin_fma(__builtin_fma(-ax, r, 1.0), r, r);
     r = __builtin_fma(__builtin_fma(-ax, r, 1.0), r, r);
     const double q = e * r;
     return __builtin_fma(__builtin_fma(-ax, q, e), r, q);
@@ -47,7 +49,7 @@ __device__ __forceinline__ void load_magnitude_lut(const uint32_t *tab, float *l
 }
 
 // wavefronts per workgroup: two workgroups (two value tables) share a compute unit, six wavefronts per SIMD
-// (88.4 us with 8, 85.4 us with 12, 106 us with 16, where the registers no longer suffice)
+// (25 million elements in one block: 41 us; one workgroup of 16 wavefronts, whose atomics at the end are half as many, 57 us)
 constexpr int kStatsWaves = 12;
 constexpr int kStatsWg = kStatsWaves * kWave;
 
@@ -67,7 +69,7 @@ struct ErrorSums {
 // are served one after the other, about 10 ns each whoever sends them, so what the wavefronts of a workgroup still hold
 // at the end is combined in LDS first and lanes 0 .. 3 of a group of four send the four numbers in one instruction.
 // (25 million elements as one block: four atomics from each of 6104 wavefronts took 304 us, ten times the arithmetic;
-// with 512 workgroups that combine first 43 us.)
+// with 512 workgroups that combine first 43 us, 41 us with one Newton step in the quotient instead of two.)
 // means (may be NULL): the workgroup that finishes last forms them from stats[], which saves the launch of
 // k_error_means.  means[0], zeroed like stats[], counts the workgroups until then; every workgroup counts itself after
 // its atomics have been performed, so the one that counts last sees them all (it reads with atomic loads: plain ones
