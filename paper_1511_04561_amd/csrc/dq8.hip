@@ -392,7 +392,7 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
     // three wavefronts per compute unit are the best when every unit is a whole full-size one; four otherwise
     // (smaller units, or blocks that end inside units)
     const size_t full_unit = (size_t)q * 4 * kWave;
-    int wpc = (Bq >= n || Bq % full_unit == 0) ? g_tune.amax_wpc : 4;
+    int wpc = Bq % full_unit == 0 ? g_tune.amax_wpc : 4;
     fit_unit_to_block(Bq, &q, &wpc);
     if (g_tune.amax_waste && Bq < n) {
         // A block that is not whole units ends in a short unit, whose lanes repeat loads.  Smaller units (down to
@@ -410,7 +410,11 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
         q = best;
         wpc = best_wpc;
     }
-    Plan p = make_plan(n, block, st.cus, wpc, 1, kWavesPerWg, (size_t)q * 4 * kWave);
+    const size_t unit = (size_t)q * 4 * kWave;
+    Plan p = make_plan(n, block, st.cus, wpc, 1, kWavesPerWg, unit);
+    // blocks of whole units: the array's whole units, a shorter last one extra
+    const bool whole = p.B % unit == 0 && ((uintptr_t)x & 3) == 0;
+    if (whole) p.n_units = n / unit;
     size_t per_wave = 0;
     if (p.upb > 1) {
         if (!zeroed) {
@@ -421,9 +425,13 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
         }
         per_wave = (p.n_units + p.n_teams - 1) / p.n_teams;
     }
-#define DQ8_AMAX(Q, NT)                                                                                          \
-    hipLaunchKernelGGL((k_absmax<Q, NT>), dim3(p.grid), dim3(kWg), 0, stream, x, n, p.B, p.nb, p.upb, p.n_units, \
-                       p.n_teams, per_wave, scales)
+#define DQ8_AMAX(Q, NT)                                                                                                \
+    if (whole)                                                                                                         \
+        hipLaunchKernelGGL((k_absmax_whole<Q, NT>), dim3(p.grid), dim3(kWg), 0, stream, x, n, p.upb, p.n_units,        \
+                           p.n_teams, per_wave, scales);                                                               \
+    else                                                                                                               \
+        hipLaunchKernelGGL((k_absmax<Q, NT>), dim3(p.grid), dim3(kWg), 0, stream, x, n, p.B, p.nb, p.upb, p.n_units,   \
+                           p.n_teams, per_wave, scales)
 #define DQ8_AMAX_Q(NT)                      \
     switch (q) {                            \
     case 1: DQ8_AMAX(1, NT); break;         \

@@ -1,0 +1,67 @@
+"""What the compiler makes of loops whose rate depends on it (CPU only: hipcc writes gfx950 assembly without a GPU).
+
+A streaming loop runs at memory speed only while its loads stay in flight.  Changes of the source that look harmless
+(a second way to load, a condition around the loads) have made the compiler wait for all of them at once, which no test of
+the results shows."""
+import functools
+import os
+import re
+import shutil
+import subprocess
+import tempfile
+
+import pytest
+
+from paper_1511_04561_amd import build
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(build.hipcc()) or shutil.which(build.hipcc())), reason="needs hipcc")
+
+#: kernels of the headers, as explicit instantiations
+KERNELS = """
+template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def assembly():
+    """Kernel name without its namespace -> list of basic blocks, each a list of instructions."""
+    with tempfile.TemporaryDirectory() as d:
+        src, out = os.path.join(d, "kernels.hip"), os.path.join(d, "kernels.s")
+        with open(src, "w") as f:
+            f.write('#include <hip/hip_runtime.h>\n#include "dq8_device.hpp"\n#include "dq8_kernels_codec.hpp"\nnamespace {\n%s}\n' % KERNELS)
+        flags = [f for f in build.FLAGS if f != "-shared"]
+        subprocess.check_call([build.hipcc()] + flags + ["-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "-S",
+                                                        "--cuda-device-only", "-o", out, src])
+        with open(out) as f:
+            lines = f.read().split("\n")
+    kernels, blocks = {}, None
+    for line in lines:
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            blocks = kernels.setdefault(re.sub(r"^_ZN12_GLOBAL__N_1\d\d?", "", m.group(1)), [[]])
+        elif line.startswith(".Lfunc_end"):
+            blocks = None
+        elif blocks is not None and re.match(r"^\.LBB\w+:", line):
+            blocks.append([])
+        elif blocks is not None and re.match(r"^\s+(v_|s_|ds_|global_|buffer_|flat_|scratch_)", line):
+            blocks[-1].append(line.split(";")[0].strip())
+            if blocks[-1][-1].startswith("s_cbranch"):
+                blocks.append([])
+    return kernels
+
+
+def kernel(prefix):
+    found = [b for name, b in assembly().items() if name.startswith(prefix)]
+    assert len(found) == 1, prefix
+    return found[0]
+
+
+def waits(block):
+    """The vmcnt of the block's waits, in order."""
+    return [int(m.group(1)) for i in block for m in re.finditer(r"vmcnt\((\d+)\)", i)]
+
+
+def test_block_maxima_keep_their_loads_in_flight():
+    """k_absmax_whole takes its sixteen quads in groups of four and requests each again at once: a wait leaves twelve loads."""
+    loops = [b for b in kernel("k_absmax_wholeILi16ELi1E") if sum(i.startswith("global_load_dwordx4") for i in b) == 16 and waits(b)]
+    assert sum(min(waits(b)) >= 12 for b in loops) == 1, [waits(b) for b in loops]

@@ -53,6 +53,19 @@ def test_blocks_that_start_at_any_element(dq8, n, block, offset):
     check_encode_decode(dq8, (n + offset + 1) % 4, x, block, x_off=offset, c_off=(offset + 1) % 4, tag="offsets %d" % offset)
 
 
+@pytest.mark.parametrize("block,blocks", [(256, 40), (512, 3100), (1024, 1), (1024, 3073), (2048, 7), (4096, 1), (4096, 769), (8192, 5), (12288, 300)])
+@pytest.mark.parametrize("rest", [0, 1, 3, 4, 5, 255])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_maxima_of_blocks_of_whole_units(dq8, block, blocks, rest, offset):
+    """One unit and several per wavefront and per block, a wavefront more than the grid, a shorter last block."""
+    n = block * blocks + rest
+    rng = np.random.Generator(np.random.PCG64(6900 + n % 91))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    x[rng.integers(0, n, 1 + n // 997)] *= -50.0  # the maxima of few elements, anywhere in their units
+    want = np.maximum.reduceat(np.abs(x), np.arange(0, n, block))
+    same_bits(dq8.absmax(dev(x, offset), block), want, "maxima")
+
+
 # units of 1024 and 4096 elements and a last one of four or more; 1 to 3 elements that are in none; a wavefront, a workgroup, more
 # than the grid; the array from which maxima take 16 quads per lane (16 Mi elements), and a little less
 @pytest.mark.parametrize("n", [3, 4, 5, 1027, 1028, 8 * 1024 + 1, 4096 * 1024 + 2, (1 << 24) - 1, (1 << 24) + 4099])
