@@ -565,9 +565,23 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
 #undef DQ8_ENC_LONG
         return after_launch("k_encode_long", stream);
     }
-#define DQ8_ENC(WPB, QL, FUSED, FD)                                                                               \
-    hipLaunchKernelGGL((k_encode<WPB, QL, 1, FUSED, FD>), dim3(p.grid), dim3(kWg), lds, stream, tab, x, n, p.B, p.nb, \
-                       p.upb, p.n_units, p.n_teams, scales, codes)
+    // EVERY (one wavefront per unit with 1, 2 or 8 quads per lane): no unit of fewer than four elements but the array's last,
+    // which the kernel does after its loop.  Not with 4 quads per lane, where the plain loop already keeps its loads ahead
+    // (blocks of 1000, given scales: 56.4 us against 57.0 with EVERY), nor for teams, which it costs registers (4000:
+    // 55.8 against 58.4 us).
+    uint32_t under = 0;
+    const bool every = units_of_quads(p, n, unit, &under) && ((uintptr_t)x & 3) == 0;
+    const size_t n_long = p.n_units - (every && under != 0 ? 1 : 0);
+#define DQ8_ENC(WPB, QL, FUSED, FD)                                                                                   \
+    hipLaunchKernelGGL((k_encode<WPB, QL, 1, FUSED, FD, false>), dim3(p.grid), dim3(kWg), lds, stream, tab, x, n, p.B,    \
+                       p.nb, p.upb, p.n_units, p.n_teams, 0u, scales, codes)
+#define DQ8_ENC_E(QL, FUSED)                                                                                           \
+    if (every) {                                                                                                       \
+        hipLaunchKernelGGL((k_encode<1, QL, 1, FUSED, true, true>), dim3(p.grid), dim3(kWg), lds, stream, tab, x, n, p.B, \
+                           p.nb, p.upb, n_long, p.n_teams, under, scales, codes);                                      \
+    } else {                                                                                                           \
+        DQ8_ENC(1, QL, FUSED, true);                                                                                   \
+    }
 #define DQ8_ENC_F(WPB, QL, FD)       \
     if (fused) {                     \
         DQ8_ENC(WPB, QL, true, FD);  \
@@ -585,12 +599,24 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
         } else {
             DQ8_ENC_F(4, 4, false)
         }
+    } else if (fused && ql <= 2) {
+        if (ql == 1) {
+            DQ8_ENC(1, 1, true, true);
+        } else {
+            DQ8_ENC(1, 2, true, true);
+        }
     } else {
         switch (ql) {
-        case 1: DQ8_ENC_F(1, 1, true) break;
-        case 2: DQ8_ENC_F(1, 2, true) break;
+        case 1: DQ8_ENC_E(1, false) break;
+        case 2: DQ8_ENC_E(2, false) break;
         case 4: DQ8_ENC_F(1, 4, true) break;
-        case 8: DQ8_ENC_F(1, 8, true) break;
+        case 8:
+            if (fused) {
+                DQ8_ENC_E(8, true)
+            } else {
+                DQ8_ENC_E(8, false)
+            }
+            break;
         default:
             if (fd) {
                 DQ8_ENC_F(1, 16, true)
@@ -600,6 +626,7 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
             break;
         }
     }
+#undef DQ8_ENC_E
 #undef DQ8_ENC_F
 #undef DQ8_ENC
     return after_launch("k_encode", stream);

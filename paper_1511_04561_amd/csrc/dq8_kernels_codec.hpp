@@ -286,7 +286,11 @@ __global__ __launch_bounds__(kOneWg) void k_encode_one(const uint32_t *__restric
 // A unit shorter than that (a block that is not a power of two, the end of a block or of the
 // array) takes the same path (see quad_start); only units of fewer than four elements, and floats at addresses that
 // are not a multiple of 4, go element by element.
-template <int WPB, int QL, int NT, bool FUSED, bool FASTDIV>
+// EVERY: the host has seen that there are no such units, but for one at the end of the array that is not counted among the
+// units.  The loads then stand in the loop without a condition.  With one, the compiler has to reckon with registers of
+// a unit that was loaded and not used, and waits for every load before it forms the next addresses (given scales,
+// 61.1 M elements: blocks of 100 175.3 us, of 200 101.5 us; so 87.4 and 59.9 us).
+template <int WPB, int QL, int NT, bool FUSED, bool FASTDIV, bool EVERY>
 struct Encoder {
     static constexpr int Q = QL;
     static constexpr uint32_t TEAM = kWave * WPB;
@@ -313,7 +317,7 @@ struct Encoder {
     {
         sl.un = unit_of<U>(u, n, B, nb, upb);
         const float *px = x + sl.un.start;
-        sl.fast = sl.un.len >= 4 && ((uintptr_t)x & 3) == 0;
+        sl.fast = EVERY || (sl.un.len >= 4 && ((uintptr_t)x & 3) == 0);
         if (sl.fast) {
 #pragma unroll
             for (int it = 0; it < Q; ++it) {
@@ -383,13 +387,24 @@ struct Encoder {
     }
 };
 
-template <int WPB, int QL, int NT, bool FUSED, bool FASTDIV>
+// One wavefront compresses a last block of fewer than four elements (pointers to its elements, code bytes and scale).
+__device__ __forceinline__ void encode_under_a_quad(const Search &sr, const float *px, uint32_t len, float *scale, uint8_t *pc, uint32_t lane)
+{
+    const float v = lane < len ? px[lane] : 0.0f;
+    const float s = u2f(wave_max_u32(abs_bits(v)));
+    const float d = s == 0.0f ? 1.0f : s;
+    if (lane == 0) *scale = s;
+    if (lane < len) pc[lane] = (uint8_t)code_exact(sr, v, d);
+}
+
+// tail: with EVERY, the elements of a last unit of fewer than four (0: none); unused otherwise.
+template <int WPB, int QL, int NT, bool FUSED, bool FASTDIV, bool EVERY>
 __global__ __launch_bounds__(kWg) void k_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
-                                               size_t B, size_t nb, size_t upb, size_t n_units, size_t n_teams,
+                                               size_t B, size_t nb, size_t upb, size_t n_units, size_t n_teams, uint32_t tail,
                                                float *__restrict__ scales, uint8_t *__restrict__ codes)
 {
     static_assert(WPB == 1 || WPB == kWavesPerWg, "a team is one wavefront or the whole workgroup");
-    using Enc = Encoder<WPB, QL, NT, FUSED, FASTDIV>;
+    using Enc = Encoder<WPB, QL, NT, FUSED, FASTDIV, EVERY>;
     extern __shared__ uint32_t lds[];
     Enc e;
     e.x = x;
@@ -409,6 +424,20 @@ __global__ __launch_bounds__(kWg) void k_encode(const uint32_t *__restrict__ tab
     if (u < n_units) e.fetch(u, a);  // the first loads are in flight while the table is copied
     e.sr = load_bucket_table(tab, lds + kTeamSlots);
     __syncthreads();
+    if constexpr (EVERY) {
+        walk_units(u, n_units, n_teams, a, b, [&](size_t v, typename Enc::Slot &sl) { e.fetch(v, sl); },
+                   [&](size_t, typename Enc::Slot &sl) { e.process(sl); });
+        if (tail != 0 && blockIdx.x == gridDim.x - 1 && e.wave == 0) {
+            const size_t at = n - tail;
+            if (FUSED) {
+                encode_under_a_quad(e.sr, x + at, tail, scales + nb - 1, codes + at, e.lane);
+            } else if (e.lane < tail) {
+                const float s = scales[nb - 1];
+                codes[at + e.lane] = (uint8_t)code_exact(e.sr, x[at + e.lane], s == 0.0f ? 1.0f : s);
+            }
+        }
+        return;
+    }
     while (u < n_units) {
         size_t nx = u + n_teams;
         if (nx < n_units) e.fetch(nx, b);
@@ -530,16 +559,6 @@ __global__ __launch_bounds__(kWg) void k_encode_full(const uint32_t *__restrict_
             pc[tl] = (uint8_t)encode_one<FASTDIV>(sr, px[tl], d, r, recip);
         }
     }
-}
-
-// One wavefront compresses a last block of fewer than four elements (pointers to its elements, code bytes and scale).
-__device__ __forceinline__ void encode_under_a_quad(const Search &sr, const float *px, uint32_t len, float *scale, uint8_t *pc, uint32_t lane)
-{
-    const float v = lane < len ? px[lane] : 0.0f;
-    const float s = u2f(wave_max_u32(abs_bits(v)));
-    const float d = s == 0.0f ? 1.0f : s;
-    if (lane == 0) *scale = s;
-    if (lane < len) pc[lane] = (uint8_t)code_exact(sr, v, d);
 }
 
 // Compression of blocks of up to QL * 256 elements, one wavefront per block: k_encode_long without the exchange

@@ -91,6 +91,16 @@ inline Plan make_plan(size_t n, size_t block, int cus, int waves_per_cu, int wpb
     return p;
 }
 
+// Whether every unit of the plan has at least four elements (a quad), the array's last one apart: its length goes to
+// *tail when it is shorter, else 0.  False when that one is all there is.
+inline bool units_of_quads(const Plan &p, size_t n, size_t unit, uint32_t *tail)
+{
+    const size_t piece = p.B % unit, last = (n - (p.nb - 1) * p.B) % unit;
+    *tail = last < 4 ? (uint32_t)last : 0;
+    if (p.nb > 1 && piece != 0 && piece < 4) return false;
+    return p.n_units > (*tail != 0 ? 1u : 0u);
+}
+
 // ---- blocks of 4 .. 128 elements (powers of two): many blocks per 1024-element unit of a wavefront
 
 constexpr int kSmallQ = 4;                          // quads per lane

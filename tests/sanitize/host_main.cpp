@@ -92,6 +92,22 @@ static void check_plans()
             check_units<1024>(n, b);
             check_units<4096>(n, b);
         }
+    // units of at least four elements but the array's last
+    for (size_t unit : {(size_t)256, (size_t)512, (size_t)1024, (size_t)2048})
+        for (size_t b : {(size_t)0, (size_t)1, (size_t)3, (size_t)4, (size_t)5, (size_t)100, unit - 1, unit, unit + 1, unit + 3, unit + 4, 3 * unit + 2, two32 + 7})
+            for (size_t n : {(size_t)1, (size_t)3, (size_t)4, (size_t)7, (size_t)1001, 5 * unit + 1, 5 * unit + 4, 40 * unit + 3}) {
+                const Plan p = make_plan(n, b, 256, 32, 1, kWavesPerWg, unit);
+                uint32_t tail = 99, shortest = 99, last = 0;
+                const bool quads = units_of_quads(p, n, unit, &tail);
+                for (size_t u = 0; u < p.n_units; ++u) {
+                    const size_t blk = p.upb == 1 ? u : u / p.upb, at = blk * p.B + (u - blk * p.upb) * unit;
+                    const size_t ends = (blk + 1) * p.B < n ? (blk + 1) * p.B : n;
+                    last = (uint32_t)(ends - at < unit ? ends - at : unit);
+                    if (u + 1 < p.n_units && last < shortest) shortest = last;
+                }
+                CHECK(quads == (shortest >= 4 && (p.n_units > 1 || last >= 4)), "units of quads: n %zu block %zu unit %zu", n, b, unit);
+                CHECK(!quads || tail == (last < 4 ? last : 0), "tail %u: n %zu block %zu unit %zu", tail, n, b, unit);
+            }
     // teams of one to four wavefronts (twelve wavefronts per workgroup), a block of up to W x 1024 elements per team
     for (int W = 1; W <= 4; ++W)
         for (size_t b : {(size_t)(W * 1024), (size_t)(W * 1024 - 24), (size_t)((W - 1) * 1024 + 4)})

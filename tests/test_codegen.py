@@ -19,6 +19,7 @@ pytestmark = pytest.mark.skipif(not (os.path.exists(build.hipcc()) or shutil.whi
 #: kernels of the headers, as explicit instantiations
 KERNELS = """
 template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
+template __global__ void k_encode<1, 2, 1, false, true, true>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
 """
 
 
@@ -65,3 +66,13 @@ def test_block_maxima_keep_their_loads_in_flight():
     """k_absmax_whole takes its sixteen quads in groups of four and requests each again at once: a wait leaves twelve loads."""
     loops = [b for b in kernel("k_absmax_wholeILi16ELi1E") if sum(i.startswith("global_load_dwordx4") for i in b) == 16 and waits(b)]
     assert sum(min(waits(b)) >= 12 for b in loops) == 1, [waits(b) for b in loops]
+
+
+def test_compression_requests_the_next_block_before_it_waits():
+    """k_encode without conditions around its loads: in its loop a block is requested while the one before it is on its way."""
+    slots = []
+    for b in kernel("k_encodeILi1ELi2ELi1ELb0ELb1ELb1E")[1:]:
+        loads = [i for i, ins in enumerate(b) if ins.startswith("global_load_dwordx4")]
+        if len(loads) == 2 and waits(b):  # in the loop, where a block's loads are followed by the wait for the one before
+            slots.append(waits(b[:loads[-1]]))
+    assert len(slots) == 2 and [] in slots, slots

@@ -54,8 +54,7 @@ def test_blocks_that_start_at_any_element(dq8, n, block, offset):
 
 
 @pytest.mark.parametrize("block,blocks", [(256, 40), (512, 3100), (1024, 1), (1024, 3073), (2048, 7), (4096, 1), (4096, 769), (8192, 5), (12288, 300)])
-@pytest.mark.parametrize("rest", [0, 1, 3, 4, 5, 255])
-@pytest.mark.parametrize("offset", [0, 3])
+@pytest.mark.parametrize("rest,offset", [(0, 3), (1, 0), (3, 3), (4, 0), (255, 3)])
 def test_maxima_of_blocks_of_whole_units(dq8, block, blocks, rest, offset):
     """One unit and several per wavefront and per block, a wavefront more than the grid, a shorter last block."""
     n = block * blocks + rest
@@ -64,6 +63,26 @@ def test_maxima_of_blocks_of_whole_units(dq8, block, blocks, rest, offset):
     x[rng.integers(0, n, 1 + n // 997)] *= -50.0  # the maxima of few elements, anywhere in their units
     want = np.maximum.reduceat(np.abs(x), np.arange(0, n, block))
     same_bits(dq8.absmax(dev(x, offset), block), want, "maxima")
+
+
+@pytest.mark.parametrize("block,blocks", [(1, 3000), (3, 3000), (5, 9000), (9, 8193), (100, 700), (255, 9), (257, 8200), (500, 3), (1000, 30), (1025, 4100), (1500, 40),
+                                          (1536, 9), (2048, 2100), (4000, 12)])
+@pytest.mark.parametrize("rest,offset", [(0, 0), (1, 1), (3, 0), (4, 1)])
+def test_given_scales_and_general_blocks(dq8, block, blocks, rest, offset):
+    """Blocks whose scales are handed in or computed in the general kernel; a last block of fewer than four elements."""
+    n = block * blocks + min(rest, block - 1)
+    rng = np.random.Generator(np.random.PCG64(7700 + n % 93))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    kind = (block + rest) % 4
+    check_encode_decode(dq8, kind, x, block, x_off=offset, c_off=3 * offset, tag="general")
+    given = np.exp(rng.uniform(2, 4, oracle.dq8_oracle.n_blocks(n, block))).astype(np.float32)
+    given[::7] = 0.0
+    x[np.repeat(given, block)[:n] == 0.0] *= np.float32(0.1)
+    want, _ = oracle.encode(kind, x, block, scales=given)
+    gc = Guarded(n, np.uint8, offset)
+    dq8.encode(kind, dev(x, offset), block, scales=dev(given), codes=gc.t, scales_given=True)
+    same_bits(gc.t, want, "given scales")
+    gc.check("given scales")
 
 
 # units of 1024 and 4096 elements and a last one of four or more; 1 to 3 elements that are in none; a wavefront, a workgroup, more
