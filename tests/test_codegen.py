@@ -20,12 +20,13 @@ pytestmark = pytest.mark.skipif(not (os.path.exists(build.hipcc()) or shutil.whi
 KERNELS = """
 template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
 template __global__ void k_encode<1, 2, 1, false, true, true>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
+template __global__ void k_decode_flat<16, 8, 2, 4>(const uint32_t *, const uint8_t *, const float *, uint64_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t, uint64_t, uint32_t, float *);
 """
 
 
 @functools.lru_cache(maxsize=None)
 def assembly():
-    """Kernel name without its namespace -> list of basic blocks, each a list of instructions."""
+    """Kernel name without its namespace -> list of basic blocks, each a list of instructions; and -> vector registers."""
     with tempfile.TemporaryDirectory() as d:
         src, out = os.path.join(d, "kernels.hip"), os.path.join(d, "kernels.s")
         with open(src, "w") as f:
@@ -35,11 +36,14 @@ def assembly():
                                                         "--cuda-device-only", "-o", out, src])
         with open(out) as f:
             lines = f.read().split("\n")
-    kernels, blocks = {}, None
+    kernels, registers, blocks, name = {}, {}, None, None
     for line in lines:
         m = re.match(r"^(_Z\w+):", line)
         if m:
-            blocks = kernels.setdefault(re.sub(r"^_ZN12_GLOBAL__N_1\d\d?", "", m.group(1)), [[]])
+            name = re.sub(r"^_ZN12_GLOBAL__N_1\d\d?", "", m.group(1))
+            blocks = kernels.setdefault(name, [[]])
+        elif line.startswith("; NumVgprs:"):
+            registers[name] = int(line.split(":")[1])
         elif line.startswith(".Lfunc_end"):
             blocks = None
         elif blocks is not None and re.match(r"^\.LBB\w+:", line):
@@ -48,11 +52,12 @@ def assembly():
             blocks[-1].append(line.split(";")[0].strip())
             if blocks[-1][-1].startswith("s_cbranch"):
                 blocks.append([])
-    return kernels
+    return kernels, registers
 
 
-def kernel(prefix):
-    found = [b for name, b in assembly().items() if name.startswith(prefix)]
+def kernel(prefix, what=0):
+    """Basic blocks (0) or vector registers (1) of a kernel."""
+    found = [b for name, b in assembly()[what].items() if name.startswith(prefix)]
     assert len(found) == 1, prefix
     return found[0]
 
@@ -76,3 +81,8 @@ def test_compression_requests_the_next_block_before_it_waits():
         if len(loads) == 2 and waits(b):  # in the loop, where a block's loads are followed by the wait for the one before
             slots.append(waits(b[:loads[-1]]))
     assert len(slots) == 2 and [] in slots, slots
+
+
+def test_expansion_by_position_keeps_no_store_offsets():
+    """k_decode_flat: registers of sixteen code words, the scales and a quad, not of sixteen store offsets besides."""
+    assert kernel("k_decode_flatILi16ELi8E", 1) <= 76
