@@ -1525,11 +1525,16 @@ int dq8_decode_segments(int kind, const uint8_t *codes, const float *scales, siz
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves);
+    const int wpw = segment_waves(st->cus, n, n_seg);
+    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves, false, wpw);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)out & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    hipLaunchKernelGGL(k_seg_decode, dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, codes, scales, n, bounds, (uint32_t)n_seg, units,
-                       p.n_waves, out);
+    if (wpw == kSegWaves)
+        hipLaunchKernelGGL((k_seg_decode<kSegWaves>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, codes, scales, n, bounds,
+                           (uint32_t)n_seg, units, p.n_waves, out);
+    else
+        hipLaunchKernelGGL((k_seg_decode<2 * kSegWaves>), dim3(p.grid), dim3(2 * kSegWg), p.lds, stream, tab, codes, scales, n, bounds,
+                           (uint32_t)n_seg, units, p.n_waves, out);
     return after_launch("k_seg_decode", stream);
 }
 

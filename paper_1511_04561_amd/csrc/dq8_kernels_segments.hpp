@@ -303,11 +303,14 @@ __global__ __launch_bounds__(kSegWg) void k_seg_encode(const uint32_t *__restric
     });
 }
 
-// Decompression with the segments' scales.  (61 M elements: 64.8 us with conditions around the loads, 56.6 us so, with two
-// workgroups per compute unit; 61.5 us with one, 61 to 66 us with 8 or 16 code words per lane.  Plain stores: 50.8 us,
-// but the kernel that follows waits for the caches to be written back: compression and expansion together 180 instead
-// of 150 us.)
-__global__ __launch_bounds__(kSegWg) void k_seg_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
+// Decompression with the segments' scales.  (61 M elements: 64.8 us with conditions around the loads, 58.1 us so, with two
+// workgroups per compute unit; 61 to 66 us with 8 or 16 code words per lane or a copy of the words instead of two slots.
+// Plain stores: 50.8 us, but the kernel that follows waits for the caches to be written back: compression and expansion
+// together 180 instead of 150 us.)  The stores of a whole unit stand without a condition: 4 Mi elements 7.4 -> 7.0 us.
+// WAVES: 8, or 16 where segment_waves() says so: with 4095 segments only one workgroup's tables fit, and 16 wavefronts
+// instead of 8 take 64.3 us for 61 M elements instead of 85.9, 10.4 instead of 17.4 for 8 Mi.
+template <int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
                                                        const float *__restrict__ scales, size_t n,
                                                        const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
                                                        size_t n_waves, float *__restrict__ out)
@@ -323,7 +326,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_decode(const uint32_t *__restric
 #pragma unroll
         for (int j = 0; j < kSegQ; ++j) sl.w[j] = ldg_codes<1>(codes + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
     };
-    const size_t u0 = first_unit(kSegWaves);
+    const size_t u0 = first_unit(WAVES);
     if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are built
     load_bounds(bounds, n_seg, n, seg_lds);
     load_lut(tab, lut);
@@ -338,7 +341,10 @@ __global__ __launch_bounds__(kSegWg) void k_seg_decode(const uint32_t *__restric
             r.y = lut_at<1>(lut, sl.w[j], lane4) * s.y;
             r.z = lut_at<2>(lut, sl.w[j], lane4) * s.z;
             r.w = lut_at<3>(lut, sl.w[j], lane4) * s.w;
-            if (k * 4 < q.len) stg_floats<2>(po + quad_start(k, q.len), r);
+            if (q.len == (uint32_t)kSegUnit)
+                stg_floats<2>(po + 4 * k, r);
+            else if (k * 4 < q.len)
+                stg_floats<2>(po + quad_start(k, q.len), r);
         };
         if (q.first == q.last) {
             const float s = scales[q.first];

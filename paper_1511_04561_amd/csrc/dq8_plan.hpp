@@ -137,16 +137,25 @@ inline SmallPlan make_small_plan(size_t n, int cus, int waves_per_cu, int wpw)
 
 // ---- tensors back to back, one scale each
 
+// Wavefronts per workgroup of the kernels that keep a value table beside the bounds: kSegWaves, two such workgroups on a
+// compute unit, or twice that where only one workgroup's tables fit and there are units for more than one each.
+constexpr size_t kLdsPerCu = 160 * 1024, kValueTableBytes = 64 * 1024;
+inline int segment_waves(int cus, size_t n, size_t n_seg)
+{
+    const bool two_fit = 2 * (kValueTableBytes + (n_seg + 1) * sizeof(uint64_t)) <= kLdsPerCu;
+    return two_fit || n <= (size_t)cus * kSegWaves * kSegUnit ? kSegWaves : 2 * kSegWaves;
+}
+
 struct SegPlan {
     size_t n_units, n_items, n_waves, lds;
     uint32_t group;
     unsigned grid;
 };
 
-// Units of kSegUnit elements on up to `waves_per_cu` wavefronts per compute unit, kSegWaves per workgroup.
+// Units of kSegUnit elements on up to `waves_per_cu` wavefronts per compute unit, `waves_per_wg` per workgroup.
 // grouped (the maxima): an item of work is four units when a workgroup per compute unit still gets two items or more
 // per wavefront, else one unit (short arrays: as many wavefronts as there are units).
-inline SegPlan make_segment_plan(int cus, size_t n, size_t n_seg, int waves_per_cu, bool grouped = false)
+inline SegPlan make_segment_plan(int cus, size_t n, size_t n_seg, int waves_per_cu, bool grouped = false, int waves_per_wg = kSegWaves)
 {
     SegPlan p;
     p.n_units = (n + kSegUnit - 1) / kSegUnit;
@@ -155,8 +164,8 @@ inline SegPlan make_segment_plan(int cus, size_t n, size_t n_seg, int waves_per_
     if (p.group == 4) waves = (size_t)cus * kSegWaves;
     p.n_items = (p.n_units + p.group - 1) / p.group;
     if (waves > p.n_items) waves = p.n_items;
-    p.grid = (unsigned)((waves + kSegWaves - 1) / kSegWaves);
-    p.n_waves = (size_t)p.grid * kSegWaves;
+    p.grid = (unsigned)((waves + waves_per_wg - 1) / waves_per_wg);
+    p.n_waves = (size_t)p.grid * waves_per_wg;
     p.lds = (n_seg + 1) * sizeof(uint64_t);
     return p;
 }

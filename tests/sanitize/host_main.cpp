@@ -132,6 +132,15 @@ static void check_plans()
                 CHECK(p.n_waves <= (size_t)256 * 32 && p.lds == 18 * sizeof(uint64_t), "segment plan of %zu: size", n);
                 CHECK(p.group == 1 || p.n_items >= 2 * p.n_waves, "segment plan of %zu: too few items of four", n);
             }
+    // two workgroups with a value table on a compute unit while both fit its LDS; one of twice the size, where there is work for it, above
+    for (size_t n : {(size_t)1000, (size_t)1 << 21, ((size_t)1 << 21) + 1, (size_t)61100840})
+        for (size_t n_seg : {(size_t)1, (size_t)2047, (size_t)2048, (size_t)DQ8_MAX_SEGMENTS}) {
+            const int w = segment_waves(256, n, n_seg);
+            CHECK(w == (n_seg > 2047 && n > ((size_t)1 << 21) ? 2 * kSegWaves : kSegWaves), "%zu segments of %zu elements: %d", n_seg, n, w);
+            const SegPlan p = make_segment_plan(256, n, n_seg, 2 * kSegWaves, false, w);
+            const size_t fit = kLdsPerCu / (kValueTableBytes + p.lds), busy = (p.grid + 255) / 256;
+            CHECK(busy <= fit && p.n_waves == (size_t)p.grid * w, "%zu segments of %zu elements: %zu workgroups, %zu fit", n_seg, n, busy, fit);
+        }
     for (int K = 0; K <= DQ8_MAX_K; ++K) {
         const int c = chunk_size(K);
         CHECK(c >= 1 && c <= 8, "chunk of %d workers: %d", K, c);

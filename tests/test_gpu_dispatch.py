@@ -108,3 +108,21 @@ def test_segments_and_whole_arrays_at_any_element(dq8, n, offset):
                                        out=go.t, local=dev(x, offset))
     same_bits(go.t, want, "segment average")
     go.check("segment average")
+
+
+@pytest.mark.parametrize("n_seg", [2047, 2048, 4095])
+@pytest.mark.parametrize("n", [(1 << 21) - 5, (1 << 21) + 1027, 5 * (1 << 20) + 3])
+def test_many_segments(dq8, n_seg, n):
+    """Up to and beyond the number of segments whose bounds fit twice beside the value tables; one workgroup per compute unit and more."""
+    rng = np.random.Generator(np.random.PCG64(8600 + n % 83 + n_seg))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    bounds = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n_seg - 1)), [n]])
+    check_segments(dq8, n % 4, x, bounds, tag="many")
+    K = 2 + n_seg % 2
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
+    want = oracle.decode_accumulate_avg_segments(0, cl, sl, bounds)
+    go = Guarded(n, np.float32)
+    dq8.decode_accumulate_avg_segments(0, [dev(c) for c in cl], [dev(s) for s in sl], bounds_dev(bounds), out=go.t)
+    same_bits(go.t, want, "segment average")
+    go.check("segment average")
