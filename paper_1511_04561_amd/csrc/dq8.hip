@@ -1560,15 +1560,16 @@ int dq8_decode_accumulate_avg_segments(int kind, const uint8_t *const *codes, co
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 16);
+    const int wpw = segment_waves(st->cus, n, n_seg);
+    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves, false, wpw);
     const size_t units = whole_units(n, kSegUnit, (((uintptr_t)out | (uintptr_t)local) & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    if (K <= 4)  // all workers' codes in flight at once
-        hipLaunchKernelGGL((k_seg_avg<4>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds, (uint32_t)n_seg,
-                           units, p.n_waves, out);
+    if (wpw == kSegWaves)
+        hipLaunchKernelGGL((k_seg_avg<kSegWaves>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds,
+                           (uint32_t)n_seg, units, p.n_waves, out);
     else
-        hipLaunchKernelGGL((k_seg_avg<8>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds, (uint32_t)n_seg,
-                           units, p.n_waves, out);
+        hipLaunchKernelGGL((k_seg_avg<2 * kSegWaves>), dim3(p.grid), dim3(2 * kSegWg), p.lds, stream, tab, wp, K, local, n, bounds,
+                           (uint32_t)n_seg, units, p.n_waves, out);
     return after_launch("k_seg_avg", stream);
 }
 

@@ -365,15 +365,19 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
 
 // Decompression of K workers' buffers and their average (optionally with a local fp32 array as the first term)
 // with the segments' scales: the ordered sum of the other averaging kernels (product and sum rounded separately,
-// workers in index order, then the division by the number of terms), any number of workers, AHEAD at a time in flight.
-template <int AHEAD>
-__global__ __launch_bounds__(kSegWg) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
+// workers in index order, then the division by the number of terms), any number of workers, two at a time in flight: every
+// place past the last worker costs the loads of a worker, and every further pair of places registers of wavefronts (30.6 M
+// elements in 16 segments with 1, 2, 4, 8, 9 workers: 27.3, 37.5, 49, 72, 80 us with two at a time; 38, 52, 57, 84, 100 us
+// with four, 8 workers with eight 83 us).  WAVES as in k_seg_decode.
+template <int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
                                                     const float *__restrict__ local, size_t n,
                                                     const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
                                                     size_t n_waves, float *__restrict__ out)
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     extern __shared__ uint64_t seg_lds[];
+    constexpr int AHEAD = 2;
     const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
     const int terms = K + (local ? 1 : 0);
     const float fk = (float)terms;
@@ -403,7 +407,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_avg(const uint32_t *__restrict__
         }
         if (K > 0) fetch_workers(start, len, 0);
     };
-    size_t u = first_unit(kSegWaves);
+    size_t u = first_unit(WAVES);
     if (u < n_units) fetch(u);  // the first loads are in flight while the tables are built
     load_bounds(bounds, n_seg, n, seg_lds);
     load_lut(tab, lut);

@@ -126,3 +126,20 @@ def test_many_segments(dq8, n_seg, n):
     dq8.decode_accumulate_avg_segments(0, [dev(c) for c in cl], [dev(s) for s in sl], bounds_dev(bounds), out=go.t)
     same_bits(go.t, want, "segment average")
     go.check("segment average")
+
+
+@pytest.mark.parametrize("K,local", [(0, True), (1, False), (1, True), (2, False), (3, True), (4, True), (9, False), (32, False), (32, True)])
+def test_segment_average_of_any_number_of_workers(dq8, K, local):
+    """Whole pairs of workers and a last one by itself, over several units per wavefront."""
+    n, n_seg = 5 * (1 << 20) + 7, 40
+    rng = np.random.Generator(np.random.PCG64(8800 + K))
+    bounds = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n_seg - 1)), [n]])
+    x = rng.standard_normal(n).astype(np.float32) if local else None
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
+    want = oracle.decode_accumulate_avg_segments(2, cl, sl, bounds, local=x)
+    go = Guarded(n, np.float32)
+    dq8.decode_accumulate_avg_segments(2, [dev(c, k % 4) for k, c in enumerate(cl)], [dev(s) for s in sl], bounds_dev(bounds), out=go.t,
+                                       local=dev(x) if local else None)
+    same_bits(go.t, want, "segment average")
+    go.check("segment average")
