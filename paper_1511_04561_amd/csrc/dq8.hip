@@ -1496,16 +1496,26 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
         rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream);
         if (rc) return rc;
     }
-    SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves);
+    const bool many = n >= (size_t)st->cus * 32 * 4 * kSegUnit;
+    SegPlan p = many ? make_segment_plan(st->cus, n, n_seg, 32, false, 2 * kSegWaves) : make_segment_plan(st->cus, n, n_seg, 24);
     p.lds += (size_t)st->search_words[kind] * sizeof(uint32_t);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)x & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    if (st->has_remap[kind])
-        hipLaunchKernelGGL((k_seg_encode<true>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, units,
-                           p.n_waves, scales, codes);
-    else
-        hipLaunchKernelGGL((k_seg_encode<false>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, units,
-                           p.n_waves, scales, codes);
+#define DQ8_SEG_ENC(RM, W)                                                                                                  \
+    hipLaunchKernelGGL((k_seg_encode<RM, W>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, \
+                       units, p.n_waves, scales, codes)
+    if (st->has_remap[kind]) {
+        if (many)
+            DQ8_SEG_ENC(true, 2 * kSegWaves);
+        else
+            DQ8_SEG_ENC(true, kSegWaves);
+    } else {
+        if (many)
+            DQ8_SEG_ENC(false, 2 * kSegWaves);
+        else
+            DQ8_SEG_ENC(false, kSegWaves);
+    }
+#undef DQ8_SEG_ENC
     return after_launch("k_seg_encode", stream);
 }
 

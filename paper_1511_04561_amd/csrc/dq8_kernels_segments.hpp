@@ -245,36 +245,40 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
         if (best[i] != 0) atomicMax(reinterpret_cast<unsigned int *>(scales) + i, best[i]);
 }
 
-// Compression with the segments' scales (computed by k_seg_absmax or handed in).  (61 M elements right after their
-// maxima: 49 us with 8, 16, 24 or 32 wavefronts per compute unit.)
-template <bool REMAP>
-__global__ __launch_bounds__(kSegWg) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
-                                                       const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
-                                                       size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
+// Compression with the segments' scales (computed by k_seg_absmax or handed in).
+// One unit's registers, requested again as soon as its codes are formed, and one copy of the code: 64 registers and 13 KB
+// of instructions, where two sets of registers in turn had 90 and 47 KB, too many for the wavefronts that short arrays live
+// on (16 Mi elements, given scales: 15.3 us so, 14.5 us now; 8 Mi 7.8 and 6.5).  The first loads come after the tables: in
+// front of them, the tables wait until those loads have come (4 Mi: 5.0 against 4.7 us).
+// WAVES: 8, 24 wavefronts on a compute unit, or on arrays of at least four units for each of 32 wavefronts 16 and 32:
+// 61 M elements 54.0 against 52.3 us, 16 Mi 14.5 against 14.8, 4 Mi 4.7 against 5.4.
+template <bool REMAP, int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                             const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                             size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
 {
     extern __shared__ uint64_t seg_lds[];  // the bounds (n_seg + 1 entries), then the search table
     const uint32_t lane = threadIdx.x & 63;
-    struct Slot {
-        v4f v[kSegQ];
-    } a, b;
-    auto fetch = [&](size_t u, Slot &sl) {
+    v4f v[kSegQ];
+    auto fetch = [&](size_t u) {
         const uint32_t len = seg_unit_len<kSegUnit>(u, n);
 #pragma unroll
-        for (int j = 0; j < kSegQ; ++j) sl.v[j] = ldg_floats<1>(x + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
+        for (int j = 0; j < kSegQ; ++j) v[j] = ldg_floats<1>(x + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
     };
-    const size_t u0 = first_unit(kSegWaves);
-    if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are copied
     load_bounds(bounds, n_seg, n, seg_lds);
-    Search sr = load_bucket_table(tab, reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1), kSegWg);
+    Search sr = load_bucket_table(tab, reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1), kWave * WAVES);
     sr.marks = REMAP;
     __syncthreads();
-    walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
+    size_t u = first_unit(WAVES);
+    if (u < n_units) fetch(u);
+    while (u < n_units) {
         const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        u += n_waves;
         uint32_t cw[kSegQ];
         if (q.first == q.last) {
             const float s = scales[q.first];
             const float d = s == 0.0f ? 1.0f : s;
-            encode_quads<true, kSegQ>(sr, sl.v, d, 1.0f / d, reciprocal_ok(d), cw);
+            encode_quads<true, kSegQ>(sr, v, d, 1.0f / d, reciprocal_ok(d), cw);
         } else {
             const SegQuads sq = segments_of_quads(seg_lds, q, lane);
             v4f d[kSegQ];
@@ -282,21 +286,27 @@ __global__ __launch_bounds__(kSegWg) void k_seg_encode(const uint32_t *__restric
             for (int j = 0; j < kSegQ; ++j) d[j] = scales_of_quad(scales, sq, j);
 #pragma unroll
             for (int j = 0; j < kSegQ; ++j) {
-                const v4f v = sl.v[j];
-                const uint32_t s0 = search_sum_exact(sr, v.x / (d[j].x == 0.0f ? 1.0f : d[j].x));
-                const uint32_t s1 = search_sum_exact(sr, v.y / (d[j].y == 0.0f ? 1.0f : d[j].y));
-                const uint32_t s2 = search_sum_exact(sr, v.z / (d[j].z == 0.0f ? 1.0f : d[j].z));
-                const uint32_t s3 = search_sum_exact(sr, v.w / (d[j].w == 0.0f ? 1.0f : d[j].w));
-                cw[j] = pack_codes(sr, s0, s1, s2, s3, v);
+                const v4f t = v[j];
+                const uint32_t s0 = search_sum_exact(sr, t.x / (d[j].x == 0.0f ? 1.0f : d[j].x));
+                const uint32_t s1 = search_sum_exact(sr, t.y / (d[j].y == 0.0f ? 1.0f : d[j].y));
+                const uint32_t s2 = search_sum_exact(sr, t.z / (d[j].z == 0.0f ? 1.0f : d[j].z));
+                const uint32_t s3 = search_sum_exact(sr, t.w / (d[j].w == 0.0f ? 1.0f : d[j].w));
+                cw[j] = pack_codes(sr, s0, s1, s2, s3, t);
             }
         }
+        if (u < n_units) fetch(u);  // the next unit's loads fly while the codes are stored and its segment is looked up
         uint8_t *pc = codes + q.start;
+        if (q.len == (uint32_t)kSegUnit) {
 #pragma unroll
-        for (int j = 0; j < kSegQ; ++j) {
-            const uint32_t k = j * kWave + lane;
-            if (k * 4 < q.len) stg_codes<1>(pc, quad_start(k, q.len), cw[j]);
+            for (int j = 0; j < kSegQ; ++j) stg_codes<1>(pc, 4 * (j * kWave + lane), cw[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kSegQ; ++j) {
+                const uint32_t k = j * kWave + lane;
+                if (k * 4 < q.len) stg_codes<1>(pc, quad_start(k, q.len), cw[j]);
+            }
         }
-    });
+    }
     for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves, [&](size_t i, uint32_t seg) {
         const float s = scales[seg];
         codes[i] = (uint8_t)code_exact(sr, x[i], s == 0.0f ? 1.0f : s);

@@ -21,6 +21,8 @@ KERNELS = """
 template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
 template __global__ void k_encode<1, 2, 1, false, true, true>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
 template __global__ void k_decode_flat<16, 8, 2, 4>(const uint32_t *, const uint8_t *, const float *, uint64_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t, uint64_t, uint32_t, float *);
+template __global__ void k_seg_encode<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
+template __global__ void k_seg_encode<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
 """
 
 
@@ -30,7 +32,7 @@ def assembly():
     with tempfile.TemporaryDirectory() as d:
         src, out = os.path.join(d, "kernels.hip"), os.path.join(d, "kernels.s")
         with open(src, "w") as f:
-            f.write('#include <hip/hip_runtime.h>\n#include "dq8_device.hpp"\n#include "dq8_kernels_codec.hpp"\nnamespace {\n%s}\n' % KERNELS)
+            f.write('#include <hip/hip_runtime.h>\n#include "dq8_device.hpp"\n#include "dq8_kernels_codec.hpp"\n#include "dq8_kernels_segments.hpp"\nnamespace {\n%s}\n' % KERNELS)
         flags = [f for f in build.FLAGS if f != "-shared"]
         subprocess.check_call([build.hipcc()] + flags + ["-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "-S",
                                                         "--cuda-device-only", "-o", out, src])
@@ -86,3 +88,11 @@ def test_compression_requests_the_next_block_before_it_waits():
 def test_expansion_by_position_keeps_no_store_offsets():
     """k_decode_flat: registers of sixteen code words, the scales and a quad, not of sixteen store offsets besides."""
     assert kernel("k_decode_flatILi16ELi8E", 1) <= 76
+
+
+@pytest.mark.parametrize("marks,waves", [(0, 8), (1, 16)])
+def test_segment_compression_leaves_room_for_wavefronts(marks, waves):
+    """k_seg_encode: 32 wavefronts of it fit the registers of a compute unit, and its code is not several times its loop."""
+    name = "k_seg_encodeILb%dELi%dE" % (marks, waves)
+    assert kernel(name, 1) <= 64
+    assert sum(len(b) for b in kernel(name)) < 3000
