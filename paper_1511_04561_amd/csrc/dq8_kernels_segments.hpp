@@ -246,12 +246,13 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
 }
 
 // Compression with the segments' scales (computed by k_seg_absmax or handed in).
-// One unit's registers, requested again as soon as its codes are formed, and one copy of the code: 64 registers and 13 KB
+// One unit's registers, requested again as soon as its codes are formed, and one copy of the code: 65 registers and 13 KB
 // of instructions, where two sets of registers in turn had 90 and 47 KB, too many for the wavefronts that short arrays live
-// on (16 Mi elements, given scales: 15.3 us so, 14.5 us now; 8 Mi 7.8 and 6.5).  The first loads come after the tables: in
+// on (16 Mi elements, given scales: 15.3 us so, 14.5 us now; 8 Mi 7.8 and 6.9).  The first loads come after the tables: in
 // front of them, the tables wait until those loads have come (4 Mi: 5.0 against 4.7 us).
-// WAVES: 8, 24 wavefronts on a compute unit, or on arrays of at least four units for each of 32 wavefronts 16 and 32:
-// 61 M elements 54.0 against 52.3 us, 16 Mi 14.5 against 14.8, 4 Mi 4.7 against 5.4.
+// WAVES: 8, with 24 wavefronts on a compute unit, or, on arrays of at least four units for each of 32 wavefronts, 16 with
+// two workgroups per compute unit one after the other: 61 M elements 54.0 against 52.4 us, 16 Mi 14.5 against 14.8, 4 Mi
+// 4.7 against 5.4.  (64 registers, so that both workgroups are resident: 53.9 us.)
 template <bool REMAP, int WAVES>
 __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
                                                              const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
