@@ -650,8 +650,12 @@ int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n
     const size_t lds = (size_t)st.search_words[kind] * sizeof(uint32_t);
     int rc;
     bool zeroed = false;
+    // Shared blocks: the workgroup that ends last forms the means where it has few rows to read.  It reads them from memory, and
+    // with many of them that takes longer than one more launch (given scales, in a graph, last workgroup / k_error_means: 1,
+    // 100 and 300 blocks 14.1 / 14.1, 15.0 / 14.8 and 15.1 / 15.1 us, 1000 blocks 12.5 / 11.3, 5000 blocks 20.3 / 15.4).
+    const bool last_forms = !own && means && p.nb <= 256;
     if (!own) {  // one kernel clears the rows, the count of workgroups in means[0] and, for blocks of several units, the scales
-        const size_t zero_words = 8 * p.nb, zero_scales = given ? 0 : p.nb, zero_means = means ? 4 : 0;
+        const size_t zero_words = 8 * p.nb, zero_scales = given ? 0 : p.nb, zero_means = last_forms ? 4 : 0;
         const size_t most = zero_words > zero_means ? zero_words : zero_means;
         hipLaunchKernelGGL(k_fill_zero_three, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, stream,
                            reinterpret_cast<float *>(stats), zero_words, scales, zero_scales, reinterpret_cast<float *>(means), zero_means);
@@ -667,15 +671,15 @@ int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n
         const unsigned grid = (unsigned)(all_waves / kStatsWaves);
         hipLaunchKernelGGL((k_error_stats<Q, true>), dim3(grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
                            p.n_units, (size_t)0, all_waves, scales, stats, (double *)nullptr);
-        rc = after_launch("k_error_stats", stream);
-        if (rc || !means) return rc;
-        hipLaunchKernelGGL(k_error_means, dim3(1), dim3(kMeansThreads), 0, stream, stats, p.nb, n, means);
-        return after_launch("k_error_means", stream);
+    } else {
+        const size_t per_wave = (p.n_units + n_waves - 1) / n_waves;
+        hipLaunchKernelGGL((k_error_stats<Q, false>), dim3(p.grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
+                           p.n_units, per_wave, n_waves, scales, stats, last_forms ? means : (double *)nullptr);
     }
-    const size_t per_wave = (p.n_units + n_waves - 1) / n_waves;
-    hipLaunchKernelGGL((k_error_stats<Q, false>), dim3(p.grid), dim3(kStatsWg), lds, stream, tab, x, n, p.B, p.nb, p.upb,
-                       p.n_units, per_wave, n_waves, scales, stats, means);
-    return after_launch("k_error_stats", stream);
+    rc = after_launch("k_error_stats", stream);
+    if (rc || !means || last_forms) return rc;
+    hipLaunchKernelGGL(k_error_means, dim3(1), dim3(kMeansThreads), 0, stream, stats, p.nb, n, means);
+    return after_launch("k_error_means", stream);
 }
 
 int launch_decode(const DeviceState &st, int kind, const uint8_t *codes, const float *scales, size_t n, size_t block,

@@ -70,7 +70,7 @@ struct ErrorSums {
 // at the end is combined in LDS first and lanes 0 .. 3 of a group of four send the four numbers in one instruction.
 // (25 million elements as one block: four atomics from each of 6104 wavefronts took 304 us, ten times the arithmetic;
 // with 512 workgroups that combine first 43 us, 41 us with one Newton step in the quotient instead of two.)
-// means (may be NULL): the workgroup that finishes last forms them from stats[], which saves the launch of
+// means (may be NULL; NULL too where there are many blocks): the workgroup that finishes last forms them from stats[], which saves the launch of
 // k_error_means.  means[0], zeroed like stats[], counts the workgroups until then; every workgroup counts itself after
 // its atomics have been performed, so the one that counts last sees them all (it reads with atomic loads: plain ones
 // could come from its own compute unit's cache).  Nothing but atomics has to be seen, so waiting for them is enough: a
@@ -352,9 +352,10 @@ __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const
 
 // Means over all blocks from the per-block statistics: means[0] = (sum of absolute errors) / n,
 // means[1] = (sum of relative errors) / (number of non-zero inputs), 0 when there is none.
-// For the statistics kernel in which wavefronts own whole blocks.  One workgroup of 1024 threads; thread t adds blocks
-// t, t + 1024, ... in that order and the threads' sums are combined by a fixed tree, so the result is the same in every
-// launch.  (A separate launch: that kernel needs no zeroed memory, and a count of its workgroups would.)
+// After the statistics kernel in which wavefronts own whole blocks (that one needs no zeroed memory, and a count of its
+// workgroups would) and after the other one where there are many blocks.  One workgroup of 1024 threads; thread t adds
+// blocks t, t + 1024, ... in that order and the threads' sums are combined by a fixed tree, so the result is the same
+// in every launch.
 constexpr uint32_t kMeansThreads = 1024;
 __global__ __launch_bounds__(kMeansThreads) void k_error_means(const double *__restrict__ stats, size_t nb, size_t n,
                                                               double *__restrict__ means)

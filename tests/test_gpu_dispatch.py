@@ -26,6 +26,7 @@ def dq8():
     (1, 0), (11 * 1024 + 5, 0),         # one workgroup of twelve wavefronts, some of them without work
     (12 * 1024, 0), (13 * 1024 + 1, 0),  # exactly one workgroup, and one wavefront more
     (40 * 5120 + 3, 5120),              # blocks that end inside a workgroup's runs: it holds several at the end
+    (256 * 700, 700), (256 * 700 + 1, 700),  # the last workgroup forms the means, and one block too many for that
     (800 * 100, 100), (2500 * 1100 + 7, 1100),  # a block or two per wavefront; more blocks than the last workgroup has threads
     (12 * 1024 * 512 + 4099, 0),        # two units per wavefront, the grid full
     (12 * 1024 * 512 * 2 + 1, 6144 * 1024)])
