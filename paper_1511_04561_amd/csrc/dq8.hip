@@ -351,9 +351,10 @@ unsigned one_block_grid(const DeviceState &st, size_t n, size_t unit, int per_cu
     return (unsigned)(all < most ? all : most);
 }
 
-// `zeroed`: the caller has set the scales to +0 already.  `again`: a kernel that reads x follows.
+// `zeroed`: the caller has set the scales to +0 already.  `plain_upto`: arrays that are one block of up to this many elements are
+// read with plain loads (0: none; see kPlainBeforeCompression).
 int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream,
-                  bool zeroed = false, bool again = false)
+                  bool zeroed = false, size_t plain_upto = 0)
 {
     const size_t Bq = block_length(n, block);
     if (Bq == n && n > (size_t)kUnit) {  // one block of several units
@@ -368,12 +369,13 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
         const size_t unit = wide ? 4096 : 1024, units = whole_units(n, unit, aligned);
         const unsigned grid = one_block_grid(st, n, unit, 1);
         const size_t waves = (size_t)grid * kOneWaves;
+        const bool plain = n <= plain_upto;
 #define DQ8_AMAX_ONE(Q, NT) hipLaunchKernelGGL((k_absmax_one<Q, NT>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, scales)
-        if (wide && again)
+        if (wide && plain)
             DQ8_AMAX_ONE(16, 0);
         else if (wide)
             DQ8_AMAX_ONE(16, 1);
-        else if (again)
+        else if (plain)
             DQ8_AMAX_ONE(4, 0);
         else
             DQ8_AMAX_ONE(4, 1);
@@ -664,7 +666,7 @@ int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n
         zeroed = true;
     }
     if (!given) {
-        rc = launch_absmax(st, x, n, block, scales, stream, zeroed, true);
+        rc = launch_absmax(st, x, n, block, scales, stream, zeroed, kPlainBeforeStatistics);
         if (rc) return rc;
     }
     if (own) {
@@ -1270,8 +1272,9 @@ static int check_segments(const char *who, size_t n, const uint64_t *bounds, siz
     return DQ8_OK;
 }
 
+// plain_upto as in launch_absmax.
 static int launch_segment_absmax(const DeviceState &st, const float *x, size_t n, const uint64_t *bounds, size_t n_seg,
-                          float *scales, hipStream_t stream)
+                          float *scales, hipStream_t stream, size_t plain_upto)
 {
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, stream, scales, n_seg);
     int rc = after_launch("k_fill_zero", stream);
@@ -1279,12 +1282,16 @@ static int launch_segment_absmax(const DeviceState &st, const float *x, size_t n
     const SegPlan p = make_segment_plan(st.cus, n, n_seg, kSegWaves, true);
     const size_t units = whole_units(n, (size_t)p.group * kSegUnit, ((uintptr_t)x & 3) == 0);
     const size_t lds = p.lds + n_seg * sizeof(uint32_t);
-    if (p.group == 4)
-        hipLaunchKernelGGL((k_seg_absmax<4 * kSegQ>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units,
-                           p.n_waves, scales);
+#define DQ8_SEG_AMAX(Q, NT)                                                                                                  \
+    hipLaunchKernelGGL((k_seg_absmax<Q, NT>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units, \
+                       p.n_waves, scales)
+    if (p.group == 4 && n > plain_upto)
+        DQ8_SEG_AMAX(4 * kSegQ, 1);
+    else if (p.group == 4)
+        DQ8_SEG_AMAX(4 * kSegQ, 0);
     else
-        hipLaunchKernelGGL((k_seg_absmax<kSegQ>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units,
-                           p.n_waves, scales);
+        DQ8_SEG_AMAX(kSegQ, 0);
+#undef DQ8_SEG_AMAX
     return after_launch("k_seg_absmax", stream);
 }
 
@@ -1329,7 +1336,7 @@ int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, 
     // the block fits one unit: absmax and encode in one kernel
     const bool fused = !given && Bq <= (g_tune.enc_long ? kLongestHeldBlock : (size_t)kUnit);
     if (!given && !fused) {
-        rc = launch_absmax(*st, x, n, block, scales, stream, false, true);
+        rc = launch_absmax(*st, x, n, block, scales, stream, false, kPlainBeforeCompression);
         if (rc) return rc;
     }
     return launch_encode(*st, kind, x, n, block, scales, codes, fused, stream);
@@ -1475,7 +1482,7 @@ int dq8_absmax_segments(const float *x, size_t n, const uint64_t *bounds, size_t
     DeviceState *st;
     rc = device_state(&st);
     if (rc) return rc;
-    return launch_segment_absmax(*st, x, n, bounds, n_seg, scales, static_cast<hipStream_t>(hip_stream));
+    return launch_segment_absmax(*st, x, n, bounds, n_seg, scales, static_cast<hipStream_t>(hip_stream), kCachedFloats);
 }
 
 int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *bounds, size_t n_seg, float *scales,
@@ -1497,7 +1504,7 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (!(flags & DQ8_SCALES_GIVEN)) {
-        rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream);
+        rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream, kPlainBeforeCompression);
         if (rc) return rc;
     }
     const bool many = n >= (size_t)st->cus * 32 * 4 * kSegUnit;

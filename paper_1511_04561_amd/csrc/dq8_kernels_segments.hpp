@@ -171,10 +171,10 @@ __device__ __forceinline__ void for_each_element(const uint64_t *lds, uint32_t n
 // other, about 10 ns each, and the walk by position brings every workgroup to every long segment.
 // Units of Q * 256 elements: 16 quads per lane on long arrays, 4 where that leaves wavefronts without work (the plan's
 // items of four units and of one).
-// Plain loads: the array stays in the memory-side cache (256 MB), from which k_seg_encode reads it again; with
-// non-temporal loads here that second pass takes 33.4 instead of 26.8 us at 37.7 M elements and 53 instead of 43 us at
-// 61 M, this one 1 to 2 us less.
-template <int Q>
+// NT = 0, plain loads, where the array or much of it is still in the memory-side cache when k_seg_encode reads it again
+// (kPlainBeforeCompression; by itself up to kCachedFloats): with non-temporal loads here k_seg_encode takes 33.4 instead of 26.8 us
+// at 37.7 M elements and 53 instead of 43 us at 61 M, this one 1 to 2 us less.  By itself, 1000 M: 643 plain, 574 us.
+template <int Q, int NT>
 __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__ x, size_t n, const uint64_t *__restrict__ bounds,
                                                        uint32_t n_seg, size_t n_units, size_t n_waves, float *__restrict__ scales)
 {
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
     auto fetch = [&](size_t u) {
         const uint32_t len = seg_unit_len<U>(u, n);
 #pragma unroll
-        for (int j = 0; j < Q; ++j) v[j] = ldg_floats<0>(x + u * (size_t)U, quad_start(j * kWave + lane, len));
+        for (int j = 0; j < Q; ++j) v[j] = ldg_floats<NT>(x + u * (size_t)U, quad_start(j * kWave + lane, len));
     };
     size_t u = first_unit(kSegWaves);
     if (u < n_units) fetch(u);
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
                 const SegSpan part = open_part(seg_lds, n_seg, q, at, lane);
                 v4f w[kSegQ];
 #pragma unroll
-                for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<0>(x + part.start, quad_start(j * kWave + lane, part.len));
+                for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<NT>(x + part.start, quad_start(j * kWave + lane, part.len));
                 const SegQuads sq = segments_of_quads(seg_lds, part, lane);
 #pragma unroll
                 for (int j = 0; j < kSegQ; ++j) {

@@ -135,6 +135,14 @@ inline SmallPlan make_small_plan(size_t n, int cus, int waves_per_cu, int wpw)
     return p;
 }
 
+// Arrays that are read twice, first for their maxima: up to this many floats the first pass reads with plain loads, so that
+// the second finds them in the memory-side cache, which holds kCachedFloats; longer arrays with non-temporal loads.
+// What follows decides how far beyond the cache that pays (plain against non-temporal, both passes).  A compression, which
+// reads the part that is left at the rate of the cache: 100 M floats 145.8 / 149.2 us, 300 M 440 / 448, 500 M 745 / 755,
+// 1000 M 1570 / 1531.  The error statistics, which are bound by arithmetic: 50 M 96.3 / 96.4, 68 M 126 / 122, 1000 M 1590 / 1515.
+constexpr size_t kCachedFloats = (size_t)1 << 26;
+constexpr size_t kPlainBeforeCompression = (size_t)1 << 29, kPlainBeforeStatistics = kCachedFloats;
+
 // ---- tensors back to back, one scale each
 
 // Wavefronts per workgroup of the kernels that keep a value table beside the bounds: kSegWaves, two such workgroups on a
