@@ -144,3 +144,34 @@ def test_segment_average_of_any_number_of_workers(dq8, K, local):
                                        local=dev(x) if local else None)
     same_bits(go.t, want, "segment average")
     go.check("segment average")
+
+
+@pytest.mark.parametrize("rest,offset", [(1025, 0), (2050, 1), (3075, 3), (1027, 0), (4095, 1)])
+def test_segment_maxima_of_a_last_part_under_a_quad(dq8, rest, offset):
+    """16 quads per lane, and a last unit with several segments whose last 1024 elements are 1, 2 or 3: every largest value stands
+    where only that part, or only the one before it, sees it."""
+    n = (1 << 24) + rest
+    rng = np.random.Generator(np.random.PCG64(8700 + rest))
+    x = rng.uniform(-1, 1, n).astype(np.float32)
+    bounds = np.array([0, 5, n - 1030, n - 5, n - 2, n - 1, n])
+    for i in (1, 2, 4, 7):
+        x[n - i] = np.float32(-8 - i)
+    want = np.maximum.reduceat(np.abs(x), bounds[:-1])
+    gx, gs = Guarded(n, np.float32, offset, data=x), Guarded(len(bounds) - 1, np.float32)
+    dq8.absmax_segments(gx.t, bounds_dev(bounds), scales=gs.t)
+    same_bits(gs.t, want, "segment maxima")
+    gs.check("segment maxima")
+
+
+@pytest.mark.parametrize("block", [0, 4096])
+@pytest.mark.parametrize("more", [-4097, -1, 0, 1, 5, 4096])
+def test_expansion_at_the_longest_short_array(dq8, block, more):
+    """Arrays with about as many units of 4096 elements as the chip has compute units: units of 1024 up to there."""
+    n = 4096 * torch.cuda.get_device_properties(0).multi_processor_count + more
+    rng = np.random.Generator(np.random.PCG64(8900 + more % 89))
+    codes = rng.integers(0, 256, n).astype(np.uint8)
+    scales = np.exp(rng.uniform(-8, 8, oracle.dq8_oracle.n_blocks(n, block))).astype(np.float32)
+    go = Guarded(n, np.float32, more % 4)
+    dq8.decode(more % 4, dev(codes, 1), dev(scales), block, out=go.t)
+    same_bits(go.t, oracle.decode(more % 4, codes, scales, block), "expansion")
+    go.check("expansion")
