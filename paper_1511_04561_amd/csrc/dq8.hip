@@ -340,17 +340,6 @@ WorkerPtrs advance_workers(const WorkerPtrs &wp, int K, size_t done, size_t bloc
     return r;
 }
 
-// Units of `unit` elements: a last one of fewer than four elements is none, and there are none at all when floats lie at
-// addresses that are no multiple of 4.
-size_t whole_units(size_t n, size_t unit, bool aligned) { return aligned ? n / unit + (n % unit >= 4) : 0; }
-
-// Grid of the kernels for an array that is one block: workgroups of kOneWaves wavefronts, up to per_cu on a compute unit.
-unsigned one_block_grid(const DeviceState &st, size_t n, size_t unit, int per_cu)
-{
-    const size_t all = (n + unit * kOneWaves - 1) / (unit * kOneWaves), most = (size_t)st.cus * (size_t)per_cu;
-    return (unsigned)(all < most ? all : most);
-}
-
 // `zeroed`: the caller has set the scales to +0 already.  `plain_upto`: arrays that are one block of up to this many elements are
 // read with plain loads (0: none; see kPlainBeforeCompression).
 int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream,
@@ -367,7 +356,7 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
         // the number of wavefronts counts
         const bool wide = n >= (size_t)st.cus * kOneWaves * 2 * 4096, aligned = ((uintptr_t)x & 3) == 0;
         const size_t unit = wide ? 4096 : 1024, units = whole_units(n, unit, aligned);
-        const unsigned grid = one_block_grid(st, n, unit, 1);
+        const unsigned grid = one_block_grid(st.cus, n, unit, 1);
         const size_t waves = (size_t)grid * kOneWaves;
         const bool plain = n <= plain_upto;
 #define DQ8_AMAX_ONE(Q, NT) hipLaunchKernelGGL((k_absmax_one<Q, NT>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, scales)
@@ -471,7 +460,7 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
     const size_t lds = ((size_t)st.search_words[kind] + kTeamSlots) * sizeof(uint32_t);
     if (!fused && p.nb == 1) {  // one scale, in memory
         const size_t units = whole_units(n, 1024, ((uintptr_t)x & 3) == 0);
-        const unsigned grid = one_block_grid(st, n, 1024, 2);
+        const unsigned grid = one_block_grid(st.cus, n, 1024, 2);
         const size_t waves = (size_t)grid * kOneWaves, olds = (size_t)st.search_words[kind] * sizeof(uint32_t);
         if (st.has_remap[kind])
             hipLaunchKernelGGL((k_encode_one<true>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, codes);

@@ -473,14 +473,6 @@ __device__ __forceinline__ void stg_floats(float *p, v4f v)
         *reinterpret_cast<v4f_any *>(p) = v;
 }
 
-// Where quad q of a run of len >= 4 elements starts: at 4 q, or, for the last quad of a run that is no whole number of
-// quads and for every quad past it, four elements before the end.  The overlap is read twice (a maximum does not
-// change) and written twice with the same bytes; quads with 4 q >= len are loaded (valid memory, no branch) and not stored.
-__device__ __forceinline__ uint32_t quad_start(uint32_t q, uint32_t len)
-{
-    return q * 4 < len - 4 ? q * 4 : len - 4;
-}
-
 __device__ __forceinline__ uint32_t wave_in_wg() { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // Index of this wavefront in the grid = the first unit it owns; held in scalar registers.

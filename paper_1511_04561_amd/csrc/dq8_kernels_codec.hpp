@@ -190,7 +190,6 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
 // which takes the second pass over 37.7 M elements from 33.4 to 26.8 us and costs this one a microsecond.
 // n_units: whole units and a last one of at least four elements (see quad_start); the elements past them (at most three;
 // all of them when x is no multiple of 4) go one by one.
-constexpr int kOneWaves = 8;
 constexpr int kOneWg = kWave * kOneWaves;
 
 template <int Q, int NT>

@@ -135,6 +135,19 @@ inline SmallPlan make_small_plan(size_t n, int cus, int waves_per_cu, int wpw)
     return p;
 }
 
+// ---- kernels that walk an array by position
+
+// Units of `unit` elements: a last one of fewer than four elements is none, and there are none at all when floats lie at
+// addresses that are no multiple of 4.  The elements in no unit go one by one.
+inline size_t whole_units(size_t n, size_t unit, bool aligned) { return aligned ? n / unit + (n % unit >= 4) : 0; }
+
+// Grid for an array that is one block: workgroups of kOneWaves wavefronts, up to per_cu on a compute unit.
+inline unsigned one_block_grid(int cus, size_t n, size_t unit, int per_cu)
+{
+    const size_t all = (n + unit * kOneWaves - 1) / (unit * kOneWaves), most = (size_t)cus * (size_t)per_cu;
+    return (unsigned)(all < most ? all : most);
+}
+
 // Arrays that are read twice, first for their maxima: up to this many floats the first pass reads with plain loads, so that
 // the second finds them in the memory-side cache, which holds kCachedFloats; longer arrays with non-temporal loads.
 // What follows decides how far beyond the cache that pays (plain against non-temporal, both passes).  A compression, which
@@ -155,22 +168,22 @@ inline int segment_waves(int cus, size_t n, size_t n_seg)
 }
 
 struct SegPlan {
-    size_t n_units, n_items, n_waves, lds;
+    size_t n_items, n_waves, lds;
     uint32_t group;
     unsigned grid;
 };
 
-// Units of kSegUnit elements on up to `waves_per_cu` wavefronts per compute unit, `waves_per_wg` per workgroup.
+// Items of work, units of kSegUnit elements, on up to `waves_per_cu` wavefronts per compute unit, `waves_per_wg` per workgroup.
 // grouped (the maxima): an item of work is four units when a workgroup per compute unit still gets two items or more
 // per wavefront, else one unit (short arrays: as many wavefronts as there are units).
 inline SegPlan make_segment_plan(int cus, size_t n, size_t n_seg, int waves_per_cu, bool grouped = false, int waves_per_wg = kSegWaves)
 {
     SegPlan p;
-    p.n_units = (n + kSegUnit - 1) / kSegUnit;
+    const size_t n_units = (n + kSegUnit - 1) / kSegUnit;
     size_t waves = (size_t)cus * (size_t)waves_per_cu;
-    p.group = grouped && p.n_units >= (size_t)cus * kSegWaves * 8 ? 4u : 1u;
+    p.group = grouped && n_units >= (size_t)cus * kSegWaves * 8 ? 4u : 1u;
     if (p.group == 4) waves = (size_t)cus * kSegWaves;
-    p.n_items = (p.n_units + p.group - 1) / p.group;
+    p.n_items = (n_units + p.group - 1) / p.group;
     if (waves > p.n_items) waves = p.n_items;
     p.grid = (unsigned)((waves + waves_per_wg - 1) / waves_per_wg);
     p.n_waves = (size_t)p.grid * waves_per_wg;

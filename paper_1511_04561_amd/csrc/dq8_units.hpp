@@ -24,6 +24,17 @@ constexpr int kSegQ = 4;                     // quads per lane
 constexpr int kSegUnit = kSegQ * 4 * kWave;  // 1024 elements per unit
 constexpr int kSegWaves = 8;                 // wavefronts per workgroup
 
+// The kernels for an array that is one block.
+constexpr int kOneWaves = 8;  // wavefronts per workgroup
+
+// Where quad q of a run of len >= 4 elements starts: at 4 q, or, for the last quad of a run that is no whole number of
+// quads and for every quad past it, four elements before the end.  The overlap is read twice (a maximum does not
+// change) and written twice with the same bytes; quads with 4 q >= len are loaded (valid memory, no branch) and not stored.
+DQ8_HD uint32_t quad_start(uint32_t q, uint32_t len)
+{
+    return q * 4 < len - 4 ? q * 4 : len - 4;
+}
+
 // Geometry of unit u.  All values are wave-uniform.
 struct Unit {
     size_t block;   // scale index

@@ -79,6 +79,38 @@ static void check_units(size_t n, size_t block)
     }
 }
 
+// Kernels that walk an array by position: whole units and the elements that go one by one, as the kernels cover them.
+static void check_positions()
+{
+    for (size_t unit : {(size_t)1024, (size_t)4096})
+        for (size_t base : {(size_t)0, unit, 3 * unit, 17 * unit, (size_t)1 << 32})
+            for (size_t more = 0; more < unit + 8; more += more < 16 || more + 16 >= unit ? 1 : 61) {
+                const size_t n = base + more;
+                if (n == 0) continue;
+                for (int per_cu : {1, 2}) {
+                    const unsigned grid = one_block_grid(256, n, unit, per_cu);
+                    CHECK(grid >= 1 && grid <= 256u * (unsigned)per_cu, "grid %u for %zu", grid, n);
+                    CHECK((size_t)grid * kOneWaves * unit < n + kOneWaves * unit, "grid %u for %zu: workgroups without work", grid, n);
+                }
+                CHECK(whole_units(n, unit, false) == 0, "units at unaligned floats");
+                const size_t units = whole_units(n, unit, true), from = units * unit;
+                CHECK(from >= n ? from - n < unit : n - from < 4, "%zu units of %zu leave %zu elements", units, unit, n);
+                if (units == 0) continue;
+                const size_t start = (units - 1) * unit;  // the last unit, the only one that may be short
+                const uint32_t len = n - start < unit ? (uint32_t)(n - start) : (uint32_t)unit;
+                CHECK(len >= 4 && start + len + (from < n ? n - from : 0) == n, "last unit of %zu: %u elements", n, len);
+                std::vector<bool> seen(len);
+                for (uint32_t q = 0; q < unit / 4; ++q) {
+                    const uint32_t at = quad_start(q, len);  // loaded by every lane, stored where 4 q < len
+                    CHECK(at + 4 <= len, "quad %u of %u elements starts at %u", q, len, at);
+                    if (q * 4 < len)
+                        for (uint32_t c = 0; c < 4 && at + c < len; ++c) seen[at + c] = true;
+                    if ((q + 1) * 4 <= len) CHECK(at == 4 * q, "quad %u of %u elements starts at %u", q, len, at);
+                }
+                for (uint32_t i = 0; i < len; ++i) CHECK(seen[i], "element %u of %u is in no quad", i, len);
+            }
+}
+
 static void check_plans()
 {
     const size_t two32 = (size_t)1 << 32;
@@ -121,17 +153,20 @@ static void check_plans()
                 CHECK(un.block == p.nb - 1 && un.start == (p.nb - 1) * b && un.start + un.len == n && un.len <= (uint32_t)(W * 1024),
                       "team plan: last unit of n %zu block %zu", n, b);
             }
-    // tensors back to back: units of 1024 elements, items of one or four units, sixteen wavefronts per workgroup
+    // tensors back to back: units of 1024 elements, items of one or four units
     for (size_t n : {(size_t)1, (size_t)1023, (size_t)1024, (size_t)1025, (size_t)1863690, (size_t)61100840, two32 + 12305})
-        for (int wpc : {16, 32})
-            for (bool grouped : {false, true}) {
-                const SegPlan p = make_segment_plan(256, n, 17, wpc, grouped);
-                CHECK(p.n_units == (n + 1023) / 1024 && (p.group == 1 || (grouped && p.group == 4)), "segment plan of %zu", n);
-                CHECK(p.n_items * p.group >= p.n_units && (p.n_items - 1) * p.group < p.n_units, "segment plan of %zu: items", n);
-                CHECK(p.grid >= 1 && p.n_waves == (size_t)p.grid * kSegWaves && p.n_waves < p.n_items + kSegWaves, "segment plan of %zu: grid", n);
-                CHECK(p.n_waves <= (size_t)256 * 32 && p.lds == 18 * sizeof(uint64_t), "segment plan of %zu: size", n);
-                CHECK(p.group == 1 || p.n_items >= 2 * p.n_waves, "segment plan of %zu: too few items of four", n);
-            }
+        for (int wpc : {8, 16, 24, 32})
+            for (int wpw : {kSegWaves, 2 * kSegWaves})
+                for (bool grouped : {false, true}) {
+                    if (grouped && (wpc != kSegWaves || wpw != kSegWaves)) continue;  // the maxima: one workgroup per compute unit
+                    const SegPlan p = make_segment_plan(256, n, 17, wpc, grouped, wpw);
+                    const size_t units = (n + kSegUnit - 1) / kSegUnit;
+                    CHECK(p.group == 1 || (grouped && p.group == 4), "segment plan of %zu", n);
+                    CHECK(p.n_items * p.group >= units && (p.n_items - 1) * p.group < units, "segment plan of %zu: items", n);
+                    CHECK(p.grid >= 1 && p.n_waves == (size_t)p.grid * wpw && p.n_waves < p.n_items + wpw, "segment plan of %zu: grid", n);
+                    CHECK(p.n_waves <= (size_t)256 * wpc + wpw && p.lds == 18 * sizeof(uint64_t), "segment plan of %zu: size", n);
+                    CHECK(p.group == 1 || p.n_items >= 2 * p.n_waves, "segment plan of %zu: too few items of four", n);
+                }
     // two workgroups with a value table on a compute unit while both fit its LDS; one of twice the size, where there is work for it, above
     for (size_t n : {(size_t)1000, (size_t)1 << 21, ((size_t)1 << 21) + 1, (size_t)61100840})
         for (size_t n_seg : {(size_t)1, (size_t)2047, (size_t)2048, (size_t)DQ8_MAX_SEGMENTS}) {
@@ -163,6 +198,7 @@ static void check_plans()
 int main()
 {
     check_tables();
+    check_positions();
     check_plans();
     if (failures) {
         std::printf("%d checks failed\n", failures);
