@@ -81,6 +81,17 @@ def _dev(t, dtype, what):
     return t
 
 
+def _device_and_stream_calls(c):
+    """The current device and the raw handle of a device's current stream, as calls: those of torch's C module `c` (private names,
+    seen in torch 2.10) where it has both, else the public ones."""
+    if hasattr(c, "_cuda_getDevice") and hasattr(c, "_cuda_getCurrentRawStream"):
+        return c._cuda_getDevice, c._cuda_getCurrentRawStream
+    return torch.cuda.current_device, lambda index: torch.cuda.current_stream(index).cuda_stream
+
+
+_current_device, _raw_stream = _device_and_stream_calls(torch._C)
+
+
 def _enqueue(fn, index, *args):
     """Calls the library function `fn` with `args` and torch's current stream on device `index`, which is made current for the
     call if it is not.
@@ -88,12 +99,11 @@ def _enqueue(fn, index, *args):
     The stream is asked for as the raw handle: torch.cuda.current_stream() builds a Stream object first, which took 2.9 us
     of the 8.0 us that a call on 4096 elements took (the handle: 0.07 us; such a call now: 5.4 us, 3.5 of
     them in the library, most of that one kernel launch)."""
-    c = torch._C
-    if index == c._cuda_getDevice():
-        rc = fn(*args, c._cuda_getCurrentRawStream(index))
+    if index == _current_device():
+        rc = fn(*args, _raw_stream(index))
     else:
         with torch.cuda.device(index):
-            rc = fn(*args, c._cuda_getCurrentRawStream(index))
+            rc = fn(*args, _raw_stream(index))
     if rc != 0:
         _check(rc, fn.__name__)
 

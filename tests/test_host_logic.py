@@ -348,3 +348,20 @@ def test_chunk_sizes_leave_few_empty_places(L):
         assert all(waste <= (-K % d) for d in range(3, 9)), (K, c)
         assert all(d <= c for d in range(3, 9) if (-K % d) == waste), (K, c)
     assert [got[K] for K in (3, 4, 5, 6, 7, 8, 10, 16, 24, 32)] == [3, 4, 5, 6, 7, 8, 5, 8, 8, 8]
+
+
+def test_stream_handles_without_private_names_of_torch(monkeypatch):
+    """A torch whose C module lacks the private calls is asked through the public ones."""
+    import types
+
+    import torch
+    from paper_1511_04561_amd import dq8
+    private = types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda index: 70 + index)
+    device, stream = dq8._device_and_stream_calls(private)
+    assert device() == 3 and stream(2) == 72
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda index: types.SimpleNamespace(cuda_stream=40 + index))
+    for missing in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        part = types.SimpleNamespace(**{k: v for k, v in vars(private).items() if k != missing})
+        device, stream = dq8._device_and_stream_calls(part)
+        assert device() == 1 and stream(2) == 42
