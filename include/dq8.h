@@ -23,10 +23,14 @@
  *   - Inputs must be finite.  With DQ8_SCALES_GIVEN every scale must be finite and >= 0 (a zero
  *     scale means "do not divide") and the quotient x / scale must be finite; the sign bit of a
  *     code is taken from x, which is the sign of the quotient only for such scales.
- *   - Any pointer alignment and any n / block are accepted.  The fast paths need
- *     16-byte aligned `x` / `out`, 4-byte aligned `codes`, and block % 4 == 0 (or a single
- *     block); anything else runs on slower paths with the same results.  Blocks of 4096
- *     elements are the fastest; other lengths come close (the units of work follow the block
+ *   - Any pointer alignment and any n / block are accepted, with the same results.  What the fast paths need:
+ *       dq8_absmax, dq8_encode, dq8_decode and the calls for segments: `x`, `out` and `local` at a multiple
+ *         of 4 bytes (any float array); `codes` may start at any byte.  Units of fewer than four
+ *         elements go one by one, and dq8_decode is faster where block % 4 == 0 or there is one block.
+ *       dq8_decode_accumulate_avg[_local], dq8_decode_avg_encode, dq8_error_stats, and every call with
+ *         blocks of 4 to 128 elements that are powers of two (up to 512 for dq8_encode): also 16-byte
+ *         aligned `x` / `out` / `local`, 4-byte aligned `codes`, and block % 4 == 0 (or a single block).
+ *     Blocks of 4096 elements are the fastest; other lengths come close (the units of work follow the block
  *     or, where a block need not be held, the position in the array; powers of two from 4 to
  *     128 elements have kernels that pack many blocks into a wavefront); other lengths below
  *     256 use a fraction of each wavefront in the calls that compress.

@@ -7,15 +7,15 @@
 // outside [0, n): the kernels walk the array in units of 1024 elements by position, and the segment of an
 // element is looked up, never the elements of a segment.  Entries that do not ascend give meaningless
 // results inside the arrays.
-// A wavefront takes a unit at a time, its loads (which do not depend on the segments) issued a unit ahead and without a
-// condition, as in k_encode_full.  The segment of the unit's first element comes from two votes over the bounds (64
+// A wavefront takes a unit at a time, its loads (which do not depend on the segments) issued before the stores of the unit
+// before it (k_seg_decode: a unit ahead, as in k_encode_full).  The segment of the unit's first element comes from two votes over the bounds (64
 // evenly spaced ones, then the 64 of the stretch the first vote names).  A unit inside one segment goes on with that
 // segment's scale; in any other unit every lane looks the segments of its elements up between the unit's first and last
 // segment and the same registers go on with scales per quad (per element in the rows of quads in which a segment ends).
 // What bounds the kernels: HBM on long arrays, latency on short ones.  Mixed units used to walk sixteen consecutive
 // elements per lane one after the other: the convnet's ten tensors (1.76 M elements), seven workers and the own
-// gradients averaged: 30.7 us, 11.8 us now (8.3 us when no segment ends inside a unit); that set compressed 16.0 -> 10.4 us; the
-// AlexNet-shaped bucket's sixteen matrices (61 M elements), maxima 53.8 -> 42.5 and compression 59.4 -> 49.0 us.
+// gradients averaged: 30.7 us, 11.8 us now (8.3 us when no segment ends inside a unit); that set compressed 16.0 -> 9.8 us; the
+// AlexNet-shaped bucket's sixteen matrices (61 M elements), maxima 53.8 -> 42.4 and compression 59.4 -> 46.6 us.
 // Elements that are in no unit (fewer than four at the end of the array; all of them when floats lie at addresses that
 // are no multiple of 4) go one by one.
 #pragma once
