@@ -98,7 +98,7 @@ int device_state(DeviceState **out)
             if (rc) return fail(DQ8_ERR_KIND, "table construction failed for kind %d (status %d)", k, rc);
             dq8::pack_tables(t, image[k]);
             st.has_remap[k] = t.has_marks;
-            st.search_words[k] = t.n_bucket;
+            st.search_words[k] = (t.n_bucket + 3) / 4 * 4;  // copied in quads
         }
         void *sym = nullptr;
         DQ8_HIP(hipGetSymbolAddress(&sym, HIP_SYMBOL(g_tables)));
@@ -1498,7 +1498,7 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
     }
     const bool many = n >= (size_t)st->cus * 32 * 4 * kSegUnit;
     SegPlan p = many ? make_segment_plan(st->cus, n, n_seg, 32, false, 2 * kSegWaves) : make_segment_plan(st->cus, n, n_seg, 24);
-    p.lds += (size_t)st->search_words[kind] * sizeof(uint32_t);
+    p.lds = seg_bounds_words(n_seg) * sizeof(uint64_t) + (size_t)st->search_words[kind] * sizeof(uint32_t);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)x & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
 #define DQ8_SEG_ENC(RM, W)                                                                                                  \

@@ -347,30 +347,92 @@ __device__ __forceinline__ uint32_t encode_one(const Search &sr, float x, float 
     return code_exact(sr, x, d);
 }
 
-// Copies the bucket table to LDS with all `n_threads` threads of the workgroup; the caller synchronises
-// the workgroup before using it.
-__device__ __forceinline__ Search load_bucket_table(const uint32_t *tab, uint32_t *lds, uint32_t n_threads = kWg)
+// The tables of a data type on their way to LDS.  What a workgroup does before its first unit is all that a short array's call
+// consists of, and that is a chain of waits: so the whole image is requested at once (128 bits per thread and round, the
+// number of rounds known when the kernel is compiled) and only then written to LDS.  A loop that loads a word, waits and
+// writes it is eleven round trips for the dynamic tree's 2796 words and 256 threads (compression of 4096 elements in a
+// graph: 3.4 -> 2.6 us; 4 Mi in blocks of 4096: 7.1 -> 6.1).
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+constexpr uint32_t kBucketQuads = dq8::kBucketCapacity / 4;  // the image holds these whether or not the type uses them all
+static_assert(kBucketOff % 4 == 0 && dq8::kBucketCapacity % 4 == 0, "128-bit accesses to the table image");
+
+template <uint32_t THREADS>
+struct BucketWords {
+    static constexpr uint32_t kRounds = (kBucketQuads + THREADS - 1) / THREADS;
+    v4u w[kRounds];
+};
+
+template <uint32_t THREADS>
+__device__ __forceinline__ BucketWords<THREADS> request_bucket_table(const uint32_t *tab)
 {
-    const uint32_t nbk = tab[kNBucketOff];
-    for (uint32_t i = threadIdx.x; i < nbk; i += n_threads) lds[i] = tab[kBucketOff + i];
+    BucketWords<THREADS> b;
+    const v4u *src = reinterpret_cast<const v4u *>(tab + kBucketOff);
+#pragma unroll
+    for (uint32_t i = 0; i < b.kRounds; ++i) {
+        const uint32_t q = threadIdx.x + i * THREADS;
+        b.w[i] = src[q < kBucketQuads ? q : kBucketQuads - 1];
+    }
+    return b;
+}
+
+// Writes the type's words, rounded up to whole quads, to lds (16-byte aligned) with all THREADS threads of the workgroup; the
+// caller synchronises the workgroup before the first lookup.
+template <uint32_t THREADS>
+__device__ __forceinline__ Search place_bucket_table(const uint32_t *tab, const BucketWords<THREADS> &b, uint32_t *lds)
+{
+    const uint32_t nbk = tab[kNBucketOff], quads = (nbk + 3) / 4;
+#pragma unroll
+    for (uint32_t i = 0; i < b.kRounds; ++i) {
+        const uint32_t q = threadIdx.x + i * THREADS;
+        if (q < quads) reinterpret_cast<v4u *>(lds)[q] = b.w[i];
+    }
     return make_search(lds, tab[kLoKeyOff], nbk, tab[kHasMarksOff] != 0);
+}
+
+template <uint32_t THREADS>
+__device__ __forceinline__ Search load_bucket_table(const uint32_t *tab, uint32_t *lds)
+{
+    return place_bucket_table<THREADS>(tab, request_bucket_table<THREADS>(tab), lds);
 }
 
 // Decode table in LDS, one copy per lane: entry (code, lane) at byte address code * 256 +
 // lane * 4.  Lanes L and L + 32 share a bank but are served in different halves of the access,
 // so a lookup never conflicts, and the address is two byte fields - code in byte 1, lane * 4 in
 // byte 0 - which one v_perm_b32 assembles straight from a packed word of four codes.
-// Thread t < 256 owns code t (workgroups have at least 256 threads).  The caller synchronises before the
-// first lookup.
+// place_lut writes row threadIdx.x & 255 of the table with val; the THREADS / 256 threads that a row has share its
+// sixteen quads.  Every thread starts at another quad: rows are 256 bytes, so threads that wrote the same quad of their rows
+// would all meet in four banks (64 KiB take about 4000 clocks that way and 500 so: expansion of 4096 elements in a graph
+// 3.7 -> 2.4 us, 4 Mi in blocks of 4096: 6.1 -> 4.8).  The caller synchronises before the first lookup.
+template <uint32_t THREADS>
+__device__ __forceinline__ void place_lut(float val, float *lds)
+{
+    static_assert(THREADS >= 256, "a thread for every row");
+    constexpr uint32_t kShare = THREADS / 256, kQuads = kLutCopies / 4;
+    if (THREADS % 256 != 0 && threadIdx.x >= 256 * kShare) return;
+    const v4f four = {val, val, val, val};
+    v4f *row = reinterpret_cast<v4f *>(lds + (threadIdx.x & 255) * kLutCopies);
+    const uint32_t part = threadIdx.x >> 8;
+#pragma unroll
+    for (uint32_t c = 0; c < kQuads; c += kShare)
+        if (kQuads % kShare == 0 || c + part < kQuads) row[(c + part + threadIdx.x) % kQuads] = four;
+}
+
+__device__ __forceinline__ float request_lut(const uint32_t *tab) { return u2f(tab[kCbOff + (threadIdx.x & 255)]); }
+
+template <uint32_t THREADS>
 __device__ __forceinline__ void load_lut(const uint32_t *tab, float *lds)
 {
-    if (threadIdx.x < 256) {
-        const float val = u2f(tab[kCbOff + threadIdx.x]);
-        const v4f four = {val, val, val, val};
-        v4f *row = reinterpret_cast<v4f *>(lds + threadIdx.x * kLutCopies);
-#pragma unroll
-        for (int c = 0; c < kLutCopies / 4; ++c) row[c] = four;
-    }
+    place_lut<THREADS>(request_lut(tab), lds);
+}
+
+// Both tables.
+template <uint32_t THREADS>
+__device__ __forceinline__ Search load_tables(const uint32_t *tab, float *lut, uint32_t *bucket_lds)
+{
+    const float val = request_lut(tab);
+    const BucketWords<THREADS> words = request_bucket_table<THREADS>(tab);
+    place_lut<THREADS>(val, lut);
+    return place_bucket_table<THREADS>(tab, words, bucket_lds);
 }
 
 // Table value of code number J (0..3) of the packed word w, for the lane whose byte offset

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg(const uint32_t *__re
         }
     };
     if (u < n_units) open_unit(u, un, fast, aligned);
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     while (u < n_units) {
         float *po = out + un.start;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_full(const uint32_t 
     uint32_t u = (uint32_t)first_unit(WPW);
     Slot a, b;
     if (u < n_full) fetch(u, a);  // the first loads are in flight while the table is built
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     if (u < n_full) {
         for (;;) {
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_flat(const uint32_t 
     }
     Slot a, b;
     if (u < n_full) fetch(u, a);  // the first loads are in flight while the table is built
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     if (u < n_full) {
         for (;;) {
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_chunks(const uint32_
     Slot a, b;
     const bool any = u < n_full && n_chunks > 0;
     if (any) fetch(u, 0, a);  // the first loads are in flight while the table is built
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     if (any) {
         for (;;) {

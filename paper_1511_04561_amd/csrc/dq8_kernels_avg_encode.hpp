@@ -42,9 +42,9 @@ __global__ __launch_bounds__(kWave * WPW, WPW / 2) void k_avg_block(const uint32
     auto mean_of = [&](float acc) { return pow2 ? acc * rk : acc / fk; };
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t lane4 = lane * 4;
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     Search sr = make_search(bucket_lds, tab[kLoKeyOff], tab[kNBucketOff]);
-    if (codes_out) sr = load_bucket_table(tab, bucket_lds, kWave * WPW);
+    if (codes_out) sr = load_bucket_table<kWave * WPW>(tab, bucket_lds);
     __syncthreads();
     for (size_t u = first_unit(WPW); u < n_units; u += n_waves) {
         const Unit un = unit_of<U>(u, n, B, nb, upb);
@@ -260,8 +260,7 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
     const uint32_t lane4 = lane * 4;
     uint32_t *slots = dyn_lds;
     uint32_t phase = 0;
-    load_lut(tab, lut);
-    const Search sr = load_bucket_table(tab, dyn_lds + kLongSlots, kLongTeam);
+    const Search sr = load_tables<kLongTeam>(tab, lut, dyn_lds + kLongSlots);
     __syncthreads();
     // Maximum over the workgroup of the wave maxima m, through LDS; one barrier per call.
     auto team_max = [&](uint32_t m) {
@@ -721,11 +720,8 @@ __global__ __launch_bounds__(kWave * W * TEAMS, W * TEAMS == 12 ? 3 : 4) void k_
     typename Avg::Slot a, b;
     e.open(u, a);
     e.load_all(a);  // the first loads are in flight while the tables are copied
-    load_lut(tab, lut);
-    {
-        e.sr = load_bucket_table(tab, dyn_lds + kSlots, kWave * W * TEAMS);
-        e.sr.marks = REMAP;  // known at compile time: no test for marked code bytes in the loop
-    }
+    e.sr = load_tables<kWave * W * TEAMS>(tab, lut, dyn_lds + kSlots);
+    e.sr.marks = REMAP;  // known at compile time: no test for marked code bytes in the loop
     __syncthreads();
     // `steady` (even) leading iterations in which this and the next unit of every team are whole
     // aligned units, then the general ones.

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kOneWg) void k_encode_one(const uint32_t *__restric
     const float d = s == 0.0f ? 1.0f : s;
     const float r = 1.0f / d;
     const bool recip = reciprocal_ok(d);
-    Search sr = load_bucket_table(tab, lds, kOneWg);
+    Search sr = load_bucket_table<kOneWg>(tab, lds);
     sr.marks = REMAP;
     __syncthreads();
     walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kWg) void k_encode(const uint32_t *__restrict__ tab
     size_t u = WPB == 1 ? first_unit() : (size_t)blockIdx.x;
     typename Enc::Slot a, b;
     if (u < n_units) e.fetch(u, a);  // the first loads are in flight while the table is copied
-    e.sr = load_bucket_table(tab, lds + kTeamSlots);
+    e.sr = load_bucket_table<kWg>(tab, lds + kTeamSlots);
     __syncthreads();
     if constexpr (EVERY) {
         walk_units(u, n_units, n_teams, a, b, [&](size_t v, typename Enc::Slot &sl) { e.fetch(v, sl); },
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(kWg) void k_encode_full(const uint32_t *__restrict_
     uint32_t u = blockIdx.x;
     v4f a[Q], b[Q];
     if (u < n_full) fetch(u, a);  // the first loads are in flight while the table is copied
-    sr = load_bucket_table(tab, lds + kTeamSlots);
+    sr = load_bucket_table<kWg>(tab, lds + kTeamSlots);
     sr.marks = REMAP;  // known at compile time: no test for marked code bytes in the loop
     __syncthreads();
     // Steady state: the fetch of the next block is unconditional and comes before the work on the
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_encode_wave(const uint32_t *__r
     uint32_t u = (uint32_t)first_unit(WPW);
     v4f a[Q], b[Q];
     if (u < n_units) fetch(u, a);  // the first loads are in flight while the table is copied
-    sr = load_bucket_table(tab, lds, kWave * WPW);
+    sr = load_bucket_table<kWave * WPW>(tab, lds);
     sr.marks = REMAP;  // known at compile time: no test for marked code bytes in the loop
     __syncthreads();
     // steady state as in k_encode_full: the next block's loads are issued unconditionally before the work on
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_flat(const uint32_t *__r
         for (int t = 0; t < NS; ++t) sc[t] = scales[bb + t < nb ? bb + t : nb - 1];
     };
     if (u < n_units) open_unit(u, b0);  // the first loads are in flight while the table is built
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     while (u < n_units) {
         uint32_t cur[Q];
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
     uint32_t u = blockIdx.x;
     v4f a[Q], b[Q];
     if (u < n_units) fetch(u, a);  // the first loads are in flight while the table is copied
-    sr = load_bucket_table(tab, lds + kTeamSlots);
+    sr = load_bucket_table<kWg>(tab, lds + kTeamSlots);
     sr.marks = REMAP;  // known at compile time: no test for marked code bytes in the loop
     __syncthreads();
     // steady state as in k_encode_full: the next block's loads are issued unconditionally before the work on
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restri
         }
     };
     if (u < n_units) open_unit(u, un, fast);  // the first loads are in flight while the table is built
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     while (u < n_units) {
         const float s = scales[un.block];

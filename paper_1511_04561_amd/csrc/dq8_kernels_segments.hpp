@@ -258,7 +258,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
                                                              const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
                                                              size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
 {
-    extern __shared__ uint64_t seg_lds[];  // the bounds (n_seg + 1 entries), then the search table
+    extern __shared__ uint64_t seg_lds[];  // the bounds (seg_bounds_words(n_seg) entries), then the search table
     const uint32_t lane = threadIdx.x & 63;
     v4f v[kSegQ];
     auto fetch = [&](size_t u) {
@@ -266,8 +266,9 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
 #pragma unroll
         for (int j = 0; j < kSegQ; ++j) v[j] = ldg_floats<1>(x + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
     };
+    const BucketWords<kWave * WAVES> words = request_bucket_table<kWave * WAVES>(tab);
     load_bounds(bounds, n_seg, n, seg_lds);
-    Search sr = load_bucket_table(tab, reinterpret_cast<uint32_t *>(seg_lds + n_seg + 1), kWave * WAVES);
+    Search sr = place_bucket_table(tab, words, reinterpret_cast<uint32_t *>(seg_lds + seg_bounds_words(n_seg)));
     sr.marks = REMAP;
     __syncthreads();
     size_t u = first_unit(WAVES);
@@ -339,8 +340,9 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
     };
     const size_t u0 = first_unit(WAVES);
     if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are built
+    const float lut_value = request_lut(tab);
     load_bounds(bounds, n_seg, n, seg_lds);
-    load_lut(tab, lut);
+    place_lut<kWave * WAVES>(lut_value, lut);
     __syncthreads();
     walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
         const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
@@ -420,8 +422,9 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__rest
     };
     size_t u = first_unit(WAVES);
     if (u < n_units) fetch(u);  // the first loads are in flight while the tables are built
+    const float lut_value = request_lut(tab);
     load_bounds(bounds, n_seg, n, seg_lds);
-    load_lut(tab, lut);
+    place_lut<kWave * WAVES>(lut_value, lut);
     __syncthreads();
     for (; u < n_units; u += n_waves) {
         const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kWg) void k_small_encode(const uint32_t *__restrict
     constexpr int GL = G > kWave ? kWave : G;     // lanes of a row that belong to one block
     static_assert(Q % R == 0, "a block does not straddle units");
     extern __shared__ uint32_t lds[];
-    const Search sr = load_bucket_table(tab, lds);
+    const Search sr = load_bucket_table<kWg>(tab, lds);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63;
     for (size_t u = first_unit(); u < n_units; u += n_waves) {
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_small_decode(const uint32_t *__
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     constexpr int U = Q * 4 * kWave;
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
     for (size_t u = first_unit(WPW); u < n_units; u += n_waves) {
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_small_avg(const uint32_t *__res
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     constexpr int U = Q * 4 * kWave;
-    load_lut(tab, lut);
+    load_lut<kWave * WPW>(tab, lut);
     __syncthreads();
     const int terms = K + (local ? 1 : 0);
     const float fk = (float)terms;
@@ -221,8 +221,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_small_avg_encode(const uint32_t
     constexpr int R = G > kWave ? G / kWave : 1;  // rows of 64 quads per block
     constexpr int GL = G > kWave ? kWave : G;     // lanes of a row that belong to one block
     static_assert(Q % R == 0, "a block does not straddle units");
-    load_lut(tab, lut);
-    const Search sr = load_bucket_table(tab, bucket_lds, kWave * WPW);
+    const Search sr = load_tables<kWave * WPW>(tab, lut, bucket_lds);
     __syncthreads();
     const int terms = K + (local ? 1 : 0);
     const float fk = (float)terms;

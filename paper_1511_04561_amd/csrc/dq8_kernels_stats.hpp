@@ -35,17 +35,10 @@ __device__ __forceinline__ double quotient_of_magnitudes(double e, double ax)
 
 // Magnitude table for the lookup above: row b (b = 0 .. 255, a possibly marked code byte) holds the table value
 // of the code that byte stands for, 64 copies (one per lane); entry (b, lane) at byte address b * 256 + lane * 4.
-// Thread t < 256 fills row t.  The caller synchronises before the first lookup.
-__device__ __forceinline__ void load_magnitude_lut(const uint32_t *tab, float *lds)
+// (see place_lut).
+__device__ __forceinline__ float request_magnitude_lut(const uint32_t *tab)
 {
-    if (threadIdx.x < 256) {
-        const uint32_t code = fix_marked_codes(threadIdx.x) & 0x7Fu;
-        const float val = u2f(tab[kCbOff + code]);
-        const v4f four = {val, val, val, val};
-        v4f *row = reinterpret_cast<v4f *>(lds + threadIdx.x * kLutCopies);
-#pragma unroll
-        for (int c = 0; c < kLutCopies / 4; ++c) row[c] = four;
-    }
+    return u2f(tab[kCbOff + (fix_marked_codes(threadIdx.x & 255) & 0x7Fu)]);
 }
 
 // wavefronts per workgroup: two workgroups (two value tables) share a compute unit, six wavefronts per SIMD
@@ -86,8 +79,10 @@ __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const
     constexpr int U = Q * 4 * kWave;
     __shared__ __align__(256) float lut[256 * kLutCopies];
     extern __shared__ uint32_t bucket_lds[];
-    load_magnitude_lut(tab, lut);
-    const Search sr = load_bucket_table(tab, bucket_lds, kStatsWg);
+    const float lut_value = request_magnitude_lut(tab);
+    const BucketWords<kStatsWg> words = request_bucket_table<kStatsWg>(tab);
+    place_lut<kStatsWg>(lut_value, lut);
+    const Search sr = place_bucket_table(tab, words, bucket_lds);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
     const size_t wave = first_unit(kStatsWaves);

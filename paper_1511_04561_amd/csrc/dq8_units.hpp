@@ -24,6 +24,9 @@ constexpr int kSegQ = 4;                     // quads per lane
 constexpr int kSegUnit = kSegQ * 4 * kWave;  // 1024 elements per unit
 constexpr int kSegWaves = 8;                 // wavefronts per workgroup
 
+// LDS entries that the n_seg + 1 bounds take where a table of 16-byte words follows them.
+DQ8_HD uint32_t seg_bounds_words(size_t n_seg) { return (uint32_t)((n_seg + 2) / 2 * 2); }
+
 // The kernels for an array that is one block.
 constexpr int kOneWaves = 8;  // wavefronts per workgroup
 
