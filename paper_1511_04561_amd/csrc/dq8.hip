@@ -623,6 +623,34 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
     return after_launch("k_encode", stream);
 }
 
+// Compression of a short array that is one block (n from 4 to kNearLongest, x a multiple of 4): every workgroup of 4096 elements
+// forms the maximum of the whole array.
+int launch_encode_near(const DeviceState &st, int kind, const float *x, size_t n, float *scale, uint8_t *codes, hipStream_t stream)
+{
+    const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
+    const size_t lds = ((size_t)kNearWaves + st.search_words[kind]) * sizeof(uint32_t);
+    const unsigned grid = (unsigned)((n + kNearSlice - 1) / kNearSlice);
+#define DQ8_NEAR(R)                                                                                                             \
+    if (st.has_remap[kind])                                                                                                     \
+        hipLaunchKernelGGL((k_encode_near<R, true>), dim3(grid), dim3(kNearWg), lds, stream, tab, x, (uint32_t)n, scale, codes);  \
+    else                                                                                                                        \
+        hipLaunchKernelGGL((k_encode_near<R, false>), dim3(grid), dim3(kNearWg), lds, stream, tab, x, (uint32_t)n, scale, codes)
+    if (grid <= 1)
+        DQ8_NEAR(1);
+    else if (grid <= 2)
+        DQ8_NEAR(2);
+    else if (grid <= 4)
+        DQ8_NEAR(4);
+    else if (grid <= 8)
+        DQ8_NEAR(8);
+    else if (grid <= 16)
+        DQ8_NEAR(16);
+    else
+        DQ8_NEAR(24);
+#undef DQ8_NEAR
+    return after_launch("k_encode_near", stream);
+}
+
 // Error statistics of compress-then-decompress into stats[4 nb] (and means[2] when not NULL); given: the scales are
 // an input, otherwise they are the block maxima and written first.
 int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n, size_t block, float *scales, bool given,
@@ -1322,6 +1350,8 @@ int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, 
     codes += done;
     scales += done / Bq;
     n -= done;
+    if (!given && Bq == n && n >= 4 && n <= kNearLongest && ((uintptr_t)x & 3) == 0)
+        return launch_encode_near(*st, kind, x, n, scales, codes, stream);
     // the block fits one unit: absmax and encode in one kernel
     const bool fused = !given && Bq <= (g_tune.enc_long ? kLongestHeldBlock : (size_t)kUnit);
     if (!given && !fused) {
@@ -1492,6 +1522,16 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (!(flags & DQ8_SCALES_GIVEN) && n >= 4 && n <= kNearLongest && ((uintptr_t)x & 3) == 0) {
+        const uint32_t *table = st->tables + (size_t)kind * kTableWords;
+        const unsigned grid = (unsigned)((n + kNearSlice - 1) / kNearSlice);
+        const size_t lds = seg_bounds_words(n_seg) * sizeof(uint64_t) + (st->search_words[kind] + n_seg) * sizeof(uint32_t);
+        if (st->has_remap[kind])
+            hipLaunchKernelGGL(k_seg_near<true>, dim3(grid), dim3(kNearWg), lds, stream, table, x, (uint32_t)n, bounds, (uint32_t)n_seg, scales, codes);
+        else
+            hipLaunchKernelGGL(k_seg_near<false>, dim3(grid), dim3(kNearWg), lds, stream, table, x, (uint32_t)n, bounds, (uint32_t)n_seg, scales, codes);
+        return after_launch("k_seg_near", stream);
+    }
     if (!(flags & DQ8_SCALES_GIVEN)) {
         rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream, kPlainBeforeCompression);
         if (rc) return rc;

@@ -148,6 +148,10 @@ inline unsigned one_block_grid(int cus, size_t n, size_t unit, int per_cu)
     return (unsigned)(all < most ? all : most);
 }
 
+// The longest array whose maxima every workgroup forms by itself (k_encode_near, k_seg_near): at this length one workgroup reads
+// 384 KiB, and one launch takes 5.3 us (one scale; 20 segments 6.6) where three take 7.0 (11.1).
+constexpr size_t kNearLongest = 98304;
+
 // Arrays that are read twice, first for their maxima: up to this many floats the first pass reads with plain loads, so that
 // the second finds them in the memory-side cache, which holds kCachedFloats; longer arrays with non-temporal loads.
 // What follows decides how far beyond the cache that pays (plain against non-temporal, both passes).  A compression, which

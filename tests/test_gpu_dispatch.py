@@ -175,3 +175,24 @@ def test_expansion_at_the_longest_short_array(dq8, block, more):
     dq8.decode(more % 4, dev(codes, 1), dev(scales), block, out=go.t)
     same_bits(go.t, oracle.decode(more % 4, codes, scales, block), "expansion")
     go.check("expansion")
+
+
+# slices of 4096 elements and a last one of 1, 2, 3 and more; the kernels that take 1, 2, 4, 8, 16 and 24 slices; the longest array and one more
+@pytest.mark.parametrize("n", [4, 7, 4095, 4096, 4097, 8194, 16387, 16388, 32769, 65536, 65537, 98301, 98304, 98305])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_short_arrays_in_one_launch(dq8, n, offset):
+    """Arrays with one scale, and tensors back to back, whose maxima every workgroup forms by itself: segments shorter than a quad,
+    empty ones at the start, inside and at the end, one that spans all slices, more segments than threads."""
+    rng = np.random.Generator(np.random.PCG64(9100 + n % 97 + offset))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    kind = (n + offset) % 4
+    for at in {0, n // 2, n - 1}:  # the maximum at either end and inside
+        y = x.copy()
+        y[at] = -3.0
+        check_encode_decode(dq8, kind, y, 0, x_off=offset, c_off=offset, tag="one scale")
+    check_encode_decode(dq8, (kind + 1) % 4, np.zeros(n, np.float32), 0, x_off=offset, c_off=offset, tag="zeros")
+    inner = rng.integers(0, n + 1, 6)
+    near = np.minimum(n, [1, 3, 4, 4095, 4096, 4096, 4099, 8191, 12288])
+    for cuts in ([], [n // 3], inner, near, n - near, np.concatenate([[0, 0], inner, [n, n]]), rng.integers(0, n + 1, 2000)):
+        bounds = np.concatenate([[0], np.sort(np.asarray(cuts, np.int64)), [n]])
+        check_segments(dq8, (kind + len(bounds)) % 4, x, bounds, x_off=offset, c_off=(offset + n) % 4, tag="%d segments" % (len(bounds) - 1))
