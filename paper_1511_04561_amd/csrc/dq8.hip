@@ -1579,12 +1579,17 @@ int dq8_decode_segments(int kind, const uint8_t *codes, const float *scales, siz
     const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves, false, wpw);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)out & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    if (wpw == kSegWaves)
-        hipLaunchKernelGGL((k_seg_decode<kSegWaves>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, codes, scales, n, bounds,
-                           (uint32_t)n_seg, units, p.n_waves, out);
+    const size_t lds = p.lds + (scales_fit_near(n_seg) ? n_seg * sizeof(float) : 0);
+#define DQ8_SEG_DEC(W, NEAR)                                                                                                  \
+    hipLaunchKernelGGL((k_seg_decode<W, NEAR>), dim3(p.grid), dim3(kWave * (W)), lds, stream, tab, codes, scales, n, bounds, \
+                       (uint32_t)n_seg, units, p.n_waves, out)
+    if (scales_fit_near(n_seg))  // two workgroups' tables fit
+        DQ8_SEG_DEC(kSegWaves, true);
+    else if (wpw == kSegWaves)
+        DQ8_SEG_DEC(kSegWaves, false);
     else
-        hipLaunchKernelGGL((k_seg_decode<2 * kSegWaves>), dim3(p.grid), dim3(2 * kSegWg), p.lds, stream, tab, codes, scales, n, bounds,
-                           (uint32_t)n_seg, units, p.n_waves, out);
+        DQ8_SEG_DEC(2 * kSegWaves, false);
+#undef DQ8_SEG_DEC
     return after_launch("k_seg_decode", stream);
 }
 
@@ -1614,12 +1619,23 @@ int dq8_decode_accumulate_avg_segments(int kind, const uint8_t *const *codes, co
     const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves, false, wpw);
     const size_t units = whole_units(n, kSegUnit, (((uintptr_t)out | (uintptr_t)local) & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    if (wpw == kSegWaves)
-        hipLaunchKernelGGL((k_seg_avg<kSegWaves>), dim3(p.grid), dim3(kSegWg), p.lds, stream, tab, wp, K, local, n, bounds,
-                           (uint32_t)n_seg, units, p.n_waves, out);
+    const bool near = scales_fit_near((size_t)K * n_seg);
+    const size_t lds = p.lds + (near ? (size_t)K * n_seg * sizeof(float) : 0);
+    const bool one_unit = units <= p.n_waves, one_workgroup = p.grid <= (unsigned)st->cus;
+#define DQ8_SEG_AVG(W, AHEAD, NEAR)                                                                                           \
+    hipLaunchKernelGGL((k_seg_avg<W, AHEAD, NEAR>), dim3(p.grid), dim3(kWave * (W)), lds, stream, tab, wp, K, local, n, bounds, \
+                       (uint32_t)n_seg, units, p.n_waves, out)
+    if (near && one_unit && one_workgroup && K > 4)
+        DQ8_SEG_AVG(kSegWaves, 8, true);
+    else if (near && one_unit && K > 2)
+        DQ8_SEG_AVG(kSegWaves, 4, true);
+    else if (near)  // two workgroups' tables fit
+        DQ8_SEG_AVG(kSegWaves, 2, true);
+    else if (wpw == kSegWaves)
+        DQ8_SEG_AVG(kSegWaves, 2, false);
     else
-        hipLaunchKernelGGL((k_seg_avg<2 * kSegWaves>), dim3(p.grid), dim3(2 * kSegWg), p.lds, stream, tab, wp, K, local, n, bounds,
-                           (uint32_t)n_seg, units, p.n_waves, out);
+        DQ8_SEG_AVG(2 * kSegWaves, 2, false);
+#undef DQ8_SEG_AVG
     return after_launch("k_seg_avg", stream);
 }
 

@@ -27,19 +27,44 @@ namespace {
 constexpr int kSegMax = DQ8_MAX_SEGMENTS;  // segments per call: the bounds fit 32 KiB of LDS
 constexpr int kSegWg = kWave * kSegWaves;
 
+// The bounds as a workgroup holds them: all of them in LDS, and, where a wavefront has a lane for each (fewer than 64
+// segments), one per lane in a register, so that the segment of a unit is one vote without a wait for LDS.
+struct SegBounds {
+    const uint64_t *lds;
+    uint32_t n_seg;
+    uint64_t own;  // bound number lane, the largest number in lanes past the last bound
+};
+
 // Copies bounds[0 .. n_seg] to LDS, clamped to n.  The caller synchronises the workgroup.
-__device__ __forceinline__ void load_bounds(const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n, uint64_t *lds)
+__device__ __forceinline__ SegBounds load_bounds(const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n, uint64_t *lds, uint32_t lane)
 {
-    for (uint32_t i = threadIdx.x; i <= n_seg; i += blockDim.x) {
-        const uint64_t b = bounds[i];
-        lds[i] = b < (uint64_t)n ? b : (uint64_t)n;
+    SegBounds r = {lds, n_seg, ~(uint64_t)0};
+    if (n_seg < (uint32_t)kWave) {
+        if (lane <= n_seg) {
+            const uint64_t b = bounds[lane];
+            r.own = b < (uint64_t)n ? b : (uint64_t)n;
+            if (threadIdx.x <= n_seg) lds[lane] = r.own;
+        }
+    } else {
+        for (uint32_t i = threadIdx.x; i <= n_seg; i += blockDim.x) {
+            const uint64_t b = bounds[i];
+            lds[i] = b < (uint64_t)n ? b : (uint64_t)n;
+        }
     }
+    return r;
 }
 
 // The last segment whose first element is at or before element v (the same v in every lane), at most
-// n_seg - 1: two votes of the wavefront.
-__device__ __forceinline__ uint32_t segment_of_uniform(const uint64_t *lds, uint32_t n_seg, uint64_t v, uint32_t lane)
+// n_seg - 1: one vote of the wavefront, or two over the bounds in LDS.
+__device__ __forceinline__ uint32_t segment_of_uniform(const SegBounds &sb, uint64_t v, uint32_t lane)
 {
+    const uint32_t n_seg = sb.n_seg;
+    if (n_seg < (uint32_t)kWave) {
+        const uint32_t c = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(sb.own <= v));
+        const uint32_t s = c ? c - 1 : 0;
+        return s < n_seg - 1 ? s : n_seg - 1;
+    }
+    const uint64_t *lds = sb.lds;
     const uint32_t stride = (n_seg + kWave) / kWave;  // ceil((n_seg + 1) / 64), at most 64
     uint32_t i = lane * stride;
     i = i < n_seg ? i : n_seg;
@@ -74,15 +99,15 @@ struct SegSpan {
     uint32_t len, first, last;
 };
 
-__device__ __forceinline__ SegSpan open_span(const uint64_t *lds, uint32_t n_seg, size_t start, uint32_t len, uint32_t lane)
+__device__ __forceinline__ SegSpan open_span(const SegBounds &sb, size_t start, uint32_t len, uint32_t lane)
 {
     SegSpan q;
     q.start = start;
     q.len = len;
-    q.first = segment_of_uniform(lds, n_seg, start, lane);
+    q.first = segment_of_uniform(sb, start, lane);
     q.last = q.first;
-    if (q.first != n_seg - 1 && lds[q.first + 1] < start + len) {
-        const uint32_t s = segment_of_uniform(lds, n_seg, start + len - 1, lane);
+    if (sb.n_seg < (uint32_t)kWave || (q.first != sb.n_seg - 1 && sb.lds[q.first + 1] < start + len)) {
+        const uint32_t s = segment_of_uniform(sb, start + len - 1, lane);
         q.last = s > q.first ? s : q.first;
     }
     return q;
@@ -91,11 +116,11 @@ __device__ __forceinline__ SegSpan open_span(const uint64_t *lds, uint32_t n_seg
 // Elements at .. of a unit with several segments, up to 1024 of them and at least four: where fewer are left, the unit's
 // last four (some of them once more).  Units of more than 1024 elements are read again for this: their registers would
 // have to be indexed at run time, and few units hold several segments.
-__device__ __forceinline__ SegSpan open_part(const uint64_t *lds, uint32_t n_seg, const SegSpan &unit, uint32_t at, uint32_t lane)
+__device__ __forceinline__ SegSpan open_part(const SegBounds &sb, const SegSpan &unit, uint32_t at, uint32_t lane)
 {
     const uint32_t left = unit.len - at;
-    if (left >= 4) return open_span(lds, n_seg, unit.start + at, left < (uint32_t)kSegUnit ? left : (uint32_t)kSegUnit, lane);
-    return open_span(lds, n_seg, unit.start + unit.len - 4, 4, lane);
+    if (left >= 4) return open_span(sb, unit.start + at, left < (uint32_t)kSegUnit ? left : (uint32_t)kSegUnit, lane);
+    return open_span(sb, unit.start + unit.len - 4, 4, lane);
 }
 
 // Segments of the elements that a lane holds of a stretch of 1024: quads quad_start(j * 64 + lane, len), j = 0 .. 3.
@@ -107,15 +132,47 @@ struct SegQuads {
     bool split[ROWS];
 };
 
+// Few segments in the stretch (mostly two): every lane counts, for each of its elements, the segments that have begun at or
+// before it, one bound after the other; no wait but for the bound, no branch.  More than kCountedSegments: a search per quad
+// and steps from element to element.  The
+// search and the steps wait for LDS three to ten times: expansion of 200 000 elements in 20 segments, in a graph,
+// 4.9 / 4.0 us, of 3000 in 60 6.4 / 6.4, and counting 20 bounds in a unit 7.4.
+constexpr uint32_t kCountedSegments = 16;
+
 template <int ROWS = kSegQ>
-__device__ __forceinline__ SegQuads<ROWS> segments_of_quads(const uint64_t *lds, const SegSpan &q, uint32_t lane, uint32_t row = 0)
+__device__ __forceinline__ SegQuads<ROWS> segments_of_quads(const SegBounds &sb, const SegSpan &q, uint32_t lane, uint32_t row = 0)
 {
     SegQuads<ROWS> r;
+    const uint64_t *lds = sb.lds;
+    const uint32_t span = q.last - q.first;
+    if (span <= kCountedSegments) {
+        // the low half of bound i in a scalar register
+        auto bound = [&](uint32_t i) {
+            if (sb.n_seg < (uint32_t)kWave) return (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sb.own, (int)i);
+            return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)lds[i]);
+        };
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r.seg[j][c] = q.first;
+#pragma unroll 1
+        for (uint32_t i = q.first + 1; i <= q.last; ++i) {
+            const int32_t at = (int32_t)(bound(i) - (uint32_t)q.start);  // in the stretch, so below 4096
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+                const int32_t off = (int32_t)quad_start(row + j * kWave + lane, q.len);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r.seg[j][c] += off >= at - c ? 1u : 0u;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) r.split[j] = __builtin_amdgcn_ballot_w64(r.seg[j][3] != r.seg[j][0]) != 0;
+        return r;
+    }
     // Whether segment i has begun at offset off of the stretch, for i in (first, last]: those begin inside the stretch,
     // so the difference fits 32 bits.
     auto begun = [&](uint32_t i, uint32_t off) { return (uint32_t)lds[i] - (uint32_t)q.start <= off; };
-    const uint32_t span = q.last - q.first;
-    const uint32_t top = span ? 1u << (31 - __builtin_clz(span)) : 0;
+    const uint32_t top = 1u << (31 - __builtin_clz(span));
 #pragma unroll
     for (int j = 0; j < ROWS; ++j) r.seg[j][0] = q.first;
     for (uint32_t step = top; step != 0; step >>= 1) {
@@ -195,7 +252,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
     };
     size_t u = first_unit(kSegWaves);
     if (u < n_units) fetch(u);
-    load_bounds(bounds, n_seg, n, seg_lds);
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
     for (uint32_t i = threadIdx.x; i < n_seg; i += kSegWg) best[i] = 0;
     __syncthreads();
     uint32_t run = 0, run_seg = 0;  // of the whole units of one segment so far
@@ -205,7 +262,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
         run = 0;
     };
     for (; u < n_units; u += n_waves) {
-        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)U, seg_unit_len<U>(u, n), lane);
+        const SegSpan q = open_span(sb, u * (size_t)U, seg_unit_len<U>(u, n), lane);
         if (q.first == q.last) {
             float fm = 0.0f;
 #pragma unroll
@@ -218,11 +275,11 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
             run = run > f2u(fm) ? run : f2u(fm);
         } else {
             for (uint32_t at = 0; at < q.len; at += kSegUnit) {
-                const SegSpan part = open_part(seg_lds, n_seg, q, at, lane);
+                const SegSpan part = open_part(sb, q, at, lane);
                 v4f w[kSegQ];
 #pragma unroll
                 for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<NT>(x + part.start, quad_start(j * kWave + lane, part.len));
-                const SegQuads<kSegQ> sq = segments_of_quads(seg_lds, part, lane);
+                const SegQuads<kSegQ> sq = segments_of_quads(sb, part, lane);
 #pragma unroll
                 for (int j = 0; j < kSegQ; ++j) {
                     const uint32_t a[4] = {abs_bits(w[j].x), abs_bits(w[j].y), abs_bits(w[j].z), abs_bits(w[j].w)};
@@ -272,14 +329,14 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
         for (int j = 0; j < kSegQ; ++j) v[j] = ldg_floats<1>(x + u * (size_t)kSegUnit, quad_start(j * kWave + lane, len));
     };
     const BucketWords<kWave * WAVES> words = request_bucket_table<kWave * WAVES>(tab);
-    load_bounds(bounds, n_seg, n, seg_lds);
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
     Search sr = place_bucket_table(tab, words, reinterpret_cast<uint32_t *>(seg_lds + seg_bounds_words(n_seg)));
     sr.marks = REMAP;
     __syncthreads();
     size_t u = first_unit(WAVES);
     if (u < n_units) fetch(u);
     while (u < n_units) {
-        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        const SegSpan q = open_span(sb, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
         u += n_waves;
         uint32_t cw[kSegQ];
         if (q.first == q.last) {
@@ -287,7 +344,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
             const float d = s == 0.0f ? 1.0f : s;
             encode_quads<true, kSegQ>(sr, v, d, 1.0f / d, reciprocal_ok(d), cw);
         } else {
-            const SegQuads<kSegQ> sq = segments_of_quads(seg_lds, q, lane);
+            const SegQuads<kSegQ> sq = segments_of_quads(sb, q, lane);
             v4f d[kSegQ];
 #pragma unroll
             for (int j = 0; j < kSegQ; ++j) d[j] = scales_of_quad(scales, sq, j);
@@ -340,14 +397,14 @@ __global__ __launch_bounds__(kNearWg) void k_seg_near(const uint32_t *__restrict
     v4f own[1];
     own[0] = ldg_floats<0>(x + begin, quad_start(threadIdx.x, to - begin));
     const BucketWords<kNearWg> words = request_bucket_table<kNearWg>(tab);
-    load_bounds(bounds, n_seg, n, seg_lds);
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
     uint32_t *table = reinterpret_cast<uint32_t *>(seg_lds + seg_bounds_words(n_seg));
     Search sr = place_bucket_table(tab, words, table);
     sr.marks = REMAP;
     uint32_t *best = table + (tab[kNBucketOff] + 3) / 4 * 4;
     for (uint32_t i = threadIdx.x; i < n_seg; i += kNearWg) best[i] = 0;
     __syncthreads();
-    const SegSpan q = open_span(seg_lds, n_seg, begin, to - begin, lane);
+    const SegSpan q = open_span(sb, begin, to - begin, lane);
     // Segment 0 takes what lies before its first element, the last one what lies beyond its end.
     auto start_of = [&](uint32_t i) { return i == 0 ? 0u : (uint32_t)seg_lds[i]; };
     auto end_of = [&](uint32_t i) { return i == n_seg - 1 ? n : (uint32_t)seg_lds[i + 1]; };
@@ -377,7 +434,7 @@ __global__ __launch_bounds__(kNearWg) void k_seg_near(const uint32_t *__restrict
     SegQuads<1> sq;
     if (q.first != q.last) {
         whole_segment(q.last);
-        sq = segments_of_quads<1>(seg_lds, q, lane, wave_in_wg() * kWave);
+        sq = segments_of_quads<1>(sb, q, lane, wave_in_wg() * kWave);
         const uint32_t a[4] = {abs_bits(own[0].x), abs_bits(own[0].y), abs_bits(own[0].z), abs_bits(own[0].w)};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -412,7 +469,10 @@ __global__ __launch_bounds__(kNearWg) void k_seg_near(const uint32_t *__restrict
 // together 180 instead of 150 us.)  The stores of a whole unit stand without a condition: 4 Mi elements 7.4 -> 7.0 us.
 // WAVES: 8, or 16 where segment_waves() says so: with 4095 segments only one workgroup's tables fit, and 16 wavefronts
 // instead of 8 take 64.3 us for 61 M elements instead of 85.9, 10.4 instead of 17.4 for 8 Mi.
-template <int WAVES>
+// NEAR: the segments' scales are copied to LDS with the bounds.  Fetched when a unit's segment is known they are one more
+// round trip to memory for the wavefront, and four gathers for a unit with several segments: 8 Mi elements in 40 segments 8.6
+// / 7.5 us.
+template <int WAVES, bool NEAR>
 __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
                                                        const float *__restrict__ scales, size_t n,
                                                        const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
@@ -432,11 +492,15 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
     const size_t u0 = first_unit(WAVES);
     if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the tables are built
     const float lut_value = request_lut(tab);
-    load_bounds(bounds, n_seg, n, seg_lds);
+    float *near = reinterpret_cast<float *>(seg_lds + n_seg + 1);
+    if (NEAR)
+        for (uint32_t i = threadIdx.x; i < n_seg; i += kWave * WAVES) near[i] = scales[i];
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
     place_lut<kWave * WAVES>(lut_value, lut);
     __syncthreads();
+    const float *sc = NEAR ? near : scales;
     walk_units(u0, n_units, n_waves, a, b, fetch, [&](size_t u, Slot &sl) {
-        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        const SegSpan q = open_span(sb, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
         float *po = out + q.start;
         auto expand = [&](int j, v4f s) {
             const uint32_t k = j * kWave + lane;
@@ -451,20 +515,20 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
                 stg_floats<2>(po + quad_start(k, q.len), r);
         };
         if (q.first == q.last) {
-            const float s = scales[q.first];
+            const float s = sc[q.first];
 #pragma unroll
             for (int j = 0; j < kSegQ; ++j) expand(j, v4f{s, s, s, s});
         } else {
-            const SegQuads<kSegQ> sq = segments_of_quads(seg_lds, q, lane);
+            const SegQuads<kSegQ> sq = segments_of_quads(sb, q, lane);
             v4f s[kSegQ];
 #pragma unroll
-            for (int j = 0; j < kSegQ; ++j) s[j] = scales_of_quad(scales, sq, j);
+            for (int j = 0; j < kSegQ; ++j) s[j] = scales_of_quad(sc, sq, j);
 #pragma unroll
             for (int j = 0; j < kSegQ; ++j) expand(j, s[j]);
         }
     });
     for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves,
-                     [&](size_t i, uint32_t seg) { out[i] = lut_code(lut, codes[i], lane4) * scales[seg]; });
+                     [&](size_t i, uint32_t seg) { out[i] = lut_code(lut, codes[i], lane4) * sc[seg]; });
 }
 
 // Decompression of K workers' buffers and their average (optionally with a local fp32 array as the first term)
@@ -473,15 +537,19 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
 // place past the last worker costs the loads of a worker, and every further pair of places registers of wavefronts (30.6 M
 // elements in 16 segments with 1, 2, 4, 8, 9 workers: 27.3, 37.5, 49, 72, 80 us with two at a time; 38, 52, 57, 84, 100 us
 // with four, 8 workers with eight 83 us).  WAVES as in k_seg_decode.
-template <int WAVES>
-__global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
+// AHEAD = 8: on arrays that are no more than a unit for every wavefront there is no next unit whose loads could cover the wait
+// for a pair of workers, so all of them (the first eight) are requested before the tables are built.
+// NEAR: all workers' scales in LDS (see k_seg_decode), row k for worker k.
+// 1.76 M elements in 10 segments, seven workers and a local term, in a graph: 10.4 us with two ahead and the scales in memory, 8.5
+// so; 3 M, three workers 10.5 / 8.1.  Eight ahead with two workgroups on a compute unit, 4 Mi, eight workers: 20.3 us, 14.7 with two.
+template <int WAVES, int AHEAD, bool NEAR>
+__global__ __launch_bounds__(kWave *WAVES, AHEAD == 8 ? 2 : 4) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
                                                     const float *__restrict__ local, size_t n,
                                                     const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
                                                     size_t n_waves, float *__restrict__ out)
 {
     __shared__ __align__(256) float lut[256 * kLutCopies];
     extern __shared__ uint64_t seg_lds[];
-    constexpr int AHEAD = 2;
     const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
     const int terms = K + (local ? 1 : 0);
     const float fk = (float)terms;
@@ -514,11 +582,16 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__rest
     size_t u = first_unit(WAVES);
     if (u < n_units) fetch(u);  // the first loads are in flight while the tables are built
     const float lut_value = request_lut(tab);
-    load_bounds(bounds, n_seg, n, seg_lds);
+    float *near = reinterpret_cast<float *>(seg_lds + n_seg + 1);
+    if (NEAR)
+        for (uint32_t k = wave_in_wg(); k < (uint32_t)K; k += WAVES)
+            for (uint32_t i = lane; i < n_seg; i += kWave) near[k * n_seg + i] = p.scales[k][i];
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
     place_lut<kWave * WAVES>(lut_value, lut);
     __syncthreads();
+    auto scales_of = [&](int k) -> const float * { return NEAR ? near + (uint32_t)k * n_seg : p.scales[k]; };
     for (; u < n_units; u += n_waves) {
-        const SegSpan q = open_span(seg_lds, n_seg, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
+        const SegSpan q = open_span(sb, u * (size_t)kSegUnit, seg_unit_len<kSegUnit>(u, n), lane);
 #pragma unroll
         for (int j = 0; j < kSegQ; ++j)  // the sum starts at +0: a local -0 becomes +0
             acc[j] = v4f{0.0f + acc[j].x, 0.0f + acc[j].y, 0.0f + acc[j].z, 0.0f + acc[j].w};
@@ -533,7 +606,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__rest
                 if (k0 != 0) fetch_workers(q.start, q.len, k0);
                 float s[AHEAD];
 #pragma unroll
-                for (int c = 0; c < AHEAD; ++c) s[c] = p.scales[k0 + c < K ? k0 + c : K - 1][q.first];
+                for (int c = 0; c < AHEAD; ++c) s[c] = scales_of(k0 + c < K ? k0 + c : K - 1)[q.first];
 #pragma unroll
                 for (int c = 0; c < AHEAD; ++c) {
                     if (k0 + c < K) {
@@ -543,27 +616,42 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__rest
                 }
             }
         } else {
-            const SegQuads<kSegQ> sq = segments_of_quads(seg_lds, q, lane);
+            const SegQuads<kSegQ> sq = segments_of_quads(sb, q, lane);
             for (int k0 = 0; k0 < K; k0 += AHEAD) {
                 if (k0 != 0) fetch_workers(q.start, q.len, k0);
-                float s[AHEAD][kSegQ];
+                if (NEAR) {  // LDS: no need to ask for the scales of several workers at once
 #pragma unroll
-                for (int c = 0; c < AHEAD; ++c)
+                    for (int c = 0; c < AHEAD; ++c) {
+                        if (k0 + c < K) {
+                            // The row is the compiler's only here: it would form the addresses of all rows' scales, 16
+                            // registers each, before the loop.
+                            uint32_t row = (uint32_t)(k0 + c) * n_seg;
+                            asm volatile("" : "+s"(row));
+                            const float *sk = near + row;
 #pragma unroll
-                    for (int j = 0; j < kSegQ; ++j) s[c][j] = p.scales[k0 + c < K ? k0 + c : K - 1][sq.seg[j][0]];
+                            for (int j = 0; j < kSegQ; ++j) add(c, j, scales_of_quad(sk, sq, j));
+                        }
+                    }
+                } else {
+                    float s[AHEAD][kSegQ];
 #pragma unroll
-                for (int j = 0; j < kSegQ; ++j) {
-                    if (!sq.split[j]) {
+                    for (int c = 0; c < AHEAD; ++c)
 #pragma unroll
-                        for (int c = 0; c < AHEAD; ++c)
-                            if (k0 + c < K) add(c, j, v4f{s[c][j], s[c][j], s[c][j], s[c][j]});
-                    } else {
-                        v4f t[AHEAD];
+                        for (int j = 0; j < kSegQ; ++j) s[c][j] = scales_of(k0 + c < K ? k0 + c : K - 1)[sq.seg[j][0]];
 #pragma unroll
-                        for (int c = 0; c < AHEAD; ++c) t[c] = scales_of_quad(p.scales[k0 + c < K ? k0 + c : K - 1], sq, j);
+                    for (int j = 0; j < kSegQ; ++j) {
+                        if (!sq.split[j]) {
 #pragma unroll
-                        for (int c = 0; c < AHEAD; ++c)
-                            if (k0 + c < K) add(c, j, t[c]);
+                            for (int c = 0; c < AHEAD; ++c)
+                                if (k0 + c < K) add(c, j, v4f{s[c][j], s[c][j], s[c][j], s[c][j]});
+                        } else {
+                            v4f t[AHEAD];
+#pragma unroll
+                            for (int c = 0; c < AHEAD; ++c) t[c] = scales_of_quad(scales_of(k0 + c < K ? k0 + c : K - 1), sq, j);
+#pragma unroll
+                            for (int c = 0; c < AHEAD; ++c)
+                                if (k0 + c < K) add(c, j, t[c]);
+                        }
                     }
                 }
             }
@@ -582,7 +670,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_avg(const uint32_t *__rest
     for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves, [&](size_t i, uint32_t seg) {
         float a = 0.0f;
         if (local) a = a + local[i];
-        for (int k = 0; k < K; ++k) a = a + lut_code(lut, p.codes[k][i], lane4) * p.scales[k][seg];
+        for (int k = 0; k < K; ++k) a = a + lut_code(lut, p.codes[k][i], lane4) * scales_of(k)[seg];
         out[i] = mean_of(a);
     });
 }

@@ -171,6 +171,12 @@ inline int segment_waves(int cus, size_t n, size_t n_seg)
     return two_fit || n <= (size_t)cus * kSegWaves * kSegUnit ? kSegWaves : 2 * kSegWaves;
 }
 
+// Whether the kernels with a value table copy `count` scales to LDS beside the bounds of at most as many segments: two workgroups
+// of kSegWaves still fit a compute unit then.
+constexpr size_t kNearScales = 1024;
+static_assert(2 * (kValueTableBytes + (kNearScales + 1) * sizeof(uint64_t) + kNearScales * sizeof(float)) <= kLdsPerCu, "two workgroups");
+inline bool scales_fit_near(size_t count) { return count <= kNearScales; }
+
 struct SegPlan {
     size_t n_items, n_waves, lds;
     uint32_t group;

@@ -196,3 +196,26 @@ def test_short_arrays_in_one_launch(dq8, n, offset):
     for cuts in ([], [n // 3], inner, near, n - near, np.concatenate([[0, 0], inner, [n, n]]), rng.integers(0, n + 1, 2000)):
         bounds = np.concatenate([[0], np.sort(np.asarray(cuts, np.int64)), [n]])
         check_segments(dq8, (kind + len(bounds)) % 4, x, bounds, x_off=offset, c_off=(offset + n) % 4, tag="%d segments" % (len(bounds) - 1))
+
+
+# bounds in registers up to 63 segments; scales of all workers in LDS up to 1024; at most 16 bounds inside a unit are counted one by
+# one; all workers' codes requested at once (up to 4, up to 8) where no wavefront has a second unit
+@pytest.mark.parametrize("n_seg,K", [(1, 3), (2, 8), (16, 4), (17, 5), (18, 9), (63, 2), (64, 3), (65, 4), (128, 8), (129, 8), (341, 3), (342, 3), (1024, 1), (1025, 1)])
+@pytest.mark.parametrize("n", [5003, 256 * 8 * 1024 - 3, 256 * 16 * 1024 + 5000])
+def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
+    """All bounds inside one unit, and spread over the array; workers averaged with and without a local term."""
+    rng = np.random.Generator(np.random.PCG64(9500 + n % 97 + n_seg))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    kind = (n + n_seg) % 4
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    for low, high in ((1025, 2047), (0, n + 1)):
+        bounds = np.concatenate([[0], np.sort(rng.integers(low, high, n_seg - 1)), [n]])
+        check_segments(dq8, kind, x, bounds, tag="%d segments" % n_seg)
+        sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
+        local = x if low else None
+        want = oracle.decode_accumulate_avg_segments(kind, cl, sl, bounds, local=local)
+        go = Guarded(n, np.float32)
+        dq8.decode_accumulate_avg_segments(kind, [dev(c) for c in cl], [dev(s) for s in sl], bounds_dev(bounds), out=go.t,
+                                           local=None if local is None else dev(local))
+        same_bits(go.t, want, "segment average")
+        go.check("segment average")
