@@ -1,4 +1,4 @@
-"""Builds libdq8.so (HIP kernels + C ABI) for gfx950 next to this file.
+"""Builds libdq8.so (HIP kernels + C ABI) for gfx950 and _binding.so (its calls from Python) next to this file.
 
 hipcc cross-compiles without a GPU.  Flags that matter for the results:
   -ffp-contract=off   the decode-and-average sum rounds product and sum separately;
@@ -13,6 +13,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdq8.so")
+BINDING = os.path.join(HERE, "_binding.so")  # Python extension over torch's C++ headers; finds the library's calls by address
+BINDING_SOURCE = os.path.join(CSRC, "dq8_binding.cpp")
 SOURCES = ["dq8.hip", "dq8_avg_short.hip", "dq8_avg_long.hip", "dq8_tables.cpp"]
 HEADERS = ["dq8_internal.h", "dq8_launch.hpp", "dq8_tables.hpp", "dq8_device.hpp", "dq8_plan.hpp", "dq8_units.hpp", "dq8_arith.hpp", "dq8_kernels_codec.hpp", "dq8_kernels_avg.hpp",
            "dq8_kernels_avg_encode.hpp", "dq8_kernels_stats.hpp", "dq8_kernels_small.hpp", "dq8_kernels_segments.hpp", os.path.join(ROOT, "include", "dq8.h")]
@@ -31,6 +33,33 @@ def hipcc():
 def command(out=LIB, extra=()):
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     return [hipcc()] + FLAGS + list(extra) + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", out] + srcs
+
+
+def binding_command(out=BINDING):
+    import sysconfig
+    from torch.utils import cpp_extension
+    torch_lib = cpp_extension.library_paths()[0]
+    includes = cpp_extension.include_paths() + [os.path.join(cpp_extension.ROCM_HOME or "/opt/rocm", "include"), sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+            + [a for d in includes for a in ("-isystem", d)] + ["-I", os.path.join(ROOT, "include"), "-o", out, BINDING_SOURCE]
+            + ["-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+
+
+def binding_stale():
+    return not os.path.exists(BINDING) or any(os.path.getmtime(d) > os.path.getmtime(BINDING)
+                                              for d in (BINDING_SOURCE, os.path.join(ROOT, "include", "dq8.h")))
+
+
+def build_binding(force=True, verbose=False):
+    if not force and not binding_stale():
+        return BINDING
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    cmd = binding_command(tmp)
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 def stale():
@@ -71,7 +100,8 @@ def _compile_and_link(out, extra=(), verbose=False):
 
 
 def build(force=True, verbose=False, extra=()):
-    """Compiles the library; with force=False only when it is missing or older than a source."""
+    """Compiles the library and the binding; with force=False only what is missing or older than a source."""
+    build_binding(force, verbose)
     if not force and not stale():
         return LIB
     tmp = LIB + ".tmp%d" % os.getpid()

@@ -3,6 +3,9 @@
 Every function takes torch CUDA tensors (device memory) and enqueues the library's
 HIP kernels on torch's current stream.  Nothing is computed here and there is no
 fallback: if libdq8.so is missing or a call fails, an exception is raised.
+
+A call with ordinary arguments is marshalled by the extension _binding.so (csrc/dq8_binding.cpp); it returns None for
+any other, which then takes the code here: the same library call, and the place where wrong arguments are reported.
 """
 import ctypes
 import os
@@ -19,13 +22,23 @@ LIB_PATH = os.environ.get("DQ8_LIBRARY") or os.path.join(_HERE, "libdq8.so")
 _lib = None
 
 
+class _Unbound:
+    """Stands for the extension until the library is loaded: every call takes the code here, which loads it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_native = _Unbound()
+
+
 class Dq8Error(RuntimeError):
     pass
 
 
 def lib():
     """The loaded shared library (loaded on first use)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise Dq8Error("%s not found: build it with `python -m paper_1511_04561_amd.build` "
@@ -55,8 +68,19 @@ def lib():
         L.dq8_model_speedup.restype = ci
         L.dq8_model_penalty.restype = ci
         L.dq8_last_error.restype = ctypes.c_char_p
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise Dq8Error("%s/_binding.so cannot be loaded (%s): build it with `python -m paper_1511_04561_amd.build`" % (_HERE, e)) from e
+        _binding.bind(Dq8Error, {name: ctypes.cast(getattr(L, name), vp).value for name in _BOUND})
+        _native = _binding
         _lib = L
     return _lib
+
+
+_BOUND = ("dq8_absmax", "dq8_encode", "dq8_decode", "dq8_absmax_segments", "dq8_encode_segments", "dq8_decode_segments",
+          "dq8_decode_accumulate_avg", "dq8_decode_accumulate_avg_local", "dq8_decode_accumulate_avg_segments",
+          "dq8_decode_avg_encode", "dq8_error_stats", "dq8_last_error")
 
 
 def _check(rc, what):
@@ -96,9 +120,8 @@ def _enqueue(fn, index, *args):
     """Calls the library function `fn` with `args` and torch's current stream on device `index`, which is made current for the
     call if it is not.
 
-    The stream is asked for as the raw handle: torch.cuda.current_stream() builds a Stream object first, which took 2.9 us
-    of the 8.0 us that a call on 4096 elements took (the handle: 0.07 us; such a call now: 5.4 us, 3.5 of
-    them in the library, most of that one kernel launch)."""
+    The stream is asked for as the raw handle: torch.cuda.current_stream() builds a Stream object first (2.9 us; the handle
+    0.07)."""
     if index == _current_device():
         rc = fn(*args, _raw_stream(index))
     else:
@@ -120,6 +143,9 @@ def init():
 
 
 def absmax(x, block=0, scales=None):
+    done = _native.absmax(x, block, scales)
+    if done is not None:
+        return done
     x = _dev(x, torch.float32, "x")
     n = x.numel()
     if scales is None:
@@ -133,6 +159,9 @@ def absmax(x, block=0, scales=None):
 
 def encode(kind, x, block=0, scales=None, codes=None, scales_given=False):
     """Returns (codes, scales).  With scales_given the passed scales are used as they are."""
+    done = _native.encode(kind, x, block, scales, codes, scales_given)
+    if done is not None:
+        return done
     x = _dev(x, torch.float32, "x")
     n = x.numel()
     if scales is None:
@@ -151,6 +180,9 @@ def encode(kind, x, block=0, scales=None, codes=None, scales_given=False):
 
 
 def decode(kind, codes, scales, block=0, out=None):
+    done = _native.decode(kind, codes, scales, block, out)
+    if done is not None:
+        return done
     codes = _dev(codes, torch.uint8, "codes")
     scales = _dev(scales, torch.float32, "scales")
     n = codes.numel()
@@ -177,6 +209,9 @@ def _bounds(bounds, n):
 
 
 def absmax_segments(x, bounds, scales=None):
+    done = _native.absmax_segments(x, bounds, scales)
+    if done is not None:
+        return done
     x = _dev(x, torch.float32, "x")
     b, n_seg = _bounds(bounds, x.numel())
     if scales is None:
@@ -190,6 +225,9 @@ def absmax_segments(x, bounds, scales=None):
 
 def encode_segments(kind, x, bounds, scales=None, codes=None, scales_given=False):
     """Tensors back to back in x, one scale each.  Returns (codes, scales)."""
+    done = _native.encode_segments(kind, x, bounds, scales, codes, scales_given)
+    if done is not None:
+        return done
     x = _dev(x, torch.float32, "x")
     n = x.numel()
     b, n_seg = _bounds(bounds, n)
@@ -209,6 +247,9 @@ def encode_segments(kind, x, bounds, scales=None, codes=None, scales_given=False
 
 
 def decode_segments(kind, codes, scales, bounds, out=None):
+    done = _native.decode_segments(kind, codes, scales, bounds, out)
+    if done is not None:
+        return done
     codes = _dev(codes, torch.uint8, "codes")
     scales = _dev(scales, torch.float32, "scales")
     n = codes.numel()
@@ -245,6 +286,9 @@ def _workers(codes_list, scales_list, block, n=None):
 
 def decode_accumulate_avg(kind, codes_list, scales_list, block=0, out=None, local=None):
     """Mean of the K decoded buffers; with ``local`` (fp32) that array is the first of K + 1 terms."""
+    done = _native.decode_accumulate_avg(kind, codes_list, scales_list, block, out, local)
+    if done is not None:
+        return done
     if local is not None:
         _dev(local, torch.float32, "local")
     K, n, cp, sp = _workers(codes_list, scales_list, block, None if local is None else local.numel())
@@ -264,6 +308,9 @@ def decode_accumulate_avg(kind, codes_list, scales_list, block=0, out=None, loca
 
 def decode_accumulate_avg_segments(kind, codes_list, scales_list, bounds, out=None, local=None):
     """Mean of the K decoded buffers of tensors back to back, one scale per tensor and worker."""
+    done = _native.decode_accumulate_avg_segments(kind, codes_list, scales_list, bounds, out, local)
+    if done is not None:
+        return done
     if local is not None:
         _dev(local, torch.float32, "local")
     K = len(codes_list)
@@ -290,6 +337,9 @@ def decode_accumulate_avg_segments(kind, codes_list, scales_list, bounds, out=No
 
 def decode_avg_encode(kind, codes_list, scales_list, block=0, local=None, scales=None, codes=None):
     """Average the K buffers (with ``local`` as first term if given) and compress the average: (codes, scales)."""
+    done = _native.decode_avg_encode(kind, codes_list, scales_list, block, local, scales, codes)
+    if done is not None:
+        return done
     if local is not None:
         _dev(local, torch.float32, "local")
     K, n, cp, sp = _workers(codes_list, scales_list, block, None if local is None else local.numel())
@@ -313,6 +363,9 @@ def error_stats(kind, x, block=0, scales=None, scales_given=False, stats=None, m
     Returns (stats float64[nb, 4], means float64[2]) on the device: per block the sum of absolute errors,
     the sum of relative errors over non-zero inputs, the number of non-zero inputs and the largest absolute
     error; means = (mean absolute error, mean relative error over non-zero inputs)."""
+    done = _native.error_stats(kind, x, block, scales, scales_given, stats, means)
+    if done is not None:
+        return done
     x = _dev(x, torch.float32, "x")
     n = x.numel()
     nb = n_blocks(n, block)

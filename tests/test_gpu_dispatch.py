@@ -219,3 +219,60 @@ def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
                                            local=None if local is None else dev(local))
         same_bits(go.t, want, "segment average")
         go.check("segment average")
+
+
+def test_calls_marshalled_by_the_extension_and_by_python(dq8, monkeypatch):
+    """Ordinary arguments go through the extension, any others are declined there before anything has happened; both ways give the
+    same bytes, on a side stream too, and errors are those of dq8.py."""
+    native = dq8._native
+    n, nb, n_seg = 5003, 5, 3
+    rng = np.random.Generator(np.random.PCG64(9900))
+    x, bounds = dev(rng.standard_normal(n).astype(np.float32)), bounds_dev(np.array([0, 7, 4099, n]))
+    codes, scales = [dev(rng.integers(0, 256, n).astype(np.uint8)) for _ in range(3)], [dev(np.full(nb, 0.5 + k, np.float32)) for k in range(3)]
+    new = lambda m, t=torch.float32: torch.empty(m, dtype=t, device="cuda")  # noqa: E731
+    calls = [("absmax", lambda: [x, 1024, None]), ("absmax", lambda: [x, 0, new(1)]),
+             ("encode", lambda: [0, x, 1024, None, None, False]), ("encode", lambda: [1, x, 1024, scales[1], new(n, torch.uint8), True]),
+             ("decode", lambda: [2, codes[0], scales[0], 1024, None]), ("absmax_segments", lambda: [x, bounds, None]),
+             ("encode_segments", lambda: [3, x, bounds, None, new(n, torch.uint8), False]),
+             ("decode_segments", lambda: [0, codes[1], scales[1], bounds, new(n)]),
+             ("decode_accumulate_avg", lambda: [0, codes, scales, 1024, None, None]), ("decode_accumulate_avg", lambda: [0, (), (), 1024, None, x]),
+             ("decode_accumulate_avg_segments", lambda: [1, codes, tuple(scales), bounds, None, x]),
+             ("decode_avg_encode", lambda: [2, codes, scales, 1024, x, None, None]),
+             ("error_stats", lambda: [0, x, 0, None, False, new((1, 4), torch.float64), new(2, torch.float64)])]
+    flat = lambda r: [t.cpu().numpy().tobytes() for t in (r if isinstance(r, tuple) else (r,))]  # noqa: E731
+    side = torch.cuda.Stream()
+    for name, args in calls:
+        got = getattr(native, name)(*args())
+        assert got is not None, name
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            beside = getattr(native, name)(*args())
+        side.synchronize()
+        with monkeypatch.context() as m:
+            m.setattr(dq8, "_native", dq8._Unbound())
+            want = getattr(dq8, name)(*args())
+        if name != "error_stats":
+            assert flat(got) == flat(want) == flat(beside), name
+        else:
+            assert np.allclose(got[0].cpu().numpy(), want[0].cpu().numpy(), rtol=1e-12) and got[1] is not want[1]
+        # an argument that is not ordinary: a tensor subclass, a wrong type, a strided view, an integer of another type
+        class Sub(torch.Tensor):
+            pass
+        for i, a in enumerate(args()):
+            odd = {torch.Tensor: lambda: [a.as_subclass(Sub), a.to(torch.float16), torch.stack([a, a], -1)[..., 0], a.cpu()],
+                   int: lambda: [np.int64(a), -1], bool: lambda: [int(a)], list: lambda: [iter(a), a[:1] + [None], a * 11], type(None): lambda: ["x"]}.get(type(a), lambda: [])()
+            for o in odd:
+                if isinstance(o, torch.Tensor) and o.is_contiguous() and o.is_cuda and type(o) is torch.Tensor and o.dtype == a.dtype:
+                    continue
+                changed = args()
+                changed[i] = o
+                assert getattr(native, name)(*changed) is None, (name, i, o)
+    assert native.encode(0, new(0), 0, None, None, False) is None and dq8.encode(0, new(0))[0].numel() == 0
+    out = new(n)
+    assert dq8.decode(2, codes[0], scales[0], 1024, out=out) is out
+    with pytest.raises(ValueError, match="out too small"):
+        dq8.decode(2, codes[0], scales[0], 1024, out=new(n - 1))
+    with pytest.raises(dq8.Dq8Error, match="dq8_encode failed .status 2.: unknown data type 9"):
+        dq8.encode(9, x)
+    with pytest.raises(Exception):  # a transformed tensor has no address; the same with and without the extension
+        torch.vmap(lambda v: dq8.absmax(v, 0))(x[:64].view(8, 8))
