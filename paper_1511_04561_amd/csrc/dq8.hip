@@ -341,13 +341,15 @@ WorkerPtrs advance_workers(const WorkerPtrs &wp, int K, size_t done, size_t bloc
 }
 
 // `zeroed`: the caller has set the scales to +0 already.  `plain_upto`: arrays that are one block of up to this many elements are
-// read with plain loads (0: none; see kPlainBeforeCompression).
+// read with plain loads (0: none; see kPlainBeforeCompression).  `parts`, if not NULL: scratch memory for kMostParts numbers, for an
+// array that is one block of more than kUnit elements; *n_parts maxima of pieces of the array go there and
+// *scales is not written.
 int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block, float *scales, hipStream_t stream,
-                  bool zeroed = false, size_t plain_upto = 0)
+                  bool zeroed = false, size_t plain_upto = 0, float *parts = nullptr, uint32_t *n_parts = nullptr)
 {
     const size_t Bq = block_length(n, block);
     if (Bq == n && n > (size_t)kUnit) {  // one block of several units
-        if (!zeroed) {
+        if (!zeroed && !parts) {
             hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(256), 0, stream, scales, (size_t)1);
             const int rc = after_launch("k_fill_zero", stream);
             if (rc) return rc;
@@ -359,15 +361,21 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
         const unsigned grid = one_block_grid(st.cus, n, unit, 1);
         const size_t waves = (size_t)grid * kOneWaves;
         const bool plain = n <= plain_upto;
-#define DQ8_AMAX_ONE(Q, NT) hipLaunchKernelGGL((k_absmax_one<Q, NT>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, scales)
-        if (wide && plain)
+        if (parts) *n_parts = grid;
+#define DQ8_AMAX_ONE(Q, NT)                                                                                                 \
+    if (parts)                                                                                                              \
+        hipLaunchKernelGGL((k_absmax_one<Q, NT, true>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, parts);     \
+    else                                                                                                                    \
+        hipLaunchKernelGGL((k_absmax_one<Q, NT, false>), dim3(grid), dim3(kOneWg), 0, stream, x, n, units, waves, scales)
+        if (wide && plain) {
             DQ8_AMAX_ONE(16, 0);
-        else if (wide)
+        } else if (wide) {
             DQ8_AMAX_ONE(16, 1);
-        else if (plain)
+        } else if (plain) {
             DQ8_AMAX_ONE(4, 0);
-        else
+        } else {
             DQ8_AMAX_ONE(4, 1);
+        }
 #undef DQ8_AMAX_ONE
         return after_launch("k_absmax_one", stream);
     }
@@ -441,8 +449,9 @@ int launch_absmax(const DeviceState &st, const float *x, size_t n, size_t block,
     return after_launch("k_absmax", stream);
 }
 
+// `parts`, n_parts: see launch_absmax.
 int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, size_t block, float *scales, uint8_t *codes,
-                  bool fused, hipStream_t stream)
+                  bool fused, hipStream_t stream, const float *parts = nullptr, uint32_t n_parts = 0)
 {
     // Unit = the smallest power of two that holds a block, from 256 elements up to 4096 (scales given) or 16384
     // (scales computed here).  4096 and more: a team of four wavefronts per unit with 4, 8 or 16 quads per lane.
@@ -462,10 +471,18 @@ int launch_encode(const DeviceState &st, int kind, const float *x, size_t n, siz
         const size_t units = whole_units(n, 1024, ((uintptr_t)x & 3) == 0);
         const unsigned grid = one_block_grid(st.cus, n, 1024, 2);
         const size_t waves = (size_t)grid * kOneWaves, olds = (size_t)st.search_words[kind] * sizeof(uint32_t);
-        if (st.has_remap[kind])
-            hipLaunchKernelGGL((k_encode_one<true>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, codes);
+#define DQ8_ENC_ONE(RM, PARTS)                                                                                             \
+    hipLaunchKernelGGL((k_encode_one<RM, PARTS>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, \
+                       parts, n_parts, codes)
+        if (st.has_remap[kind] && parts)
+            DQ8_ENC_ONE(true, true);
+        else if (st.has_remap[kind])
+            DQ8_ENC_ONE(true, false);
+        else if (parts)
+            DQ8_ENC_ONE(false, true);
         else
-            hipLaunchKernelGGL((k_encode_one<false>), dim3(grid), dim3(kOneWg), olds, stream, tab, x, n, units, waves, scales, codes);
+            DQ8_ENC_ONE(false, false);
+#undef DQ8_ENC_ONE
         return after_launch("k_encode_one", stream);
     }
     // Whole aligned blocks of exactly one unit: the kernel without slow paths in its loop.
@@ -1289,25 +1306,34 @@ static int check_segments(const char *who, size_t n, const uint64_t *bounds, siz
     return DQ8_OK;
 }
 
-// plain_upto as in launch_absmax.
+// plain_upto as in launch_absmax.  `parts`, if not NULL: scratch memory for n_seg * kMostParts numbers; row i gets the maxima of
+// segment i of *n_parts workgroups and the scales are not written.
 static int launch_segment_absmax(const DeviceState &st, const float *x, size_t n, const uint64_t *bounds, size_t n_seg,
-                          float *scales, hipStream_t stream, size_t plain_upto)
+                          float *scales, hipStream_t stream, size_t plain_upto, float *parts = nullptr, uint32_t *n_parts = nullptr)
 {
-    hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, stream, scales, n_seg);
-    int rc = after_launch("k_fill_zero", stream);
-    if (rc) return rc;
+    if (!parts) {
+        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, stream, scales, n_seg);
+        int rc = after_launch("k_fill_zero", stream);
+        if (rc) return rc;
+    }
     const SegPlan p = make_segment_plan(st.cus, n, n_seg, kSegWaves, true);
     const size_t units = whole_units(n, (size_t)p.group * kSegUnit, ((uintptr_t)x & 3) == 0);
     const size_t lds = p.lds + n_seg * sizeof(uint32_t);
-#define DQ8_SEG_AMAX(Q, NT)                                                                                                  \
-    hipLaunchKernelGGL((k_seg_absmax<Q, NT>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg, units, \
-                       p.n_waves, scales)
-    if (p.group == 4 && n > plain_upto)
+    if (parts) *n_parts = p.grid;  // at most a workgroup per compute unit
+#define DQ8_SEG_AMAX(Q, NT)                                                                                                        \
+    if (parts)                                                                                                                     \
+        hipLaunchKernelGGL((k_seg_absmax<Q, NT, true>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg,      \
+                           units, p.n_waves, parts);                                                                               \
+    else                                                                                                                           \
+        hipLaunchKernelGGL((k_seg_absmax<Q, NT, false>), dim3(p.grid), dim3(kSegWg), lds, stream, x, n, bounds, (uint32_t)n_seg,     \
+                           units, p.n_waves, scales)
+    if (p.group == 4 && n > plain_upto) {
         DQ8_SEG_AMAX(4 * kSegQ, 1);
-    else if (p.group == 4)
+    } else if (p.group == 4) {
         DQ8_SEG_AMAX(4 * kSegQ, 0);
-    else
+    } else {
         DQ8_SEG_AMAX(kSegQ, 0);
+    }
 #undef DQ8_SEG_AMAX
     return after_launch("k_seg_absmax", stream);
 }
@@ -1325,8 +1351,20 @@ int dq8_absmax(const float *x, size_t n, size_t block, float *scales, void *hip_
     return launch_absmax(*st, x, n, block, scales, static_cast<hipStream_t>(hip_stream));
 }
 
+size_t dq8_workspace_bytes(size_t n, size_t block, unsigned flags)
+{
+    const bool whole = block_length(n, block) == n && n > kNearLongest && !(flags & DQ8_SCALES_GIVEN);
+    return whole ? kMostParts * sizeof(float) : 0;
+}
+
 int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, uint8_t *codes, unsigned flags,
                void *hip_stream)
+{
+    return dq8_encode_ws(kind, x, n, block, scales, codes, flags, nullptr, 0, hip_stream);
+}
+
+int dq8_encode_ws(int kind, const float *x, size_t n, size_t block, float *scales, uint8_t *codes, unsigned flags,
+                  void *workspace, size_t workspace_bytes, void *hip_stream)
 {
     int rc = check_kind(kind);
     if (rc) return rc;
@@ -1341,6 +1379,15 @@ int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, 
     const size_t nbq = (n + Bq - 1) / Bq;
     if (overlaps(x, n * 4, codes, n) || overlaps(x, n * 4, scales, nbq * 4) || overlaps(codes, n, scales, nbq * 4))
         return fail(DQ8_ERR_ARG, "dq8_encode: buffers overlap");
+    const size_t useful = dq8_workspace_bytes(n, block, flags);
+    float *parts = nullptr;
+    if (workspace && useful != 0 && workspace_bytes >= useful && st->cus <= (int)kMostParts) {
+        if ((uintptr_t)workspace & 3) return fail(DQ8_ERR_ARG, "dq8_encode_ws: workspace not aligned to 4 bytes");
+        if (overlaps(workspace, useful, x, n * 4) || overlaps(workspace, useful, codes, n) || overlaps(workspace, useful, scales, nbq * 4))
+            return fail(DQ8_ERR_ARG, "dq8_encode_ws: workspace overlaps another buffer");
+        parts = static_cast<float *>(workspace);
+    }
+    uint32_t n_parts = 0;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool given = (flags & DQ8_SCALES_GIVEN) != 0;
     size_t done = 0;
@@ -1355,10 +1402,10 @@ int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, 
     // the block fits one unit: absmax and encode in one kernel
     const bool fused = !given && Bq <= (g_tune.enc_long ? kLongestHeldBlock : (size_t)kUnit);
     if (!given && !fused) {
-        rc = launch_absmax(*st, x, n, block, scales, stream, false, kPlainBeforeCompression);
+        rc = launch_absmax(*st, x, n, block, scales, stream, false, kPlainBeforeCompression, parts, &n_parts);
         if (rc) return rc;
     }
-    return launch_encode(*st, kind, x, n, block, scales, codes, fused, stream);
+    return launch_encode(*st, kind, x, n, block, scales, codes, fused, stream, fused || given ? nullptr : parts, n_parts);
 }
 
 int dq8_decode(int kind, const uint8_t *codes, const float *scales, size_t n, size_t block, float *out,
@@ -1504,8 +1551,20 @@ int dq8_absmax_segments(const float *x, size_t n, const uint64_t *bounds, size_t
     return launch_segment_absmax(*st, x, n, bounds, n_seg, scales, static_cast<hipStream_t>(hip_stream), kCachedFloats);
 }
 
+size_t dq8_workspace_bytes_segments(size_t n, size_t n_seg, unsigned flags)
+{
+    const bool parts = n > kNearLongest && n_seg <= kMostSegmentsInParts && !(flags & DQ8_SCALES_GIVEN);
+    return parts ? n_seg * kMostParts * sizeof(float) : 0;
+}
+
 int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *bounds, size_t n_seg, float *scales,
                         uint8_t *codes, unsigned flags, void *hip_stream)
+{
+    return dq8_encode_segments_ws(kind, x, n, bounds, n_seg, scales, codes, flags, nullptr, 0, hip_stream);
+}
+
+int dq8_encode_segments_ws(int kind, const float *x, size_t n, const uint64_t *bounds, size_t n_seg, float *scales,
+                           uint8_t *codes, unsigned flags, void *workspace, size_t workspace_bytes, void *hip_stream)
 {
     static const char who[] = "dq8_encode_segments";
     int rc = check_kind(kind);
@@ -1532,29 +1591,47 @@ int dq8_encode_segments(int kind, const float *x, size_t n, const uint64_t *boun
             hipLaunchKernelGGL(k_seg_near<false>, dim3(grid), dim3(kNearWg), lds, stream, table, x, (uint32_t)n, bounds, (uint32_t)n_seg, scales, codes);
         return after_launch("k_seg_near", stream);
     }
+    const size_t useful = dq8_workspace_bytes_segments(n, n_seg, flags);
+    float *parts = nullptr;
+    if (workspace && useful != 0 && workspace_bytes >= useful && st->cus <= (int)kMostParts) {
+        if ((uintptr_t)workspace & 3) return fail(DQ8_ERR_ARG, "dq8_encode_segments_ws: workspace not aligned to 4 bytes");
+        if (overlaps(workspace, useful, x, n * 4) || overlaps(workspace, useful, codes, n) || overlaps(workspace, useful, scales, n_seg * 4) ||
+            overlaps(workspace, useful, bounds, (n_seg + 1) * 8))
+            return fail(DQ8_ERR_ARG, "dq8_encode_segments_ws: workspace overlaps another buffer");
+        parts = static_cast<float *>(workspace);
+    }
+    uint32_t n_parts = 0;
     if (!(flags & DQ8_SCALES_GIVEN)) {
-        rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream, kPlainBeforeCompression);
+        rc = launch_segment_absmax(*st, x, n, bounds, n_seg, scales, stream, kPlainBeforeCompression, parts, &n_parts);
         if (rc) return rc;
     }
     const bool many = n >= (size_t)st->cus * 32 * 4 * kSegUnit;
     SegPlan p = many ? make_segment_plan(st->cus, n, n_seg, 32, false, 2 * kSegWaves) : make_segment_plan(st->cus, n, n_seg, 24);
-    p.lds = seg_bounds_words(n_seg) * sizeof(uint64_t) + (size_t)st->search_words[kind] * sizeof(uint32_t);
+    const bool copied = scales_fit_near(n_seg);
+    p.lds = seg_bounds_words(n_seg) * sizeof(uint64_t) + (size_t)st->search_words[kind] * sizeof(uint32_t) +
+            (copied ? n_seg * sizeof(float) : 0);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)x & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-#define DQ8_SEG_ENC(RM, W)                                                                                                  \
-    hipLaunchKernelGGL((k_seg_encode<RM, W>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, \
-                       units, p.n_waves, scales, codes)
-    if (st->has_remap[kind]) {
-        if (many)
-            DQ8_SEG_ENC(true, 2 * kSegWaves);
-        else
-            DQ8_SEG_ENC(true, kSegWaves);
+#define DQ8_SEG_ENC(RM, W, FROM)                                                                                            \
+    hipLaunchKernelGGL((k_seg_encode<RM, W, FROM>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds,       \
+                       (uint32_t)n_seg, units, p.n_waves, scales, parts, n_parts, codes)
+#define DQ8_SEG_ENC_FROM(RM, W)                 \
+    if (parts)                                  \
+        DQ8_SEG_ENC(RM, W, kScalesFromParts);   \
+    else if (copied)                            \
+        DQ8_SEG_ENC(RM, W, kScalesCopied);      \
+    else                                        \
+        DQ8_SEG_ENC(RM, W, kScalesInMemory)
+    if (st->has_remap[kind] && many) {
+        DQ8_SEG_ENC_FROM(true, 2 * kSegWaves);
+    } else if (st->has_remap[kind]) {
+        DQ8_SEG_ENC_FROM(true, kSegWaves);
+    } else if (many) {
+        DQ8_SEG_ENC_FROM(false, 2 * kSegWaves);
     } else {
-        if (many)
-            DQ8_SEG_ENC(false, 2 * kSegWaves);
-        else
-            DQ8_SEG_ENC(false, kSegWaves);
+        DQ8_SEG_ENC_FROM(false, kSegWaves);
     }
+#undef DQ8_SEG_ENC_FROM
 #undef DQ8_SEG_ENC
     return after_launch("k_seg_encode", stream);
 }

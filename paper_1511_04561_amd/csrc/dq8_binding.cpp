@@ -30,10 +30,12 @@ namespace {
 // The library's entry points (set by bind(); null until then: every call returns None) and dq8.Dq8Error.
 struct Library {
     decltype(&dq8_absmax) absmax;
-    decltype(&dq8_encode) encode;
+    decltype(&dq8_encode_ws) encode;
+    decltype(&dq8_workspace_bytes) workspace;
     decltype(&dq8_decode) decode;
     decltype(&dq8_absmax_segments) absmax_segments;
-    decltype(&dq8_encode_segments) encode_segments;
+    decltype(&dq8_encode_segments_ws) encode_segments;
+    decltype(&dq8_workspace_bytes_segments) workspace_segments;
     decltype(&dq8_decode_segments) decode_segments;
     decltype(&dq8_decode_accumulate_avg) avg;
     decltype(&dq8_decode_accumulate_avg_local) avg_local;
@@ -134,6 +136,22 @@ struct Output {
     {
         if (given != Py_None) return Py_NewRef(given);
         return THPVariable_Wrap(made);
+    }
+};
+
+// Scratch memory of one call.  It goes back to torch's allocator when the call returns; the allocator hands it to later work on
+// the same stream only, which runs after this call's kernels.
+struct Scratch {
+    at::Tensor made;
+    void *ptr = nullptr;
+    size_t bytes;
+
+    Scratch(size_t n, const at::Tensor &like) : bytes(n)
+    {
+        if (n == 0) return;
+        made = at::empty({(int64_t)n}, like.options().dtype(at::kByte).requires_grad(false));
+        if (made.key_set().has_any(kTransformed)) throw Decline();
+        ptr = made.data_ptr();
     }
 };
 
@@ -242,9 +260,11 @@ PyObject *encode(PyObject *const *a)  // kind, x, block, scales, codes, scales_g
     if (x.n == 0 || (given && a[3] == Py_None)) throw Decline();
     void *stream = stream_for(*x.t);
     const Output scales(a[3], n_blocks(x.n, block), at::kFloat, *x.t), codes(a[4], x.n, at::kByte, *x.t);
+    const unsigned flags = given ? DQ8_SCALES_GIVEN : 0u;
+    const Scratch scratch(g_lib.workspace(x.n, block, flags), *x.t);
     if (!enqueue("dq8_encode", [&] {
             return g_lib.encode(kind, static_cast<float *>(x.ptr), x.n, block, static_cast<float *>(scales.ptr),
-                                static_cast<uint8_t *>(codes.ptr), given ? DQ8_SCALES_GIVEN : 0u, stream);
+                                static_cast<uint8_t *>(codes.ptr), flags, scratch.ptr, scratch.bytes, stream);
         }))
         return nullptr;
     return pair(codes, scales);
@@ -297,10 +317,12 @@ PyObject *encode_segments(PyObject *const *a)  // kind, x, bounds, scales, codes
     if (x.n == 0 || (given && a[3] == Py_None)) throw Decline();
     void *stream = stream_for(*x.t);
     const Output scales(a[3], n_seg, at::kFloat, *x.t), codes(a[4], x.n, at::kByte, *x.t);
+    const unsigned flags = given ? DQ8_SCALES_GIVEN : 0u;
+    const Scratch scratch(g_lib.workspace_segments(x.n, n_seg, flags), *x.t);
     if (!enqueue("dq8_encode_segments", [&] {
             return g_lib.encode_segments(kind, static_cast<float *>(x.ptr), x.n, static_cast<uint64_t *>(bounds.ptr), n_seg,
-                                         static_cast<float *>(scales.ptr), static_cast<uint8_t *>(codes.ptr),
-                                         given ? DQ8_SCALES_GIVEN : 0u, stream);
+                                         static_cast<float *>(scales.ptr), static_cast<uint8_t *>(codes.ptr), flags,
+                                         scratch.ptr, scratch.bytes, stream);
         }))
         return nullptr;
     return pair(codes, scales);
@@ -423,10 +445,12 @@ PyObject *bind(PyObject *, PyObject *args)
         ok = ok && p;
     };
     take(l.absmax, "dq8_absmax");
-    take(l.encode, "dq8_encode");
+    take(l.encode, "dq8_encode_ws");
+    take(l.workspace, "dq8_workspace_bytes");
     take(l.decode, "dq8_decode");
     take(l.absmax_segments, "dq8_absmax_segments");
-    take(l.encode_segments, "dq8_encode_segments");
+    take(l.encode_segments, "dq8_encode_segments_ws");
+    take(l.workspace_segments, "dq8_workspace_bytes_segments");
     take(l.decode_segments, "dq8_decode_segments");
     take(l.avg, "dq8_decode_accumulate_avg");
     take(l.avg_local, "dq8_decode_accumulate_avg_local");

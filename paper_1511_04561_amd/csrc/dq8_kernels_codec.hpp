@@ -190,9 +190,12 @@ __global__ __launch_bounds__(kWg) void k_absmax(const float *__restrict__ x, siz
 // which takes the second pass over 37.7 M elements from 33.4 to 26.8 us and costs this one a microsecond.
 // n_units: whole units and a last one of at least four elements (see quad_start); the elements past them (at most three;
 // all of them when x is no multiple of 4) go one by one.
+// PARTS: workgroup w stores its maximum to scale[w] instead, scratch memory of the call, for k_encode_one<.., true> to read: no
+// zero fill before this kernel and no atomics in it (both passes, in a graph: 131 072 elements 6.6 -> 5.5 us, 1 Mi 8.0 -> 5.9, 8 Mi
+// 16.1 -> 12.8, 37.7 M 57.5 -> 56.3).
 constexpr int kOneWg = kWave * kOneWaves;
 
-template <int Q, int NT>
+template <int Q, int NT, bool PARTS>
 __global__ __launch_bounds__(kOneWg) void k_absmax_one(const float *__restrict__ x, size_t n, size_t n_units, size_t n_waves,
                                                        float *__restrict__ scale)
 {
@@ -227,17 +230,34 @@ __global__ __launch_bounds__(kOneWg) void k_absmax_one(const float *__restrict__
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int w = 1; w < kOneWaves; ++w) m = m > part[w] ? m : part[w];
-        if (m != 0) atomicMax(reinterpret_cast<unsigned int *>(scale), m);
+        if (PARTS)
+            scale[blockIdx.x] = u2f(m);
+        else if (m != 0)
+            atomicMax(reinterpret_cast<unsigned int *>(scale), m);
     }
+}
+
+// The largest of n_parts <= kMostParts non-negative numbers (1 <= n_parts), by one wavefront, to all its lanes.
+__device__ __forceinline__ uint32_t max_of_parts(const float *__restrict__ parts, uint32_t n_parts, uint32_t lane)
+{
+    uint32_t m = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kMostParts / kWave; ++j) {
+        const uint32_t i = j * kWave + lane, p = f2u(parts[i < n_parts ? i : n_parts - 1]);
+        m = m > p ? m : p;
+    }
+    return wave_max_u32(m);
 }
 
 // Compression of an array that is one block with its scale in memory: units of 1024 elements, the next unit's loads always
 // ahead (37.7 M elements right after k_absmax_one: 30.3 us; 36.6 us in k_encode, which has conditions in its loop).
 // n_units as in k_absmax_one.
-template <bool REMAP>
+// PARTS: the scale is the largest of the n_parts maxima that k_absmax_one<.., true> left, formed by every wavefront by itself; the
+// first workgroup stores it.
+template <bool REMAP, bool PARTS>
 __global__ __launch_bounds__(kOneWg) void k_encode_one(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
-                                                       size_t n_units, size_t n_waves, const float *__restrict__ scale,
-                                                       uint8_t *__restrict__ codes)
+                                                       size_t n_units, size_t n_waves, float *__restrict__ scale,
+                                                       const float *__restrict__ parts, uint32_t n_parts, uint8_t *__restrict__ codes)
 {
     constexpr int Q = 4, U = Q * 4 * kWave;
     extern __shared__ uint32_t lds[];  // the bucket table
@@ -252,7 +272,8 @@ __global__ __launch_bounds__(kOneWg) void k_encode_one(const uint32_t *__restric
     };
     const size_t u0 = first_unit(kOneWaves);
     if (u0 < n_units) fetch(u0, a);  // the first loads are in flight while the table is copied
-    const float s = *scale;
+    const float s = PARTS ? u2f(max_of_parts(parts, n_parts, lane)) : *scale;
+    if (PARTS && blockIdx.x == 0 && threadIdx.x == 0) *scale = s;
     const float d = s == 0.0f ? 1.0f : s;
     const float r = 1.0f / d;
     const bool recip = reciprocal_ok(d);

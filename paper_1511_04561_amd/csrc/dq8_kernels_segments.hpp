@@ -236,7 +236,9 @@ __device__ __forceinline__ void for_each_element(const uint64_t *lds, uint32_t n
 // NT = 0, plain loads, where the array or much of it is still in the memory-side cache when k_seg_encode reads it again
 // (kPlainBeforeCompression; by itself up to kCachedFloats): with non-temporal loads here k_seg_encode takes 33.4 instead of 26.8 us
 // at 37.7 M elements and 53 instead of 43 us at 61 M, this one 1 to 2 us less.  By itself, 1000 M: 643 plain, 574 us.
-template <int Q, int NT>
+// PARTS: workgroup w stores its maximum of segment i to scales[i * kMostParts + w] instead, scratch memory of the call, for
+// k_seg_encode to combine: no zero fill before this kernel and no atomics.
+template <int Q, int NT, bool PARTS>
 __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__ x, size_t n, const uint64_t *__restrict__ bounds,
                                                        uint32_t n_seg, size_t n_units, size_t n_waves, float *__restrict__ scales)
 {
@@ -303,8 +305,12 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
         if (a != 0) atomicMax(best + seg, a);
     });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n_seg; i += kSegWg)
-        if (best[i] != 0) atomicMax(reinterpret_cast<unsigned int *>(scales) + i, best[i]);
+    for (uint32_t i = threadIdx.x; i < n_seg; i += kSegWg) {
+        if (PARTS)
+            scales[i * kMostParts + blockIdx.x] = u2f(best[i]);
+        else if (best[i] != 0)
+            atomicMax(reinterpret_cast<unsigned int *>(scales) + i, best[i]);
+    }
 }
 
 // Compression with the segments' scales (computed by k_seg_absmax or handed in).
@@ -315,12 +321,19 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
 // WAVES: 8, with 24 wavefronts on a compute unit, or, on arrays of at least four units for each of 32 wavefronts, 16 with
 // two workgroups per compute unit one after the other: 61 M elements 54.0 against 52.4 us, 16 Mi 14.5 against 14.8, 4 Mi
 // 4.7 against 5.4.  (64 registers, so that both workgroups are resident: 53.9 us.)
-template <bool REMAP, int WAVES>
+// FROM: where a unit finds its scale: in memory; in LDS, copied there with the bounds; or in LDS, formed from the maxima that the
+// n_parts workgroups of k_seg_absmax<.., true> left in `parts` (a wavefront takes four segments at a time, the first workgroup
+// stores the scales).  In a graph, before (zero fill, maxima with atomics, scales in memory) and now: 200 000
+// elements in 20 segments 8.9 / 8.3 us, 1.76 M in 10 10.2 / 7.8, 8 Mi in 40 17.3 / 15.8, 61 M in 16 90.4 / 90.0.
+enum SegScales { kScalesInMemory, kScalesCopied, kScalesFromParts };
+
+template <bool REMAP, int WAVES, SegScales FROM>
 __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
                                                              const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
-                                                             size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
+                                                             size_t n_waves, float *__restrict__ scales, const float *__restrict__ parts,
+                                                             uint32_t n_parts, uint8_t *__restrict__ codes)
 {
-    extern __shared__ uint64_t seg_lds[];  // the bounds (seg_bounds_words(n_seg) entries), then the search table
+    extern __shared__ uint64_t seg_lds[];  // the bounds (seg_bounds_words(n_seg) entries), the search table, the scales
     const uint32_t lane = threadIdx.x & 63;
     v4f v[kSegQ];
     auto fetch = [&](size_t u) {
@@ -330,9 +343,28 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
     };
     const BucketWords<kWave * WAVES> words = request_bucket_table<kWave * WAVES>(tab);
     const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
-    Search sr = place_bucket_table(tab, words, reinterpret_cast<uint32_t *>(seg_lds + seg_bounds_words(n_seg)));
+    uint32_t *table = reinterpret_cast<uint32_t *>(seg_lds + seg_bounds_words(n_seg));
+    float *near = reinterpret_cast<float *>(table + (tab[kNBucketOff] + 3) / 4 * 4);
+    if (FROM == kScalesCopied)
+        for (uint32_t i = threadIdx.x; i < n_seg; i += kWave * WAVES) near[i] = scales[i];
+    if (FROM == kScalesFromParts) {
+        constexpr uint32_t AT_ONCE = 4;
+        for (uint32_t i = wave_in_wg() * AT_ONCE; i < n_seg; i += WAVES * AT_ONCE) {
+            uint32_t m[AT_ONCE];
+#pragma unroll
+            for (uint32_t j = 0; j < AT_ONCE; ++j) m[j] = max_of_parts(parts + (i + j < n_seg ? i + j : i) * kMostParts, n_parts, lane);
+#pragma unroll
+            for (uint32_t j = 0; j < AT_ONCE; ++j)
+                if (lane == 0 && i + j < n_seg) {
+                    near[i + j] = u2f(m[j]);
+                    if (blockIdx.x == 0) scales[i + j] = u2f(m[j]);
+                }
+        }
+    }
+    Search sr = place_bucket_table(tab, words, table);
     sr.marks = REMAP;
     __syncthreads();
+    const float *sc = FROM == kScalesInMemory ? scales : near;
     size_t u = first_unit(WAVES);
     if (u < n_units) fetch(u);
     while (u < n_units) {
@@ -340,14 +372,14 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
         u += n_waves;
         uint32_t cw[kSegQ];
         if (q.first == q.last) {
-            const float s = scales[q.first];
+            const float s = sc[q.first];
             const float d = s == 0.0f ? 1.0f : s;
             encode_quads<true, kSegQ>(sr, v, d, 1.0f / d, reciprocal_ok(d), cw);
         } else {
             const SegQuads<kSegQ> sq = segments_of_quads(sb, q, lane);
             v4f d[kSegQ];
 #pragma unroll
-            for (int j = 0; j < kSegQ; ++j) d[j] = scales_of_quad(scales, sq, j);
+            for (int j = 0; j < kSegQ; ++j) d[j] = scales_of_quad(sc, sq, j);
 #pragma unroll
             for (int j = 0; j < kSegQ; ++j) {
                 const v4f t = v[j];
@@ -372,7 +404,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
         }
     }
     for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves, [&](size_t i, uint32_t seg) {
-        const float s = scales[seg];
+        const float s = sc[seg];
         codes[i] = (uint8_t)code_exact(sr, x[i], s == 0.0f ? 1.0f : s);
     });
 }

@@ -177,6 +177,11 @@ constexpr size_t kNearScales = 1024;
 static_assert(2 * (kValueTableBytes + (kNearScales + 1) * sizeof(uint64_t) + kNearScales * sizeof(float)) <= kLdsPerCu, "two workgroups");
 inline bool scales_fit_near(size_t count) { return count <= kNearScales; }
 
+// Segments whose maxima the workgroups of the maximum pass leave in scratch memory (one row of kMostParts numbers each) for the
+// compression to combine: a wavefront of that one combines four rows at a time, so with 64 segments two rounds of
+// loads in front of the first unit, which is what a zero fill costs; rows of one call take 64 KiB.
+constexpr size_t kMostSegmentsInParts = 64;
+
 struct SegPlan {
     size_t n_items, n_waves, lds;
     uint32_t group;

@@ -30,6 +30,9 @@ DQ8_HD uint32_t seg_bounds_words(size_t n_seg) { return (uint32_t)((n_seg + 2) /
 // The kernels for an array that is one block.
 constexpr int kOneWaves = 8;  // wavefronts per workgroup
 
+// Workgroups of a maximum pass whose maxima the pass that follows combines, at most (scratch memory of the call).
+constexpr uint32_t kMostParts = 256;
+
 // Where quad q of a run of len >= 4 elements starts: at 4 q, or, for the last quad of a run that is no whole number of
 // quads and for every quad past it, four elements before the end.  The overlap is read twice (a maximum does not
 // change) and written twice with the same bytes; quads with 4 q >= len are loaded (valid memory, no branch) and not stored.

@@ -200,8 +200,9 @@ def test_short_arrays_in_one_launch(dq8, n, offset):
 
 # bounds in registers up to 63 segments; scales of all workers in LDS up to 1024; at most 16 bounds inside a unit are counted one by
 # one; all workers' codes requested at once (up to 4, up to 8) where no wavefront has a second unit
-@pytest.mark.parametrize("n_seg,K", [(1, 3), (2, 8), (16, 4), (17, 5), (18, 9), (63, 2), (64, 3), (65, 4), (128, 8), (129, 8), (341, 3), (342, 3), (1024, 1), (1025, 1)])
-@pytest.mark.parametrize("n", [5003, 256 * 8 * 1024 - 3, 256 * 16 * 1024 + 5000])
+@pytest.mark.parametrize("n,n_seg,K", [(5003, 1, 3), (5003, 2, 8), (5003, 16, 4), (5003, 17, 5), (5003, 18, 9), (5003, 63, 2), (5003, 64, 3), (5003, 65, 4), (5003, 128, 8),
+                                       (5003, 129, 8), (5003, 341, 3), (5003, 342, 3), (5003, 1024, 1), (5003, 1025, 1), (256 * 8 * 1024 - 3, 18, 8),
+                                       (256 * 8 * 1024 + 1, 17, 5), (256 * 16 * 1024 + 5000, 65, 3)])
 def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
     """All bounds inside one unit, and spread over the array; workers averaged with and without a local term."""
     rng = np.random.Generator(np.random.PCG64(9500 + n % 97 + n_seg))
@@ -276,3 +277,50 @@ def test_calls_marshalled_by_the_extension_and_by_python(dq8, monkeypatch):
         dq8.encode(9, x)
     with pytest.raises(Exception):  # a transformed tensor has no address; the same with and without the extension
         torch.vmap(lambda v: dq8.absmax(v, 0))(x[:64].view(8, 8))
+
+
+@pytest.mark.parametrize("n,n_seg", [(98305, 1), (98305, 4), (98305, 63), (98305, 65), (8192 * 63 + 1, 33), (256 * 8192, 64), (256 * 8192 + 3, 1),
+                                     (256 * 8192 + 3, 5), ((1 << 24) + 4099, 1), ((1 << 24) + 4099, 64)])
+def test_compression_with_and_without_scratch_memory(dq8, monkeypatch, n, n_seg):
+    """Maxima merged through scratch memory (the extension hands it in), and without (the code of dq8.py does not); segments that begin
+    and end in the same unit, long ones, empty ones; scratch memory that holds the largest numbers before the call."""
+    rng = np.random.Generator(np.random.PCG64(9700 + n % 97 + n_seg))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    kind, offset = (n + n_seg) % 4, n_seg % 3
+    bounds = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n_seg - 1)), [n]])
+    bounds[n_seg // 2] = bounds[n_seg // 2 + 1]
+    bounds[0] = 0
+    torch.full((1 << 18,), 3e38, device="cuda")  # given back at once: the allocator's next blocks
+    for _ in range(2):
+        if n_seg == 1:
+            check_encode_decode(dq8, kind, x, 0, x_off=offset, c_off=offset, tag="one scale")
+        check_segments(dq8, kind, x, bounds, x_off=offset, c_off=offset, tag="%d segments" % n_seg)
+        monkeypatch.setattr(dq8, "_native", dq8._Unbound())
+
+
+def test_scratch_memory_of_the_c_calls(dq8):
+    """Too few bytes are not used; a workspace at an odd address or on top of another array is refused."""
+    import ctypes
+    L, n, vp, sz = dq8.lib(), 200000, ctypes.c_void_p, ctypes.c_size_t
+    L.dq8_workspace_bytes.restype = L.dq8_workspace_bytes_segments.restype = sz
+    x = dev(np.random.Generator(np.random.PCG64(9800)).standard_normal(n).astype(np.float32))
+    codes, scale, work = torch.empty(n, dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda"), torch.empty(4096, dtype=torch.uint8, device="cuda")
+    bounds, stream = bounds_dev(np.array([0, n])), torch.cuda.current_stream().cuda_stream
+    want = [t.cpu().numpy().tobytes() for t in dq8.encode(0, x)]
+    need = L.dq8_workspace_bytes(sz(n), sz(0), 0)
+    assert need == L.dq8_workspace_bytes_segments(sz(n), sz(1), 0) == 1024
+    assert 0 == L.dq8_workspace_bytes(sz(n), sz(0), 1) == L.dq8_workspace_bytes(sz(n), sz(4096), 0) == L.dq8_workspace_bytes_segments(sz(n), sz(65), 0)
+
+    def calls(w, size):
+        return (L.dq8_encode_ws(0, vp(x.data_ptr()), sz(n), sz(0), vp(scale.data_ptr()), vp(codes.data_ptr()), 0, vp(w), sz(size), vp(stream)),
+                L.dq8_encode_segments_ws(0, vp(x.data_ptr()), sz(n), vp(bounds.data_ptr()), sz(1), vp(scale.data_ptr()), vp(codes.data_ptr()), 0, vp(w),
+                                         sz(size), vp(stream)))
+    for w, size in ((work.data_ptr(), need), (work.data_ptr() + 4, need), (work.data_ptr() + 1, need - 1), (None, need)):
+        codes.zero_()
+        scale.zero_()
+        assert calls(w, size) == (0, 0)
+        assert [codes.cpu().numpy().tobytes(), scale.cpu().numpy().tobytes()] == want
+    for w in (work.data_ptr() + 1, x.data_ptr() + 4 * n - 4, codes.data_ptr(), scale.data_ptr(), x.data_ptr() - need + 4):
+        assert calls(w, need) == (3, 3)
+    assert L.dq8_encode_segments_ws(0, vp(x.data_ptr()), sz(n), vp(bounds.data_ptr()), sz(1), vp(scale.data_ptr()), vp(codes.data_ptr()), 0,
+                                    vp(bounds.data_ptr()), sz(need), vp(stream)) == 3
