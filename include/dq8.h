@@ -244,6 +244,11 @@ int dq8_decode_avg_encode(int kind, const uint8_t *const *codes, const float *co
  */
 int dq8_error_stats(int kind, const float *x, size_t n, size_t block, float *scales, unsigned flags, double *stats,
                     double *means, void *hip_stream);
+/* The same with scratch memory (see dq8_encode_ws), 8-byte aligned here: the statistics of a long array that is one block then
+ * go there by workgroup and are added in a fixed order, so that the sums do not differ between calls. */
+size_t dq8_workspace_bytes_stats(size_t n, size_t block, unsigned flags);
+int dq8_error_stats_ws(int kind, const float *x, size_t n, size_t block, float *scales, unsigned flags, double *stats,
+                       double *means, void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /*
  * Single-node speed-up model (Appendix, "A theoretical single node model for 4 GPUs"): the

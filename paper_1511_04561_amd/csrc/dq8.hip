@@ -670,9 +670,40 @@ int launch_encode_near(const DeviceState &st, int kind, const float *x, size_t n
 
 // Error statistics of compress-then-decompress into stats[4 nb] (and means[2] when not NULL); given: the scales are
 // an input, otherwise they are the block maxima and written first.
+// work: NULL, or scratch memory of dq8_workspace_bytes_stats() bytes for an array that is one block.
 int launch_error_stats(const DeviceState &st, int kind, const float *x, size_t n, size_t block, float *scales, bool given,
-                       double *stats, double *means, hipStream_t stream)
+                       double *stats, double *means, void *work, hipStream_t stream)
 {
+    if (work && ((uintptr_t)x & 3) == 0) {
+        double *rows = static_cast<double *>(work);
+        float *parts = reinterpret_cast<float *>(rows + 4 * kMostStatsRows);
+        uint32_t n_parts = 0;
+        if (!given) {
+            const int rc = launch_absmax(st, x, n, block, scales, stream, false, kPlainBeforeStatistics, parts, &n_parts);
+            if (rc) return rc;
+        }
+        const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
+        const size_t lds = (size_t)st.search_words[kind] * sizeof(uint32_t), units = n / 1024;
+        const bool spread = units <= (size_t)st.cus * 4;
+        const size_t waves = spread ? 4 : kStatsWaves, all = ((units ? units : 1) + waves - 1) / waves;
+        const unsigned grid = (unsigned)(all < 2 * (size_t)st.cus ? all : 2 * (size_t)st.cus);
+#define DQ8_STATS_ONE(W, FROM)                                                                                              \
+    hipLaunchKernelGGL((k_error_stats_one<W, FROM>), dim3(grid), dim3(kWave * (W)), lds, stream, tab, x, n, units, grid * waves, \
+                       scales, parts, n_parts, rows)
+        if (spread && given)
+            DQ8_STATS_ONE(4, false);
+        else if (spread)
+            DQ8_STATS_ONE(4, true);
+        else if (given)
+            DQ8_STATS_ONE(kStatsWaves, false);
+        else
+            DQ8_STATS_ONE(kStatsWaves, true);
+#undef DQ8_STATS_ONE
+        const int rc = after_launch("k_error_stats_one", stream);
+        if (rc) return rc;
+        hipLaunchKernelGGL(k_error_finish, dim3(1), dim3(kFinishThreads), 0, stream, rows, grid, n, stats, means);
+        return after_launch("k_error_finish", stream);
+    }
     constexpr int Q = 4;
     constexpr int kWavesPerCu = 2 * kStatsWaves;  // two workgroups
     Plan p = make_plan(n, block, st.cus, kWavesPerCu, 1, kStatsWaves, (size_t)Q * 4 * kWave);
@@ -1716,8 +1747,20 @@ int dq8_decode_accumulate_avg_segments(int kind, const uint8_t *const *codes, co
     return after_launch("k_seg_avg", stream);
 }
 
+size_t dq8_workspace_bytes_stats(size_t n, size_t block, unsigned flags)
+{
+    const bool whole = block_length(n, block) == n && n > (size_t)kUnit;
+    return whole ? kMostStatsRows * 4 * sizeof(double) + kMostParts * sizeof(float) : 0;
+}
+
 int dq8_error_stats(int kind, const float *x, size_t n, size_t block, float *scales, unsigned flags, double *stats,
                     double *means, void *hip_stream)
+{
+    return dq8_error_stats_ws(kind, x, n, block, scales, flags, stats, means, nullptr, 0, hip_stream);
+}
+
+int dq8_error_stats_ws(int kind, const float *x, size_t n, size_t block, float *scales, unsigned flags, double *stats,
+                       double *means, void *workspace, size_t workspace_bytes, void *hip_stream)
 {
     static const char who[] = "dq8_error_stats";
     int rc = check_kind(kind);
@@ -1735,8 +1778,17 @@ int dq8_error_stats(int kind, const float *x, size_t n, size_t block, float *sca
     DeviceState *st;
     rc = device_state(&st);
     if (rc) return rc;
+    const size_t useful = dq8_workspace_bytes_stats(n, block, flags);
+    void *work = nullptr;
+    if (workspace && useful != 0 && workspace_bytes >= useful && st->cus <= (int)kMostParts) {
+        if ((uintptr_t)workspace & 7) return fail(DQ8_ERR_ARG, "dq8_error_stats_ws: workspace not aligned to 8 bytes");
+        if (overlaps(workspace, useful, x, n * 4) || overlaps(workspace, useful, scales, nbq * 4) || overlaps(workspace, useful, stats, nbq * 32) ||
+            (means && overlaps(workspace, useful, means, 16)))
+            return fail(DQ8_ERR_ARG, "dq8_error_stats_ws: workspace overlaps another buffer");
+        work = workspace;
+    }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    return launch_error_stats(*st, kind, x, n, block, scales, (flags & DQ8_SCALES_GIVEN) != 0, stats, means, stream);
+    return launch_error_stats(*st, kind, x, n, block, scales, (flags & DQ8_SCALES_GIVEN) != 0, stats, means, work, stream);
 }
 
 int dq8_model_penalty(const double *transfer_ms, const double *compute_ms, size_t count, double *penalty_ms)

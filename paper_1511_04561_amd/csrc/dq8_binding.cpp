@@ -41,7 +41,8 @@ struct Library {
     decltype(&dq8_decode_accumulate_avg_local) avg_local;
     decltype(&dq8_decode_accumulate_avg_segments) avg_segments;
     decltype(&dq8_decode_avg_encode) avg_encode;
-    decltype(&dq8_error_stats) error_stats;
+    decltype(&dq8_error_stats_ws) error_stats;
+    decltype(&dq8_workspace_bytes_stats) workspace_stats;
     decltype(&dq8_last_error) last_error;
 } g_lib;
 PyObject *g_error = nullptr;
@@ -422,9 +423,11 @@ PyObject *error_stats(PyObject *const *a)  // kind, x, block, scales, scales_giv
     void *stream = stream_for(*x.t);
     const size_t nb = n_blocks(x.n, block);
     const Output scales(a[3], nb, at::kFloat, *x.t), stats(a[5], 4 * nb, at::kDouble, *x.t), means(a[6], 2, at::kDouble, *x.t);
+    const unsigned flags = given ? DQ8_SCALES_GIVEN : 0u;
+    const Scratch scratch(g_lib.workspace_stats(x.n, block, flags), *x.t);
     if (!enqueue("dq8_error_stats", [&] {
-            return g_lib.error_stats(kind, static_cast<float *>(x.ptr), x.n, block, static_cast<float *>(scales.ptr),
-                                     given ? DQ8_SCALES_GIVEN : 0u, static_cast<double *>(stats.ptr), static_cast<double *>(means.ptr), stream);
+            return g_lib.error_stats(kind, static_cast<float *>(x.ptr), x.n, block, static_cast<float *>(scales.ptr), flags,
+                                     static_cast<double *>(stats.ptr), static_cast<double *>(means.ptr), scratch.ptr, scratch.bytes, stream);
         }))
         return nullptr;
     return pair(stats, means);
@@ -456,7 +459,8 @@ PyObject *bind(PyObject *, PyObject *args)
     take(l.avg_local, "dq8_decode_accumulate_avg_local");
     take(l.avg_segments, "dq8_decode_accumulate_avg_segments");
     take(l.avg_encode, "dq8_decode_avg_encode");
-    take(l.error_stats, "dq8_error_stats");
+    take(l.error_stats, "dq8_error_stats_ws");
+    take(l.workspace_stats, "dq8_workspace_bytes_stats");
     take(l.last_error, "dq8_last_error");
     if (!ok) return nullptr;
     g_lib = l;

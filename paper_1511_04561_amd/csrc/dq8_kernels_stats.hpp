@@ -1,6 +1,7 @@
 // dq8 kernels for the approximation-error statistics.
 #pragma once
 #include "dq8_device.hpp"
+#include "dq8_kernels_codec.hpp"
 
 namespace {
 
@@ -342,6 +343,195 @@ __global__ __launch_bounds__(kStatsWg, kStatsWaves / 2) void k_error_stats(const
             means[0] = a / (double)n;
             means[1] = c > 0.0 ? r / c : 0.0;
         }
+    }
+}
+
+// The statistics of an array that is one block, with scratch memory: workgroup w stores its four numbers to rows[4 w .. 4 w + 3] and
+// k_error_finish adds the rows in a fixed order.  k_error_stats<.., false> on one block ends in four atomics and a count from each
+// of 512 workgroups, all on one cache line and at the same time, and needs them zeroed before.  The block's scale and reciprocal
+// are the same for all units; only the quads with a value next to a threshold are looked up again with true divisions (here
+// all sixteen values of a lane were, in one unit of seven).
+// FROM_PARTS: the scale is the largest of the n_parts maxima at `parts` and the first workgroup stores it; otherwise *scale.
+// WAVES: 12 with two workgroups per compute unit, or 4 where the array is no more than a unit for four wavefronts of every
+// compute unit: then the units spread over more of them.  What bounds it is the vector units, see k_error_stats.
+// Device time in a graph, k_error_stats and now (with the passes before and after): 25 M elements 57.2 / 46.0 us, of these
+// 39 / 27 the statistics; 1 M 16.5 / 10.2; 100 000 14.3 / 8.9; given scale 25 M 40.8 / 28.9.
+// n_units whole units, strided over the grid.
+template <int WAVES, bool FROM_PARTS>
+__global__ __launch_bounds__(kWave *WAVES, WAVES / 2) void k_error_stats_one(const uint32_t *__restrict__ tab, const float *__restrict__ x,
+                                                                             size_t n, size_t n_units, size_t n_waves,
+                                                                             float *__restrict__ scale, const float *__restrict__ parts,
+                                                                             uint32_t n_parts, double *__restrict__ rows)
+{
+    constexpr int Q = 4, U = Q * 4 * kWave;
+    __shared__ __align__(256) float lut[256 * kLutCopies];
+    extern __shared__ uint32_t bucket_lds[];
+    const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
+    const float lut_value = request_magnitude_lut(tab);
+    const BucketWords<kWave * WAVES> words = request_bucket_table<kWave * WAVES>(tab);
+    constexpr int H = 2;  // quads worked on at a time
+    v4f v[Q / H][H];
+    auto fetch = [&](size_t u, int h) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) v[h][j] = ldg_floats<1>(x + u * (size_t)U, 4 * ((h * H + j) * kWave + lane));
+    };
+    const size_t u0 = first_unit(WAVES);
+    if (u0 < n_units) {
+#pragma unroll
+        for (int h = 0; h < Q / H; ++h) fetch(u0, h);
+    }
+    const float s = FROM_PARTS ? u2f(max_of_parts(parts, n_parts, lane)) : *scale;
+    if (FROM_PARTS && blockIdx.x == 0 && threadIdx.x == 0) *scale = s;
+    place_lut<kWave * WAVES>(lut_value * __builtin_fabsf(s), lut);  // one scale: the products are formed once per code
+    const Search sr = place_bucket_table(tab, words, bucket_lds);
+    __syncthreads();
+    const float d = s == 0.0f ? 1.0f : s;
+    const float r = 1.0f / d;
+    const bool recip = reciprocal_ok(d);
+
+    double sum_abs = 0.0, sum_rel = 0.0, worst = 0.0;
+    uint64_t count = 0;  // wave-uniform
+    auto add = [&](float xv, float qmag) {  // xv not zero
+        const double ax = (double)__builtin_fabsf(xv);
+        const double e = __builtin_fabs((double)qmag - ax);
+        sum_abs += e;
+        worst = __builtin_fmax(worst, e);
+        sum_rel += quotient_of_magnitudes(e, ax);
+    };
+    // A zero has an error (a type need not have the value 0) but no relative one: the error is added here, and the pair becomes
+    // one that adds nothing.  Whether it was one.
+    auto take_zero = [&](float &xv, float &qmag) {
+        const bool z = xv == 0.0f;
+        const double e = z ? (double)qmag : 0.0;
+        sum_abs += e;
+        worst = __builtin_fmax(worst, e);
+        xv = z ? 1.0f : xv;
+        qmag = z ? 1.0f : qmag;
+        return z;
+    };
+    // byte 1 of the address = byte 2 of the sum (the code field), byte 0 = lane * 4
+    auto magnitude = [&](uint32_t sm) {
+        const uint32_t addr = __builtin_amdgcn_perm(sm, lane4, 0x0C0C0600u);
+        return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(lut) + addr);
+    };
+    auto work = [&](const v4f (&v)[H]) {
+        float xs[H][4], qm[H][4], least = u2f(0x7F800000u);
+        uint32_t sum[H][4], key[H], all = 0xFFFFu;
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            xs[j][0] = v[j].x;
+            xs[j][1] = v[j].y;
+            xs[j][2] = v[j].z;
+            xs[j][3] = v[j].w;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[j][c] = search_sum(sr, xs[j][c] * r);
+        }
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            const uint32_t k01 = near_key(sum[j][0]) < near_key(sum[j][1]) ? near_key(sum[j][0]) : near_key(sum[j][1]);
+            const uint32_t k23 = near_key(sum[j][2]) < near_key(sum[j][3]) ? near_key(sum[j][2]) : near_key(sum[j][3]);
+            key[j] = recip ? (k01 < k23 ? k01 : k23) : 0;
+            all = all < key[j] ? all : key[j];
+        }
+        if (__builtin_amdgcn_ballot_w64(all <= 2 * kNearWindow) != 0) {
+#pragma unroll
+            for (int j = 0; j < H; ++j)
+                if (__builtin_amdgcn_ballot_w64(key[j] <= 2 * kNearWindow) != 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sum[j][c] = search_sum_exact(sr, xs[j][c] / d);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {  // all lookups first, so that their latencies overlap
+                qm[j][c] = magnitude(sum[j][c]);
+                least = __builtin_fminf(least, __builtin_fabsf(xs[j][c]));
+            }
+        count += (uint64_t)(H * 4 * kWave);
+        if (__builtin_amdgcn_ballot_w64(least == 0.0f) != 0) {
+#pragma unroll
+            for (int j = 0; j < H; ++j)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) count -= (uint64_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(take_zero(xs[j][c], qm[j][c])));
+        }
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) add(xs[j][c], qm[j][c]);
+    };
+    // One set of registers, two quads requested again as soon as they are done with (from the last unit a second time, where there
+    // is no next one): two sets and four quads at a time need more registers than six wavefronts per SIMD have.
+    for (size_t u = u0; u < n_units; u += n_waves) {
+        const size_t next = u + n_waves < n_units ? u + n_waves : u;
+#pragma unroll
+        for (int h = 0; h < Q / H; ++h) {
+            work(v[h]);
+            fetch(next, h);
+        }
+    }
+    // the elements past the units, 64 per wavefront, from the wavefront after the last unit's on
+    for (size_t i0 = n_units * (size_t)U + (u0 + n_waves - n_units % n_waves) % n_waves * kWave; i0 < n; i0 += n_waves * kWave) {
+        const bool in = i0 + lane < n;
+        float xv = in ? x[i0 + lane] : 0.0f;
+        float q = in ? magnitude(search_sum_exact(sr, xv / d)) : 0.0f;  // a lane past the end: a zero without an error
+        count += (uint64_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(!take_zero(xv, q)));
+        add(xv, q);
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        sum_abs += __shfl_xor(sum_abs, m);
+        sum_rel += __shfl_xor(sum_rel, m);
+        worst = __builtin_fmax(worst, __shfl_xor(worst, m));
+    }
+    __syncthreads();  // the value table is not needed any more
+    double *post = reinterpret_cast<double *>(lut);
+    if (lane == 0) {
+        double *p = post + 4 * wave_in_wg();
+        p[0] = sum_abs;
+        p[1] = sum_rel;
+        p[2] = (double)count;
+        p[3] = worst;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double v = post[threadIdx.x];
+        for (int w = 1; w < WAVES; ++w) {
+            const double o = post[4 * w + threadIdx.x];
+            v = threadIdx.x == 3 ? __builtin_fmax(v, o) : v + o;
+        }
+        rows[4 * (size_t)blockIdx.x + threadIdx.x] = v;
+    }
+}
+
+// The rows of k_error_stats_one to the statistics of the block and, where means is not NULL, its means.  One workgroup; wavefront c
+// takes number c of all rows, lane l rows l, l + 64, ..., and the lanes' results are combined by a fixed tree: the same sums in
+// every launch.
+constexpr uint32_t kFinishThreads = 4 * kWave;
+__global__ __launch_bounds__(kFinishThreads) void k_error_finish(const double *__restrict__ rows, uint32_t n_rows, size_t n,
+                                                                double *__restrict__ stats, double *__restrict__ means)
+{
+    __shared__ double all[4];
+    const uint32_t lane = threadIdx.x & 63, c = wave_in_wg();
+    double v = 0.0;
+#pragma unroll 8
+    for (uint32_t i = lane; i < n_rows; i += kWave) {
+        const double o = rows[4 * i + c];
+        v = c == 3 ? __builtin_fmax(v, o) : v + o;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        const double o = __shfl_xor(v, m);
+        v = c == 3 ? __builtin_fmax(v, o) : v + o;
+    }
+    if (lane == 0) {
+        stats[c] = v;
+        all[c] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && means) {
+        means[0] = all[0] / (double)n;
+        means[1] = all[2] > 0.0 ? all[1] / all[2] : 0.0;
     }
 }
 

@@ -32,6 +32,8 @@ constexpr int kOneWaves = 8;  // wavefronts per workgroup
 
 // Workgroups of a maximum pass whose maxima the pass that follows combines, at most (scratch memory of the call).
 constexpr uint32_t kMostParts = 256;
+// Workgroups of the error statistics of one block, two per compute unit: rows of four numbers in scratch memory.
+constexpr uint32_t kMostStatsRows = 2 * kMostParts;
 
 // Where quad q of a run of len >= 4 elements starts: at 4 q, or, for the last quad of a run that is no whole number of
 // quads and for every quad past it, four elements before the end.  The overlap is read twice (a maximum does not

@@ -81,7 +81,7 @@ def lib():
 _BOUND = ("dq8_absmax", "dq8_encode_ws", "dq8_workspace_bytes", "dq8_decode", "dq8_absmax_segments", "dq8_encode_segments_ws",
           "dq8_workspace_bytes_segments", "dq8_decode_segments",
           "dq8_decode_accumulate_avg", "dq8_decode_accumulate_avg_local", "dq8_decode_accumulate_avg_segments",
-          "dq8_decode_avg_encode", "dq8_error_stats", "dq8_last_error")
+          "dq8_decode_avg_encode", "dq8_error_stats_ws", "dq8_workspace_bytes_stats", "dq8_last_error")
 
 
 def _check(rc, what):

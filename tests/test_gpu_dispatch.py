@@ -324,3 +324,37 @@ def test_scratch_memory_of_the_c_calls(dq8):
         assert calls(w, need) == (3, 3)
     assert L.dq8_encode_segments_ws(0, vp(x.data_ptr()), sz(n), vp(bounds.data_ptr()), sz(1), vp(scale.data_ptr()), vp(codes.data_ptr()), 0,
                                     vp(bounds.data_ptr()), sz(need), vp(stream)) == 3
+
+
+# whole units only, elements past them for one wavefront and for several; four wavefronts per workgroup up to four units per compute
+# unit and one unit more; a second unit for some wavefronts
+@pytest.mark.parametrize("n", [4097, 5 * 1024 + 63, 9 * 1024 + 65, 30 * 1024 + 1023, 1024 * 1024, 1025 * 1024 + 1, 6144 * 1024 + 1025])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_error_stats_of_one_block(dq8, monkeypatch, n, offset):
+    """With scratch memory (the same bytes in every call) and without; no zeros, few, and almost nothing else; a given scale of 0."""
+    rng = np.random.Generator(np.random.PCG64(6300 + n % 97))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-6, 0, n))).astype(np.float32)
+    few = x.copy()
+    few[[0, n // 2, n - 1]] = 0.0
+
+    def both(kind, y, given=None):
+        got = check_error_stats(dq8, kind, y, 0, given=given, tag="scratch")
+        assert got.tobytes() == check_error_stats(dq8, kind, y, 0, given=given, tag="again").tobytes()
+        with monkeypatch.context() as m:
+            m.setattr(dq8, "_native", dq8._Unbound())
+            check_error_stats(dq8, kind, y, 0, given=given, tag="none")
+        return got
+    if offset:  # an address that is aligned for an element only
+        t = dev(x, offset)
+        stats, means = torch.empty((1, 4), dtype=torch.float64, device="cuda"), torch.empty(2, dtype=torch.float64, device="cuda")
+        want, _ = oracle.error_stats(n % 4, x, 0)
+        got = dq8.error_stats(n % 4, t, 0, stats=stats, means=means)[0].cpu().numpy()
+        assert got[:, 2:].tobytes() == want[:, 2:].tobytes() and np.all(np.abs(got - want) <= 2 * n * 2.0 ** -53 * want)
+        return
+    both(n % 4, x)
+    both((n + 1) % 4, few, np.array([4.0], np.float32))
+    both(2, np.zeros(n, np.float32), np.array([0.0], np.float32))
+    for at, v in ((0, 0.3), (n // 2, -1e-7), (n - 1, 0.77))[:3 if n < 1 << 20 else 0]:  # sums of one term that is not 0: the term itself
+        one = np.zeros(n, np.float32)
+        one[at] = v
+        assert both(at % 2, one, np.array([0.9], np.float32)).tobytes() == oracle.error_stats(at % 2, one, 0, scales=np.array([0.9], np.float32))[0].tobytes()
