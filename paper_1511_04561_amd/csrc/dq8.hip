@@ -829,7 +829,14 @@ int launch_decode(const DeviceState &st, int kind, const uint8_t *codes, const f
         switch (wpw) {
         case 16: DQ8_DEC_R(16, 16) break;
         case 8: DQ8_DEC_R(16, 8) break;
-        default: DQ8_DEC_R(16, 4) break;
+        default:
+            if (!ragged && n >= kCodesFromCache)
+                hipLaunchKernelGGL((k_decode<16, 2, 4, false, 0>), dim3(p.grid), dim3(kWave * 4), 0, stream, tab, codes, scales, n, p.B,
+                                   p.nb, p.upb, p.n_units, p.n_teams, out);
+            else {
+                DQ8_DEC_R(16, 4)
+            }
+            break;
         }
         break;
     }
@@ -1691,6 +1698,13 @@ int dq8_decode_segments(int kind, const uint8_t *codes, const float *scales, siz
 #define DQ8_SEG_DEC(W, NEAR)                                                                                                  \
     hipLaunchKernelGGL((k_seg_decode<W, NEAR>), dim3(p.grid), dim3(kWave * (W)), lds, stream, tab, codes, scales, n, bounds, \
                        (uint32_t)n_seg, units, p.n_waves, out)
+    if (n_seg < (size_t)kWave && n >= kLongSegments) {
+        const size_t long_units = whole_units(n, kUnit, ((uintptr_t)out & 3) == 0);
+        const Plan lp = make_plan(n, 0, st->cus, 4, 1);
+        hipLaunchKernelGGL(k_seg_decode_long, dim3(lp.grid), dim3(kWg), lds, stream, tab, codes, scales, n, bounds, (uint32_t)n_seg,
+                           long_units, lp.n_teams, out);
+        return after_launch("k_seg_decode_long", stream);
+    }
     if (scales_fit_near(n_seg))  // two workgroups' tables fit
         DQ8_SEG_DEC(kSegWaves, true);
     else if (wpw == kSegWaves)

@@ -884,7 +884,9 @@ __global__ __launch_bounds__(kWg) void k_encode_long(const uint32_t *__restrict_
 // RAGGED = true (chosen by the host when blocks are not whole units): a short unit of four elements or more stays on
 // the pipelined path (see quad_start).  Otherwise a short unit is the last of the array: its loads are not ahead, but
 // in flight together.
-template <int Q, int NT, int WPW, bool RAGGED>
+// LD: cache policy of the code loads.  Plain (0) on long arrays: codes that were written or read a short while ago are then taken
+// from the memory-side cache and stay there (kCodesFromCache).
+template <int Q, int NT, int WPW, bool RAGGED, int LD = NT>
 __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
                                                        const float *__restrict__ scales, size_t n, size_t B, size_t nb,
                                                        size_t upb, size_t n_units, size_t n_waves, float *__restrict__ out)
@@ -913,7 +915,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restri
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
                 const uint32_t i = j * kWave + lane;
-                w[j] = ldg_codes<NT>(pc, RAGGED ? quad_start(i, q.len) : 4 * i);
+                w[j] = ldg_codes<LD>(pc, RAGGED ? quad_start(i, q.len) : 4 * i);
             }
         }
     };
@@ -944,7 +946,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode(const uint32_t *__restri
             if (!RAGGED && un.len >= 4 && ((uintptr_t)out & 3) == 0) {  // the short last unit of the array
                 uint32_t cur[Q];
 #pragma unroll
-                for (int j = 0; j < Q; ++j) cur[j] = ldg_codes<NT>(pc, quad_start(j * kWave + lane, un.len));
+                for (int j = 0; j < Q; ++j) cur[j] = ldg_codes<LD>(pc, quad_start(j * kWave + lane, un.len));
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {
                     const uint32_t q = j * kWave + lane;

@@ -113,9 +113,9 @@ __device__ __forceinline__ SegSpan open_span(const SegBounds &sb, size_t start, 
     return q;
 }
 
-// Elements at .. of a unit with several segments, up to 1024 of them and at least four: where fewer are left, the unit's
-// last four (some of them once more).  Units of more than 1024 elements are read again for this: their registers would
-// have to be indexed at run time, and few units hold several segments.
+// Elements at .. of a short last unit, up to 1024 of them and at least four: where fewer are left, the unit's last four (some of
+// them once more).  A short unit of more than 1024 elements is read again for this: its registers would have to be indexed at
+// run time.
 __device__ __forceinline__ SegSpan open_part(const SegBounds &sb, const SegSpan &unit, uint32_t at, uint32_t lane)
 {
     const uint32_t left = unit.len - at;
@@ -233,6 +233,8 @@ __device__ __forceinline__ void for_each_element(const uint64_t *lds, uint32_t n
 // other, about 10 ns each, and the walk by position brings every workgroup to every long segment.
 // Units of Q * 256 elements: 16 quads per lane on long arrays, 4 where that leaves wavefronts without work (the plan's
 // items of four units and of one).
+// A unit with several segments goes on with the registers it was loaded into (read again, it kept its wavefront and the kernel
+// longer: maxima and compression of 25 M elements in 30 segments 42.1 us, 41.2 so).
 // NT = 0, plain loads, where the array or much of it is still in the memory-side cache when k_seg_encode reads it again
 // (kPlainBeforeCompression; by itself up to kCachedFloats): with non-temporal loads here k_seg_encode takes 33.4 instead of 26.8 us
 // at 37.7 M elements and 53 instead of 43 us at 61 M, this one 1 to 2 us less.  By itself, 1000 M: 643 plain, 574 us.
@@ -276,11 +278,7 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
             }
             run = run > f2u(fm) ? run : f2u(fm);
         } else {
-            for (uint32_t at = 0; at < q.len; at += kSegUnit) {
-                const SegSpan part = open_part(sb, q, at, lane);
-                v4f w[kSegQ];
-#pragma unroll
-                for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<NT>(x + part.start, quad_start(j * kWave + lane, part.len));
+            auto merge = [&](const SegSpan &part, const v4f (&w)[kSegQ]) {
                 const SegQuads<kSegQ> sq = segments_of_quads(sb, part, lane);
 #pragma unroll
                 for (int j = 0; j < kSegQ; ++j) {
@@ -294,6 +292,24 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
                         const uint32_t m = m01 > m23 ? m01 : m23;
                         if (m != 0) atomicMax(best + sq.seg[j][0], m);
                     }
+                }
+            };
+            if constexpr (Q == kSegQ) {
+                merge(q, v);
+            } else if (q.len == (uint32_t)U) {
+#pragma unroll
+                for (int p = 0; p < Q; p += kSegQ) {
+                    const v4f w[kSegQ] = {v[p], v[p + 1], v[p + 2], v[p + 3]};
+                    merge(open_span(sb, q.start + p * 4 * kWave, kSegUnit, lane), w);
+                }
+            } else {  // the short last unit
+#pragma unroll 1
+                for (uint32_t at = 0; at < q.len; at += kSegUnit) {
+                    const SegSpan part = open_part(sb, q, at, lane);
+                    v4f w[kSegQ];
+#pragma unroll
+                    for (int j = 0; j < kSegQ; ++j) w[j] = ldg_floats<NT>(x + part.start, quad_start(j * kWave + lane, part.len));
+                    merge(part, w);
                 }
             }
             if (u + n_waves < n_units) fetch(u + n_waves);
@@ -561,6 +577,84 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_decode(const uint32_t *__r
     });
     for_each_element(seg_lds, n_seg, n_units * (size_t)kSegUnit, n, n_waves,
                      [&](size_t i, uint32_t seg) { out[i] = lut_code(lut, codes[i], lane4) * sc[seg]; });
+}
+
+// The same for long arrays and fewer than 64 segments, in the shape of k_decode: units of 4096 elements, sixteen code words per lane,
+// four wavefronts per compute unit, the words copied before the next unit's are requested.  A unit with several segments goes
+// on with the same words: read again it kept its wavefront, and with it the kernel, 4 us longer. In
+// a graph, k_seg_decode / this: 12 Mi elements in 12 segments 13.7 / 11.4 us, 25 M in 30 24.8 / 22.0, 61 M in 16 56.4 / 51.6 (k_decode on
+// one segment: 49.4); 8 Mi in 40 7.5 / 8.5 with the codes in the cache, 9.5 / 9.3 without.
+__global__ __launch_bounds__(kWg) void k_seg_decode_long(const uint32_t *__restrict__ tab, const uint8_t *__restrict__ codes,
+                                                         const float *__restrict__ scales, size_t n, const uint64_t *__restrict__ bounds,
+                                                         uint32_t n_seg, size_t n_units, size_t n_waves, float *__restrict__ out)
+{
+    constexpr int Q = kUnitQuads;
+    __shared__ __align__(256) float lut[256 * kLutCopies];
+    extern __shared__ uint64_t seg_lds[];
+    const uint32_t lane = threadIdx.x & 63, lane4 = lane * 4;
+    float *near = reinterpret_cast<float *>(seg_lds + n_seg + 1);
+    uint32_t w[Q];
+    auto fetch = [&](size_t u) {
+        const uint32_t len = cap_to_unit<kUnit>(n - u * (size_t)kUnit);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) w[j] = ldg_codes<0>(codes + u * (size_t)kUnit, quad_start(j * kWave + lane, len));
+    };
+    size_t u = first_unit();
+    if (u < n_units) fetch(u);  // the first loads are in flight while the tables are built
+    const float lut_value = request_lut(tab);
+    if (threadIdx.x < n_seg) near[threadIdx.x] = scales[threadIdx.x];
+    const SegBounds sb = load_bounds(bounds, n_seg, n, seg_lds, lane);
+    place_lut<kWg>(lut_value, lut);
+    __syncthreads();
+    auto expand = [&](uint32_t cw, v4f s) {
+        v4f r;
+        r.x = lut_at<0>(lut, cw, lane4) * s.x;
+        r.y = lut_at<1>(lut, cw, lane4) * s.y;
+        r.z = lut_at<2>(lut, cw, lane4) * s.z;
+        r.w = lut_at<3>(lut, cw, lane4) * s.w;
+        return r;
+    };
+    while (u < n_units) {
+        const SegSpan q = open_span(sb, u * (size_t)kUnit, cap_to_unit<kUnit>(n - u * (size_t)kUnit), lane);
+        u += n_waves;
+        if (q.len == (uint32_t)kUnit) {
+            uint32_t cur[Q];
+#pragma unroll
+            for (int j = 0; j < Q; ++j) cur[j] = w[j];
+            if (u < n_units) fetch(u);
+            float *po = out + q.start;
+            if (q.first == q.last) {
+                const float s = near[q.first];
+#pragma unroll
+                for (int j = 0; j < Q; ++j) stg_floats<2>(po + 4 * (j * kWave + lane), expand(cur[j], v4f{s, s, s, s}));
+            } else {
+#pragma unroll
+                for (int p = 0; p < Q; p += kSegQ) {
+                    const SegQuads<kSegQ> sq = segments_of_quads(sb, open_span(sb, q.start + p * 4 * kWave, kSegUnit, lane), lane);
+#pragma unroll
+                    for (int j = 0; j < kSegQ; ++j) stg_floats<2>(po + 4 * ((p + j) * kWave + lane), expand(cur[p + j], scales_of_quad(near, sq, j)));
+                }
+            }
+        } else {  // the short last unit
+#pragma unroll 1
+            for (uint32_t at = 0; at < q.len; at += kSegUnit) {
+                const SegSpan part = open_part(sb, q, at, lane);
+                const SegQuads<kSegQ> sq = segments_of_quads(sb, part, lane);
+                uint32_t cur[kSegQ];
+#pragma unroll
+                for (int j = 0; j < kSegQ; ++j) cur[j] = ldg_codes<0>(codes + part.start, quad_start(j * kWave + lane, part.len));
+#pragma unroll
+                for (int j = 0; j < kSegQ; ++j) {
+                    const uint32_t k = j * kWave + lane;
+                    const v4f r = expand(cur[j], scales_of_quad(near, sq, j));
+                    if (k * 4 < part.len) stg_floats<2>(out + part.start + quad_start(k, part.len), r);
+                }
+            }
+            if (u < n_units) fetch(u);
+        }
+    }
+    for_each_element(seg_lds, n_seg, n_units * (size_t)kUnit, n, n_waves,
+                     [&](size_t i, uint32_t seg) { out[i] = lut_code(lut, codes[i], lane4) * near[seg]; });
 }
 
 // Decompression of K workers' buffers and their average (optionally with a local fp32 array as the first term)

@@ -160,7 +160,16 @@ constexpr size_t kNearLongest = 98304;
 constexpr size_t kCachedFloats = (size_t)1 << 26;
 constexpr size_t kPlainBeforeCompression = (size_t)1 << 29, kPlainBeforeStatistics = kCachedFloats;
 
+// Expansion of at least this many elements reads the codes with plain loads: in a graph 61 M codes from
+// memory 50.1 / 49.4 us, from the memory-side cache 50.2 / 45.6; 16 Mi 15.6 / 14.2; 8 Mi 8.16 / 8.26.
+constexpr size_t kCodesFromCache = (size_t)1 << 24;
+
 // ---- tensors back to back, one scale each
+
+// Expansion of at least this many elements in fewer than 64 segments takes units of 4096 elements (k_seg_decode_long, figures
+// there): below, units of 1024 on sixteen wavefronts per compute unit are no more than two or three each.
+constexpr size_t kLongSegments = (size_t)10 << 20;
+
 
 // Wavefronts per workgroup of the kernels that keep a value table beside the bounds: kSegWaves, two such workgroups on a
 // compute unit, or twice that where only one workgroup's tables fit and there are units for more than one each.

@@ -358,3 +358,15 @@ def test_error_stats_of_one_block(dq8, monkeypatch, n, offset):
         one = np.zeros(n, np.float32)
         one[at] = v
         assert both(at % 2, one, np.array([0.9], np.float32)).tobytes() == oracle.error_stats(at % 2, one, 0, scales=np.array([0.9], np.float32))[0].tobytes()
+
+
+# units of 4096 elements (from 10 Mi elements on) and of 1024; whole, and with a last one of 1, 3, 4 and 1027 elements; 63 segments and 64
+@pytest.mark.parametrize("n", [(10 << 20) - 1, 10 << 20, (10 << 20) + 3, (10 << 20) + 4, (12 << 20) + 1027])
+@pytest.mark.parametrize("n_seg", [2, 63, 64])
+def test_long_sets_of_tensors(dq8, n, n_seg):
+    """Segments that end inside a unit, several in one part of a unit, in its first and last quad, and in the array's last unit."""
+    rng = np.random.Generator(np.random.PCG64(9950 + n % 97 + n_seg))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    close = 4096 * 700 + np.array([0, 1, 3, 1023, 1024, 1025, 2050, 4093, 4095, 4096 + 5, 8192])
+    inner = np.sort(np.concatenate([rng.integers(0, n + 1, max(0, n_seg - 14)), close, [n - 1, n - 2]])[-(n_seg - 1):])
+    check_segments(dq8, n % 4, x, np.concatenate([[0], inner, [n]]), x_off=n % 3, c_off=n % 4, tag="long")
