@@ -1650,16 +1650,17 @@ int dq8_encode_segments_ws(int kind, const float *x, size_t n, const uint64_t *b
             (copied ? n_seg * sizeof(float) : 0);
     const size_t units = whole_units(n, kSegUnit, ((uintptr_t)x & 3) == 0);
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-#define DQ8_SEG_ENC(RM, W, FROM)                                                                                            \
-    hipLaunchKernelGGL((k_seg_encode<RM, W, FROM>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds,       \
-                       (uint32_t)n_seg, units, p.n_waves, scales, parts, n_parts, codes)
-#define DQ8_SEG_ENC_FROM(RM, W)                 \
-    if (parts)                                  \
-        DQ8_SEG_ENC(RM, W, kScalesFromParts);   \
-    else if (copied)                            \
-        DQ8_SEG_ENC(RM, W, kScalesCopied);      \
-    else                                        \
-        DQ8_SEG_ENC(RM, W, kScalesInMemory)
+#define DQ8_SEG_ENC(KERNEL, RM, W)                                                                                         \
+    hipLaunchKernelGGL((KERNEL<RM, W>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds, (uint32_t)n_seg, \
+                       units, p.n_waves, scales, codes)
+#define DQ8_SEG_ENC_FROM(RM, W)                                                                                               \
+    if (parts)                                                                                                                \
+        hipLaunchKernelGGL((k_seg_encode_parts<RM, W>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, x, n, bounds,     \
+                           (uint32_t)n_seg, units, p.n_waves, parts, n_parts, scales, codes);                                  \
+    else if (copied)                                                                                                          \
+        DQ8_SEG_ENC(k_seg_encode_copied, RM, W);                                                                               \
+    else                                                                                                                      \
+        DQ8_SEG_ENC(k_seg_encode, RM, W)
     if (st->has_remap[kind] && many) {
         DQ8_SEG_ENC_FROM(true, 2 * kSegWaves);
     } else if (st->has_remap[kind]) {

@@ -39,9 +39,8 @@ int launch_avg_long_tu(int cus, const uint32_t *tab, uint32_t search_words, cons
     size_t teams = (size_t)cus * 2;  // two workgroups' tables fit the LDS of a compute unit
     if (teams > nb) teams = nb;
     const size_t lds = ((size_t)search_words + kLongSlots) * sizeof(uint32_t);
-    // The register path needs 32-bit accesses to the codes and 128-bit ones to local at every block start.
-    bool aligned = K >= 1 && (nb == 1 || (B & 3) == 0) && ((uintptr_t)codes_out & 3) == 0 && ((uintptr_t)local & 15) == 0;
-    for (int k = 0; k < K; ++k) aligned = aligned && ((uintptr_t)wp.codes[k] & 3) == 0;
+    // The register path takes blocks that start at any element (see quad_start).
+    const bool aligned = K >= 1 && ((uintptr_t)local & 3) == 0;
 #define DQ8_AVG_LONG(QL, NB, KT)                                                                                              \
     hipLaunchKernelGGL((k_avg_long<QL, NB, 2, KT>), dim3((unsigned)teams), dim3(kLongTeam), lds, stream, tab, wp, K, local, n, \
                        B, nb, (uint32_t)teams, (uint32_t)aligned, scales_out, codes_out)

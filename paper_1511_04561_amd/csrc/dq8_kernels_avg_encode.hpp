@@ -225,10 +225,9 @@ __global__ __launch_bounds__(kWave * WPW, WPW / 2) void k_avg_block(const uint32
 //    start of a block it would be the wavefront's youngest load, and waiting for it would drain everything);
 //  - a place past the workgroup's last block repeats its last block (valid memory, result unused);
 //  - a lane whose quad lies past the end of a block loads the block's last quad and stores nothing.
-// `aligned` (from the host): every buffer allows 32-bit accesses to the codes and 128-bit ones to local at
-// every block start, and there is at least one worker.  Then every block of whole quads takes this path (all
-// but perhaps the array's last block); any other block goes quad by quad or element by element and forms its
-// means once for the maximum and once for the compression.
+// `aligned` (from the host): local is a multiple of 4, and there is at least one worker.  Then every block takes this path (see
+// quad_start), but a last one of fewer than four elements; any other block goes quad by quad or element by element and forms
+// its means once for the maximum and once for the compression.
 // Calls f(first quad, G) for the groups 0, 1, ... of G quads each, in order.
 template <int G, typename F, int... I>
 __device__ __forceinline__ void encode_groups(F &f, std::integer_sequence<int, I...>)
@@ -241,7 +240,7 @@ constexpr int kLongTeam = kLongWaves * kWave;  // its threads
 constexpr int kLongSlots = 2 * kLongWaves;     // LDS words for the maxima (two phases)
 
 template <int QL, int NB, int NT, int KT>
-__global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restrict__ tab, WorkerPtrs p, int K_rt,
+__global__ __launch_bounds__(kLongTeam, 4) void k_avg_long(const uint32_t *__restrict__ tab, WorkerPtrs p, int K_rt,
                                                  const float *__restrict__ local, size_t n, size_t B, size_t nb,
                                                  uint32_t n_teams, uint32_t aligned, float *__restrict__ scales_out,
                                                  uint8_t *__restrict__ codes_out)
@@ -274,9 +273,9 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
     };
     auto length_of = [&](size_t blk) { return (uint32_t)(n - blk * B < B ? n - blk * B : B); };
-    // Blocks 0 .. n_stream - 1 take the register path: all of them when the array's last block is whole quads.
+    // Blocks 0 .. n_stream - 1 take the register path: all of them unless the array's last block is shorter than a quad.
     const uint32_t last_len = length_of(nb - 1);
-    const size_t n_stream = !aligned ? 0 : ((last_len >= 4 && (last_len & 3) == 0) ? nb : nb - 1);
+    const size_t n_stream = !aligned ? 0 : (last_len >= 4 ? nb : nb - 1);
     if (blockIdx.x < n_stream) {
         const int Kp = (K + NB - 1) / NB * NB;  // places per block
         uint32_t w[NB][Q];                      // the sets of code words
@@ -284,14 +283,11 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
         // Requests place `place` of block b: scale and code words of worker `place`, or of the last worker again.
         auto request = [&](uint32_t(&ww)[Q], float &sc, size_t b, int place) {
             const int worker = place < K ? place : K - 1;
-            const uint32_t last = (length_of(b) >> 2) - 1;
+            const uint32_t len = length_of(b);
             sc = ldg<0>(p.scales[worker] + b);
-            const uint32_t *c4 = reinterpret_cast<const uint32_t *>(p.codes[worker] + b * B);
+            const uint8_t *pc = p.codes[worker] + b * B;
 #pragma unroll
-            for (int j = 0; j < Q; ++j) {
-                const uint32_t i = j * kLongTeam + tl;
-                ww[j] = ldg_at<NT>(c4, i < last ? i : last);
-            }
+            for (int j = 0; j < Q; ++j) ww[j] = ldg_codes<NT>(pc, quad_start(j * kLongTeam + tl, len));
         };
         // (one set after the other, as in the loop below: the waits there are counted for the worse of the two orders)
 #pragma unroll
@@ -302,15 +298,11 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
         for (size_t blk = blockIdx.x; blk < n_stream; blk += n_teams) {
             const size_t start = blk * B;
             const size_t next = blk + n_teams < n_stream ? blk + n_teams : blk;  // after the last block: this one again
-            const uint32_t nq = length_of(blk) >> 2, last = nq - 1;
+            const uint32_t len = length_of(blk);
             v4f acc[Q];
             if (local) {  // not requested ahead: the sums are still in use when the code words of this block set out
-                const v4f *l4 = reinterpret_cast<const v4f *>(local + start);
 #pragma unroll
-                for (int j = 0; j < Q; ++j) {
-                    const uint32_t i = j * kLongTeam + tl;
-                    acc[j] = ldg_at<NT>(l4, i < last ? i : last);
-                }
+                for (int j = 0; j < Q; ++j) acc[j] = ldg_floats<NT>(local + start, quad_start(j * kLongTeam + tl, len));
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {  // the sum starts at +0: a local -0 becomes +0
                     acc[j].x = 0.0f + acc[j].x;
@@ -362,7 +354,7 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
             const float d = s == 0.0f ? 1.0f : s;
             const float r = 1.0f / d;
             const bool recip = reciprocal_ok(d);
-            uint32_t *c4 = reinterpret_cast<uint32_t *>(codes_out + start);
+            uint8_t *pc = codes_out + start;
             // quads whose table lookups are issued together: four, and what is left of Q after the groups of four
             auto encode_group = [&](auto first, auto count) {
                 constexpr int g = decltype(first)::value, G = decltype(count)::value;
@@ -372,8 +364,10 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
                 for (int j = 0; j < G; ++j) vv[j] = acc[g + j];
                 encode_quads<true, G>(sr, vv, pre, d, r, recip, cw);
 #pragma unroll
-                for (int j = 0; j < G; ++j)
-                    if ((g + j) * kLongTeam + tl < nq) stg<1>(c4 + (g + j) * kLongTeam + tl, cw[j]);
+                for (int j = 0; j < G; ++j) {
+                    const uint32_t i = (g + j) * kLongTeam + tl;
+                    if (i * 4 < len) stg_codes<1>(pc, quad_start(i, len), cw[j]);
+                }
             };
             // groups of four quads, of two where a lane holds seven or eight (the sums of a group are all live at
             // once; with larger groups two workgroups no longer fit a compute unit's registers), one group after the other
@@ -455,8 +449,7 @@ __global__ __launch_bounds__(kLongTeam) void k_avg_long(const uint32_t *__restri
 // TEAMS teams share a workgroup and its tables; the workgroup barrier that separates the
 // exchange of the maxima from their use is executed by every wavefront the same number of
 // times (`iters`), whether or not its team still has a unit.
-// RAGGED = true (chosen by the host for blocks shorter than the unit): a unit of fewer whole aligned quads
-// takes the register path as well.
+// RAGGED = true (chosen by the host): blocks shorter than the unit.
 // MULTI = true: more workers than KT, taken KT at a time in `passes` passes over the same registers; a
 // place of the last pass that has no worker repeats worker K - 1 with scale 0 (the product is a zero, and
 // adding a zero leaves a sum that started at +0 unchanged).  K is then a run-time value.
@@ -512,38 +505,32 @@ struct AvgTeam {
         sl.fast = false;
         if (!sl.active) return;
         sl.un = unit_of<kUnit>(u, n, B, nb, 1);
-        // whole aligned quads: a short unit takes the register path too (see load_worker)
-        bool f = (RAGGED ? (sl.un.len >= 4 && (sl.un.len & 3) == 0) : sl.un.len == (uint32_t)kTeamUnit) &&
-                 (((uintptr_t)(codes_out + sl.un.start) & 3) == 0);
-        if (MULTI) {
-            for (int k = 0; k < K; ++k) f = f && (((uintptr_t)(p.codes[k] + sl.un.start) & 3) == 0);
-        } else {
-#pragma unroll
-            for (int k = 0; k < KT; ++k) f = f && (((uintptr_t)(p.codes[k] + sl.un.start) & 3) == 0);
-        }
-        if (local) f = f && (((uintptr_t)(local + sl.un.start) & 15) == 0);
-        sl.fast = f;
+        // short units and any alignment too (see quad_start): the array's last block, element by element and with every
+        // mean formed twice, took as long as the rest of a short array (1 Mi + 4095 elements, eight workers: 15.9 us, 8.7
+        // so; 16 workers 84 and 12.6, 20 M elements 140 and 69)
+        sl.fast = sl.un.len >= 4 && ((uintptr_t)local & 3) == 0;
     }
 
-    // This lane's j-th quad of the unit; WHOLE promises a whole unit, otherwise a quad past the
-    // end of a shorter unit becomes the unit's last one (an unconditional load of valid memory whose result
-    // is not stored and cannot change the maximum).
+    // First element of this lane's j-th quad of the unit; WHOLE promises a whole unit.
     template <bool WHOLE>
     __device__ __forceinline__ uint32_t quad_of(const Slot &sl, int j) const
     {
         const uint32_t i = j * kTeam + tl;
-        if (WHOLE || !RAGGED) return i;
-        const uint32_t last = (sl.un.len >> 2) - 1;
-        return i < last ? i : last;
+        return WHOLE ? 4 * i : quad_start(i, sl.un.len);
     }
 
     // Code words of `worker` for unit sl into place k.
     template <bool WHOLE>
     __device__ __forceinline__ void load_worker(const Slot &sl, int k, int worker)
     {
-        const uint32_t *c4 = reinterpret_cast<const uint32_t *>(p.codes[worker] + sl.un.start);
+        const uint8_t *pc = p.codes[worker] + sl.un.start;
 #pragma unroll
-        for (int j = 0; j < Q; ++j) w[k][j] = ldg_at<NT>(c4, quad_of<WHOLE>(sl, j));
+        for (int j = 0; j < Q; ++j) {
+            if (WHOLE)
+                w[k][j] = ldg_at<NT>(reinterpret_cast<const uint32_t *>(pc), j * kTeam + tl);
+            else
+                w[k][j] = ldg_codes<NT>(pc, quad_of<false>(sl, j));
+        }
     }
 
     __device__ __forceinline__ void load_all(const Slot &sl)
@@ -569,10 +556,14 @@ struct AvgTeam {
         bool in_range = !pow2 && !local;
         if (STEADY || (sl.active && sl.fast)) {
             if (local) {  // not prefetched: the code words take the registers
-                const v4f *l4 = reinterpret_cast<const v4f *>(local + sl.un.start);
+                const float *pl = local + sl.un.start;
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {  // the sum starts at +0: a local -0 becomes +0
-                    const v4f l = ldg<NT>(l4 + quad_of<STEADY>(sl, j));
+                    v4f l;
+                    if (STEADY)
+                        l = ldg<NT>(reinterpret_cast<const v4f *>(pl) + j * kTeam + tl);
+                    else
+                        l = ldg_floats<NT>(pl, quad_of<false>(sl, j));
                     acc[j].x = 0.0f + l.x;
                     acc[j].y = 0.0f + l.y;
                     acc[j].z = 0.0f + l.z;
@@ -668,12 +659,17 @@ struct AvgTeam {
         const float r = 1.0f / d;
         const bool recip = reciprocal_ok(d);
         if (STEADY || sl.fast) {
-            uint32_t *c4 = reinterpret_cast<uint32_t *>(codes_out + sl.un.start);
+            uint8_t *pc = codes_out + sl.un.start;
             uint32_t cw[Q];
             encode_quads<FASTDIV, Q>(sr, acc, pre, d, r, recip, cw);
 #pragma unroll
-            for (int j = 0; j < Q; ++j)
-                if (STEADY || !RAGGED || j * kTeam + tl < (sl.un.len >> 2)) stg<1>(c4 + j * kTeam + tl, cw[j]);
+            for (int j = 0; j < Q; ++j) {
+                const uint32_t i = j * kTeam + tl;
+                if (STEADY)
+                    stg<1>(reinterpret_cast<uint32_t *>(pc) + i, cw[j]);
+                else if (i * 4 < sl.un.len)
+                    stg_codes<1>(pc, quad_start(i, sl.un.len), cw[j]);
+            }
         } else {
             for (uint32_t i = tl; i < sl.un.len; i += kTeam)
                 codes_out[sl.un.start + i] = (uint8_t)encode_one<FASTDIV>(sr, mean_at(sl.un, i), d, r, recip);

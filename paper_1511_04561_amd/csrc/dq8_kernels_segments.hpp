@@ -344,10 +344,10 @@ __global__ __launch_bounds__(kSegWg) void k_seg_absmax(const float *__restrict__
 enum SegScales { kScalesInMemory, kScalesCopied, kScalesFromParts };
 
 template <bool REMAP, int WAVES, SegScales FROM>
-__global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
-                                                             const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
-                                                             size_t n_waves, float *__restrict__ scales, const float *__restrict__ parts,
-                                                             uint32_t n_parts, uint8_t *__restrict__ codes)
+__device__ __forceinline__ void encode_segments_body(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                     const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units, size_t n_waves,
+                                                     const float *__restrict__ scales, float *__restrict__ scales_out,
+                                                     const float *__restrict__ parts, uint32_t n_parts, uint8_t *__restrict__ codes)
 {
     extern __shared__ uint64_t seg_lds[];  // the bounds (seg_bounds_words(n_seg) entries), the search table, the scales
     const uint32_t lane = threadIdx.x & 63;
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
             for (uint32_t j = 0; j < AT_ONCE; ++j)
                 if (lane == 0 && i + j < n_seg) {
                     near[i + j] = u2f(m[j]);
-                    if (blockIdx.x == 0) scales[i + j] = u2f(m[j]);
+                    if (blockIdx.x == 0) scales_out[i + j] = u2f(m[j]);
                 }
         }
     }
@@ -423,6 +423,32 @@ __global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__r
         const float s = sc[seg];
         codes[i] = (uint8_t)code_exact(sr, x[i], s == 0.0f ? 1.0f : s);
     });
+}
+
+template <bool REMAP, int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_encode(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                             const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                             size_t n_waves, const float *__restrict__ scales, uint8_t *__restrict__ codes)
+{
+    encode_segments_body<REMAP, WAVES, kScalesInMemory>(tab, x, n, bounds, n_seg, n_units, n_waves, scales, nullptr, nullptr, 0, codes);
+}
+
+template <bool REMAP, int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_encode_copied(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                                    const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                                    size_t n_waves, const float *__restrict__ scales,
+                                                                    uint8_t *__restrict__ codes)
+{
+    encode_segments_body<REMAP, WAVES, kScalesCopied>(tab, x, n, bounds, n_seg, n_units, n_waves, scales, nullptr, nullptr, 0, codes);
+}
+
+template <bool REMAP, int WAVES>
+__global__ __launch_bounds__(kWave *WAVES) void k_seg_encode_parts(const uint32_t *__restrict__ tab, const float *__restrict__ x, size_t n,
+                                                                   const uint64_t *__restrict__ bounds, uint32_t n_seg, size_t n_units,
+                                                                   size_t n_waves, const float *__restrict__ parts, uint32_t n_parts,
+                                                                   float *__restrict__ scales, uint8_t *__restrict__ codes)
+{
+    encode_segments_body<REMAP, WAVES, kScalesFromParts>(tab, x, n, bounds, n_seg, n_units, n_waves, nullptr, scales, parts, n_parts, codes);
 }
 
 // Maxima and compression of a short array in one launch: k_encode_near for segments.  A workgroup of sixteen wavefronts

@@ -370,3 +370,33 @@ def test_long_sets_of_tensors(dq8, n, n_seg):
     close = 4096 * 700 + np.array([0, 1, 3, 1023, 1024, 1025, 2050, 4093, 4095, 4096 + 5, 8192])
     inner = np.sort(np.concatenate([rng.integers(0, n + 1, max(0, n_seg - 14)), close, [n - 1, n - 2]])[-(n_seg - 1):])
     check_segments(dq8, n % 4, x, np.concatenate([[0], inner, [n]]), x_off=n % 3, c_off=n % 4, tag="long")
+
+
+# a last block of 1, 3, 4, 5 elements, one short of whole quads and one short of whole; teams of one to four wavefronts and a workgroup
+# per block; all workers unrolled, in passes, in chunks
+@pytest.mark.parametrize("block,K", [(512, 2), (1000, 4), (1024, 1), (2048, 8), (3000, 5), (3500, 3), (4096, 6), (4096, 7), (4096, 9), (4096, 16), (5000, 2), (8192, 8),
+                                     (12288, 11), (16384, 7)])
+@pytest.mark.parametrize("rest", [1, 3, 4, 5, 257, -2])
+@pytest.mark.parametrize("local", [False, True])
+def test_averages_with_a_last_block_of_any_length(dq8, block, K, rest, local):
+    """Averages and averages compressed again whose last block is no whole number of quads, at any alignment of an element."""
+    n = block * (5 if block < 8192 else 3) + rest % block
+    rng = np.random.Generator(np.random.PCG64(9970 + n % 97 + K))
+    kind, nb, off = (n + K) % 4, -(-n // block), (K + rest) % 4
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-4, 4, nb)).astype(np.float32) for _ in range(K)]
+    x = rng.standard_normal(n).astype(np.float32) if local else None
+    want = oracle.decode_accumulate_avg(kind, cl, sl, block, local=x)
+    codes, scales = [dev(c, (off + k) % 4 if rest % 2 else 0) for k, c in enumerate(cl)], [dev(s) for s in sl]
+    mine = None if x is None else dev(x, off)
+    go = Guarded(n, np.float32)
+    dq8.decode_accumulate_avg(kind, codes, scales, block, out=go.t, local=mine)
+    same_bits(go.t, want, "average")
+    go.check("average")
+    wc, ws = oracle.encode(kind, want, block)
+    gc, gs = Guarded(n, np.uint8, off), Guarded(nb, np.float32)
+    dq8.decode_avg_encode(kind, codes, scales, block, local=mine, scales=gs.t, codes=gc.t)
+    same_bits(gc.t, wc, "codes of the average")
+    same_bits(gs.t, ws, "scales of the average")
+    gc.check("codes of the average")
+    gs.check("scales of the average")
