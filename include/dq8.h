@@ -27,7 +27,8 @@
  *       dq8_absmax, dq8_encode, dq8_decode and the calls for segments: `x`, `out` and `local` at a multiple
  *         of 4 bytes (any float array); `codes` may start at any byte.  Units of fewer than four
  *         elements go one by one, and dq8_decode is faster where block % 4 == 0 or there is one block.
- *       dq8_decode_accumulate_avg[_local], dq8_decode_avg_encode, dq8_error_stats, and every call with
+ *       dq8_decode_avg_encode: the same, fastest with 16-byte aligned `local` and 4-byte aligned codes.
+ *       dq8_decode_accumulate_avg[_local], dq8_error_stats (without scratch memory), and every call with
  *         blocks of 4 to 128 elements that are powers of two (up to 512 for dq8_encode): also 16-byte
  *         aligned `x` / `out` / `local`, 4-byte aligned `codes`, and block % 4 == 0 (or a single block).
  *     Blocks of 4096 elements are the fastest; other lengths come close (the units of work follow the block
@@ -123,8 +124,8 @@ int dq8_absmax(const float *x, size_t n, size_t block, float *scales, void *hip_
  * maxima unless flags has DQ8_SCALES_GIVEN, in which case they are read.
  * `codes` and `scales` must not overlap `x`.
  * x is read once when a block has at most 16384 elements (a block is held in registers between
- * the maximum and the quantisation); longer blocks, block == 0 on a longer array included,
- * take a maximum pass and a quantisation pass: x is read twice.
+ * the maximum and the quantisation); longer blocks take a maximum pass and a quantisation pass: x is
+ * read twice.  An array of up to 98304 elements that is one block is compressed in one launch.
  */
 int dq8_encode(int kind, const float *x, size_t n, size_t block, float *scales, uint8_t *codes,
                unsigned flags, void *hip_stream);
