@@ -17,7 +17,7 @@ BINDING = os.path.join(HERE, "_binding.so")  # Python extension over torch's C++
 BINDING_SOURCE = os.path.join(CSRC, "dq8_binding.cpp")
 SOURCES = ["dq8.hip", "dq8_avg_short.hip", "dq8_avg_long.hip", "dq8_tables.cpp"]
 HEADERS = ["dq8_internal.h", "dq8_launch.hpp", "dq8_tables.hpp", "dq8_device.hpp", "dq8_plan.hpp", "dq8_units.hpp", "dq8_arith.hpp", "dq8_kernels_codec.hpp", "dq8_kernels_avg.hpp",
-           "dq8_kernels_avg_encode.hpp", "dq8_kernels_stats.hpp", "dq8_kernels_small.hpp", "dq8_kernels_segments.hpp", os.path.join(ROOT, "include", "dq8.h")]
+           "dq8_kernels_avg_encode.hpp", "dq8_kernels_stats.hpp", "dq8_kernels_small.hpp", "dq8_kernels_segments.hpp", os.path.join(ROOT, "include", "dq8.h"), os.path.join(ROOT, "include", "dq8_workspace.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wextra", "-Wno-unused-parameter", "-Wno-unknown-cuda-version"]
@@ -47,7 +47,7 @@ def binding_command(out=BINDING):
 
 def binding_stale():
     return not os.path.exists(BINDING) or any(os.path.getmtime(d) > os.path.getmtime(BINDING)
-                                              for d in (BINDING_SOURCE, os.path.join(ROOT, "include", "dq8.h")))
+                                              for d in (BINDING_SOURCE, os.path.join(ROOT, "include", "dq8.h"), os.path.join(ROOT, "include", "dq8_workspace.h")))
 
 
 def build_binding(force=True, verbose=False):

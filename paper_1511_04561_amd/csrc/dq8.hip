@@ -36,6 +36,7 @@
 #include <mutex>
 
 #include "dq8.h"
+#include "dq8_workspace.h"
 #include "dq8_internal.h"
 #include "dq8_launch.hpp"
 #include "dq8_plan.hpp"

@@ -23,7 +23,7 @@
 #include <cstdint>
 #include <exception>
 
-#include "dq8.h"
+#include "dq8_workspace.h"
 
 namespace {
 
