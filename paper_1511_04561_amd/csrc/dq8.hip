@@ -1739,23 +1739,20 @@ int dq8_decode_accumulate_avg_segments(int kind, const uint8_t *const *codes, co
     rc = device_state(&st);
     if (rc) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int wpw = segment_waves(st->cus, n, n_seg);
-    const SegPlan p = make_segment_plan(st->cus, n, n_seg, 2 * kSegWaves, false, wpw);
     const size_t units = whole_units(n, kSegUnit, (((uintptr_t)out | (uintptr_t)local) & 3) == 0);
+    const SegAverage a = make_segment_average(st->cus, n, n_seg, K, units);
+    const SegPlan &p = a.plan;
     const uint32_t *tab = st->tables + (size_t)kind * kTableWords;
-    const bool near = scales_fit_near((size_t)K * n_seg);
-    const size_t lds = p.lds + (near ? (size_t)K * n_seg * sizeof(float) : 0);
-    const bool one_unit = units <= p.n_waves, one_workgroup = p.grid <= (unsigned)st->cus;
-#define DQ8_SEG_AVG(W, AHEAD, NEAR)                                                                                           \
-    hipLaunchKernelGGL((k_seg_avg<W, AHEAD, NEAR>), dim3(p.grid), dim3(kWave * (W)), lds, stream, tab, wp, K, local, n, bounds, \
+#define DQ8_SEG_AVG(W, AHEAD, NEAR)                                                                                             \
+    hipLaunchKernelGGL((k_seg_avg<W, AHEAD, NEAR>), dim3(p.grid), dim3(kWave * (W)), p.lds, stream, tab, wp, K, local, n, bounds, \
                        (uint32_t)n_seg, units, p.n_waves, out)
-    if (near && one_unit && one_workgroup && K > 4)
+    if (a.near && a.ahead == 8)
         DQ8_SEG_AVG(kSegWaves, 8, true);
-    else if (near && one_unit && K > 2)
+    else if (a.near && a.ahead == 4)
         DQ8_SEG_AVG(kSegWaves, 4, true);
-    else if (near)  // two workgroups' tables fit
+    else if (a.near)
         DQ8_SEG_AVG(kSegWaves, 2, true);
-    else if (wpw == kSegWaves)
+    else if (a.waves == kSegWaves)
         DQ8_SEG_AVG(kSegWaves, 2, false);
     else
         DQ8_SEG_AVG(2 * kSegWaves, 2, false);

@@ -215,4 +215,24 @@ inline SegPlan make_segment_plan(int cus, size_t n, size_t n_seg, int waves_per_
     return p;
 }
 
+// Which form of the averaging kernel a call takes, and its launch: the plan is made for the form's wavefronts per workgroup, which
+// the kernel numbers its wavefronts by.  near: the scales are in LDS, only beside bounds of which two workgroups' fit (without a
+// worker there are no scales, however many segments).  ahead: workers requested at once, figures at the kernel.
+struct SegAverage {
+    SegPlan plan;
+    int waves, ahead;
+    bool near;
+};
+inline SegAverage make_segment_average(int cus, size_t n, size_t n_seg, int K, size_t units)
+{
+    SegAverage a;
+    a.waves = segment_waves(cus, n, n_seg);
+    a.plan = make_segment_plan(cus, n, n_seg, 2 * kSegWaves, false, a.waves);
+    a.near = a.waves == kSegWaves && scales_fit_near((size_t)K * n_seg);
+    if (a.near) a.plan.lds += (size_t)K * n_seg * sizeof(float);
+    const bool one_unit = units <= a.plan.n_waves, one_workgroup = a.plan.grid <= (unsigned)cus;
+    a.ahead = a.near && one_unit && one_workgroup && K > 4 ? 8 : (a.near && one_unit && K > 2 ? 4 : 2);
+    return a;
+}
+
 }  // namespace

@@ -176,6 +176,19 @@ static void check_plans()
             const size_t fit = kLdsPerCu / (kValueTableBytes + p.lds), busy = (p.grid + 255) / 256;
             CHECK(busy <= fit && p.n_waves == (size_t)p.grid * w, "%zu segments of %zu elements: %zu workgroups, %zu fit", n_seg, n, busy, fit);
         }
+    // the average: the plan is for the wavefronts of the form it names, and what is resident fits the LDS
+    for (size_t n : {(size_t)1, (size_t)5003, (size_t)1 << 21, ((size_t)1 << 21) + 1, ((size_t)1 << 22) + 3, (size_t)61100840})
+        for (size_t n_seg : {(size_t)1, (size_t)32, (size_t)33, (size_t)1024, (size_t)1025, (size_t)2047, (size_t)2048, (size_t)DQ8_MAX_SEGMENTS})
+            for (int K = 0; K <= DQ8_MAX_K; ++K)
+                for (bool aligned : {false, true}) {
+                    const size_t units = whole_units(n, kSegUnit, aligned);
+                    const SegAverage a = make_segment_average(256, n, n_seg, K, units);
+                    CHECK(a.waves == segment_waves(256, n, n_seg) && a.plan.n_waves == (size_t)a.plan.grid * a.waves, "average of %zu segments of %zu, K %d: %d wavefronts", n_seg, n, K, a.waves);
+                    CHECK(!a.near || (a.waves == kSegWaves && (size_t)K * n_seg <= kNearScales), "average of %zu segments of %zu, K %d: scales in LDS", n_seg, n, K);
+                    CHECK(a.plan.lds == (n_seg + 1) * 8 + (a.near ? (size_t)K * n_seg * 4 : 0), "average of %zu segments of %zu, K %d: LDS", n_seg, n, K);
+                    CHECK(a.ahead == 2 || (a.near && (a.ahead == 4 || a.ahead == 8) && units <= a.plan.n_waves), "average of %zu segments of %zu, K %d: ahead", n_seg, n, K);
+                    CHECK((a.plan.grid + 255) / 256 <= kLdsPerCu / (kValueTableBytes + a.plan.lds), "average of %zu segments of %zu, K %d: workgroups", n_seg, n, K);
+                }
     for (int K = 0; K <= DQ8_MAX_K; ++K) {
         const int c = chunk_size(K);
         CHECK(c >= 1 && c <= 8, "chunk of %d workers: %d", K, c);

@@ -222,6 +222,24 @@ def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
         go.check("segment average")
 
 
+# more than 2047 segments in more than a unit for eight wavefronts of every compute unit: workgroups of sixteen, with and without workers
+@pytest.mark.parametrize("n_seg,K", [(2047, 0), (2048, 0), (4095, 0), (2048, 1), (4095, 3)])
+@pytest.mark.parametrize("more", [0, 1, 5000])
+def test_averages_of_many_segments(dq8, n_seg, K, more):
+    """The local term alone and with workers: every element is written, whichever workgroups the launch takes."""
+    n = 256 * 8 * 1024 + more
+    rng = np.random.Generator(np.random.PCG64(9600 + n_seg + K + more))
+    bounds = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n_seg - 1)), [n]])
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
+    local = rng.standard_normal(n).astype(np.float32)
+    for off in (0, 1):
+        go = Guarded(n, np.float32)
+        dq8.decode_accumulate_avg_segments(more % 4, [dev(c) for c in cl], [dev(s) for s in sl], bounds_dev(bounds), out=go.t, local=dev(local, off))
+        same_bits(go.t, oracle.decode_accumulate_avg_segments(more % 4, cl, sl, bounds, local=local), "segment average")
+        go.check("segment average")
+
+
 def test_calls_marshalled_by_the_extension_and_by_python(dq8, monkeypatch):
     """Ordinary arguments go through the extension, any others are declined there before anything has happened; both ways give the
     same bytes, on a side stream too, and errors are those of dq8.py."""
