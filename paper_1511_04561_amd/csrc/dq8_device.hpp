@@ -377,22 +377,30 @@ __device__ __forceinline__ BucketWords<THREADS> request_bucket_table(const uint3
 
 // Writes the type's words, rounded up to whole quads, to lds (16-byte aligned) with all THREADS threads of the workgroup; the
 // caller synchronises the workgroup before the first lookup.
-template <uint32_t THREADS>
+// SETTLED: every thread waits for all its words, also those past the type's.  Otherwise, for the compiler, the words of a thread
+// that has nothing to write are still on their way when the loop over the units begins, and waits of that loop count
+// them: k_encode with a wavefront per unit then waits for the next unit's loads too early (61 M elements, given scales, blocks of 1000:
+// 57.7 us with the words copied one by one, 58.7 without SETTLED, 57.3 with; 1024: 54.2, 54.0, 53.2).  Not for the kernels in
+// which four wavefronts share a unit: those are faster without (k_encode, given scales, 3000: 61.9 against 65.3; k_encode_full
+// 49.1 against 50.6; k_encode_long, 8192: 53.0 against 54.5), k_encode_wave in blocks of 1000 too (56.9 against 57.2).
+template <uint32_t THREADS, bool SETTLED = false>
 __device__ __forceinline__ Search place_bucket_table(const uint32_t *tab, const BucketWords<THREADS> &b, uint32_t *lds)
 {
     const uint32_t nbk = tab[kNBucketOff], quads = (nbk + 3) / 4;
 #pragma unroll
     for (uint32_t i = 0; i < b.kRounds; ++i) {
         const uint32_t q = threadIdx.x + i * THREADS;
-        if (q < quads) reinterpret_cast<v4u *>(lds)[q] = b.w[i];
+        v4u w = b.w[i];
+        if (SETTLED) asm volatile("" : "+v"(w));
+        if (q < quads) reinterpret_cast<v4u *>(lds)[q] = w;
     }
     return make_search(lds, tab[kLoKeyOff], nbk, tab[kHasMarksOff] != 0);
 }
 
-template <uint32_t THREADS>
+template <uint32_t THREADS, bool SETTLED = false>
 __device__ __forceinline__ Search load_bucket_table(const uint32_t *tab, uint32_t *lds)
 {
-    return place_bucket_table<THREADS>(tab, request_bucket_table<THREADS>(tab), lds);
+    return place_bucket_table<THREADS, SETTLED>(tab, request_bucket_table<THREADS>(tab), lds);
 }
 
 // Decode table in LDS, one copy per lane: entry (code, lane) at byte address code * 256 +

@@ -484,7 +484,7 @@ __global__ __launch_bounds__(kWg) void k_encode(const uint32_t *__restrict__ tab
     size_t u = WPB == 1 ? first_unit() : (size_t)blockIdx.x;
     typename Enc::Slot a, b;
     if (u < n_units) e.fetch(u, a);  // the first loads are in flight while the table is copied
-    e.sr = load_bucket_table<kWg>(tab, lds + kTeamSlots);
+    e.sr = load_bucket_table<kWg, WPB == 1>(tab, lds + kTeamSlots);
     __syncthreads();
     if constexpr (EVERY) {
         walk_units(u, n_units, n_teams, a, b, [&](size_t v, typename Enc::Slot &sl) { e.fetch(v, sl); },

@@ -20,6 +20,7 @@ pytestmark = pytest.mark.skipif(not (os.path.exists(build.hipcc()) or shutil.whi
 KERNELS = """
 template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
 template __global__ void k_encode<1, 2, 1, false, true, true>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
+template __global__ void k_encode<1, 4, 1, false, true, false>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
 template __global__ void k_decode_flat<16, 8, 2, 4>(const uint32_t *, const uint8_t *, const float *, uint64_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t, uint64_t, uint32_t, float *);
 template __global__ void k_seg_encode<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
 template __global__ void k_seg_encode<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
@@ -83,6 +84,14 @@ def test_compression_requests_the_next_block_before_it_waits():
         if len(loads) == 2 and waits(b):  # in the loop, where a block's loads are followed by the wait for the one before
             slots.append(waits(b[:loads[-1]]))
     assert len(slots) == 2 and [] in slots, slots
+
+
+def test_compression_has_its_table_before_its_loop():
+    """k_encode with a wavefront per unit: no load of the search table is left, in any thread, when the workgroup meets in front of the
+    loop, whose waits would count it."""
+    meet = [b for b in kernel("k_encodeILi1ELi4ELi1ELb0ELb1ELb0E") if any(i.startswith("s_barrier") for i in b)]
+    assert len(meet) == 1
+    assert any(i.startswith("ds_write_b128") for i in meet[0]) and waits(meet[0])[-1] == 0, meet[0]
 
 
 def test_expansion_by_position_keeps_no_store_offsets():
