@@ -1,7 +1,8 @@
 """GPU: the library's calls recorded into a HIP graph and replayed.
 
-After dq8.init() no call allocates, frees, synchronises or clears memory with a memset node (the error statistics
-clear their sums with a small kernel), so a sequence of calls can be captured on a stream and replayed.  Every
+After dq8.init() no call whose outputs are handed in allocates while its stream is captured, and none synchronises or clears
+memory with a memset node (the error statistics clear their sums with a small kernel), so a sequence of calls can be captured on a
+stream and replayed.  Every
 replay, with new contents in the same input buffers and eager work and synchronisations between the replays, is
 compared with the oracle bit for bit.
 """
@@ -179,3 +180,75 @@ def test_segment_calls_recorded_in_a_graph(dq8):
         want_c, want_s = oracle.encode_segments(0, host, bounds)
         assert bits(scales) == want_s.tobytes() and bits(codes) == want_c.tobytes()
         assert bits(out) == oracle.decode_segments(0, want_c, want_s, bounds).tobytes()
+
+
+def test_long_arrays_recorded_in_a_graph(dq8):
+    """The calls that take scratch memory outside a graph (one scale for a long array, tensors back to back, statistics of one
+    block): a captured call allocates nothing, so that a replay writes to the call's own arrays only."""
+    n, kind = 300001, 0
+    bounds = np.array([0, 5, 5, 70000, 200003, n])
+    f32, u8 = (lambda m: torch.empty(m, device="cuda")), (lambda m: torch.empty(m, dtype=torch.uint8, device="cuda"))
+    x, bd = f32(n), torch.from_numpy(bounds).cuda()
+    c1, s1, c2, s2, s3 = u8(n), f32(1), u8(n), f32(5), f32(1)
+    stats, means = torch.empty((1, 4), dtype=torch.float64, device="cuda"), torch.empty(2, dtype=torch.float64, device="cuda")
+
+    def calls():
+        dq8.encode(kind, x, 0, scales=s1, codes=c1)
+        dq8.encode_segments(kind, x, bd, scales=s2, codes=c2)
+        dq8.error_stats(kind, x, 0, scales=s3, stats=stats, means=means)
+
+    side = torch.cuda.Stream()
+    x.zero_()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        calls()
+        made = torch.cuda.memory_stats()["allocation.all.allocated"] - before
+    assert made == 0
+    for rep in range(1, 4):
+        host = workloads.tensor(5, 4, worker=rep, limit=n)
+        x.copy_(torch.from_numpy(host))
+        for t in (s1, s2, s3, stats, means):
+            t.fill_(7.0)
+        c1.fill_(0xEE)
+        c2.fill_(0xEE)
+        other = [torch.full((1 << k,), 3.0, device="cuda") for k in range(4, 16)]  # eager work between the replays
+        with torch.cuda.stream(side):
+            other += [torch.full((1 << k,), 3.0, device="cuda") for k in range(4, 16)]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want_c, want_s = oracle.encode(kind, host, 0)
+        assert bits(c1) == want_c.tobytes() and bits(s1) == want_s.tobytes() == bits(s3)
+        want_c, want_s = oracle.encode_segments(kind, host, bounds)
+        assert bits(c2) == want_c.tobytes() and bits(s2) == want_s.tobytes()
+        want_stats, want_means = oracle.error_stats(kind, host, 0)
+        assert np.array_equal(stats.cpu().numpy()[:, 2:], want_stats[:, 2:])
+        assert np.allclose(stats.cpu().numpy(), want_stats, rtol=1e-12, atol=0) and np.allclose(means.cpu().numpy(), want_means, rtol=1e-12, atol=0)
+        assert all(bool((t == 3.0).all()) for t in other)
+
+
+def test_scratch_memory_on_two_streams(dq8):
+    """Long compressions on two streams at once: each call's scratch memory is its own stream's, handed on from call to call."""
+    n, kind = 500001, 1
+    bounds = np.array([0, 1000, 400000, n])
+    bd = torch.from_numpy(bounds).cuda()
+    host = [workloads.tensor(5, 4, worker=k, limit=n) * np.float32(4.0 ** k) for k in range(6)]
+    xs = [torch.from_numpy(h).cuda() for h in host]
+    outs = [(torch.empty(n, dtype=torch.uint8, device="cuda"), torch.empty(3, device="cuda")) for _ in range(12)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i, x in enumerate(xs):
+        with torch.cuda.stream(streams[i % 2]):
+            dq8.encode(kind, x, 0, scales=outs[i][1], codes=outs[i][0])
+            dq8.encode_segments(kind, x, bd, scales=outs[6 + i][1], codes=outs[6 + i][0])
+    torch.cuda.synchronize()
+    for i, h in enumerate(host):
+        want_c, want_s = oracle.encode(kind, h, 0)
+        assert bits(outs[i][0]) == want_c.tobytes() and bits(outs[i][1][:1]) == want_s.tobytes()
+        want_c, want_s = oracle.encode_segments(kind, h, bounds)
+        assert bits(outs[6 + i][0]) == want_c.tobytes() and bits(outs[6 + i][1]) == want_s.tobytes()
