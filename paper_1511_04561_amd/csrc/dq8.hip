@@ -884,7 +884,7 @@ int launch_avg_team(const DeviceState &st, int kind, const WorkerPtrs &wp, int K
 {
     const size_t Bq = block_length(n, block);
     if (Bq <= 3 * 1024 && short_team_k(K, Bq)) return launch_avg_short_team(st, kind, wp, K, local, n, block, scales_out, codes_out, stream);
-    const bool ragged = Bq != (size_t)kUnit;  // shorter blocks: the variant whose register path takes short units
+    const bool ragged = Bq != (size_t)kUnit;  // shorter blocks: no steady iterations, three teams
     const bool tuned_k = K == 2 || K == 4 || K == 8;  // the worker counts with a variant for 2 teams
     // Teams per workgroup: 3; 4 when each team has few code words in flight (up to `avg_teams4_upto` workers);
     // avg_teams overrides this where the variant exists.
@@ -905,19 +905,17 @@ int launch_avg_team(const DeviceState &st, int kind, const WorkerPtrs &wp, int K
     }
     const uint32_t *tab = st.tables + (size_t)kind * kTableWords;
     const size_t lds = ((size_t)st.search_words[kind] + 2 * teams * kWavesPerWg) * sizeof(uint32_t);
-#define DQ8_TEAM_M(KT, RM, T, RG, MU)                                                                                     \
-    hipLaunchKernelGGL((k_avg_team<KT, 1, true, T, RM, RG, MU>), dim3(p.grid), dim3(kWg * T), lds, stream, tab, wp, K, local, \
+#define DQ8_TEAM_M(KT, RM, T, MU)                                                                                     \
+    hipLaunchKernelGGL((k_avg_team<KT, 1, true, T, RM, MU>), dim3(p.grid), dim3(kWg * T), lds, stream, tab, wp, K, local, \
                        n, p.B, p.nb, p.n_units, p.n_teams, iters, steady, scales_out, codes_out)
-#define DQ8_TEAM(KT, RM, T, RG) DQ8_TEAM_M(KT, RM, T, RG, false)
-#define DQ8_TEAM_T(KT, RM)              \
-    if (ragged) {                       \
-        DQ8_TEAM(KT, RM, 3, true);      \
-    } else if (teams == 3) {            \
-        DQ8_TEAM(KT, RM, 3, false);     \
-    } else if (teams == 4) {            \
-        DQ8_TEAM(KT, RM, 4, false);     \
-    } else {                            \
-        DQ8_TEAM(KT, RM, 2, false);     \
+#define DQ8_TEAM(KT, RM, T) DQ8_TEAM_M(KT, RM, T, false)
+#define DQ8_TEAM_T(KT, RM)       \
+    if (teams == 3) {            \
+        DQ8_TEAM(KT, RM, 3);     \
+    } else if (teams == 4) {     \
+        DQ8_TEAM(KT, RM, 4);     \
+    } else {                     \
+        DQ8_TEAM(KT, RM, 2);     \
     }
 #define DQ8_TEAM_RM(KT)          \
     if (st.has_remap[kind]) {    \
@@ -926,31 +924,23 @@ int launch_avg_team(const DeviceState &st, int kind, const WorkerPtrs &wp, int K
         DQ8_TEAM_T(KT, false)    \
     }
     // K = 1, 3, 5, 6: three or four teams per workgroup; K = 7: three
-#define DQ8_TEAM_34(KT, RM)                  \
-    if (ragged) {                            \
-        DQ8_TEAM(KT, RM, 3, true);           \
-    } else if (teams == 4) {                 \
-        DQ8_TEAM(KT, RM, 4, false);          \
-    } else {                                 \
-        DQ8_TEAM(KT, RM, 3, false);          \
+#define DQ8_TEAM_34(KT, RM)      \
+    if (teams == 4) {            \
+        DQ8_TEAM(KT, RM, 4);     \
+    } else {                     \
+        DQ8_TEAM(KT, RM, 3);     \
     }
-#define DQ8_TEAM_3(KT)                       \
-    if (st.has_remap[kind]) {                \
-        DQ8_TEAM_34(KT, true)                \
-    } else {                                 \
-        DQ8_TEAM_34(KT, false)               \
+#define DQ8_TEAM_3(KT)           \
+    if (st.has_remap[kind]) {    \
+        DQ8_TEAM_34(KT, true)    \
+    } else {                     \
+        DQ8_TEAM_34(KT, false)   \
     }
-#define DQ8_TEAM_7(KT)                       \
-    if (st.has_remap[kind]) {                \
-        if (ragged) {                        \
-            DQ8_TEAM(KT, true, 3, true);     \
-        } else {                             \
-            DQ8_TEAM(KT, true, 3, false);    \
-        }                                    \
-    } else if (ragged) {                     \
-        DQ8_TEAM(KT, false, 3, true);        \
-    } else {                                 \
-        DQ8_TEAM(KT, false, 3, false);       \
+#define DQ8_TEAM_7(KT)           \
+    if (st.has_remap[kind]) {    \
+        DQ8_TEAM(KT, true, 3);   \
+    } else {                     \
+        DQ8_TEAM(KT, false, 3);  \
     }
     if (K > 8) {
         // more than 8 workers (whole 4096-blocks only): 5 to 8 at a time over the same registers, the count with the
@@ -965,9 +955,9 @@ int launch_avg_team(const DeviceState &st, int kind, const WorkerPtrs &wp, int K
         }
 #define DQ8_TEAM_MULTI(KT)                           \
     if (st.has_remap[kind]) {                        \
-        DQ8_TEAM_M(KT, true, 3, false, true);        \
+        DQ8_TEAM_M(KT, true, 3, true);               \
     } else {                                         \
-        DQ8_TEAM_M(KT, false, 3, false, true);       \
+        DQ8_TEAM_M(KT, false, 3, true);              \
     }
         switch (ch) {
         case 5: DQ8_TEAM_MULTI(5) break;

@@ -50,20 +50,14 @@ int launch_avg_short_team_tu(int cus, const uint32_t *tab, uint32_t search_words
         if (all_valid >= 2) steady = (uint32_t)((all_valid - 1) & ~(size_t)1);
     }
     const size_t lds = ((size_t)search_words + 2 * teams * kWavesPerWg) * sizeof(uint32_t);
-#define DQ8_SHORT(KT, RM, RG, WW)                                                                                          \
-    hipLaunchKernelGGL((k_avg_team<KT, 1, true, 12 / WW, RM, RG, false, WW>), dim3(p.grid), dim3(kWave * 12), lds, stream, tab, \
+#define DQ8_SHORT(KT, RM, WW)                                                                                          \
+    hipLaunchKernelGGL((k_avg_team<KT, 1, true, 12 / WW, RM, false, WW>), dim3(p.grid), dim3(kWave * 12), lds, stream, tab, \
                        wp, K, local, n, p.B, p.nb, p.n_units, p.n_teams, iters, steady, scales_out, codes_out)
-#define DQ8_SHORT_RG(KT, RM, WW)       \
-    if (ragged) {                      \
-        DQ8_SHORT(KT, RM, true, WW);   \
-    } else {                           \
-        DQ8_SHORT(KT, RM, false, WW);  \
-    }
-#define DQ8_SHORT_W(KT, RM)                      \
-    switch (W) {                                 \
-    case 1: DQ8_SHORT_RG(KT, RM, 1) break;       \
-    case 2: DQ8_SHORT_RG(KT, RM, 2) break;       \
-    default: DQ8_SHORT_RG(KT, RM, 3) break;      \
+#define DQ8_SHORT_W(KT, RM)                   \
+    switch (W) {                              \
+    case 1: DQ8_SHORT(KT, RM, 1); break;      \
+    case 2: DQ8_SHORT(KT, RM, 2); break;      \
+    default: DQ8_SHORT(KT, RM, 3); break;     \
     }
 #define DQ8_SHORT_K(KT)              \
     if (has_remap) {        \
@@ -83,7 +77,6 @@ int launch_avg_short_team_tu(int cus, const uint32_t *tab, uint32_t search_words
     }
 #undef DQ8_SHORT_K
 #undef DQ8_SHORT_W
-#undef DQ8_SHORT_RG
 #undef DQ8_SHORT
     return after_launch_of("k_avg_team", stream);
 }

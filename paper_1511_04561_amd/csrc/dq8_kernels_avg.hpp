@@ -7,7 +7,7 @@ namespace {
 // Mean of the `len` elements from `start` on by one wavefront: every lane a quad at a time, all KT workers' words at once.  A last
 // quad under four elements takes the ones before it once more (see quad_start; len >= 4 where it is not whole quads).
 // block_of(i): the block that element start + i is in (the same for a quad's four).
-template <int KT, int NT, bool LOCAL, typename Mean, typename Block>
+template <int KT, bool LOCAL, typename Mean, typename Block>
 __device__ __forceinline__ void average_quads(const WorkerPtrs &p, const float *lut, const float *__restrict__ local, size_t start,
                                               uint32_t len, uint32_t lane, Mean mean_of, Block block_of, float *__restrict__ out)
 {
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_full(const uint32_t 
         // Quad by quad, all workers' words at once: one by one the elements are eight round trips for every worker (1 Mi + 511
         // elements, eight workers: 6.1 us, 5.7 so).
         const uint32_t done = tail_len >= 4 ? tail_len : 0;
-        average_quads<KT, NT, LOCAL>(p, lut, local, start, done, lane, mean_of, [&](uint32_t) { return blk; }, out);
+        average_quads<KT, LOCAL>(p, lut, local, start, done, lane, mean_of, [&](uint32_t) { return blk; }, out);
         for (uint32_t i = done + lane; i < tail_len; i += kWave) {
             float acc = 0.0f;
             if (LOCAL) acc = acc + local[start + i];
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_flat(const uint32_t 
         const size_t start = (size_t)n_full * U;
         const size_t B = (size_t)g.bq * 4;
         const uint32_t done = tail_len & ~3u;  // see k_decode_avg_full; whole quads: blocks are, and one may end in here
-        average_quads<KT, NT, LOCAL>(p, lut, local, start, done, lane, mean_of, [&](uint32_t i) { return (start + i) / B; }, out);
+        average_quads<KT, LOCAL>(p, lut, local, start, done, lane, mean_of, [&](uint32_t i) { return (start + i) / B; }, out);
         for (uint32_t i = done + lane; i < tail_len; i += kWave) {
             const size_t blk = (start + i) / B;
             float acc = 0.0f;

@@ -449,11 +449,10 @@ __global__ __launch_bounds__(kLongTeam, 4) void k_avg_long(const uint32_t *__res
 // TEAMS teams share a workgroup and its tables; the workgroup barrier that separates the
 // exchange of the maxima from their use is executed by every wavefront the same number of
 // times (`iters`), whether or not its team still has a unit.
-// RAGGED = true (chosen by the host): blocks shorter than the unit.
 // MULTI = true: more workers than KT, taken KT at a time in `passes` passes over the same registers; a
 // place of the last pass that has no worker repeats worker K - 1 with scale 0 (the product is a zero, and
 // adding a zero leaves a sum that started at +0 unchanged).  K is then a run-time value.
-template <int KT, int NT, bool FASTDIV, int TEAMS, bool RAGGED, bool MULTI, int W>
+template <int KT, int NT, bool FASTDIV, int TEAMS, bool MULTI, int W>
 struct AvgTeam {
     static_assert(W >= 1 && W <= kWavesPerWg, "a team is one to four wavefronts");
     static constexpr int Q = 4;               // quads per lane
@@ -511,13 +510,8 @@ struct AvgTeam {
         sl.fast = sl.un.len >= 4 && ((uintptr_t)local & 3) == 0;
     }
 
-    // First element of this lane's j-th quad of the unit; WHOLE promises a whole unit.
-    template <bool WHOLE>
-    __device__ __forceinline__ uint32_t quad_of(const Slot &sl, int j) const
-    {
-        const uint32_t i = j * kTeam + tl;
-        return WHOLE ? 4 * i : quad_start(i, sl.un.len);
-    }
+    // First element of this lane's j-th quad of the unit.
+    __device__ __forceinline__ uint32_t quad_of(const Slot &sl, int j) const { return quad_start(j * kTeam + tl, sl.un.len); }
 
     // Code words of `worker` for unit sl into place k.
     template <bool WHOLE>
@@ -529,7 +523,7 @@ struct AvgTeam {
             if (WHOLE)
                 w[k][j] = ldg_at<NT>(reinterpret_cast<const uint32_t *>(pc), j * kTeam + tl);
             else
-                w[k][j] = ldg_codes<NT>(pc, quad_of<false>(sl, j));
+                w[k][j] = ldg_codes<NT>(pc, quad_of(sl, j));
         }
     }
 
@@ -563,7 +557,7 @@ struct AvgTeam {
                     if (STEADY)
                         l = ldg<NT>(reinterpret_cast<const v4f *>(pl) + j * kTeam + tl);
                     else
-                        l = ldg_floats<NT>(pl, quad_of<false>(sl, j));
+                        l = ldg_floats<NT>(pl, quad_of(sl, j));
                     acc[j].x = 0.0f + l.x;
                     acc[j].y = 0.0f + l.y;
                     acc[j].z = 0.0f + l.z;
@@ -677,7 +671,7 @@ struct AvgTeam {
     }
 };
 
-template <int KT, int NT, bool FASTDIV, int TEAMS, bool REMAP, bool RAGGED, bool MULTI, int W = kWavesPerWg>
+template <int KT, int NT, bool FASTDIV, int TEAMS, bool REMAP, bool MULTI, int W = kWavesPerWg>
 __global__ __launch_bounds__(kWave * W * TEAMS, W * TEAMS == 12 ? 3 : 4) void k_avg_team(const uint32_t *__restrict__ tab, WorkerPtrs p,
                                                             int K_rt, const float *__restrict__ local, size_t n, size_t B,
                                                             size_t nb,
@@ -688,7 +682,7 @@ __global__ __launch_bounds__(kWave * W * TEAMS, W * TEAMS == 12 ? 3 : 4) void k_
     extern __shared__ uint32_t dyn_lds[];  // 2 phases x TEAMS x 4 maxima, then the bucket table
     constexpr int kSlots = 2 * TEAMS * kWavesPerWg;
     static_assert(W * TEAMS % 4 == 0, "whole wavefronts per SIMD");
-    using Avg = AvgTeam<KT, NT, FASTDIV, TEAMS, RAGGED, MULTI, W>;
+    using Avg = AvgTeam<KT, NT, FASTDIV, TEAMS, MULTI, W>;
     Avg e(p);
     e.local = local;
     e.scales_out = scales_out;
