@@ -24,6 +24,13 @@ template __global__ void k_encode<1, 4, 1, false, true, false>(const uint32_t *,
 template __global__ void k_decode_flat<16, 8, 2, 4>(const uint32_t *, const uint8_t *, const float *, uint64_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t, uint64_t, uint32_t, float *);
 template __global__ void k_seg_encode<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
 template __global__ void k_seg_encode<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
+template __global__ void k_seg_encode_copied<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
+template __global__ void k_seg_encode_copied<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
+template __global__ void k_seg_encode_parts<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint32_t, float *, uint8_t *);
+template __global__ void k_seg_encode_parts<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint32_t, float *, uint8_t *);
+template __global__ void k_error_stats_one<12, true>(const uint32_t *, const float *, size_t, size_t, size_t, float *, const float *, uint32_t, double *);
+template __global__ void k_avg_team<8, 1, true, 3, false, false, 4>(const uint32_t *, WorkerPtrs, int, const float *, size_t, size_t, size_t, size_t, size_t, uint32_t, uint32_t, float *, uint8_t *);
+void *long_expansion = (void *)k_seg_decode_long;
 """
 
 
@@ -33,7 +40,7 @@ def assembly():
     with tempfile.TemporaryDirectory() as d:
         src, out = os.path.join(d, "kernels.hip"), os.path.join(d, "kernels.s")
         with open(src, "w") as f:
-            f.write('#include <hip/hip_runtime.h>\n#include "dq8_device.hpp"\n#include "dq8_kernels_codec.hpp"\n#include "dq8_kernels_segments.hpp"\nnamespace {\n%s}\n' % KERNELS)
+            f.write('#include <hip/hip_runtime.h>\n#include "dq8_device.hpp"\n#include "dq8_kernels_codec.hpp"\n#include "dq8_kernels_segments.hpp"\n#include "dq8_kernels_stats.hpp"\n#include "dq8_kernels_avg_encode.hpp"\nnamespace {\n%s}\n' % KERNELS)
         flags = [f for f in build.FLAGS if f != "-shared"]
         subprocess.check_call([build.hipcc()] + flags + ["-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "-S",
                                                         "--cuda-device-only", "-o", out, src])
@@ -100,8 +107,40 @@ def test_expansion_by_position_keeps_no_store_offsets():
 
 
 @pytest.mark.parametrize("marks,waves", [(0, 8), (1, 16)])
-def test_segment_compression_leaves_room_for_wavefronts(marks, waves):
-    """k_seg_encode: seven wavefronts of it fit the registers of a SIMD, and its code is not several times its loop."""
-    name = "k_seg_encodeILb%dELi%dE" % (marks, waves)
+@pytest.mark.parametrize("scales", ["", "_copied", "_parts"])
+def test_segment_compression_leaves_room_for_wavefronts(scales, marks, waves):
+    """k_seg_encode, wherever it finds the scales (copied and from parts: up to 1024 segments): seven wavefronts of it fit the
+    registers of a SIMD, and its code is not several times its loop."""
+    name = "k_seg_encode%sILb%dELi%dE" % (scales, marks, waves)
     assert kernel(name, 1) <= 72
     assert sum(len(b) for b in kernel(name)) < 3000
+
+
+def loads_of(block, words):
+    return sum(i.startswith("global_load_dword%s " % words) for i in block)
+
+
+def test_statistics_of_one_block_keep_half_a_unit_in_flight():
+    """k_error_stats_one: six wavefronts per SIMD, and in its loop a wait for two quads leaves the unit's two others on their way."""
+    assert kernel("k_error_stats_oneILi12ELb1E", 1) <= 80
+    blocks = kernel("k_error_stats_oneILi12ELb1E")
+    last = max(i for i, b in enumerate(blocks) if loads_of(b, "x4") == 2)  # where a half is requested again at the loop's end
+    first = min(i for i, b in enumerate(blocks) if waits(b) and loads_of(b, "x4") == 2)  # the other half, in its middle
+    assert first < last and loads_of(blocks[first], "x4") == 2
+    assert [w for b in blocks[first:last] for w in waits(b)] and min(w for b in blocks[first:last] for w in waits(b)) >= 2
+
+
+def test_long_sets_are_expanded_a_unit_ahead():
+    """k_seg_decode_long: the sixteen words of the next unit are requested together, and sixteen stores follow without a wait."""
+    blocks = kernel("k_seg_decode_longE")
+    assert sum(loads_of(b, "") == 16 and not waits(b) for b in blocks) >= 3  # before the loop, and for either kind of unit
+    assert sum(sum(i.startswith("global_store_dwordx4") for i in b) == 16 and not waits(b) for b in blocks) == 1
+
+
+def test_averages_compressed_again_request_all_workers_ahead():
+    """k_avg_team, eight workers of four words each: in the loop over whole units all are requested again before the first of those that
+    are waited for, at any other unit (short ones, any alignment) together."""
+    blocks = kernel("k_avg_teamILi8ELi1ELb1ELi3ELb0ELb0ELi4E")
+    steady = [b for b in blocks if loads_of(b, "") >= 32 and waits(b)]
+    assert len(steady) == 2 and all(max(waits(b)) >= 36 for b in steady), [waits(b) for b in steady]
+    assert sum(loads_of(b, "") == 32 and not waits(b) for b in blocks) >= 3  # before the loops, and the two halves of the general one

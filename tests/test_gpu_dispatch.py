@@ -293,8 +293,13 @@ def test_calls_marshalled_by_the_extension_and_by_python(dq8, monkeypatch):
         dq8.decode(2, codes[0], scales[0], 1024, out=new(n - 1))
     with pytest.raises(dq8.Dq8Error, match="dq8_encode failed .status 2.: unknown data type 9"):
         dq8.encode(9, x)
-    with pytest.raises(Exception):  # a transformed tensor has no address; the same with and without the extension
-        torch.vmap(lambda v: dq8.absmax(v, 0))(x[:64].view(8, 8))
+    def transformed(v):  # has no address: declined by the extension, refused by dq8.py
+        assert native.absmax(v, 0, None) is None
+        return dq8.absmax(v, 0)
+    for way in (native, dq8._Unbound()):
+        monkeypatch.setattr(dq8, "_native", way)
+        with pytest.raises(RuntimeError, match="Cannot access data pointer of Tensor"):
+            torch.vmap(transformed)(x[:64].view(8, 8))
 
 
 @pytest.mark.parametrize("n,n_seg", [(98305, 1), (98305, 4), (98305, 63), (98305, 65), (8192 * 63 + 1, 33), (256 * 8192, 64), (256 * 8192 + 3, 1),
@@ -342,6 +347,15 @@ def test_scratch_memory_of_the_c_calls(dq8):
         assert calls(w, need) == (3, 3)
     assert L.dq8_encode_segments_ws(0, vp(x.data_ptr()), sz(n), vp(bounds.data_ptr()), sz(1), vp(scale.data_ptr()), vp(codes.data_ptr()), 0,
                                     vp(bounds.data_ptr()), sz(need), vp(stream)) == 3
+    L.dq8_workspace_bytes_stats.restype = sz
+    need, work = L.dq8_workspace_bytes_stats(sz(n), sz(0), 0), torch.empty(1 << 15, dtype=torch.uint8, device="cuda")
+    stats, means = torch.empty(4, dtype=torch.float64, device="cuda"), torch.empty(2, dtype=torch.float64, device="cuda")
+    want = oracle.error_stats(0, x.cpu().numpy(), 0)[0]
+    for w, size, rc in ((work.data_ptr(), need, 0), (work.data_ptr() + 8, need, 0), (work.data_ptr() + 4, need - 1, 0), (None, need, 0), (work.data_ptr() + 4, need, 3),
+                        (stats.data_ptr(), need, 3), (means.data_ptr(), need, 3), (x.data_ptr() + 8, need, 3)):
+        stats.fill_(-1.0)
+        assert L.dq8_error_stats_ws(0, vp(x.data_ptr()), sz(n), sz(0), vp(scale.data_ptr()), 0, vp(stats.data_ptr()), vp(means.data_ptr()), vp(w), sz(size), vp(stream)) == rc
+        assert np.allclose(stats.cpu().numpy(), want if rc == 0 else -1.0, rtol=1e-12, atol=0)
 
 
 # whole units only, elements past them for one wavefront and for several; four wavefronts per workgroup up to four units per compute
@@ -390,8 +404,31 @@ def test_long_sets_of_tensors(dq8, n, n_seg):
     check_segments(dq8, n % 4, x, np.concatenate([[0], inner, [n]]), x_off=n % 3, c_off=n % 4, tag="long")
 
 
+# more workers than the team kernels take in these blocks: every mean of a last block that is no whole unit, or of codes at an odd address,
+# is formed for the maximum and once more for the compression
+@pytest.mark.parametrize("block,K", [(256, 9), (512, 16), (1000, 9), (1024, 16), (2048, 9), (2048, 16), (3000, 16), (4000, 11)])
+@pytest.mark.parametrize("rest,odd", [(0, 1), (1, 0), (5, 1), (-4, 0), (-1, 1)])
+def test_many_workers_in_blocks_of_any_length(dq8, block, K, rest, odd):
+    """k_avg_block: whole and short units, aligned codes and codes at odd addresses, with and without a local term."""
+    n = block * 5 + rest % block
+    rng = np.random.Generator(np.random.PCG64(9980 + n % 97 + K))
+    kind, nb = (n + K) % 4, -(-n // block)
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-4, 4, nb)).astype(np.float32) for _ in range(K)]
+    x = rng.standard_normal(n).astype(np.float32) if rest % 2 == 0 else None
+    codes, scales = [dev(c, odd * (k % 4)) for k, c in enumerate(cl)], [dev(v) for v in sl]
+    want = oracle.decode_accumulate_avg(kind, cl, sl, block, local=x)
+    wc, ws = oracle.encode(kind, want, block)
+    gc, gs = Guarded(n, np.uint8, odd), Guarded(nb, np.float32)
+    dq8.decode_avg_encode(kind, codes, scales, block, local=None if x is None else dev(x, odd), scales=gs.t, codes=gc.t)
+    same_bits(gc.t, wc, "codes of the average")
+    same_bits(gs.t, ws, "scales of the average")
+    gc.check("codes of the average")
+    gs.check("scales of the average")
+
+
 # a last block of 1, 3, 4, 5 elements, one short of whole quads and one short of whole; teams of one to four wavefronts and a workgroup
-# per block; all workers unrolled, in passes, in chunks
+# per block; all workers unrolled, in passes and in chunks (blocks of 4096 and more; other blocks with more than eight workers: above)
 @pytest.mark.parametrize("block,K", [(512, 2), (1000, 4), (1024, 1), (2048, 8), (3000, 5), (3500, 3), (4096, 6), (4096, 7), (4096, 9), (4096, 16), (5000, 2), (8192, 8),
                                      (12288, 11), (16384, 7)])
 @pytest.mark.parametrize("rest", [1, 3, 4, 5, 257, -2])

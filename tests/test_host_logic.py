@@ -34,6 +34,33 @@ def test_every_declared_symbol_is_exported(L):
         assert hasattr(L, n), n
 
 
+def test_every_call_with_scratch_memory_is_exported(L):
+    header = open(os.path.join(ROOT, "include", "dq8_workspace.h")).read()
+    header = re.sub(r"/\*.*?\*/", "", header, flags=re.S)
+    names = sorted(set(re.findall(r"\b(dq8_[a-z0-9_]+)\s*\(", header)))
+    assert names == ["dq8_encode_segments_ws", "dq8_encode_ws", "dq8_error_stats_ws", "dq8_workspace_bytes",
+                     "dq8_workspace_bytes_segments", "dq8_workspace_bytes_stats"]
+    for n in names:
+        assert hasattr(L, n), n
+
+
+def test_scratch_memory_errors_need_no_device(L):
+    """The calls with scratch memory refuse what their namesakes refuse, before they look at the scratch memory, and need none for 0 elements."""
+    buf, other = np.zeros(64, np.float32), np.zeros(64, np.uint64)
+    p, q = (a.ctypes.data_as(ctypes.c_void_p) for a in (buf, other))
+    n, z, one, many = (ctypes.c_size_t(v) for v in (16, 0, 1, 4096))
+    assert L.dq8_encode_ws(9, p, n, z, p, p, 0, q, one, None) == 2
+    assert L.dq8_encode_ws(0, p, n, z, p, p, 4, q, one, None) == 3
+    assert L.dq8_encode_ws(0, None, n, z, p, p, 0, q, one, None) == 1
+    assert L.dq8_encode_ws(0, None, z, z, None, None, 0, None, z, None) == 0
+    assert L.dq8_encode_segments_ws(0, p, n, q, many, p, p, 0, q, one, None) == 3
+    assert L.dq8_encode_segments_ws(0, p, n, None, one, p, p, 0, q, one, None) == 1
+    assert L.dq8_encode_segments_ws(0, None, z, None, z, None, None, 0, None, z, None) == 0
+    assert L.dq8_error_stats_ws(9, p, n, z, p, 0, p, None, q, one, None) == 2
+    assert L.dq8_error_stats_ws(0, p, n, z, p, 0, p, None, q, one, None) == 3  # x, scales and stats are one buffer
+    assert L.dq8_error_stats_ws(0, None, z, z, None, 0, None, None, None, z, None) == 0
+
+
 @pytest.mark.parametrize("kind", KINDS)
 def test_codebook_is_bit_identical_to_the_oracle(L, kind):
     cb = np.empty(256, np.float32)
