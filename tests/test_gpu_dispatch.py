@@ -233,10 +233,11 @@ def test_averages_of_many_segments(dq8, n_seg, K, more):
     cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
     sl = [np.exp(rng.uniform(-8, 8, n_seg)).astype(np.float32) for _ in range(K)]
     local = rng.standard_normal(n).astype(np.float32)
+    want = oracle.decode_accumulate_avg_segments(more % 4, cl, sl, bounds, local=local)
     for off in (0, 1):
         go = Guarded(n, np.float32)
         dq8.decode_accumulate_avg_segments(more % 4, [dev(c) for c in cl], [dev(s) for s in sl], bounds_dev(bounds), out=go.t, local=dev(local, off))
-        same_bits(go.t, oracle.decode_accumulate_avg_segments(more % 4, cl, sl, bounds, local=local), "segment average")
+        same_bits(go.t, want, "segment average")
         go.check("segment average")
 
 
