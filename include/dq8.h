@@ -27,10 +27,14 @@
  *       dq8_absmax, dq8_encode, dq8_decode and the calls for segments: `x`, `out` and `local` at a multiple
  *         of 4 bytes (any float array); `codes` may start at any byte.  Units of fewer than four
  *         elements go one by one, and dq8_decode is faster where block % 4 == 0 or there is one block.
- *       dq8_decode_avg_encode: the same, fastest with 16-byte aligned `local` and 4-byte aligned codes.
- *       dq8_decode_accumulate_avg[_local], dq8_error_stats (without scratch memory), and every call with
- *         blocks of 4 to 128 elements that are powers of two (up to 512 for dq8_encode): also 16-byte
- *         aligned `x` / `out` / `local`, 4-byte aligned `codes`, and block % 4 == 0 (or a single block).
+ *       dq8_decode_avg_encode with up to 8 workers in blocks of more than 512 elements (a single worker: 2048),
+ *         and with any number in blocks of 4096 and more: the same, fastest with 16-byte aligned `local` and
+ *         4-byte aligned codes.
+ *       dq8_decode_avg_encode otherwise (more workers in shorter blocks, blocks of up to 512 elements, an array of up
+ *         to 2048 elements that is one block), dq8_decode_accumulate_avg[_local], dq8_error_stats (without
+ *         scratch memory, or several blocks), and every call with blocks of 4 to 128 elements that are powers
+ *         of two (up to 512 for dq8_encode): also 16-byte aligned `x` / `out` / `local`, 4-byte aligned `codes`,
+ *         and block % 4 == 0 (or a single block).
  *     Blocks of 4096 elements are the fastest; other lengths come close (the units of work follow the block
  *     or, where a block need not be held, the position in the array; powers of two from 4 to
  *     128 elements have kernels that pack many blocks into a wavefront); other lengths below

@@ -18,7 +18,8 @@ extern "C" {
  * dq8_workspace_bytes: what dq8_encode_ws can use for these arguments, 0 when it needs none (host arithmetic).
  * dq8_encode_ws: dq8_encode with `workspace_bytes` bytes of device memory at `workspace`, 4-byte aligned, whose contents are of
  * no meaning before and after; it must not overlap the other arrays, and calls that may run at the same time must not share
- * it.  NULL or too few bytes: as dq8_encode.
+ * it.  Where the call is captured into a graph, the memory is the graph's for as long as that may be replayed.  NULL or too few
+ * bytes: as dq8_encode.
  */
 size_t dq8_workspace_bytes(size_t n, size_t block, unsigned flags);
 int dq8_encode_ws(int kind, const float *x, size_t n, size_t block, float *scales, uint8_t *codes,

@@ -804,8 +804,11 @@ int launch_decode(const DeviceState &st, int kind, const uint8_t *codes, const f
         return after_launch("k_decode_flat", stream);
     }
     // Short arrays: with no more units of 4096 elements than compute units most of the chip has no work; units of 1024 then, four
-    // wavefronts per workgroup so that the workgroups spread over the compute units (100 000 elements: 5.1 -> 3.8 us a call in
-    // a graph, 300 000: 4.6 -> 4.0, 1 Mi: 4.6 -> 4.1; longer arrays are slower that way, 2 Mi: 5.5 -> 6.5, 4 Mi: 6.9 -> 8.2).
+    // wavefronts per workgroup so that the workgroups spread over the compute units (a call in a graph, units of 4096 / 1024, 8
+    // wavefronts per compute unit: 131 072 elements 3.4 / 2.7 us, 300 000 3.7 / 2.9, 1 Mi 3.8 / 3.0).  The line dates from when every
+    // workgroup's value table cost 1.3 us more (2 Mi: 5.5 / 6.5); as the table is now, units of 1024 stay ahead up to a unit for
+    // each of those wavefronts (1.5 Mi 3.9 / 3.25, 2 Mi 3.9 / 3.5) and fall behind above (3 Mi 4.3 / 4.2, with the codes from
+    // memory 4.7 / 5.8; 4 Mi 4.8 / 4.7 and 5.4 / 6.2; 8 Mi 7.6 / 8.1 and 8.4 / 9.5).
     if (q == 16 && !ragged && p.n_units <= (size_t)st.cus) {
         const Plan sp = make_plan(n, block, st.cus, 8, 1, 4, (size_t)1024);
         hipLaunchKernelGGL((k_decode<4, 2, 4, false>), dim3(sp.grid), dim3(kWave * 4), 0, stream, tab, codes, scales, n, sp.B, sp.nb,

@@ -23,6 +23,9 @@ namespace {
 // quads stays on the register path; a lane whose quad lies past the end loads the unit's last quad
 // instead (unconditional loads of valid memory; the maximum does not change) and stores nothing.
 // This costs a register per quad for the clamped offsets, which the kernel for whole units cannot spare.
+// Any other unit (a short one where blocks are whole units, any at addresses or of lengths that are no whole quads) goes element by
+// element and forms its means twice, all by one wavefront: 16 workers, 1 Mi elements in blocks of 2048 20 us, with a last block of 2047
+// 104; blocks of 3000 51 / 166.
 template <int QL, int NT, bool FASTDIV, int WPW, bool RAGGED>
 __global__ __launch_bounds__(kWave * WPW, WPW / 2) void k_avg_block(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
                                                           const float *__restrict__ local, size_t n, size_t B,
@@ -223,6 +226,8 @@ __global__ __launch_bounds__(kWave * WPW, WPW / 2) void k_avg_block(const uint32
 //    leaves it unchanged);
 //  - the worker's scale for the block is loaded with its code words, one more load of the set (requested at the
 //    start of a block it would be the wavefront's youngest load, and waiting for it would drain everything);
+//  - 128 registers, so that two workgroups share a compute unit: with blocks of any length the form for eight workers and eight quads per
+//    lane spills two of them (blocks of 16384 102.6 us, 14 500 125.5; when it took aligned blocks only, without spills, 103.3 and 125.5);
 //  - a place past the workgroup's last block repeats its last block (valid memory, result unused);
 //  - a lane whose quad lies past the end of a block loads the block's last quad and stores nothing.
 // `aligned` (from the host): local is a multiple of 4, and there is at least one worker.  Then every block takes this path (see

@@ -693,7 +693,9 @@ __global__ __launch_bounds__(kWg) void k_seg_decode_long(const uint32_t *__restr
 // for a pair of workers, so all of them (the first eight) are requested before the tables are built.
 // NEAR: all workers' scales in LDS (see k_seg_decode), row k for worker k.
 // 1.76 M elements in 10 segments, seven workers and a local term, in a graph: 10.4 us with two ahead and the scales in memory, 8.5
-// so; 3 M, three workers 10.5 / 8.1.  Eight ahead with two workgroups on a compute unit, 4 Mi, eight workers: 20.3 us, 14.7 with two.
+// so; 3 M, three workers 10.5 / 8.1.  Four ahead in 128 registers spill two; in 168, without, one workgroup on a compute unit is
+// faster (1.76 M, four workers and a local term 7.1 / 6.7 us, 2 M, three 5.7 / 5.3) and two, which then wait for each other, slower (3 M,
+// three and a local term 8.1 / 10.5; 4 Mi, five 10.9 / 13.1).  Eight ahead with two workgroups on a compute unit, 4 Mi, eight workers: 20.3 us, 14.7 with two.
 template <int WAVES, int AHEAD, bool NEAR>
 __global__ __launch_bounds__(kWave *WAVES, AHEAD == 8 ? 2 : 4) void k_seg_avg(const uint32_t *__restrict__ tab, WorkerPtrs p, int K,
                                                     const float *__restrict__ local, size_t n,

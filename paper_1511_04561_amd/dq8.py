@@ -6,6 +6,9 @@ fallback: if libdq8.so is missing or a call fails, an exception is raised.
 
 A call with ordinary arguments is marshalled by the extension _binding.so (csrc/dq8_binding.cpp); it returns None for
 any other, which then takes the code here: the same library call, and the place where wrong arguments are reported.
+Scratch memory is handed in by the extension only, and not while the stream is captured: without it (tensors on another device
+than the current one, error statistics without `stats` and `means`, captured calls) long arrays with one scale, sets of tensors and
+the statistics of one block take a launch or two more.
 """
 import ctypes
 import os
