@@ -134,10 +134,11 @@ struct SegQuads {
 
 // Few segments in the stretch (mostly two): every lane counts, for each of its elements, the segments that have begun at or
 // before it, one bound after the other; no wait but for the bound, no branch.  More than kCountedSegments: a search per quad
-// and steps from element to element.  The
-// search and the steps wait for LDS three to ten times: expansion of 200 000 elements in 20 segments, in a graph,
-// 4.9 / 4.0 us, of 3000 in 60 6.4 / 6.4, and counting 20 bounds in a unit 7.4.
-constexpr uint32_t kCountedSegments = 16;
+// and steps from element to element, which wait for LDS three to ten times, whatever the number of bounds.  In a graph, search /
+// counting: expansion of 200 000 elements in 20 segments 4.9 / 4.0 us; 200 elements with 10 bounds inside 5.3 / 4.7, with 14 5.15 /
+// 5.3, with 16 4.4 / 5.7; their compression with given scales with 9 bounds 4.6 / 4.9, 14 4.5 / 5.6; their maxima with 12 7.0 / 6.7, with
+// 14 5.7 / 6.7.  (With 16 counted, given scales and maxima of such short sets took up to 1 us longer than with none.)
+constexpr uint32_t kCountedSegments = 12;
 
 template <int ROWS = kSegQ>
 __device__ __forceinline__ SegQuads<ROWS> segments_of_quads(const SegBounds &sb, const SegSpan &q, uint32_t lane, uint32_t row = 0)
