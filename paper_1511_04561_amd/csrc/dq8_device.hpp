@@ -381,7 +381,7 @@ __device__ __forceinline__ BucketWords<THREADS> request_bucket_table(const uint3
 // that has nothing to write are still on their way when the loop over the units begins, and waits of that loop count
 // them: k_encode with a wavefront per unit then waits for the next unit's loads too early (61 M elements, given scales, blocks of 1000:
 // 57.7 us with the words copied one by one, 58.7 without SETTLED, 57.3 with; 1024: 54.2, 54.0, 53.2).  Not for the kernels in
-// which four wavefronts share a unit: those are faster without (k_encode, given scales, 3000: 61.9 against 65.3; k_encode_full
+// which four wavefronts share a unit: those are faster without (k_encode, given scales, 3000: 63.0 against 64.0; k_encode_full
 // 49.1 against 50.6; k_encode_long, 8192: 53.0 against 54.5), k_encode_wave in blocks of 1000 too (56.9 against 57.2).
 template <uint32_t THREADS, bool SETTLED = false>
 __device__ __forceinline__ Search place_bucket_table(const uint32_t *tab, const BucketWords<THREADS> &b, uint32_t *lds)

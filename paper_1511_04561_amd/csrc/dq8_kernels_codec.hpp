@@ -483,9 +483,19 @@ __global__ __launch_bounds__(kWg) void k_encode(const uint32_t *__restrict__ tab
     e.phase = 0;
     size_t u = WPB == 1 ? first_unit() : (size_t)blockIdx.x;
     typename Enc::Slot a, b;
-    if (u < n_units) e.fetch(u, a);  // the first loads are in flight while the table is copied
-    e.sr = load_bucket_table<kWg, WPB == 1>(tab, lds + kTeamSlots);
-    __syncthreads();
+    if constexpr (WPB == 1) {
+        if (u < n_units) e.fetch(u, a);  // the first loads are in flight while the table is copied
+        e.sr = load_bucket_table<kWg, true>(tab, lds + kTeamSlots);
+        __syncthreads();
+    } else {
+        // Teams: the table first.  Its words return after the unit's in any case, and with both under way the loop is compiled with
+        // earlier waits (linear type, blocks of 3500: 61 M elements 58.6 us, 10.6 M 13.6; with the words copied one by one 57.1 and
+        // 13.0; so 57.2 and 12.7.  Given scales, blocks of 4000 at an odd float 62.9, 60.7, 61.1; 5000, 10.6 M 16.1, 15.5, 14.9; 3 M
+        // 6.8, 6.7, 5.9.  Not better: given scales, blocks of 3000, 61 M 61.7, 63.1, 63.0, and 4000 at even ones 57.0, 55.9, 57.0).
+        e.sr = load_bucket_table<kWg, FUSED>(tab, lds + kTeamSlots);
+        __syncthreads();
+        if (u < n_units) e.fetch(u, a);
+    }
     if constexpr (EVERY) {
         walk_units(u, n_units, n_teams, a, b, [&](size_t v, typename Enc::Slot &sl) { e.fetch(v, sl); },
                    [&](size_t, typename Enc::Slot &sl) { e.process(sl); });

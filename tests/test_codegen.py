@@ -21,6 +21,7 @@ KERNELS = """
 template __global__ void k_absmax_whole<16, 1>(const float *, size_t, size_t, size_t, size_t, size_t, float *);
 template __global__ void k_encode<1, 2, 1, false, true, true>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
 template __global__ void k_encode<1, 4, 1, false, true, false>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
+template __global__ void k_encode<4, 4, 1, true, true, false>(const uint32_t *, const float *, size_t, size_t, size_t, size_t, size_t, size_t, uint32_t, float *, uint8_t *);
 template __global__ void k_decode_flat<16, 8, 2, 4>(const uint32_t *, const uint8_t *, const float *, uint64_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t, uint64_t, uint32_t, float *);
 template __global__ void k_seg_encode<false, 8>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
 template __global__ void k_seg_encode<true, 16>(const uint32_t *, const float *, size_t, const uint64_t *, uint32_t, size_t, size_t, const float *, uint8_t *);
@@ -99,6 +100,15 @@ def test_compression_has_its_table_before_its_loop():
     meet = [b for b in kernel("k_encodeILi1ELi4ELi1ELb0ELb1ELb0E") if any(i.startswith("s_barrier") for i in b)]
     assert len(meet) == 1
     assert any(i.startswith("ds_write_b128") for i in meet[0]) and waits(meet[0])[-1] == 0, meet[0]
+
+
+def test_teams_have_their_table_before_their_first_unit():
+    """k_encode with a team per unit: no unit's loads set out before the workgroup has met over the table."""
+    blocks = kernel("k_encodeILi4ELi4ELi1ELb1ELb1ELb0E")
+    meet = min(i for i, b in enumerate(blocks) if any(w.startswith("s_barrier") for w in b))
+    upto = [w for b in blocks[:meet] for w in b] + blocks[meet][:[w.startswith("s_barrier") for w in blocks[meet]].index(True)]
+    loads = [w for w in upto if w.startswith("global_load_dwordx4")]
+    assert loads and not any(w.endswith(" nt") for w in loads), loads
 
 
 def test_expansion_by_position_keeps_no_store_offsets():
