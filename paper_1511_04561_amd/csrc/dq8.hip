@@ -1693,8 +1693,8 @@ int dq8_decode_segments(int kind, const uint8_t *codes, const float *scales, siz
 #define DQ8_SEG_DEC(W, NEAR)                                                                                                  \
     hipLaunchKernelGGL((k_seg_decode<W, NEAR>), dim3(p.grid), dim3(kWave * (W)), lds, stream, tab, codes, scales, n, bounds, \
                        (uint32_t)n_seg, units, p.n_waves, out)
-    if (n_seg < (size_t)kWave && n >= kLongSegments) {
-        const size_t long_units = whole_units(n, kUnit, ((uintptr_t)out & 3) == 0);
+    if (long_segment_units(n, n_seg, (uintptr_t)out)) {
+        const size_t long_units = whole_units(n, kUnit, true);
         const Plan lp = make_plan(n, 0, st->cus, 4, 1);
         hipLaunchKernelGGL(k_seg_decode_long, dim3(lp.grid), dim3(kWg), lds, stream, tab, codes, scales, n, bounds, (uint32_t)n_seg,
                            long_units, lp.n_teams, out);

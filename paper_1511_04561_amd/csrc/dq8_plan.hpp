@@ -167,9 +167,13 @@ constexpr size_t kCodesFromCache = (size_t)1 << 24;
 // ---- tensors back to back, one scale each
 
 // Expansion of at least this many elements in fewer than 64 segments takes units of 4096 elements (k_seg_decode_long, figures
-// there): below, units of 1024 on sixteen wavefronts per compute unit are no more than two or three each.
+// there): below, units of 1024 on sixteen wavefronts per compute unit are no more than two or three each.  Only where every quad that is
+// stored is a multiple of 16 bytes: four wavefronts per compute unit have too few stores on their way where each touches one cache line
+// more (30 segments, out at an odd float, units of 1024 / 4096: 11 M elements 15.2 / 18.1 us, 14 M 18.1 / 23.5, 20 M 24.4 / 27.6, 61 M 73.4 /
+// 74.0, with the codes from memory 73.3 / 76.5; aligned 14 M 11.9 / 14.8 and, from memory, 15.8 / 16.3, 20 M 15.6 / 17.0 and 21.6 / 19.5, 36 M 35.7 / 28.1, 61 M
+// 57.2 / 46.9).
 constexpr size_t kLongSegments = (size_t)10 << 20;
-
+inline bool long_segment_units(size_t n, size_t n_seg, uintptr_t out) { return n_seg < (size_t)kWave && n >= kLongSegments && (out & 15) == 0; }
 
 // Wavefronts per workgroup of the kernels that keep a value table beside the bounds: kSegWaves, two such workgroups on a
 // compute unit, or twice that where only one workgroup's tables fit and there are units for more than one each.

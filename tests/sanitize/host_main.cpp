@@ -176,6 +176,11 @@ static void check_plans()
             const size_t fit = kLdsPerCu / (kValueTableBytes + p.lds), busy = (p.grid + 255) / 256;
             CHECK(busy <= fit && p.n_waves == (size_t)p.grid * w, "%zu segments of %zu elements: %zu workgroups, %zu fit", n_seg, n, busy, fit);
         }
+    // expansion in units of 4096: long arrays, few segments, every whole unit's stores at multiples of 16 bytes
+    for (uintptr_t at = 0; at < 32; at += 4)
+        for (size_t n_seg : {(size_t)1, (size_t)63, (size_t)64})
+            for (size_t n : {kLongSegments - 1, kLongSegments})
+                CHECK(long_segment_units(n, n_seg, 4096 + at) == (n == kLongSegments && n_seg < 64 && at % 16 == 0), "units of %zu segments of %zu at %zu", n_seg, n, (size_t)at);
     // the average: the plan is for the wavefronts of the form it names, and what is resident fits the LDS
     for (size_t n : {(size_t)1, (size_t)5003, (size_t)1 << 21, ((size_t)1 << 21) + 1, ((size_t)1 << 22) + 3, (size_t)61100840})
         for (size_t n_seg : {(size_t)1, (size_t)32, (size_t)33, (size_t)1024, (size_t)1025, (size_t)2047, (size_t)2048, (size_t)DQ8_MAX_SEGMENTS})

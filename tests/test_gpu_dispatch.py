@@ -403,6 +403,17 @@ def test_long_sets_of_tensors(dq8, n, n_seg):
     close = 4096 * 700 + np.array([0, 1, 3, 1023, 1024, 1025, 2050, 4093, 4095, 4096 + 5, 8192])
     inner = np.sort(np.concatenate([rng.integers(0, n + 1, max(0, n_seg - 14)), close, [n - 1, n - 2]])[-(n_seg - 1):])
     check_segments(dq8, n % 4, x, np.concatenate([[0], inner, [n]]), x_off=n % 3, c_off=n % 4, tag="long")
+    # the larger units only where out is a multiple of 16 bytes: the same bytes at every float, from codes at every byte
+    codes, scales = dq8.encode_segments(n % 4, dev(x), bounds_dev(np.concatenate([[0], inner, [n]])))
+    expanded = []
+    for off in (0, 1, 2, 3):
+        go, at = Guarded(n, np.float32, off), torch.empty(n + off, dtype=torch.uint8, device="cuda")[off:]
+        at.copy_(codes)
+        dq8.decode_segments(n % 4, at, scales, bounds_dev(np.concatenate([[0], inner, [n]])), out=go.t)
+        go.check("expansion")
+        expanded.append(go.t)
+    assert all(torch.equal(expanded[0].view(torch.int32), e.view(torch.int32)) for e in expanded[1:])
+    same_bits(expanded[0], oracle.decode_segments(n % 4, codes.cpu().numpy(), scales.cpu().numpy(), np.concatenate([[0], inner, [n]])), "expansion")
 
 
 # more workers than the team kernels take in these blocks: every mean of a last block that is no whole unit, or of codes at an odd address,
