@@ -691,7 +691,10 @@ __global__ __launch_bounds__(kWg) void k_seg_decode_long(const uint32_t *__restr
 // elements in 16 segments with 1, 2, 4, 8, 9 workers: 27.3, 37.5, 49, 72, 80 us with two at a time; 38, 52, 57, 84, 100 us
 // with four, 8 workers with eight 83 us).  WAVES as in k_seg_decode.
 // AHEAD = 8: on arrays that are no more than a unit for every wavefront there is no next unit whose loads could cover the wait
-// for a pair of workers, so all of them (the first eight) are requested before the tables are built.
+// for a pair of workers, so all of them are requested before the tables are built.
+// Eight ahead only for up to eight workers: the empty places of a second round of eight cost a worker's loads each, from codes at odd bytes
+// more than is gained (one tensor of 60 000 elements, in a graph, two / four / eight ahead: nine workers 6.9 / 7.7 / 9.2 us, sixteen
+// 8.4 / 9.1 / 10.3; 2 M, 32 workers 20.6 / 19.1 / 20.9).
 // NEAR: all workers' scales in LDS (see k_seg_decode), row k for worker k.
 // 1.76 M elements in 10 segments, seven workers and a local term, in a graph: 10.4 us with two ahead and the scales in memory, 8.5
 // so; 3 M, three workers 10.5 / 8.1.  Four ahead in 128 registers spill two; in 168, without, one workgroup on a compute unit is

@@ -235,7 +235,7 @@ inline SegAverage make_segment_average(int cus, size_t n, size_t n_seg, int K, s
     a.near = a.waves == kSegWaves && scales_fit_near((size_t)K * n_seg);
     if (a.near) a.plan.lds += (size_t)K * n_seg * sizeof(float);
     const bool one_unit = units <= a.plan.n_waves, one_workgroup = a.plan.grid <= (unsigned)cus;
-    a.ahead = a.near && one_unit && one_workgroup && K > 4 ? 8 : (a.near && one_unit && K > 2 ? 4 : 2);
+    a.ahead = a.near && one_unit && one_workgroup && K > 4 && K <= 8 ? 8 : (a.near && one_unit && K > 2 ? 4 : 2);
     return a;
 }
 

@@ -199,8 +199,9 @@ def test_short_arrays_in_one_launch(dq8, n, offset):
 
 
 # bounds in registers up to 63 segments; scales of all workers in LDS up to 1024; at most 12 bounds inside a unit are counted one by
-# one; all workers' codes requested at once (up to 4, up to 8) where no wavefront has a second unit
-@pytest.mark.parametrize("n,n_seg,K", [(5003, 1, 3), (5003, 2, 8), (5003, 12, 3), (5003, 13, 4), (5003, 14, 6), (5003, 16, 4), (5003, 17, 5), (5003, 18, 9), (5003, 63, 2), (5003, 64, 3), (5003, 65, 4), (5003, 128, 8),
+# one; all workers' codes requested at once (up to 4, up to 8; four at a time
+# beyond) where no wavefront has a second unit
+@pytest.mark.parametrize("n,n_seg,K", [(5003, 1, 3), (5003, 2, 8), (5003, 12, 3), (5003, 13, 4), (5003, 14, 6), (5003, 16, 4), (5003, 17, 5), (5003, 18, 9), (5003, 3, 16), (60000, 1, 32), (5003, 63, 2), (5003, 64, 3), (5003, 65, 4), (5003, 128, 8),
                                        (5003, 129, 8), (5003, 341, 3), (5003, 342, 3), (5003, 1024, 1), (5003, 1025, 1), (256 * 8 * 1024 - 3, 18, 8),
                                        (256 * 8 * 1024 + 1, 17, 5), (256 * 16 * 1024 + 5000, 65, 3)])
 def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
