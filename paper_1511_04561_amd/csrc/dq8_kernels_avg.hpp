@@ -581,8 +581,11 @@ __global__ __launch_bounds__(kWave * WPW) void k_decode_avg_chunks(const uint32_
     if (tail_len != 0 && blockIdx.x == gridDim.x - 1 && wave_in_wg() == 0) {
         const size_t start = (size_t)n_full * U;
         auto block_of = [&](uint32_t i) { return FLAT ? (start + i) / ((size_t)g.bq * 4) : (size_t)(n_full >> block_shift); };
-        // see the two kernels above; up to an element per lane one by one (49 elements, 16 workers: 8.1 us, 8.8 in quads)
-        const uint32_t done = tail_len <= (uint32_t)kWave ? 0 : (FLAT ? tail_len & ~3u : tail_len);
+        // See the two kernels above; what is left after quads for all lanes one by one up to two elements per lane.  A round of quads
+        // takes as long as 140 to 250 elements one by one (blocks of 1000, 17 workers, in a graph: 117 elements 8.1 us, 10.2 in
+        // quads, 180 9.1 in quads, 8.9 one by one; 32 workers, 300 elements 13.9, 16.7 in two rounds of quads).
+        const uint32_t rest = tail_len % (4 * kWave);
+        const uint32_t done = rest <= 2 * (uint32_t)kWave ? tail_len - rest : (FLAT ? tail_len & ~3u : tail_len);
         for (uint32_t q = lane; q * 4 < done; q += kWave) {
             const uint32_t at = quad_start(q, done);
             const size_t blk = block_of(at);

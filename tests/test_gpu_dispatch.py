@@ -440,6 +440,23 @@ def test_many_workers_in_blocks_of_any_length(dq8, block, K, rest, odd):
     gs.check("scales of the average")
 
 
+# what is left after the whole units: quads for all lanes, then up to two elements per lane one by one or quads again
+@pytest.mark.parametrize("rest", [64, 65, 127, 128, 129, 131, 255, 256, 300, 384, 385, 511])
+@pytest.mark.parametrize("block,K", [(1000, 13), (4096, 17), (3000, 32)])
+def test_averages_of_many_workers_with_a_rest_of_any_length(dq8, block, K, rest):
+    """More than eight workers, units by position and inside blocks; codes at multiples of 4, out and local of 16."""
+    n = 1024 * 12 + rest
+    rng = np.random.Generator(np.random.PCG64(9990 + rest + K))
+    kind, nb = (rest + K) % 4, -(-n // block)
+    cl = [rng.integers(0, 256, n).astype(np.uint8) for _ in range(K)]
+    sl = [np.exp(rng.uniform(-4, 4, nb)).astype(np.float32) for _ in range(K)]
+    x = rng.standard_normal(n).astype(np.float32) if rest % 2 else None
+    go = Guarded(n, np.float32)
+    dq8.decode_accumulate_avg(kind, [dev(c) for c in cl], [dev(s) for s in sl], block, out=go.t, local=None if x is None else dev(x))
+    same_bits(go.t, oracle.decode_accumulate_avg(kind, cl, sl, block, local=x), "average")
+    go.check("average")
+
+
 # a last block of 1, 3, 4, 5 elements, one short of whole quads and one short of whole; teams of one to four wavefronts and a workgroup
 # per block; all workers unrolled, in passes and in chunks (blocks of 4096 and more; other blocks with more than eight workers: above)
 @pytest.mark.parametrize("block,K", [(512, 2), (1000, 4), (1024, 1), (2048, 8), (3000, 5), (3500, 3), (4096, 6), (4096, 7), (4096, 9), (4096, 16), (5000, 2), (8192, 8),
