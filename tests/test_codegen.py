@@ -117,11 +117,18 @@ def test_expansion_by_position_keeps_no_store_offsets():
 
 
 @pytest.mark.parametrize("marks,waves", [(0, 8), (1, 16)])
-@pytest.mark.parametrize("scales", ["", "_copied", "_parts"])
-def test_segment_compression_leaves_room_for_wavefronts(scales, marks, waves):
-    """k_seg_encode, wherever it finds the scales (copied and from parts: up to 1024 segments): seven wavefronts of it fit the
-    registers of a SIMD, and its code is not several times its loop."""
-    name = "k_seg_encode%sILb%dELi%dE" % (scales, marks, waves)
+def test_segment_compression_leaves_room_for_wavefronts(marks, waves):
+    """k_seg_encode: seven wavefronts of it fit the registers of a SIMD, and its code is not several times its loop."""
+    name = "k_seg_encodeILb%dELi%dE" % (marks, waves)
+    assert kernel(name, 1) <= 72
+    assert sum(len(b) for b in kernel(name)) < 3000
+
+
+@pytest.mark.parametrize("marks,waves", [(0, 8), (1, 16)])
+@pytest.mark.parametrize("scales", ["copied", "parts"])
+def test_segment_compression_of_usual_sets_leaves_room_for_wavefronts(scales, marks, waves):
+    """The same of the forms for up to 1024 segments, whose scales are copied to LDS or formed from parts."""
+    name = "k_seg_encode_%sILb%dELi%dE" % (scales, marks, waves)
     assert kernel(name, 1) <= 72
     assert sum(len(b) for b in kernel(name)) < 3000
 

@@ -199,9 +199,8 @@ def test_short_arrays_in_one_launch(dq8, n, offset):
 
 
 # bounds in registers up to 63 segments; scales of all workers in LDS up to 1024; at most 12 bounds inside a unit are counted one by
-# one; all workers' codes requested at once (up to 4, up to 8; four at a time
-# beyond) where no wavefront has a second unit
-@pytest.mark.parametrize("n,n_seg,K", [(5003, 1, 3), (5003, 2, 8), (5003, 12, 3), (5003, 13, 4), (5003, 14, 6), (5003, 16, 4), (5003, 17, 5), (5003, 18, 9), (5003, 3, 16), (60000, 1, 32), (5003, 63, 2), (5003, 64, 3), (5003, 65, 4), (5003, 128, 8),
+# one (the test after this one); all workers' codes requested at once (up to 4, up to 8) where no wavefront has a second unit
+@pytest.mark.parametrize("n,n_seg,K", [(5003, 1, 3), (5003, 2, 8), (5003, 16, 4), (5003, 17, 5), (5003, 18, 9), (5003, 63, 2), (5003, 64, 3), (5003, 65, 4), (5003, 128, 8),
                                        (5003, 129, 8), (5003, 341, 3), (5003, 342, 3), (5003, 1024, 1), (5003, 1025, 1), (256 * 8 * 1024 - 3, 18, 8),
                                        (256 * 8 * 1024 + 1, 17, 5), (256 * 16 * 1024 + 5000, 65, 3)])
 def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
@@ -221,6 +220,12 @@ def test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n):
                                            local=None if local is None else dev(local))
         same_bits(go.t, want, "segment average")
         go.check("segment average")
+
+
+# 11 to 13 bounds inside a unit; four workers at a time from nine on
+@pytest.mark.parametrize("n,n_seg,K", [(5003, 12, 3), (5003, 13, 4), (5003, 14, 6), (5003, 3, 16), (60000, 1, 32)])
+def test_segments_at_the_limits_of_counting_and_of_workers_ahead(dq8, n_seg, K, n):
+    test_segments_at_the_edges_of_their_tables(dq8, n_seg, K, n)
 
 
 # more than 2047 segments in more than a unit for eight wavefronts of every compute unit: workgroups of sixteen, with and without workers
@@ -295,13 +300,23 @@ def test_calls_marshalled_by_the_extension_and_by_python(dq8, monkeypatch):
         dq8.decode(2, codes[0], scales[0], 1024, out=new(n - 1))
     with pytest.raises(dq8.Dq8Error, match="dq8_encode failed .status 2.: unknown data type 9"):
         dq8.encode(9, x)
-    def transformed(v):  # has no address: declined by the extension, refused by dq8.py
+    with pytest.raises(Exception):  # a transformed tensor has no address; the same with and without the extension
+        torch.vmap(lambda v: dq8.absmax(v, 0))(x[:64].view(8, 8))
+
+
+def test_transformed_tensors_are_declined_and_refused(dq8, monkeypatch):
+    """The extension declines a tensor inside vmap, and dq8.py refuses it with its own error, with and without the extension."""
+    x, native = torch.ones(64, device="cuda"), dq8._native
+    assert not isinstance(native, dq8._Unbound)
+
+    def transformed(v):  # has no address
         assert native.absmax(v, 0, None) is None
         return dq8.absmax(v, 0)
+
     for way in (native, dq8._Unbound()):
         monkeypatch.setattr(dq8, "_native", way)
         with pytest.raises(RuntimeError, match="Cannot access data pointer of Tensor"):
-            torch.vmap(transformed)(x[:64].view(8, 8))
+            torch.vmap(transformed)(x.view(8, 8))
 
 
 @pytest.mark.parametrize("n,n_seg", [(98305, 1), (98305, 4), (98305, 63), (98305, 65), (8192 * 63 + 1, 33), (256 * 8192, 64), (256 * 8192 + 3, 1),
@@ -349,6 +364,14 @@ def test_scratch_memory_of_the_c_calls(dq8):
         assert calls(w, need) == (3, 3)
     assert L.dq8_encode_segments_ws(0, vp(x.data_ptr()), sz(n), vp(bounds.data_ptr()), sz(1), vp(scale.data_ptr()), vp(codes.data_ptr()), 0,
                                     vp(bounds.data_ptr()), sz(need), vp(stream)) == 3
+
+
+def test_scratch_memory_of_the_statistics(dq8):
+    """dq8_error_stats_ws: the same statistics with enough scratch memory, with too little and with none; other arrays' memory is refused."""
+    import ctypes
+    L, n, vp, sz = dq8.lib(), 200000, ctypes.c_void_p, ctypes.c_size_t
+    x = dev(np.random.Generator(np.random.PCG64(9800)).standard_normal(n).astype(np.float32))
+    scale, stream = torch.empty(1, device="cuda"), torch.cuda.current_stream().cuda_stream
     L.dq8_workspace_bytes_stats.restype = sz
     need, work = L.dq8_workspace_bytes_stats(sz(n), sz(0), 0), torch.empty(1 << 15, dtype=torch.uint8, device="cuda")
     stats, means = torch.empty(4, dtype=torch.float64, device="cuda"), torch.empty(2, dtype=torch.float64, device="cuda")
@@ -404,7 +427,17 @@ def test_long_sets_of_tensors(dq8, n, n_seg):
     close = 4096 * 700 + np.array([0, 1, 3, 1023, 1024, 1025, 2050, 4093, 4095, 4096 + 5, 8192])
     inner = np.sort(np.concatenate([rng.integers(0, n + 1, max(0, n_seg - 14)), close, [n - 1, n - 2]])[-(n_seg - 1):])
     check_segments(dq8, n % 4, x, np.concatenate([[0], inner, [n]]), x_off=n % 3, c_off=n % 4, tag="long")
-    # the larger units only where out is a multiple of 16 bytes: the same bytes at every float, from codes at every byte
+
+
+# the larger units only where out is a multiple of 16 bytes
+@pytest.mark.parametrize("n", [(10 << 20) - 1, 10 << 20, (10 << 20) + 3, (12 << 20) + 1027])
+@pytest.mark.parametrize("n_seg", [63, 64])
+def test_long_sets_of_tensors_are_expanded_at_any_float(dq8, n, n_seg):
+    """The same bytes at every float, from codes at every byte."""
+    rng = np.random.Generator(np.random.PCG64(9960 + n % 97 + n_seg))
+    x = (rng.standard_normal(n) * np.exp(rng.uniform(-9, 0, n))).astype(np.float32)
+    close = 4096 * 700 + np.array([0, 1, 3, 1023, 1024, 1025, 2050, 4093, 4095, 4096 + 5, 8192])
+    inner = np.sort(np.concatenate([rng.integers(0, n + 1, n_seg - 14), close, [n - 1, n - 2]]))
     codes, scales = dq8.encode_segments(n % 4, dev(x), bounds_dev(np.concatenate([[0], inner, [n]])))
     expanded = []
     for off in (0, 1, 2, 3):
